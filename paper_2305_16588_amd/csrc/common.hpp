@@ -21,13 +21,24 @@ constexpr int kWordsPerThread = 4;                                   // 64-bit w
 constexpr int64_t kChunkWords = int64_t(kCompactThreads) * kWordsPerThread;
 constexpr int64_t kChunkBits = kChunkWords * 64;                     // 65536 vertices per workgroup
 
-// Vertex v is bit (v << spread_shift) of a dedup bitmap.  Every sample is one atomic OR on the
-// bitmap, and atomics on the same cache line serialise; a graph whose plain bitmap is a few lines
-// or a few hundred KB therefore gets a sparser one (measured: sampling 0.060 -> 0.031 ms at 10 k
-// vertices with shift 5, 0.144 -> 0.134 ms at 2.4 M with shift 2; at 10 M and beyond any spreading
-// only adds bytes to the compaction scans).
-constexpr int kMaxSpreadShift = 5;
-constexpr int64_t kSpreadTargetBits = int64_t(1) << 24;
+// Vertex v is bit (v << spread_shift) of a dedup map, and marking it means setting that bit.
+//   shift 0      one bit per vertex, set with an atomic OR.  Scattered atomics run at about 26 G/s on this
+//                chip whatever their scope or target, so they bound the sampler of a large graph.
+//   shift 3..5   a byte, half-word or word per vertex, set with a plain store of 1 (every writer of the entry
+//                stores the same value).  Scattered stores run at 78-162 G/s and do not serialise on hot
+//                lines, but the compaction has 8-32 times as many bytes to scan.
+// Measured for three-hop batches of 8192 seeds (15, 10, 5): at 2.4 M vertices the last hop's kernel takes 25 us
+// with bytes and 54 us with atomics (the best sparser bitmap, 4 bits per vertex); a whole call 76 -> 58 us at
+// 3 M vertices, 79 -> 71 at 6 M, 81 -> 86 at 12 M, 84 -> 106 at 25 M: bytes up to 2^23 vertices, bits beyond.
+// Words instead of bytes on the smallest graphs keep neighbours' marks on different lines (10 k vertices:
+// 2 us of a 33-us call).
+constexpr int64_t kWordMapMaxVertices = int64_t(1) << 19;
+constexpr int64_t kHalfMapMaxVertices = int64_t(1) << 20;
+constexpr int64_t kByteMapMaxVertices = int64_t(1) << 23;
+inline int mark_shift(int64_t num_vertices) {
+  return num_vertices <= kWordMapMaxVertices ? 5 : num_vertices <= kHalfMapMaxVertices ? 4
+         : num_vertices <= kByteMapMaxVertices ? 3 : 0;
+}
 
 struct DeviceInfo {
   int device = 0;
@@ -57,10 +68,10 @@ struct TopoView {
 
 // ---- sampler.hip ----------------------------------------------------------
 // Expand frontier[0 .. *n_frontier) with fan-out f at hop `hop`.  Writes nbr / cnt
-// (either may be null), sets the bit of every sampled neighbour in `mark_bits` (bit v << di.spread_shift),
+// (either may be null), marks every sampled neighbour in `mark_bits` (bit v << di.spread_shift),
 // adds cnt to topo_hot[v] if topo_hot is given.  With self_bits given (first hop) the
 // frontier is the seed list: exactly `cap` ids, *n_frontier is written (= cap) instead of
-// read, and every valid seed's own bit is set in self_bits.
+// read, and every valid seed is marked in self_bits.
 void launch_sample_hop(const DeviceInfo& di, const TopoView& tv, const int32_t* frontier, int32_t* n_frontier,
                        int64_t cap, int32_t fanout, int32_t hop, uint64_t rng_seed, int32_t* nbr, int32_t* cnt,
                        uint32_t* mark_bits, uint32_t* self_bits, uint32_t* topo_hot, uint32_t* d_err, hipStream_t s);

@@ -5,13 +5,25 @@
 // whether its column ids sit in the HBM topology cache or in the CPU-resident CSR (read
 // in place over PCIe), so an uncached vertex costs one PCIe round trip, not two.  All slots draw their
 // Philox number at once; Floyd's sequential "already taken?" test becomes fanout-1
-// group broadcasts.  The kernel is bound by dependent loads and by the bitmap atomics, not by
-// issue slots, so the grid is capped at four workgroups per CU (see launch_one).
+// group broadcasts.  The kernel is bound by dependent loads and, on large graphs, by the bitmap
+// atomics, not by issue slots, so the grid is capped at four workgroups per CU (see launch_one).
 #include "common.hpp"
 #include "philox_dev.hpp"
 
 namespace lgp {
 namespace {
+
+// Mark vertex u in a dedup map (see mark_shift): a plain store where it has an entry of its own, else one bit.
+__device__ __forceinline__ void mark_vertex(uint32_t* map, int32_t u, int shift) {
+  if (shift == 3)
+    __hip_atomic_store(reinterpret_cast<uint8_t*>(map) + u, uint8_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  else if (shift == 4)
+    __hip_atomic_store(reinterpret_cast<uint16_t*>(map) + u, uint16_t(1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  else if (shift == 5)
+    __hip_atomic_store(map + u, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+  else
+    atomicOr(&map[uint32_t(u) >> 5], 1u << (uint32_t(u) & 31u));
+}
 
 template <typename IdxT, int P>
 __global__ __launch_bounds__(256) void sample_hop_kernel(
@@ -82,17 +94,13 @@ __global__ __launch_bounds__(256) void sample_hop_kernel(
           atomicOr(d_err, ERR_BAD_ID);
           u = -1;
         } else {
-          const uint64_t b = uint64_t(uint32_t(u)) << shift;
-          atomicOr(&mark_bits[b >> 5], 1u << (uint32_t(b) & 31u));
+          mark_vertex(mark_bits, u, shift);
         }
       }
       if (nbr) nbr[g * f + i] = u;
     }
     if (active && i == 0) {
-      if (self_bits && !bad) {
-        const uint64_t b = uint64_t(uint32_t(v)) << shift;
-        atomicOr(&self_bits[b >> 5], 1u << (uint32_t(b) & 31u));
-      }
+      if (self_bits && !bad) mark_vertex(self_bits, v, shift);
       const int32_t c = d < f ? d : f;
       if (cnt) cnt[g] = c;
       if (topo_hot && c > 0) atomicAdd(&topo_hot[v], uint32_t(c));
@@ -115,7 +123,7 @@ void launch_one(const DeviceInfo& di, const TopoView& tv, const int32_t* frontie
                 uint32_t* self_bits, uint32_t* topo_hot, uint32_t* d_err, hipStream_t s) {
   constexpr int G = 256 / P;
   int64_t blocks = (cap + G - 1) / G;
-  // 4 workgroups x 4 waves = 16 waves per CU.  The kernel is bound by memory-side atomics and
+  // 4 workgroups x 4 waves = 16 waves per CU.  The kernel is bound by scattered marks and
   // dependent loads, not by issue slots: 16 waves per CU are as fast as 32 when it runs alone
   // (0.133 -> 0.128 ms per batch at 2.4 M vertices, 0.1025 -> 0.100 ms at 111 M) and disturb a
   // PCIe-bound gather running beside it less (pipelined step 2.50 -> 2.43 ms).
