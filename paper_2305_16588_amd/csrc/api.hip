@@ -52,16 +52,13 @@ struct lgp_ctx {
   DeviceInfo di;
   lgp_graph g{};           // pointers already translated to device-visible addresses
   int64_t row_bytes = 0;
-  int64_t n_chunks = 0;    // dedup bitmap chunks
 
   uint64_t* row_tab = nullptr;   // per-vertex (cached?, offset, degree)
   int32_t* f_remap = nullptr;
   uint32_t* topo_hot = nullptr;
   uint32_t* feat_hot = nullptr;
   bool have_hot = false;
-  uint64_t* fbits = nullptr;   // frontier dedup bitmap
-  uint64_t* gbits = nullptr;   // gather-set dedup bitmap
-  int32_t* chunk_counts = nullptr;
+  DedupMaps maps;              // frontier and gather-set dedup maps
   uint32_t* d_err = nullptr;
   int32_t* counters = nullptr;  // {n_hit, n_miss, n_peer}
 
@@ -107,7 +104,6 @@ struct lgp_ctx {
   hipEvent_t ev_extracted = nullptr;
   int32_t* seg = nullptr;            // int32[LGP_MAX_HOPS + 2]
   int32_t* seg_counters = nullptr;   // int32[(LGP_MAX_HOPS + 1) * 3]
-  int32_t* new_counts = nullptr;     // per compaction chunk: vertices reached first by the hop
 
   int profiling = 0;        // 0 off, 1 every per-batch kernel group, 2 the two row gathers only
   bool overlap = false;     // run the miss gather on its own stream beside the hit gather
@@ -254,8 +250,8 @@ int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t
                 uint64_t rng_seed, const lgp_sample_out* out, hipStream_t s) {
   const bool hot_mode = (out == nullptr);
   const int64_t V = c->g.num_vertices;
-  uint32_t* fbits32 = reinterpret_cast<uint32_t*>(c->fbits);
-  uint32_t* gbits32 = reinterpret_cast<uint32_t*>(c->gbits);
+  uint32_t* fbits32 = reinterpret_cast<uint32_t*>(c->maps.frontier);
+  uint32_t* gbits32 = reinterpret_cast<uint32_t*>(c->maps.gather);
   int32_t* n_frontier = hot_mode ? c->hs_n : out->n_frontier;
   const TopoView tv = topo_view(c);
 
@@ -265,25 +261,25 @@ int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t
   for (int h = 0; h < n_hops; ++h) {
     // the last hop's samples only feed the gather set, so they are marked there directly -- unless
     // the caller wants the last frontier as a list of its own
-    const bool last = (h + 1 == n_hops) && !want_last;
+    const bool final_hop = h + 1 == n_hops;
     launch_sample_hop(c->di, tv, frontier, n_frontier + h, cap, fanouts[h], h, rng_seed,
-                      hot_mode ? nullptr : out->nbr[h], hot_mode ? nullptr : out->cnt[h], last ? gbits32 : fbits32,
-                      h == 0 ? gbits32 : nullptr, hot_mode ? c->topo_hot : nullptr, c->d_err, s);
-    if (!last) {
-      int32_t* next = hot_mode ? c->hs_frontier[h + 1] : out->frontier[h + 1];
-      const int64_t next_cap = hot_mode ? c->hs_cap[h + 1] : out->cap[h + 1];
-      launch_compact(c->di, c->fbits, c->gbits, c->n_chunks, c->chunk_counts, next, next_cap, n_frontier + h + 1,
-                     nullptr, c->d_err, s);
-      frontier = next;
-      cap = next_cap;
-    }
+                      hot_mode ? nullptr : out->nbr[h], hot_mode ? nullptr : out->cnt[h],
+                      final_hop && !want_last ? gbits32 : fbits32, h == 0 ? gbits32 : nullptr,
+                      hot_mode ? c->topo_hot : nullptr, c->d_err, c->maps.status, c->maps.geom.groups, s);
+    if (final_hop) break;
+    int32_t* next = hot_mode ? c->hs_frontier[h + 1] : out->frontier[h + 1];
+    const int64_t next_cap = hot_mode ? c->hs_cap[h + 1] : out->cap[h + 1];
+    launch_compact(c->di, c->maps, next, next_cap, n_frontier + h + 1, c->d_err, s);
+    frontier = next;
+    cap = next_cap;
   }
   if (hot_mode)
-    launch_compact(c->di, c->gbits, nullptr, c->n_chunks, c->chunk_counts, nullptr, 0, nullptr, c->feat_hot, c->d_err,
-                   s);
+    launch_bump(c->di, c->maps, c->feat_hot, c->hs_n, n_hops, c->hs_expansions, s);
+  else if (want_last)
+    launch_compact_both(c->di, c->maps, out->frontier[n_hops], out->cap[n_hops], n_frontier + n_hops, out->gather_ids,
+                        out->gather_cap, out->n_gather, c->d_err, s);
   else
-    launch_compact(c->di, c->gbits, nullptr, c->n_chunks, c->chunk_counts, out->gather_ids, out->gather_cap,
-                   out->n_gather, nullptr, c->d_err, s);
+    launch_compact_gather(c->di, c->maps, out->gather_ids, out->gather_cap, out->n_gather, c->d_err, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail_hip(c, e, "sampling kernel launch");
   return LGP_OK;
@@ -574,8 +570,8 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   }
   const int64_t V = g->num_vertices;
   c->di.spread_shift = mark_shift(V);
-  c->n_chunks = ((V << c->di.spread_shift) + kChunkBits - 1) / kChunkBits;
-  const size_t words = size_t(c->n_chunks) * size_t(kChunkWords);
+  c->maps.geom = map_geometry(V, c->di.spread_shift);
+  const size_t words = size_t(c->maps.geom.words());
   hipError_t e = hipSuccess;
   auto step = [&](hipError_t r) {
     if (e == hipSuccess) e = r;
@@ -584,21 +580,20 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   step(dev_alloc(&c->f_remap, size_t(V)));
   step(dev_alloc(&c->topo_hot, size_t(V)));
   step(dev_alloc(&c->feat_hot, size_t(V)));
-  step(dev_alloc(&c->fbits, words));
-  step(dev_alloc(&c->gbits, words));
-  step(dev_alloc(&c->chunk_counts, size_t(c->n_chunks)));
+  step(dev_alloc(&c->maps.frontier, words));
+  step(dev_alloc(&c->maps.gather, words));
+  step(dev_alloc(&c->maps.status, size_t(c->maps.geom.groups)));
   step(dev_alloc(&c->d_err, 1));
   step(dev_alloc(&c->counters, 3));
   step(dev_alloc(&c->hs_n, LGP_MAX_HOPS + 1));
   step(dev_alloc(&c->hs_expansions, 1));
   step(dev_alloc(&c->seg, LGP_MAX_HOPS + 2));
   step(dev_alloc(&c->seg_counters, (LGP_MAX_HOPS + 1) * 3));
-  step(dev_alloc(&c->new_counts, size_t(c->n_chunks)));
   if (e == hipSuccess) e = hipMemset(c->f_remap, 0xff, sizeof(int32_t) * size_t(V));
   if (e == hipSuccess) e = hipMemset(c->topo_hot, 0, sizeof(uint32_t) * size_t(V));
   if (e == hipSuccess) e = hipMemset(c->feat_hot, 0, sizeof(uint32_t) * size_t(V));
-  if (e == hipSuccess) e = hipMemset(c->fbits, 0, sizeof(uint64_t) * words);
-  if (e == hipSuccess) e = hipMemset(c->gbits, 0, sizeof(uint64_t) * words);
+  if (e == hipSuccess) e = hipMemset(c->maps.frontier, 0, sizeof(uint64_t) * words);
+  if (e == hipSuccess) e = hipMemset(c->maps.gather, 0, sizeof(uint64_t) * words);
   if (e == hipSuccess) e = hipMemset(c->d_err, 0, sizeof(uint32_t));
   if (e == hipSuccess) e = hipMemset(c->counters, 0, 3 * sizeof(int32_t));
   if (e == hipSuccess) e = hipMemset(c->hs_expansions, 0, sizeof(unsigned long long));
@@ -627,9 +622,9 @@ int lgp_destroy(lgp_ctx* c) {
   (void)hipSetDevice(c->di.device);
   (void)hipDeviceSynchronize();
   free_cache(c);
-  void* ptrs[] = {c->row_tab, c->f_remap, c->topo_hot, c->feat_hot, c->fbits, c->gbits, c->chunk_counts,
+  void* ptrs[] = {c->row_tab, c->f_remap, c->topo_hot, c->feat_hot, c->maps.frontier, c->maps.gather, c->maps.status,
                   c->d_err,   c->counters, c->order_t, c->order_f,  c->lists, c->hs_n, c->pos_table, c->tile_sums, c->hs_expansions,
-                  c->seg, c->seg_counters, c->new_counts};
+                  c->seg, c->seg_counters};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (int h = 0; h < LGP_MAX_HOPS; ++h)
@@ -674,7 +669,6 @@ int lgp_build_hotness(lgp_ctx* c, const int32_t* train_ids, int64_t n_train, int
     const int32_t nb = int32_t(std::min<int64_t>(batch, n_train - lo));
     st = sample_core(c, train_ids + lo, nb, fanouts, n_hops, base_seed + uint64_t(b), nullptr, s);
     if (st != LGP_OK) return st;
-    launch_accumulate_sizes(c->hs_n, n_hops, c->hs_expansions, s);
   }
   c->hs_batches = n_batches;
   c->have_hot = true;
@@ -1098,8 +1092,8 @@ int lgp_sample_extract(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const 
     if (st != LGP_OK) return st;
   }
   const TopoView tv = topo_view(c);
-  uint32_t* fbits32 = reinterpret_cast<uint32_t*>(c->fbits);
-  uint32_t* gbits32 = reinterpret_cast<uint32_t*>(c->gbits);
+  uint32_t* fbits32 = reinterpret_cast<uint32_t*>(c->maps.frontier);
+  uint32_t* gbits32 = reinterpret_cast<uint32_t*>(c->maps.gather);
   const int n_groups = n_hops + 1;
   // group 0: the seeds' rows, extracted while the first hop is being sampled
   launch_begin_listing(c->di, seeds, n_seeds, out->gather_ids, c->seg, c->seg_counters, n_groups * 3, s);
@@ -1113,14 +1107,13 @@ int lgp_sample_extract(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const 
   int64_t cap = n_seeds;
   for (int h = 0; h < n_hops && st == LGP_OK; ++h) {
     launch_sample_hop(c->di, tv, frontier, out->n_frontier + h, cap, fanouts[h], h, rng_seed, out->nbr[h], out->cnt[h],
-                      fbits32, h == 0 ? gbits32 : nullptr, nullptr, c->d_err, s);
+                      fbits32, h == 0 ? gbits32 : nullptr, nullptr, c->d_err, c->maps.status, c->maps.geom.groups, s);
     // next frontier (if anyone needs it as a list) and the vertices this hop reached first, appended to the listing
     const bool want = (h + 1 < n_hops) || out->frontier[n_hops] != nullptr;
     int32_t* next = want ? out->frontier[h + 1] : nullptr;
     const bool last = h + 1 == n_hops;
-    launch_compact_new(c->di, c->fbits, c->gbits, c->n_chunks, c->chunk_counts, c->new_counts, next,
-                       next ? out->cap[h + 1] : 0, want ? out->n_frontier + h + 1 : nullptr, out->gather_ids,
-                       out->gather_cap, c->seg + h + 1, last ? out->n_gather : nullptr, c->d_err, s);
+    launch_compact_new(c->di, c->maps, next, next ? out->cap[h + 1] : 0, want ? out->n_frontier + h + 1 : nullptr,
+                       out->gather_ids, out->gather_cap, c->seg + h + 1, last ? out->n_gather : nullptr, c->d_err, s);
     LGP_HIP(c, hipEventRecord(c->ev_group[h + 1], s));
     LGP_HIP(c, hipStreamWaitEvent(x, c->ev_group[h + 1], 0));
     st = gather_core(c, -1, out->gather_ids, out->gather_cap, nullptr, rows, c->seg_counters + 3 * (h + 1), x, nullptr, 0,
@@ -1129,7 +1122,7 @@ int lgp_sample_extract(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const 
     cap = next ? out->cap[h + 1] : 0;
   }
   // the "seen" bitmap of this batch is not compacted (the listing replaces the ascending list), so clear it whole
-  launch_fill_i32(c->di, reinterpret_cast<int32_t*>(c->gbits), c->n_chunks * kChunkWords * 2, 0, s);
+  launch_fill_i32(c->di, reinterpret_cast<int32_t*>(c->maps.gather), c->maps.geom.words() * 2, 0, s);
   if (st == LGP_OK && stats) launch_sum_stats(c->seg_counters, n_groups, stats, x);
   if (st == LGP_OK && groups) {
     LGP_HIP(c, hipMemcpyAsync(groups, c->seg, sizeof(int32_t) * size_t(n_hops + 2), hipMemcpyDeviceToDevice, x));
@@ -1283,9 +1276,9 @@ int lgp_workspace_bytes(const lgp_ctx* c, int32_t max_seeds, const int32_t* fano
   }
   const size_t V = size_t(c->g.num_vertices);
   if (fixed) {
-    const size_t bitmap = size_t(c->n_chunks) * size_t(kChunkWords) * 8;
+    const size_t map = size_t(c->maps.geom.words()) * 8;
     // row table 8 + remap 4 + two hotness vectors 4 + 4 + two rankings 4 + 4 bytes per vertex
-    *fixed = V * 28 + 2 * bitmap + size_t(c->n_chunks) * 4 + 64;
+    *fixed = V * 28 + 2 * map + size_t(c->maps.geom.groups) * 8 + 64;
   }
   if (scratch) {
     int64_t need[LGP_MAX_HOPS + 1], gather_need;

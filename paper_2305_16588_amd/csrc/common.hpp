@@ -15,21 +15,15 @@ namespace lgp {
 // Device-side error bits (sticky, OR-ed into ctx->d_err).
 enum : uint32_t { ERR_BAD_ID = 1u, ERR_OVERRUN = 2u };
 
-// One dedup bitmap chunk = what one workgroup of the compaction kernels covers.
-constexpr int kCompactThreads = 256;
-constexpr int kWordsPerThread = 4;                                   // 64-bit words
-constexpr int64_t kChunkWords = int64_t(kCompactThreads) * kWordsPerThread;
-constexpr int64_t kChunkBits = kChunkWords * 64;                     // 65536 vertices per workgroup
-
 // Vertex v is bit (v << spread_shift) of a dedup map, and marking it means setting that bit.
 //   shift 0      one bit per vertex, set with an atomic OR.  Scattered atomics run at about 26 G/s on this
 //                chip whatever their scope or target, so they bound the sampler of a large graph.
 //   shift 3..5   a byte, half-word or word per vertex, set with a plain store of 1 (every writer of the entry
 //                stores the same value).  Scattered stores run at 78-162 G/s and do not serialise on hot
 //                lines, but the compaction has 8-32 times as many bytes to scan.
-// Measured for three-hop batches of 8192 seeds (15, 10, 5): at 2.4 M vertices the last hop's kernel takes 25 us
-// with bytes and 54 us with atomics (the best sparser bitmap, 4 bits per vertex); a whole call 76 -> 58 us at
-// 3 M vertices, 79 -> 71 at 6 M, 81 -> 86 at 12 M, 84 -> 106 at 25 M: bytes up to 2^23 vertices, bits beyond.
+// Measured for three-hop calls of 8192 seeds (15, 10, 5): at 2.4 M vertices the last hop's kernel takes 25 us
+// with bytes and 54 us with atomics (the best sparser bitmap, 4 bits per vertex); a whole call bits -> bytes
+// 79 -> 49 us at 3 M vertices, 74 -> 64 at 6 M, 74 -> 77 at 12 M, 74 -> 94 at 25 M: bytes up to 2^23 vertices.
 // Words instead of bytes on the smallest graphs keep neighbours' marks on different lines (10 k vertices:
 // 2 us of a 33-us call).
 constexpr int64_t kWordMapMaxVertices = int64_t(1) << 19;
@@ -39,6 +33,37 @@ inline int mark_shift(int64_t num_vertices) {
   return num_vertices <= kWordMapMaxVertices ? 5 : num_vertices <= kHalfMapMaxVertices ? 4
          : num_vertices <= kByteMapMaxVertices ? 3 : 0;
 }
+
+// How the compaction splits a map: `groups` workgroups of kCompactThreads threads, each thread taking
+// words_per_thread 64-bit words in each of `passes` passes.  Two workgroups fit a CU, so 512 of them run at
+// once; a larger map gets wider threads, then (beyond 2^28 bits) several passes.
+constexpr int kCompactThreads = 1024;
+constexpr int64_t kCompactMaxGroups = 512;
+constexpr int kMaxPasses = 8;             // 2^31 bits / (512 groups * 1024 threads * 8 words * 64 bits)
+struct MapGeom {
+  int words_per_thread = 2;
+  int passes = 1;
+  int64_t groups = 1;
+  int64_t words() const { return groups * passes * words_per_thread * kCompactThreads; }   // allocated, >= the map
+};
+inline MapGeom map_geometry(int64_t num_vertices, int shift) {
+  const int64_t need = ((num_vertices << shift) + 63) / 64;
+  MapGeom g;
+  auto groups = [&] { const int64_t share = int64_t(g.passes) * g.words_per_thread * kCompactThreads; return (need + share - 1) / share; };
+  while (g.words_per_thread < 8 && groups() > kCompactMaxGroups) g.words_per_thread *= 2;
+  while (groups() > kCompactMaxGroups) ++g.passes;
+  g.groups = groups();
+  return g;
+}
+
+// The two dedup maps of a context and the status words of the compaction kernel (one per workgroup).  Both maps
+// are clear between calls; every hop kernel clears the status words for the compaction that follows it.
+struct DedupMaps {
+  uint64_t* frontier = nullptr;
+  uint64_t* gather = nullptr;
+  uint64_t* status = nullptr;
+  MapGeom geom;
+};
 
 struct DeviceInfo {
   int device = 0;
@@ -71,29 +96,49 @@ struct TopoView {
 // (either may be null), marks every sampled neighbour in `mark_bits` (bit v << di.spread_shift),
 // adds cnt to topo_hot[v] if topo_hot is given.  With self_bits given (first hop) the
 // frontier is the seed list: exactly `cap` ids, *n_frontier is written (= cap) instead of
-// read, and every valid seed is marked in self_bits.
+// read, and every valid seed is marked in self_bits.  status[0 .. n_status) is cleared for the compaction
+// that follows.
 void launch_sample_hop(const DeviceInfo& di, const TopoView& tv, const int32_t* frontier, int32_t* n_frontier,
                        int64_t cap, int32_t fanout, int32_t hop, uint64_t rng_seed, int32_t* nbr, int32_t* cnt,
-                       uint32_t* mark_bits, uint32_t* self_bits, uint32_t* topo_hot, uint32_t* d_err, hipStream_t s);
-
-// acc[0] += n[0] + ... + n[count - 1]   (frontier sizes of one pre-sampling batch)
-void launch_accumulate_sizes(const int32_t* n, int32_t count, unsigned long long* acc, hipStream_t s);
+                       uint32_t* mark_bits, uint32_t* self_bits, uint32_t* topo_hot, uint32_t* d_err, uint64_t* status,
+                       int64_t n_status, hipStream_t s);
 
 // ---- compact.hip ----------------------------------------------------------
-// Turn the bitmap `bits` (n_chunks * kChunkWords 64-bit words, vertex v at bit v << di.spread_shift)
-// into the ascending id list out[0 .. *n_out).  If or_into is given, bits are OR-ed into it; `bits` is
-// cleared.  If bump is given, bump[id] += 1 for every set bit.  With n_out == nullptr no
-// list is produced: only the OR / clear / bump side effects happen.
-void launch_compact(const DeviceInfo& di, uint64_t* bits, uint64_t* or_into, int64_t n_chunks, int32_t* chunk_counts,
-                    int32_t* out, int64_t out_cap, int32_t* n_out, uint32_t* bump, uint32_t* d_err, hipStream_t s);
-
-// Compaction for the intra-batch pipeline: like launch_compact(bits, or_into = seen, ...), and in addition the
-// vertices marked in `bits` but not yet in `seen` -- the ones this hop reached first -- are appended, ascending,
-// to listed[seg[0] ..], and seg[1] = seg[0] + their number (seg: device int32 pair).  With n_out == nullptr no
-// frontier list is written; n_listed, if given, also receives seg[1].  new_counts: n_chunks ints of scratch.
-void launch_compact_new(const DeviceInfo& di, uint64_t* bits, uint64_t* seen, int64_t n_chunks, int32_t* chunk_counts,
-                        int32_t* new_counts, int32_t* out, int64_t out_cap, int32_t* n_out, int32_t* listed,
-                        int64_t listed_cap, int32_t* seg, int32_t* n_listed, uint32_t* d_err, hipStream_t s);
+struct CompactArgs {
+  uint64_t* bits;
+  uint64_t* other;
+  uint64_t* status;
+  int32_t* out;       // list of the marks in `bits`, nullptr = not wanted
+  int64_t out_cap;
+  int32_t* n_out;
+  int32_t* out2;      // second list
+  int64_t out2_cap;
+  int32_t* n_out2;
+  int32_t* seg;
+  uint32_t* d_err;
+  int32_t shift, passes;
+};
+// Frontier map -> ascending id list out[0 .. *n_out); its marks are added to the gather map, the frontier map is
+// cleared.  Every compaction follows a launch_sample_hop on the same stream, which clears the status words.
+void launch_compact(const DeviceInfo& di, const DedupMaps& m, int32_t* out, int64_t out_cap, int32_t* n_out,
+                    uint32_t* d_err, hipStream_t s);
+// Gather map -> ascending id list; the gather map is cleared.
+void launch_compact_gather(const DeviceInfo& di, const DedupMaps& m, int32_t* out, int64_t out_cap, int32_t* n_out,
+                           uint32_t* d_err, hipStream_t s);
+// Both of the above in one pass: out = the frontier map's ids, all = the ids of either map; both maps are cleared.
+void launch_compact_both(const DeviceInfo& di, const DedupMaps& m, int32_t* out, int64_t out_cap, int32_t* n_out,
+                         int32_t* all, int64_t all_cap, int32_t* n_all, uint32_t* d_err, hipStream_t s);
+// Compaction for the intra-batch pipeline: like launch_compact, and in addition the vertices not yet in the gather
+// map -- the ones this hop reached first -- are appended, ascending, to listed[seg[0] ..], and seg[1] = seg[0] +
+// their number (seg: device int32 pair).  With out == nullptr no frontier list is written; n_listed, if given, also
+// receives seg[1].
+void launch_compact_new(const DeviceInfo& di, const DedupMaps& m, int32_t* out, int64_t out_cap, int32_t* n_out,
+                        int32_t* listed, int64_t listed_cap, int32_t* seg, int32_t* n_listed, uint32_t* d_err,
+                        hipStream_t s);
+// Pre-sampling: bump[id] += 1 for every id of the gather map, which is cleared; acc[0] += sizes[0] + ... (the
+// frontier sizes of the batch).
+void launch_bump(const DeviceInfo& di, const DedupMaps& m, uint32_t* bump, const int32_t* sizes, int32_t n_sizes,
+                 unsigned long long* acc, hipStream_t s);
 // seg[0] = 0, seg[1] = n_seeds, listed[0 .. n_seeds) = seeds, counters[0 .. n_counters) = 0.
 void launch_begin_listing(const DeviceInfo& di, const int32_t* seeds, int64_t n_seeds, int32_t* listed, int32_t* seg,
                           int32_t* counters, int32_t n_counters, hipStream_t s);

@@ -31,11 +31,14 @@ __global__ __launch_bounds__(256) void sample_hop_kernel(
     const int32_t* __restrict__ t_indices, int64_t num_vertices,
     const int32_t* __restrict__ frontier, int32_t* __restrict__ n_frontier, int64_t cap, int32_t f, int32_t hop,
     uint32_t k0, uint32_t k1, int32_t* __restrict__ nbr, int32_t* __restrict__ cnt, uint32_t* __restrict__ mark_bits,
-    uint32_t* __restrict__ self_bits, uint32_t* __restrict__ topo_hot, uint32_t* __restrict__ d_err, int shift) {
+    uint32_t* __restrict__ self_bits, uint32_t* __restrict__ topo_hot, uint32_t* __restrict__ d_err, int shift,
+    uint64_t* __restrict__ status, int n_status) {
   constexpr int G = 256 / P;                      // vertices per workgroup pass
   // self_bits != nullptr: this is the first hop; the frontier is the caller's seed list of `cap`
   // ids, whose size is published here and whose members are marked in the gather set.
   if (self_bits && blockIdx.x == 0 && threadIdx.x == 0) *n_frontier = int32_t(cap);
+  if (blockIdx.x == 0)
+    for (int k = threadIdx.x; k < n_status; k += 256) status[k] = 0;
   int64_t n = self_bits ? cap : int64_t(*n_frontier);
   if (n > cap) n = cap;                           // never trust a count beyond the buffer
   const int i = threadIdx.x % P;                  // sample slot
@@ -108,19 +111,10 @@ __global__ __launch_bounds__(256) void sample_hop_kernel(
   }
 }
 
-__global__ void accumulate_sizes_kernel(const int32_t* __restrict__ n, int32_t count,
-                                        unsigned long long* __restrict__ acc) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    unsigned long long sum = 0;
-    for (int32_t h = 0; h < count; ++h) sum += (unsigned long long)(n[h]);
-    acc[0] += sum;                                // one writer, stream-ordered
-  }
-}
-
 template <typename IdxT, int P>
 void launch_one(const DeviceInfo& di, const TopoView& tv, const int32_t* frontier, int32_t* n_frontier,
                 int64_t cap, int32_t f, int32_t hop, uint64_t seed, int32_t* nbr, int32_t* cnt, uint32_t* mark_bits,
-                uint32_t* self_bits, uint32_t* topo_hot, uint32_t* d_err, hipStream_t s) {
+                uint32_t* self_bits, uint32_t* topo_hot, uint32_t* d_err, uint64_t* status, int64_t n_status, hipStream_t s) {
   constexpr int G = 256 / P;
   int64_t blocks = (cap + G - 1) / G;
   // 4 workgroups x 4 waves = 16 waves per CU.  The kernel is bound by scattered marks and
@@ -133,17 +127,17 @@ void launch_one(const DeviceInfo& di, const TopoView& tv, const int32_t* frontie
   hipLaunchKernelGGL((sample_hop_kernel<IdxT, P>), dim3(unsigned(blocks)), dim3(256), 0, s,
                      tv.row_tab, static_cast<const IdxT*>(tv.h_indptr), tv.h_indices, tv.t_indices,
                      tv.num_vertices, frontier, n_frontier, cap, f, hop, uint32_t(seed), uint32_t(seed >> 32), nbr,
-                     cnt, mark_bits, self_bits, topo_hot, d_err, di.spread_shift);
+                     cnt, mark_bits, self_bits, topo_hot, d_err, di.spread_shift, status, int(n_status));
 }
 
 template <typename IdxT>
 void dispatch_p(int P, const DeviceInfo& di, const TopoView& tv, const int32_t* frontier, int32_t* n_frontier,
                 int64_t cap, int32_t f, int32_t hop, uint64_t seed, int32_t* nbr, int32_t* cnt, uint32_t* mark_bits,
-                uint32_t* self_bits, uint32_t* topo_hot, uint32_t* d_err, hipStream_t s) {
+                uint32_t* self_bits, uint32_t* topo_hot, uint32_t* d_err, uint64_t* status, int64_t n_status, hipStream_t s) {
 #define LGP_CASE(PP)                                                                                            \
   case PP:                                                                                                      \
     launch_one<IdxT, PP>(di, tv, frontier, n_frontier, cap, f, hop, seed, nbr, cnt, mark_bits, self_bits, topo_hot, \
-                         d_err, s);                                                                              \
+                         d_err, status, n_status, s);                                                            \
     break;
   switch (P) {
     LGP_CASE(1) LGP_CASE(2) LGP_CASE(4) LGP_CASE(8) LGP_CASE(16) LGP_CASE(32) LGP_CASE(64)
@@ -155,19 +149,15 @@ void dispatch_p(int P, const DeviceInfo& di, const TopoView& tv, const int32_t* 
 
 void launch_sample_hop(const DeviceInfo& di, const TopoView& tv, const int32_t* frontier, int32_t* n_frontier,
                        int64_t cap, int32_t fanout, int32_t hop, uint64_t rng_seed, int32_t* nbr, int32_t* cnt,
-                       uint32_t* mark_bits, uint32_t* self_bits, uint32_t* topo_hot, uint32_t* d_err, hipStream_t s) {
+                       uint32_t* mark_bits, uint32_t* self_bits, uint32_t* topo_hot, uint32_t* d_err, uint64_t* status, int64_t n_status, hipStream_t s) {
   int P = 1;
   while (P < fanout) P <<= 1;
   if (tv.indptr_bytes == 8)
     dispatch_p<int64_t>(P, di, tv, frontier, n_frontier, cap, fanout, hop, rng_seed, nbr, cnt, mark_bits, self_bits,
-                        topo_hot, d_err, s);
+                        topo_hot, d_err, status, n_status, s);
   else
     dispatch_p<int32_t>(P, di, tv, frontier, n_frontier, cap, fanout, hop, rng_seed, nbr, cnt, mark_bits, self_bits,
-                        topo_hot, d_err, s);
-}
-
-void launch_accumulate_sizes(const int32_t* n, int32_t count, unsigned long long* acc, hipStream_t s) {
-  hipLaunchKernelGGL(accumulate_sizes_kernel, dim3(1), dim3(64), 0, s, n, count, acc);
+                        topo_hot, d_err, status, n_status, s);
 }
 
 }  // namespace lgp
