@@ -17,12 +17,37 @@
 #include <hip/hip_ext.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace lgp {
 namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// A row is copied in chunks of sizeof(VecT) bytes.  RAGGED: row width or addresses are no multiple of that; the
+// chunks then start at any even address (global loads and stores of any width may), and the last one ends where
+// the row ends, overlapping the one before it with the same bytes.  Copying such rows in the widest chunk that
+// divides them instead leaves most of a lane's 16 bytes unused: cached rows of 150 bytes (238 k) took 74 us in
+// 2-byte chunks and take 20.5, of 602 bytes 296 and 72, of 200 bytes (8-byte chunks) 27.5 and 23.
+template <typename VecT, bool RAGGED>
+struct Chunk {
+  typedef VecT T;
+};
+template <typename VecT>
+struct Chunk<VecT, true> {
+  typedef VecT T __attribute__((aligned(2)));
+};
+struct RowShape {
+  uint32_t cpr;    // chunks per row
+  uint32_t bytes;  // row width
+  uint32_t last;   // where the last chunk starts: bytes - sizeof(VecT)
+};
+template <typename VecT, bool RAGGED>
+__device__ __forceinline__ uint32_t chunk_at(const RowShape& r, uint32_t col) {
+  const uint32_t at = col * uint32_t(sizeof(VecT));
+  return RAGGED ? (at < r.last ? at : r.last) : at;
+}
 
 __global__ void zero_counters_kernel(int32_t* counters, int n) {
   if (int(threadIdx.x) < n) counters[threadIdx.x] = 0;
@@ -130,13 +155,14 @@ __device__ __forceinline__ int32_t direct_source(const DirectIds& dir, int32_t e
 // all 64 lanes stay busy for any row width and UNROLL loads per lane are in flight
 // before the first store.  Output rows are written once and not read again by this
 // path, so they are stored non-temporally.
-template <typename VecT, int UNROLL, bool NT_LOAD>
-__global__ __launch_bounds__(256) void gather_rows_flat_kernel(const VecT* __restrict__ src, VecT* __restrict__ dst,
-                                                               uint32_t cpr, uint64_t inv_cpr,
+template <typename VecT, bool RAGGED, int UNROLL, bool NT_LOAD>
+__global__ __launch_bounds__(256) void gather_rows_flat_kernel(const char* __restrict__ src, char* __restrict__ dst,
+                                                               RowShape shape, uint64_t inv_cpr,
                                                                const int32_t* __restrict__ row,
                                                                const int32_t* __restrict__ srcrow, int64_t n_max,
                                                                const int32_t* __restrict__ n_dev, DirectIds dir,
                                                                int epw) {
+  typedef typename Chunk<VecT, RAGGED>::T Mem;
   int64_t n = n_dev ? int64_t(*n_dev) : n_max;
   int64_t lo = 0;
   if (dir.window) {                                 // entries [window[0], window[1]) only
@@ -156,6 +182,7 @@ __global__ __launch_bounds__(256) void gather_rows_flat_kernel(const VecT* __res
     const int32_t my_row = mine ? (row ? row[e] : int32_t(e)) : 0;
     const int32_t my_src = direct_source(dir, mine ? (srcrow ? srcrow[e] : int32_t(e)) : 0, mine);
     const uint32_t entries = uint32_t(n - e0 < epw ? n - e0 : epw);
+    const uint32_t cpr = shape.cpr;
     const uint32_t total = entries * cpr;          // chunks in this wave's 64 rows
     for (uint32_t f0 = 0; f0 < total; f0 += 64 * UNROLL) {
       VecT val[UNROLL];
@@ -170,13 +197,23 @@ __global__ __launch_bounds__(256) void gather_rows_flat_kernel(const VecT* __res
         const int32_t r = __shfl(my_row, int(k), 64);
         const int32_t sr = __shfl(my_src, int(k), 64);
         ok[u] = ok[u] && sr >= 0;
-        doff[u] = int64_t(r) * cpr + col;
-        if (ok[u])
-          val[u] = NT_LOAD ? __builtin_nontemporal_load(src + int64_t(sr) * cpr + col) : src[int64_t(sr) * cpr + col];
+        if (RAGGED) {
+          const uint32_t at = chunk_at<VecT, true>(shape, col);
+          doff[u] = int64_t(r) * shape.bytes + at;
+          const Mem* from = reinterpret_cast<const Mem*>(src + (int64_t(sr) * shape.bytes + at));
+          if (ok[u]) val[u] = NT_LOAD ? __builtin_nontemporal_load(from) : *from;
+        } else {                                   // whole chunks: indexes, not bytes (1 % at 256-byte rows)
+          doff[u] = int64_t(r) * cpr + col;
+          const VecT* from = reinterpret_cast<const VecT*>(src);
+          if (ok[u])
+            val[u] = NT_LOAD ? __builtin_nontemporal_load(from + int64_t(sr) * cpr + col) : from[int64_t(sr) * cpr + col];
+        }
       }
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u)
-        if (ok[u]) __builtin_nontemporal_store(val[u], dst + doff[u]);
+        if (ok[u])
+          __builtin_nontemporal_store(val[u], RAGGED ? reinterpret_cast<Mem*>(dst + doff[u])
+                                                     : reinterpret_cast<Mem*>(reinterpret_cast<VecT*>(dst) + doff[u]));
     }
   }
 }
@@ -188,11 +225,14 @@ __global__ __launch_bounds__(256) void gather_rows_flat_kernel(const VecT* __res
 // line of the row exactly once; UNROLL rows per group are in flight before the first
 // store.  Rows wider than 64 chunks are walked in 64-chunk pieces.  HBM_SOURCE selects the
 // variant used for cache hits on rows that straddle lines (cached loads, streaming stores).
-template <typename VecT, int G, int UNROLL, bool HBM_SOURCE>
-__global__ __launch_bounds__(256) void gather_rows_group_kernel(const VecT* __restrict__ src, VecT* __restrict__ dst,
-                                                                uint32_t cpr, const int32_t* __restrict__ row,
+template <typename VecT, bool RAGGED, int G, int UNROLL, bool HBM_SOURCE>
+__global__ __launch_bounds__(256) void gather_rows_group_kernel(const char* __restrict__ src, char* __restrict__ dst,
+                                                                RowShape shape, const int32_t* __restrict__ row,
                                                                 const int32_t* __restrict__ srcrow, int64_t n_max,
                                                                 const int32_t* __restrict__ n_dev, DirectIds dir) {
+  // carried pointers keep their address space only if it is spelled out
+  typedef __attribute__((address_space(1))) char Global;
+  typedef __attribute__((address_space(1))) typename Chunk<VecT, RAGGED>::T GlobalMem;
   int64_t n = n_dev ? int64_t(*n_dev) : n_max;
   int64_t lo = 0;
   if (dir.window) {
@@ -220,24 +260,42 @@ __global__ __launch_bounds__(256) void gather_rows_group_kernel(const VecT* __re
     for (int u = 0; u < UNROLL; ++u) {
       const bool ok = e0 + u < n;
       const int32_t sr = direct_source(dir, next_src[u], ok);
-      so[u] = sr >= 0 ? int64_t(sr) * cpr : -1;
-      dof[u] = int64_t(next_row[u]) * cpr;
+      so[u] = sr >= 0 ? int64_t(sr) * shape.bytes : -1;
+      dof[u] = int64_t(next_row[u]) * shape.bytes;
       const int64_t e = e0 + n_groups * UNROLL + u;
       next_src[u] = e < n ? (srcrow ? srcrow[e] : int32_t(e)) : 0;
       next_row[u] = e < n ? (row ? row[e] : int32_t(e)) : 0;
     }
-    for (uint32_t c0 = 0; c0 < cpr; c0 += G) {
-      const uint32_t col = c0 + sub;
+    // Addresses are carried from piece to piece: computed at the load they would share its registers and make it
+    // wait for the entries requested above (38 -> 44 us on 400-byte rows).
+    uint32_t at = chunk_at<VecT, RAGGED>(shape, sub);
+    const Global* from[UNROLL];
+    Global* to[UNROLL];
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      from[u] = (const Global*)(src) + (so[u] + at);
+      to[u] = (Global*)(dst) + (dof[u] + at);
+    }
+    for (uint32_t c0 = 0; c0 < shape.cpr; c0 += G) {
+      const bool in_row = c0 + sub < shape.cpr;
       VecT val[UNROLL];
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u)
-        if (so[u] >= 0 && col < cpr) val[u] = HBM_SOURCE ? src[so[u] + col] : __builtin_nontemporal_load(src + so[u] + col);
+        if (so[u] >= 0 && in_row)
+          val[u] = HBM_SOURCE ? *(const GlobalMem*)(from[u]) : __builtin_nontemporal_load((const GlobalMem*)(from[u]));
 #pragma unroll
       for (int u = 0; u < UNROLL; ++u)
-        if (so[u] >= 0 && col < cpr) {
-          if (HBM_SOURCE) __builtin_nontemporal_store(val[u], dst + dof[u] + col);
-          else dst[dof[u] + col] = val[u];
+        if (so[u] >= 0 && in_row) {
+          if (HBM_SOURCE) __builtin_nontemporal_store(val[u], (GlobalMem*)(to[u]));
+          else *(GlobalMem*)(to[u]) = val[u];
         }
+      const uint32_t next = chunk_at<VecT, RAGGED>(shape, c0 + G + sub);
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) {
+        from[u] += next - at;
+        to[u] += next - at;
+      }
+      at = next;
     }
   }
 }
@@ -263,11 +321,11 @@ void launch_on(const Where& w, K kernel, unsigned blocks, Args... args) {
   else hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, w.s, args...);
 }
 
-template <typename VecT>
-void launch_flat(const DeviceInfo& di, const void* src, void* dst, int64_t row_bytes, const int32_t* row,
+template <typename VecT, bool RAGGED>
+void launch_flat(const DeviceInfo& di, const char* src, char* dst, const RowShape& shape, const int32_t* row,
                  const int32_t* srcrow, int64_t n_max, const int32_t* n_dev, const DirectIds& dir, const Where& s) {
-  const uint32_t cpr = uint32_t(row_bytes / int64_t(sizeof(VecT)));
-  const uint64_t inv = (uint64_t(1) << 32) / cpr + 1;          // exact for flat < 64 * cpr, cpr <= 4096
+  const int64_t row_bytes = shape.bytes;
+  const uint64_t inv = (uint64_t(1) << 32) / shape.cpr + 1;          // exact for flat < 64 * cpr, cpr <= 4096
   // Three workgroups (12 waves) per CU: the flat walk keeps 4 x 16 bytes per lane in flight, and more
   // waves than that only add concurrent streams for the memory system to interleave -- measured hit
   // gather at 8 / 4 / 3 / 2 workgroups per CU: 51.3 / 48.9 / 48.3 / 49.0 us on 505 k 256-byte rows,
@@ -283,15 +341,13 @@ void launch_flat(const DeviceInfo& di, const void* src, void* dst, int64_t row_b
   // rows).  Rows that straddle lines share their boundary lines between consecutive load
   // instructions, and L2 has to merge those (non-temporal loads cost 7 % on 400-B rows).
   if (row_bytes % 128 == 0)
-    launch_on(s, gather_rows_flat_kernel<VecT, 4, true>, blocks,
-                       static_cast<const VecT*>(src), static_cast<VecT*>(dst), cpr, inv, row, srcrow, n_max, n_dev, dir, epw);
+    launch_on(s, gather_rows_flat_kernel<VecT, RAGGED, 4, true>, blocks, src, dst, shape, inv, row, srcrow, n_max, n_dev, dir, epw);
   else
-    launch_on(s, gather_rows_flat_kernel<VecT, 4, false>, blocks,
-                       static_cast<const VecT*>(src), static_cast<VecT*>(dst), cpr, inv, row, srcrow, n_max, n_dev, dir, epw);
+    launch_on(s, gather_rows_flat_kernel<VecT, RAGGED, 4, false>, blocks, src, dst, shape, inv, row, srcrow, n_max, n_dev, dir, epw);
 }
 
-template <typename VecT, int G>
-void launch_group_g(const DeviceInfo& di, const void* src, void* dst, uint32_t cpr, const int32_t* row,
+template <typename VecT, bool RAGGED, int G>
+void launch_group_g(const DeviceInfo& di, const char* src, char* dst, const RowShape& shape, const int32_t* row,
                     const int32_t* srcrow, int64_t n_max, const int32_t* n_dev, const DirectIds& dir, const Where& s) {
   constexpr int U = 4;
   // PCIe needs far fewer waves than HBM to stay saturated (bandwidth x latency is ~150 KB): one
@@ -299,42 +355,39 @@ void launch_group_g(const DeviceInfo& di, const void* src, void* dst, uint32_t c
   // (400-B rows 44.9 -> 44.0 GB/s, 2-KiB rows 57.5 -> 55.7 GB/s from 64 to 512 workgroups), because the
   // excess requests only queue up in front of the link.
   const unsigned blocks = blocks_for((s.items + (256 / G) * U - 1) / ((256 / G) * U), std::max(1, di.num_cus / 4));
-  launch_on(s, gather_rows_group_kernel<VecT, G, U, false>, blocks,
-                     static_cast<const VecT*>(src), static_cast<VecT*>(dst), cpr, row, srcrow, n_max, n_dev, dir);
+  launch_on(s, gather_rows_group_kernel<VecT, RAGGED, G, U, false>, blocks, src, dst, shape, row, srcrow, n_max, n_dev, dir);
 }
 
 // Cache hits whose rows straddle 128-byte lines (e.g. 400-byte rows): one lane group per row, one
 // row per group in flight.  Every line of a row is then requested by a single load instruction,
 // which beats the flat walk by ~5 % on such rows; rows made of whole lines stay with the flat kernel.
-template <typename VecT, int G>
-void launch_group_hbm_g(const DeviceInfo& di, const void* src, void* dst, uint32_t cpr, const int32_t* row,
+template <typename VecT, bool RAGGED, int G>
+void launch_group_hbm_g(const DeviceInfo& di, const char* src, char* dst, const RowShape& shape, const int32_t* row,
                         const int32_t* srcrow, int64_t n_max, const int32_t* n_dev, const DirectIds& dir,
                         const Where& s) {
   // one row per group in flight needs more waves than the flat walk: 6 workgroups per CU (400-byte rows,
   // 512 k hits: 138.7 / 107.6 / 95.6 / 90.7 / 91.4 us at 2 / 3 / 4 / 6 / 8 workgroups per CU)
   const unsigned blocks = blocks_for((s.items + 256 / G - 1) / (256 / G), std::min<int64_t>(s.hbm_blocks, int64_t(di.num_cus) * 6));
-  launch_on(s, gather_rows_group_kernel<VecT, G, 1, true>, blocks,
-                     static_cast<const VecT*>(src), static_cast<VecT*>(dst), cpr, row, srcrow, n_max, n_dev, dir);
+  launch_on(s, gather_rows_group_kernel<VecT, RAGGED, G, 1, true>, blocks, src, dst, shape, row, srcrow, n_max, n_dev, dir);
 }
 
-template <typename VecT>
-void launch_group_hbm(const DeviceInfo& di, const void* src, void* dst, uint32_t cpr, const int32_t* row,
+template <typename VecT, bool RAGGED>
+void launch_group_hbm(const DeviceInfo& di, const char* src, char* dst, const RowShape& shape, const int32_t* row,
                       const int32_t* srcrow, int64_t n_max, const int32_t* n_dev, const DirectIds& dir, const Where& s) {
-  if (cpr <= 4) launch_group_hbm_g<VecT, 4>(di, src, dst, cpr, row, srcrow, n_max, n_dev, dir, s);
-  else if (cpr <= 8) launch_group_hbm_g<VecT, 8>(di, src, dst, cpr, row, srcrow, n_max, n_dev, dir, s);
-  else if (cpr <= 16) launch_group_hbm_g<VecT, 16>(di, src, dst, cpr, row, srcrow, n_max, n_dev, dir, s);
-  else launch_group_hbm_g<VecT, 32>(di, src, dst, cpr, row, srcrow, n_max, n_dev, dir, s);
+  if (shape.cpr <= 4) launch_group_hbm_g<VecT, RAGGED, 4>(di, src, dst, shape, row, srcrow, n_max, n_dev, dir, s);
+  else if (shape.cpr <= 8) launch_group_hbm_g<VecT, RAGGED, 8>(di, src, dst, shape, row, srcrow, n_max, n_dev, dir, s);
+  else if (shape.cpr <= 16) launch_group_hbm_g<VecT, RAGGED, 16>(di, src, dst, shape, row, srcrow, n_max, n_dev, dir, s);
+  else launch_group_hbm_g<VecT, RAGGED, 32>(di, src, dst, shape, row, srcrow, n_max, n_dev, dir, s);
 }
 
-template <typename VecT>
-void launch_group(const DeviceInfo& di, const void* src, void* dst, int64_t row_bytes, const int32_t* row,
+template <typename VecT, bool RAGGED>
+void launch_group(const DeviceInfo& di, const char* src, char* dst, const RowShape& shape, const int32_t* row,
                   const int32_t* srcrow, int64_t n_max, const int32_t* n_dev, const DirectIds& dir, const Where& s) {
-  const uint32_t cpr = uint32_t(row_bytes / int64_t(sizeof(VecT)));
-  if (cpr <= 4) launch_group_g<VecT, 4>(di, src, dst, cpr, row, srcrow, n_max, n_dev, dir, s);
-  else if (cpr <= 8) launch_group_g<VecT, 8>(di, src, dst, cpr, row, srcrow, n_max, n_dev, dir, s);
-  else if (cpr <= 16) launch_group_g<VecT, 16>(di, src, dst, cpr, row, srcrow, n_max, n_dev, dir, s);
-  else if (cpr <= 32) launch_group_g<VecT, 32>(di, src, dst, cpr, row, srcrow, n_max, n_dev, dir, s);
-  else launch_group_g<VecT, 64>(di, src, dst, cpr, row, srcrow, n_max, n_dev, dir, s);
+  if (shape.cpr <= 4) launch_group_g<VecT, RAGGED, 4>(di, src, dst, shape, row, srcrow, n_max, n_dev, dir, s);
+  else if (shape.cpr <= 8) launch_group_g<VecT, RAGGED, 8>(di, src, dst, shape, row, srcrow, n_max, n_dev, dir, s);
+  else if (shape.cpr <= 16) launch_group_g<VecT, RAGGED, 16>(di, src, dst, shape, row, srcrow, n_max, n_dev, dir, s);
+  else if (shape.cpr <= 32) launch_group_g<VecT, RAGGED, 32>(di, src, dst, shape, row, srcrow, n_max, n_dev, dir, s);
+  else launch_group_g<VecT, RAGGED, 64>(di, src, dst, shape, row, srcrow, n_max, n_dev, dir, s);
 }
 
 }  // namespace
@@ -370,19 +423,34 @@ void launch_gather_rows(const DeviceInfo& di, const void* src, void* dst, int64_
   // gather, 2.24 ms beside a narrow one, and the step 2.49 ms instead of 2.66 ms).
   const Where s{stream, ev_start, ev_stop, int64_t(di.num_cus) * (beside_pcie ? 2 : 8),
                 (grid_items > 0 && grid_items < n_max) ? grid_items : n_max};
+  // The widest chunk that fits the row; RAGGED (see Chunk) where rows or addresses are no multiple of it.  Over PCIe
+  // a chunk that straddles two lines requests one of them a second time, so there a row that divides into at most
+  // 32 aligned chunks of 4 or 8 bytes -- one load instruction of a 32-lane group -- keeps them (200-byte rows: 240 us
+  // ragged, 233 aligned; 100-byte rows 181 / 179; but 50-byte rows of 2-byte chunks 150 ragged, 154 aligned, and
+  // rows of more chunks 302 / 329 at 300 bytes, 509 / 1060 at 602).
   const uintptr_t align = uintptr_t(src) | uintptr_t(dst) | uintptr_t(row_bytes);
-#define LGP_ROWS(VecT)                                                                        \
-  do {                                                                                        \
-    if (streaming) launch_group<VecT>(di, src, dst, row_bytes, row, srcrow, n_max, n_dev, dir, s); \
-    else if (row_bytes % 128 != 0 && row_bytes / sizeof(VecT) <= 32)                               \
-      launch_group_hbm<VecT>(di, src, dst, uint32_t(row_bytes / sizeof(VecT)), row, srcrow, n_max, n_dev, dir, s); \
-    else launch_flat<VecT>(di, src, dst, row_bytes, row, srcrow, n_max, n_dev, dir, s);            \
-  } while (0)
-  if ((align & 15u) == 0) LGP_ROWS(u32x4);
-  else if ((align & 7u) == 0) LGP_ROWS(u32x2);
-  else if ((align & 3u) == 0) LGP_ROWS(uint32_t);
-  else LGP_ROWS(uint16_t);
-#undef LGP_ROWS
+  int64_t width = row_bytes >= 16 ? 16 : row_bytes >= 8 ? 8 : row_bytes >= 4 ? 4 : 2;
+  const int64_t whole = (align & 15) == 0 ? 16 : (align & 7) == 0 ? 8 : (align & 3) == 0 ? 4 : 2;
+  if (streaming && whole >= 4 && row_bytes / whole <= 32) width = whole;
+  const RowShape shape{uint32_t((row_bytes + width - 1) / width), uint32_t(row_bytes), uint32_t(row_bytes - width)};
+  const char* from = static_cast<const char*>(src);
+  char* to = static_cast<char*>(dst);
+  auto rows = [&](auto vec, auto ragged) {
+    typedef decltype(vec) VecT;
+    constexpr bool kRagged = decltype(ragged)::value;
+    if (streaming) launch_group<VecT, kRagged>(di, from, to, shape, row, srcrow, n_max, n_dev, dir, s);
+    else if (row_bytes % 128 != 0 && shape.cpr <= 32)
+      launch_group_hbm<VecT, kRagged>(di, from, to, shape, row, srcrow, n_max, n_dev, dir, s);
+    else launch_flat<VecT, kRagged>(di, from, to, shape, row, srcrow, n_max, n_dev, dir, s);
+  };
+  auto width_of = [&](auto vec) {
+    if ((align & uintptr_t(width - 1)) == 0) rows(vec, std::false_type{});
+    else rows(vec, std::true_type{});
+  };
+  if (width == 16) width_of(u32x4{});
+  else if (width == 8) width_of(u32x2{});
+  else if (width == 4) width_of(uint32_t{});
+  else rows(uint16_t{}, std::false_type{});
 }
 
 }  // namespace lgp

@@ -74,3 +74,34 @@ def test_compaction_of_large_maps(V):
         assert (fr[2] == ref.frontier[2]).all() and listing.tolist() == ref.hop_order.tolist()
         assert rows[:listing.size].cpu().numpy().tobytes() == orc.gather(listing).tobytes()
     ctx.check()
+
+
+@pytest.mark.parametrize("row_bytes", [2, 4, 6, 10, 12, 14, 18, 30, 34, 62, 66, 126, 130, 150, 254, 258, 386, 510, 514,
+                                       1022, 1030, 2050, 4100, 8190])
+@pytest.mark.parametrize("shift", [0, 1, 2])
+def test_rows_of_any_even_width_and_alignment(row_bytes, shift):
+    """Rows copied in chunks that do not divide them, into an output that starts `shift` fp16 values off: every byte
+    of every row, and not one byte beside them, through both direct paths and the partitioned one."""
+    import paper_2305_16588_amd as lgp
+    V, D = 700, row_bytes // 2
+    rng = np.random.default_rng(row_bytes)
+    feats = lgp.pinned_empty((V, D), np.float16)
+    feats.view(np.uint16)[...] = rng.integers(0, 1 << 16, (V, D), dtype=np.uint16)
+    ctx = lgp.Context(lgp.pinned_copy(np.zeros(V + 1, np.int32)), lgp.pinned_empty(1, np.int32)[:0], feats)
+    ids = rng.integers(0, V, 611).astype(np.int32)
+    dev = torch.from_numpy(ids).cuda()
+    want = feats.view(np.uint16)[ids].reshape(-1)
+    ctx.set_hotness(np.zeros(V, np.uint32), rng.integers(0, 9, V).astype(np.uint32))
+    for n_cached in (0, 300, V):
+        ctx.build_cache(0, n_cached * row_bytes)
+        flat = torch.full((ids.size * D + 16,), 21845, dtype=torch.int16, device="cuda")
+        out = flat[shift:shift + ids.size * D].view(torch.float16).view(ids.size, D)
+        try:
+            ctx.gather_features(dev, out=out)
+        except lgp.LegionPrepError as e:
+            assert e.status == -4 and row_bytes // 2 > 4096       # refused widths stay refused
+            continue
+        got = flat.cpu().numpy().view(np.uint16)
+        assert (got[shift:shift + want.size] == want).all(), f"{n_cached} rows cached"
+        assert (got[:shift] == 21845).all() and (got[shift + want.size:] == 21845).all()
+    ctx.check()
