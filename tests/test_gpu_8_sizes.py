@@ -105,3 +105,34 @@ def test_rows_of_any_even_width_and_alignment(row_bytes, shift):
         assert (got[shift:shift + want.size] == want).all(), f"{n_cached} rows cached"
         assert (got[:shift] == 21845).all() and (got[shift + want.size:] == 21845).all()
     ctx.check()
+
+
+@pytest.mark.parametrize("V,fanouts,n_seeds", [(1, (2,), 1), (2, (2, 2), 2), (3, (1, 64), 3), (65, (5, 4), 9), (1500, (64, 3), 40),
+                                               (200_000, (3, 2), 700), (200_000, (1, 1, 1), 256), (200_000, (25, 10), 1025)])
+@pytest.mark.parametrize("span", [1.0, 0.02])
+def test_blocks_of_dense_sparse_and_clustered_frontiers(V, fanouts, n_seeds, span):
+    """The frontiers' bucket index: more and fewer ids than vertices to spread them over, ids in one corner of the
+    range (long empty stretches, full buckets), hops whose destinations are and are not whole tiles."""
+    from gpu_common import assert_batch_equal, assert_blocks_equal
+    import oracle
+    import paper_2305_16588_amd as lgp
+    rng = np.random.default_rng(V + n_seeds)
+    d = rng.integers(0, 12, V)
+    indptr = np.zeros(V + 1, np.int32)
+    np.cumsum(d, out=indptr[1:])
+    lo = int(V * (1 - span) * 0.7)
+    indices = (lo + rng.integers(0, max(1, int(V * span)), int(indptr[-1]))).astype(np.int32)
+    indices = np.minimum(indices, V - 1)
+    ctx = lgp.Context(lgp.pinned_copy(indptr), lgp.pinned_copy(indices))
+    orc = oracle.Oracle(indptr, indices, None)
+    seeds = np.sort(rng.permutation(V)[:n_seeds]).astype(np.int32)
+    seeds_dev = torch.from_numpy(seeds).cuda()
+    buf = lgp.SampleBuffers(V, n_seeds, fanouts, last_frontier=True)
+    blk = lgp.BlockBuffers(buf)
+    for rep in range(2):
+        ctx.sample_khop(seeds_dev, fanouts, 90 + rep, out=buf)
+        ctx.build_blocks(seeds_dev, fanouts, buf, out=blk)
+        ref = orc.sample_khop(seeds, fanouts, 90 + rep, blocks=True)
+        assert_batch_equal(ref, buf.to_host(seeds_dev), f"{V} {fanouts}")
+        assert_blocks_equal(ref, blk.to_host(), f"{V} {fanouts}")
+    ctx.check()
