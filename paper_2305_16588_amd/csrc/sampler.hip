@@ -6,7 +6,7 @@
 // in place over PCIe), so an uncached vertex costs one PCIe round trip, not two.  All slots draw their
 // Philox number at once; Floyd's sequential "already taken?" test becomes fanout-1
 // group broadcasts.  The kernel is bound by dependent loads and, on large graphs, by the bitmap
-// atomics, not by issue slots, so the grid is capped at four workgroups per CU (see launch_one).
+// atomics, not by issue slots, so the grid is capped at six workgroups per CU (see launch_one).
 #include "common.hpp"
 #include "philox_dev.hpp"
 
@@ -117,11 +117,10 @@ void launch_one(const DeviceInfo& di, const TopoView& tv, const int32_t* frontie
                 uint32_t* self_bits, uint32_t* topo_hot, uint32_t* d_err, uint64_t* status, int64_t n_status, hipStream_t s) {
   constexpr int G = 256 / P;
   int64_t blocks = (cap + G - 1) / G;
-  // 4 workgroups x 4 waves = 16 waves per CU.  The kernel is bound by scattered marks and
-  // dependent loads, not by issue slots: 16 waves per CU are as fast as 32 when it runs alone
-  // (0.133 -> 0.128 ms per batch at 2.4 M vertices, 0.1025 -> 0.100 ms at 111 M) and disturb a
-  // PCIe-bound gather running beside it less (pipelined step 2.50 -> 2.43 ms).
-  const int64_t full = int64_t(di.num_cus) * 4;
+  // Six workgroups (24 waves) per CU: the kernel is bound by scattered marks and dependent loads, not by issue slots.
+  // Calls at 4 / 6 / 8 per CU: 2.4 M vertices, half of the topology over PCIe 279.9 / 276.3 / 276.4 us, 111 M vertices
+  // 67.7 / 64.8 / 67.0, 250 M 63.3 / 61.7 / 63.4; sampling server step at 2.4 M 194.6 / 189.9 / 192.6.
+  const int64_t full = int64_t(di.num_cus) * 6;
   if (blocks > full) blocks = full;
   if (blocks < 1) blocks = 1;
   hipLaunchKernelGGL((sample_hop_kernel<IdxT, P>), dim3(unsigned(blocks)), dim3(256), 0, s,
