@@ -243,9 +243,9 @@ def measure(inp: Inputs, steps: int, warmup: int, reps: int, topo_frac=None, fea
     # kernel names as rocprofv3 lists them (16-byte chunks; lane groups of the next power of two >= chunks per row)
     cpr = row_bytes // 16
     grp = next(g for g in (4, 8, 16, 32, 64) if g >= min(cpr, 64))
-    hit_kernel = (f"gather_rows_group_kernel<u32x4, {grp}, 1, true>" if row_bytes % 128 and cpr <= 32
-                  else f"gather_rows_flat_kernel<u32x4, 4, {'true' if row_bytes % 128 == 0 else 'false'}>")
-    miss_kernel = f"gather_rows_group_kernel<u32x4, {grp}, 4, false>"
+    hit_kernel = (f"gather_rows_group_kernel<u32x4, false, {grp}, 1, true>" if row_bytes % 128 and cpr <= 32
+                  else f"gather_rows_flat_kernel<u32x4, false, 4, {'true' if row_bytes % 128 == 0 else 'false'}>")
+    miss_kernel = f"gather_rows_group_kernel<u32x4, false, {grp}, 4, false>"
     roofline = None
     if prof_g.n_hit and hit_rows:
         ach = hit_rows * hit_bytes_per_row / (prof_g.ms_hit * 1e-3) / 1e9
@@ -274,8 +274,7 @@ def measure(inp: Inputs, steps: int, warmup: int, reps: int, topo_frac=None, fea
         ms_call = prof.ms_sample / prof.n_sample
         ach = sampler_bytes / steps / (ms_call * 1e-3) / 1e9
         s_traffic = (prof_rec or {}).get("sampler_hbm_bytes_per_call")
-        roofline_sampler = {"bound": "hbm", "kernel": "lgp_sample_khop (sample_hop_kernel per hop, count_bits_kernel + "
-                                                      "emit_bits_kernel per dedup)",
+        roofline_sampler = {"bound": "hbm", "kernel": "lgp_sample_khop (sample_hop_kernel per hop, compact_kernel per dedup)",
                             "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                             "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": s_traffic,
                             "traffic_source": (prof_rec or {}).get("source") if s_traffic else prof_why or "no sampler figure",

@@ -121,7 +121,8 @@ int lgp_host_free(void* ptr);
  * (LGP_EINVAL if an array is not GPU-addressable) and allocates the per-vertex
  * lookup state in HBM: a row table (offset + degree + "cached" flag, 8 bytes per
  * vertex, filled from indptr), the feature remap, two hotness vectors and the dedup
- * bitmaps -- about 20.3 bytes per vertex, outside the cache budgets.  It starts with
+ * maps -- about 20.3 bytes per vertex (22 to 28 on graphs of up to 2^23 vertices, whose maps
+ * hold a byte or more per vertex), outside the cache budgets.  It starts with
  * empty caches, so sampling and gathering already work, with every column id and
  * feature row read from CPU memory (Sec. 3.2's mode with the topology kept in CPU memory).
  * Synchronous. */
@@ -332,7 +333,7 @@ int lgp_set_overlap(lgp_ctx* ctx, int enable);
 /* HBM the library holds or will allocate on its own for calls of one shape, in bytes, so that a
  * caller can budget device memory before building caches (Sec. 4.3.1: B is what is left after
  * everything else is reserved).  fixed [host] = the per-context tables that exist since
- * lgp_create (row table, feature remap, hotness vectors, dedup bitmaps, rankings once a plan
+ * lgp_create (row table, feature remap, hotness vectors, dedup maps, rankings once a plan
  * was made); scratch [host] = what pre-sampling, lgp_gather_features(_clique) with up to the
  * worst-case number of ids and lgp_build_blocks allocate on first use for batches of up to
  * max_seeds seeds with these fan-outs.  The caches themselves are reported by lgp_plan_cache /
