@@ -36,7 +36,8 @@ inline int mark_shift(int64_t num_vertices) {
 
 // How the compaction splits a map: `groups` workgroups of kCompactThreads threads, each thread taking
 // words_per_thread 64-bit words in each of `passes` passes.  Two workgroups fit a CU, so 512 of them run at
-// once; a larger map gets wider threads, then (beyond 2^28 bits) several passes.
+// once; a larger map gets wider threads, then (beyond 2^28 bits) several passes.  (Up to 1024 narrower workgroups
+// instead: 9.4 -> 11.1 us at 111 M vertices with 480 k marks, 12.9 -> 13.1 at 250 M with 506 k.)
 constexpr int kCompactThreads = 1024;
 constexpr int64_t kCompactMaxGroups = 512;
 constexpr int kMaxPasses = 8;             // 2^31 bits / (512 groups * 1024 threads * 8 words * 64 bits)
