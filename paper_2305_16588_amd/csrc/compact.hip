@@ -20,6 +20,8 @@
 // were read, they were read untouched.
 #include "common.hpp"
 
+#include <algorithm>
+
 namespace lgp {
 namespace {
 
@@ -171,7 +173,7 @@ __global__ __launch_bounds__(kCompactThreads, 8) void compact_kernel(CompactArgs
     __hip_atomic_store(&a.status[blockIdx.x], mine | kPublished, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
   const uint32_t base2 = M == kListNew ? uint32_t(a.seg[0]) : 0;
-  const uint32_t cap = uint32_t(a.out ? a.out_cap : 0), cap2 = uint32_t(a.out2_cap);      // both below 2^31
+  const uint32_t cap = uint32_t(a.out ? a.out_cap : 0), cap2 = uint32_t(a.out2_cap);      // below 2^31 (capacity())
   uint32_t pos = 0, pos2 = 0;                 // where the ids of the sub-pass begin
   for (int p = 0; p < passes; ++p) {
 #pragma unroll
@@ -354,6 +356,10 @@ void launch_mode(const MapGeom& g, CompactArgs a, hipStream_t s) {
   else hipLaunchKernelGGL((compact_kernel<M, 2, false>), grid, block, 0, s, a);
 }
 
+// A list holds fewer than 2^31 ids, and the kernel compares an id's place with the capacity in 32 bits; a caller may
+// state any capacity at or above the worst case.
+int64_t capacity(int64_t cap) { return std::min<int64_t>(cap, INT32_MAX); }
+
 CompactArgs base_args(const DeviceInfo& di, const DedupMaps& m, int32_t* out, int64_t out_cap, int32_t* n_out,
                       uint32_t* d_err) {
   CompactArgs a = {};
@@ -361,7 +367,7 @@ CompactArgs base_args(const DeviceInfo& di, const DedupMaps& m, int32_t* out, in
   a.other = m.gather;
   a.status = m.status;
   a.out = out;
-  a.out_cap = out_cap;
+  a.out_cap = capacity(out_cap);
   a.n_out = n_out;
   a.d_err = d_err;
   a.shift = di.spread_shift;
@@ -387,7 +393,7 @@ void launch_compact_both(const DeviceInfo& di, const DedupMaps& m, int32_t* out,
                          int32_t* all, int64_t all_cap, int32_t* n_all, uint32_t* d_err, hipStream_t s) {
   CompactArgs a = base_args(di, m, out, out_cap, n_out, d_err);
   a.out2 = all;
-  a.out2_cap = all_cap;
+  a.out2_cap = capacity(all_cap);
   a.n_out2 = n_all;
   launch_mode<kListUnion>(m.geom, a, s);
 }
@@ -397,7 +403,7 @@ void launch_compact_new(const DeviceInfo& di, const DedupMaps& m, int32_t* out, 
                         hipStream_t s) {
   CompactArgs a = base_args(di, m, out, out_cap, n_out, d_err);
   a.out2 = listed;
-  a.out2_cap = listed_cap;
+  a.out2_cap = capacity(listed_cap);
   a.n_out2 = n_listed;
   a.seg = seg;
   launch_mode<kListNew>(m.geom, a, s);

@@ -38,6 +38,42 @@ def test_sampling_on_both_sides_of_a_map_layout(V):
     ctx.check()
 
 
+@pytest.mark.parametrize("cap", [(1 << 31) - 1, 1 << 31, (1 << 32) - 1, 1 << 32, (1 << 32) + 5, 1 << 40])
+@pytest.mark.parametrize("V", [5000, (1 << 23) + 1])
+def test_capacities_beyond_32_bits(V, cap):
+    """A caller may state any capacity at or above the worst case, such as that of a large arena it cuts its lists
+    from: the lists are those of exactly sized buffers, through all three kinds of compaction."""
+    from gpu_common import assert_batch_equal
+    import paper_2305_16588_amd as lgp
+    ctx, orc, rng = _workload(V, 6, V + 1)
+    seeds = np.unique(rng.integers(0, V, 300)).astype(np.int32)
+    seeds_dev = torch.from_numpy(seeds).cuda()
+    fanouts = (4, 3)
+    ref = orc.sample_khop(seeds, fanouts, 11)
+    for last in (False, True):
+        buf = lgp.SampleBuffers(V, seeds.size, fanouts, last_frontier=last)
+        for t in [*buf.frontier[1:], buf.gather_ids]:
+            t.fill_(-1)
+        buf.c_struct.cap[1] = buf.c_struct.cap[2] = buf.c_struct.gather_cap = cap
+        ctx.sample_khop(seeds_dev, fanouts, 11, out=buf)
+        assert_batch_equal(ref, buf.to_host(seeds_dev), f"{V} {cap} {last}")
+    ctx.check()
+    # the intra-batch pipeline takes any frontier capacity; it gathers rows for its listing, of fewer than 2^31 ids
+    feats = lgp.pinned_empty((V, 2), np.float16)
+    feats.view(np.uint16)[...] = rng.integers(0, 1 << 16, (V, 2), dtype=np.uint16)
+    ctx = lgp.Context(*ctx._keep[:2], feats)
+    buf = lgp.SampleBuffers(V, seeds.size, fanouts, last_frontier=True)
+    rows = torch.empty((buf.gather_cap, 2), dtype=torch.float16, device="cuda")
+    for t in buf.frontier[1:]:
+        t.fill_(-1)
+    buf.c_struct.cap[1] = buf.c_struct.cap[2] = cap
+    ctx.sample_extract(seeds_dev, fanouts, 11, buf, rows)
+    fr, nbr, cnt, listing = buf.to_host(seeds_dev)
+    assert all((fr[h] == ref.frontier[h]).all() for h in (1, 2)) and listing.tolist() == ref.hop_order.tolist()
+    assert rows[:listing.size].cpu().numpy().tobytes() == feats[listing].tobytes()
+    ctx.check()
+
+
 @pytest.mark.parametrize("V", [(1 << 26) + 3, (1 << 27) + 3, (1 << 28) + 3])
 def test_compaction_of_large_maps(V):
     """The compaction's wider shares: four and eight words per thread, and several passes.  Only every 61st vertex has
