@@ -284,7 +284,9 @@ int lgp_sample_extract(lgp_ctx* ctx, const int32_t* seeds, int32_t n_seeds, cons
  * per-hop subgraph).  Takes the buffers a finished lgp_sample_khop call filled (same seeds, fanouts
  * and `sampled`, with sampled->frontier[n_hops] given) and writes, per hop h, a bipartite
  * block in CSR form whose destinations are frontier h and whose sources are frontier h+1,
- * plus for every frontier the rows of its vertices in the extracted feature matrix.
+ * plus for every frontier the rows of its vertices in the extracted feature matrix.  The caller may have
+ * reordered a frontier (its rows of nbr and cnt in the same order): positions are those in the list as it
+ * stands, but lookups in a list that is not ascending read all of it again and again and take many times longer.
  * Everything is read from device memory; no host synchronisation.  Unless lgp_reserve sized
  * the scratch beforehand, the first call (and a later one with more hops) allocates n_hops + 1
  * lookup tables of V 4-byte entries and a small scan scratch, and synchronises once. */

@@ -86,6 +86,8 @@ struct lgp_ctx {
   int32_t pos_tables = 0;
   int64_t* tile_sums = nullptr;
   int64_t tile_cap = 0;
+  uint32_t* unordered = nullptr;  // uint32[LGP_MAX_HOPS + 1]: the last call that met frontier j out of order
+  uint32_t blocks_calls = 0;
 
   // pre-sampling scratch
   int32_t* hs_frontier[LGP_MAX_HOPS] = {};
@@ -588,6 +590,7 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   step(dev_alloc(&c->hs_n, LGP_MAX_HOPS + 1));
   step(dev_alloc(&c->hs_expansions, 1));
   step(dev_alloc(&c->seg, LGP_MAX_HOPS + 2));
+  step(dev_alloc(&c->unordered, LGP_MAX_HOPS + 1));
   step(dev_alloc(&c->seg_counters, (LGP_MAX_HOPS + 1) * 3));
   if (e == hipSuccess) e = hipMemset(c->f_remap, 0xff, sizeof(int32_t) * size_t(V));
   if (e == hipSuccess) e = hipMemset(c->topo_hot, 0, sizeof(uint32_t) * size_t(V));
@@ -596,6 +599,7 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   if (e == hipSuccess) e = hipMemset(c->maps.gather, 0, sizeof(uint64_t) * words);
   if (e == hipSuccess) e = hipMemset(c->d_err, 0, sizeof(uint32_t));
   if (e == hipSuccess) e = hipMemset(c->counters, 0, 3 * sizeof(int32_t));
+  if (e == hipSuccess) e = hipMemset(c->unordered, 0, (LGP_MAX_HOPS + 1) * sizeof(uint32_t));
   if (e == hipSuccess) e = hipMemset(c->hs_expansions, 0, sizeof(unsigned long long));
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->miss_stream, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming);
@@ -624,7 +628,7 @@ int lgp_destroy(lgp_ctx* c) {
   free_cache(c);
   void* ptrs[] = {c->row_tab, c->f_remap, c->topo_hot, c->feat_hot, c->maps.frontier, c->maps.gather, c->maps.status,
                   c->d_err,   c->counters, c->order_t, c->order_f,  c->lists, c->hs_n, c->pos_table, c->tile_sums, c->hs_expansions,
-                  c->seg, c->seg_counters};
+                  c->seg, c->seg_counters, c->unordered};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (int h = 0; h < LGP_MAX_HOPS; ++h)
@@ -1183,6 +1187,9 @@ int lgp_build_blocks(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const in
   if (st != LGP_OK) return st;
   a.table = c->pos_table;
   a.tile_sums = c->tile_sums;
+  a.unordered = c->unordered;
+  a.call = ++c->blocks_calls;      // 0 marks no call: skipped after 2^32 of them
+  if (a.call == 0) a.call = c->blocks_calls = 1;
   launch_build_blocks(c->di, a, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail_hip(c, e, "graph constructor launch");

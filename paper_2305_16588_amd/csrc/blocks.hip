@@ -9,7 +9,9 @@
 // one load of the bucket and, for the minority of buckets with several ids, a search in it.  Index
 // and list together are a few MB, where a table with an entry per vertex made every write and
 // lookup a random access to hundreds of MB (2.2 M accesses of a 111 M-vertex graph: 70 us per call,
-// now 37; 630 k lookups of a 2.4 M-vertex graph 44 -> 37 us, four launches -> two).  The
+// now 37; 630 k lookups of a 2.4 M-vertex graph 44 -> 37 us, four launches -> two).  A frontier
+// that a caller has reordered is noticed while it is indexed, and its lookups take another path
+// (position_any_order).  The
 // extracted id list need not be ascending (the intra-batch pipeline lists in first-reach order),
 // so "row of vertex v in the feature matrix" stays a table of V entries that is scattered with
 // the positions and never cleared: only entries written for the current list are ever read.
@@ -135,6 +137,40 @@ __device__ __forceinline__ void positions(const int32_t* ids, int32_t n, const i
   }
 }
 
+// Position of one id per lane (-1 for u < 0 and for an id that is not in the list) in a list that is not ascending:
+// the workgroup's ids go into a hash table in LDS and the whole list passes by once.  The work grows with workgroups
+// times list, far beyond that of the bucket index, but a frontier comes out of the sampler ascending; only a caller
+// who reorders it comes here.
+constexpr int kJoinSlots = 512;                                // twice the ids of a workgroup: probing ends
+struct JoinTable {
+  int32_t id[kJoinSlots], at[kJoinSlots];
+};
+__device__ __forceinline__ uint32_t join_slot(int32_t u) { return (uint32_t(u) * 2654435761u) >> 23; }
+__device__ __forceinline__ int32_t position_any_order(const int32_t* ids, int32_t n, JoinTable* t, int32_t u) {
+  for (int k = threadIdx.x; k < kJoinSlots; k += 256) t->id[k] = t->at[k] = -1;
+  __syncthreads();
+  uint32_t mine = join_slot(u);
+  while (u >= 0) {
+    const int32_t old = atomicCAS(&t->id[mine], -1, u);
+    if (old < 0 || old == u) break;
+    mine = (mine + 1) % kJoinSlots;
+  }
+  __syncthreads();
+  for (int32_t k = threadIdx.x; k < n; k += 256) {
+    const int32_t v = ids[k];
+    if (v < 0) continue;
+    for (uint32_t s = join_slot(v); t->id[s] >= 0; s = (s + 1) % kJoinSlots)
+      if (t->id[s] == v) {
+        t->at[s] = k;
+        break;
+      }
+  }
+  __syncthreads();
+  const int32_t pos = u >= 0 ? t->at[mine] : -1;
+  __syncthreads();                                             // the table is reused by the next ids
+  return pos;
+}
+
 // Range 0: positions inside the extracted id list go to table 0.  Range j = 1 .. n_hops: bucket index of frontier j, in
 // table j.  Range n_hops + 1 + h: edge count of every tile of kScanTile destinations of hop h.
 __global__ __launch_bounds__(256) void index_lists_kernel(BlocksArgs a, Ranges rg) {
@@ -158,6 +194,7 @@ __global__ __launch_bounds__(256) void index_lists_kernel(BlocksArgs a, Ranges r
       const int64_t k = base + lane;
       const int32_t v = k < n ? ids[k] : 0, before = k > 0 && k < n ? ids[k - 1] : -1;
       const bool ok = k < n && uint32_t(v) < uint64_t(a.num_vertices) && before < v;
+      if (k < n && !ok) a.unordered[r] = a.call;               // every writer stores the same value
       const int32_t mine = v >> b.shift, prev = before < 0 ? -1 : before >> b.shift;
       fill_stretches(start, prev + 1, ok ? mine - prev : 0, int32_t(k));
       if (base + 64 >= n)                                      // this wave holds the last id
@@ -193,6 +230,7 @@ inline int32_t relabel_tile(int32_t f) {
 }
 __global__ __launch_bounds__(256, 8) void lookup_relabel_kernel(BlocksArgs a, Ranges rg) {
   __shared__ int64_t offset[256];
+  __shared__ JoinTable join;
   int index, count;
   const int r = find_range(rg, 2 * a.n_hops + 1, &index, &count);
   if (r >= a.n_hops) {
@@ -214,6 +252,7 @@ __global__ __launch_bounds__(256, 8) void lookup_relabel_kernel(BlocksArgs a, Ra
   const int32_t n_next = int32_t(clamped(a.n_frontier + h + 1, a.cap[h + 1]));
   const int32_t* start = a.table + int64_t(h + 1) * a.num_vertices;
   const Buckets b = bucket_shape(a.num_vertices, n_next);
+  const bool ascending = a.unordered[h + 1] != a.call;
   const int64_t* tile_sums = a.tile_sums + a.tile_base[h];
   int64_t* indptr = a.blk_indptr[h];
   int32_t* blk_src = a.blk_src[h];
@@ -244,6 +283,8 @@ __global__ __launch_bounds__(256, 8) void lookup_relabel_kernel(BlocksArgs a, Ra
     if (int(threadIdx.x) < tile_dst && i <= n) indptr[i] = at;    // entry n holds the edge total
     offset[threadIdx.x] = at;
     __syncthreads();
+    if (!ascending)
+      for (int q = 0; q < kRelabelLoads; ++q) pos[q] = position_any_order(next, n_next, &join, u[q]);
 #pragma unroll
     for (int q = 0; q < kRelabelLoads; ++q) {
       const uint32_t t = threadIdx.x + q * 256;

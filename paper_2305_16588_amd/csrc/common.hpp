@@ -205,6 +205,8 @@ struct BlocksArgs {
   int32_t* table;                              // n_hops + 1 tables of num_vertices entries each
   int64_t* tile_sums;                          // hop h owns cap[h] / kScanTile + 1 entries from tile_base[h]
   int64_t tile_base[LGP_MAX_HOPS];
+  uint32_t* unordered;                         // [j] == call: frontier j is not ascending (n_hops + 1 words)
+  uint32_t call;                               // number of this call (a value of its own, so that nothing is cleared)
 };
 void launch_build_blocks(const DeviceInfo& di, const BlocksArgs& a, hipStream_t s);
 

@@ -172,3 +172,49 @@ def test_blocks_of_dense_sparse_and_clustered_frontiers(V, fanouts, n_seeds, spa
         assert_batch_equal(ref, buf.to_host(seeds_dev), f"{V} {fanouts}")
         assert_blocks_equal(ref, blk.to_host(), f"{V} {fanouts}")
     ctx.check()
+
+
+@pytest.mark.parametrize("V,n_seeds,fanouts", [(3, 3, (2, 2)), (500, 60, (3, 64)), (60_000, 300, (5, 4, 3)),
+                                               (2_000_000, 1025, (7, 3))])
+@pytest.mark.parametrize("how", ["reversed", "shuffled", "two ids swapped"])
+def test_blocks_of_reordered_frontiers(V, n_seeds, fanouts, how):
+    """The graph constructor takes the frontiers in any order (their rows of samples in the same order): positions are
+    those in the lists as they stand.  Ascending lists again afterwards, on the same context."""
+    from gpu_common import assert_blocks_equal
+    import paper_2305_16588_amd as lgp
+    ctx, orc, rng = _workload(V, 9, V + n_seeds)
+    seeds = np.sort(rng.permutation(V)[:n_seeds]).astype(np.int32)
+    seeds_dev = torch.from_numpy(seeds).cuda()
+    buf = lgp.SampleBuffers(V, n_seeds, fanouts, last_frontier=True)
+    blk = lgp.BlockBuffers(buf)
+    L = len(fanouts)
+    for reordered in ((1,), (L,), tuple(range(1, L + 1)), ()):
+        ctx.sample_khop(seeds_dev, fanouts, 21, out=buf)
+        fr, nbr, cnt, gids = buf.to_host(seeds_dev)
+        fr, nbr, cnt = list(fr), list(nbr), list(cnt)
+        for h in reordered:
+            n = fr[h].size
+            perm = np.arange(n)
+            if how == "reversed":
+                perm = perm[::-1].copy()
+            elif how == "shuffled":
+                perm = rng.permutation(n)
+            elif n > 1:
+                perm[[n // 2 - 1, n - 1]] = perm[[n - 1, n // 2 - 1]]
+            fr[h] = fr[h][perm]
+            buf.frontier[h][:n] = torch.from_numpy(fr[h]).cuda()
+            if h < L:
+                nbr[h], cnt[h] = nbr[h][perm], cnt[h][perm]
+                buf.nbr[h][:n] = torch.from_numpy(nbr[h]).cuda()
+                buf.cnt[h][:n] = torch.from_numpy(cnt[h]).cuda()
+        ctx.build_blocks(seeds_dev, fanouts, buf, out=blk)
+        indptr, src, rows = blk.to_host()
+        place = np.full(V, -1, np.int32)
+        for h in range(L):
+            place[fr[h + 1]] = np.arange(fr[h + 1].size, dtype=np.int32)
+            assert (np.diff(indptr[h]) == cnt[h]).all() and indptr[h][0] == 0, f"{how} {reordered} indptr[{h}]"
+            assert (src[h] == place[nbr[h][nbr[h] >= 0]]).all(), f"{how} {reordered} blk_src[{h}]"
+        for h in range(L + 1):
+            assert (gids[rows[h]] == fr[h]).all(), f"{how} {reordered} feat_row[{h}]"
+    assert_blocks_equal(orc.sample_khop(seeds, fanouts, 21, blocks=True), (indptr, src, rows), "ascending")
+    ctx.check()
