@@ -321,6 +321,8 @@ void launch_on(const Where& w, K kernel, unsigned blocks, Args... args) {
   else hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, w.s, args...);
 }
 
+constexpr uint32_t kWideChunks = 160;   // ragged cached rows of more chunks go through the flat kernel (see by_lane_group)
+
 template <typename VecT, bool RAGGED>
 void launch_flat(const DeviceInfo& di, const char* src, char* dst, const RowShape& shape, const int32_t* row,
                  const int32_t* srcrow, int64_t n_max, const int32_t* n_dev, const DirectIds& dir, const Where& s) {
@@ -334,9 +336,14 @@ void launch_flat(const DeviceInfo& di, const char* src, char* dst, const RowShap
   // A wave takes at most 32 KiB of rows per pass (64 rows of up to 512 bytes, 16 rows of 2 KiB): the number
   // of entries is only known on the device, and with 128 KiB passes a launch of 233 k 2-KiB rows left most
   // waves with one pass and a few with two (216.6 -> 195.7 us; 379 k such rows: 311.5 -> 263.8 us).
+  // Wide ragged rows: two workgroups and 8-KiB passes, so that a wave's rows end sooner and the line two rows share is
+  // still in L2 when its other part arrives (3080 bytes, 187 k rows: 248 -> 225 us, 4100 bytes, 175 k: 295 -> 281; but
+  // 264 bytes, 584 k rows: 61 -> 68).
+  const bool wide = RAGGED && shape.cpr > kWideChunks;
   int epw = 64;
-  while (epw > 4 && int64_t(epw) * row_bytes > 32768) epw >>= 1;
-  const unsigned blocks = blocks_for((s.items + 4 * epw - 1) / (4 * epw), std::min<int64_t>(s.hbm_blocks, int64_t(di.num_cus) * 3));
+  while (epw > 4 && int64_t(epw) * row_bytes > (wide ? 8192 : 32768)) epw >>= 1;
+  const unsigned blocks = blocks_for((s.items + 4 * epw - 1) / (4 * epw),
+                                     std::min<int64_t>(s.hbm_blocks, int64_t(di.num_cus) * (wide ? 2 : 3)));
   // Rows made of whole 128-byte lines are read once: stream them past L2 (+2.5 % at 512-B and 2-KiB
   // rows).  Rows that straddle lines share their boundary lines between consecutive load
   // instructions, and L2 has to merge those (non-temporal loads cost 7 % on 400-B rows).
@@ -377,7 +384,25 @@ void launch_group_hbm(const DeviceInfo& di, const char* src, char* dst, const Ro
   if (shape.cpr <= 4) launch_group_hbm_g<VecT, RAGGED, 4>(di, src, dst, shape, row, srcrow, n_max, n_dev, dir, s);
   else if (shape.cpr <= 8) launch_group_hbm_g<VecT, RAGGED, 8>(di, src, dst, shape, row, srcrow, n_max, n_dev, dir, s);
   else if (shape.cpr <= 16) launch_group_hbm_g<VecT, RAGGED, 16>(di, src, dst, shape, row, srcrow, n_max, n_dev, dir, s);
-  else launch_group_hbm_g<VecT, RAGGED, 32>(di, src, dst, shape, row, srcrow, n_max, n_dev, dir, s);
+  else if (!RAGGED || shape.cpr <= 32) launch_group_hbm_g<VecT, RAGGED, 32>(di, src, dst, shape, row, srcrow, n_max, n_dev, dir, s);
+  else if constexpr (RAGGED) launch_group_hbm_g<VecT, RAGGED, 64>(di, src, dst, shape, row, srcrow, n_max, n_dev, dir, s);
+}
+
+// Which cached rows take the group kernel; the others, and all rows of whole lines, take the flat one.
+// Aligned chunks: rows of up to 32.  Ragged rows end inside a line and inside a chunk; where the flat walk cuts a line
+// between two store instructions, both parts can reach memory (872 bytes, 465 k rows: 408 MiB written for 387), and
+// one lane group per row avoids it -- 488 k rows of 872 bytes flat / group 188 / 163 us, 1352 bytes (220 k) 120 / 111,
+// 2056 (204 k) 197 / 177, 2312 (199 k) 199 / 184, 2568 (161 chunks, 195 k) 212 / 199; but from there the narrow flat walk
+// is ahead (2568 bytes 189, 3080 bytes 225 against 241), while on 91 k rows of 2312 bytes it is behind (76 against 71).
+// With 17 to 21 chunks a group of 32 leaves too many lanes idle: 264 bytes (584 k rows) flat / group 61 / 74 us, 328
+// bytes 72 / 81, 344 (22 chunks) 81-85 / 82, 376 (24) 79 / 79, 408 (26) 88 / 79, 456 (29) 100 / 83.
+// In aligned chunks of 8 bytes these rows took 68 (264 bytes), 77 (328), 99 (456), 168 (872), 117 (1352), 203 (2056)
+// and 201 us (2568).
+template <bool RAGGED>
+bool by_lane_group(const RowShape& r) {
+  if (r.bytes % 128 == 0) return false;
+  if (!RAGGED) return r.cpr <= 32;
+  return r.cpr <= 16 || (r.cpr > 21 && r.cpr <= kWideChunks);
 }
 
 template <typename VecT, bool RAGGED>
@@ -439,7 +464,7 @@ void launch_gather_rows(const DeviceInfo& di, const void* src, void* dst, int64_
     typedef decltype(vec) VecT;
     constexpr bool kRagged = decltype(ragged)::value;
     if (streaming) launch_group<VecT, kRagged>(di, from, to, shape, row, srcrow, n_max, n_dev, dir, s);
-    else if (row_bytes % 128 != 0 && shape.cpr <= 32)
+    else if (by_lane_group<kRagged>(shape))
       launch_group_hbm<VecT, kRagged>(di, from, to, shape, row, srcrow, n_max, n_dev, dir, s);
     else launch_flat<VecT, kRagged>(di, from, to, shape, row, srcrow, n_max, n_dev, dir, s);
   };

@@ -143,6 +143,30 @@ def test_rows_of_any_even_width_and_alignment(row_bytes, shift):
     ctx.check()
 
 
+@pytest.mark.parametrize("row_bytes", [250, 258, 262, 264, 334, 338, 344, 502, 506, 516, 520, 776, 872, 1016, 1030, 1032, 1048,
+                                       2040, 2046, 2056, 2558, 2562, 2568, 32760])
+@pytest.mark.parametrize("list_len", [1, 63, 65, 3000])
+def test_cached_rows_on_both_sides_of_a_kernel_choice(row_bytes, list_len):
+    """Ragged rows around the chunk counts at which another gather kernel takes them (16, 21, 32, 64, 128 and 160 chunks),
+    all cached and half cached, lists that do and do not fill the kernels' passes."""
+    import paper_2305_16588_amd as lgp
+    V, D = 500, row_bytes // 2
+    rng = np.random.default_rng(row_bytes + list_len)
+    feats = lgp.pinned_empty((V, D), np.float16)
+    feats.view(np.uint16)[...] = rng.integers(0, 1 << 16, (V, D), dtype=np.uint16)
+    ctx = lgp.Context(lgp.pinned_copy(np.zeros(V + 1, np.int32)), lgp.pinned_empty(1, np.int32)[:0], feats)
+    ids = rng.integers(0, V, list_len).astype(np.int32)
+    want = feats.view(np.uint16)[ids].reshape(-1)
+    ctx.set_hotness(np.zeros(V, np.uint32), rng.integers(0, 9, V).astype(np.uint32))
+    for n_cached in (V, V // 2):
+        ctx.build_cache(0, n_cached * row_bytes)
+        flat = torch.full((ids.size * D + 16,), 21845, dtype=torch.int16, device="cuda")
+        ctx.gather_features(torch.from_numpy(ids).cuda(), out=flat[:ids.size * D].view(torch.float16).view(ids.size, D))
+        got = flat.cpu().numpy().view(np.uint16)
+        assert (got[:want.size] == want).all() and (got[want.size:] == 21845).all(), f"{n_cached} rows cached"
+    ctx.check()
+
+
 @pytest.mark.parametrize("V,fanouts,n_seeds", [(1, (2,), 1), (2, (2, 2), 2), (3, (1, 64), 3), (65, (5, 4), 9), (1500, (64, 3), 40),
                                                (200_000, (3, 2), 700), (200_000, (1, 1, 1), 256), (200_000, (25, 10), 1025)])
 @pytest.mark.parametrize("span", [1.0, 0.02])
