@@ -75,28 +75,28 @@ __device__ __forceinline__ int64_t block_exclusive_scan64(int64_t x, int64_t* to
   return before + inc - x;
 }
 
-// Bucket index of an ascending list of n ids below V: bucket b holds the ids with id >> shift == b and begins at
-// start[b]; the last one ends at n.  shift >= 1, so the at most V / 2 + 1 entries fit a table of V.
+// Bucket index of an ascending list of n ids: bucket b holds the ids with (id - first) >> shift == b and begins at
+// start[b].  start[b] is set for every bucket that holds ids and for the one after it, which is where the bucket ends
+// (the last one ends at n): the ids looked up are in the list, so the entries of other empty buckets are never read, and
+// a list crowded into parts of the id range costs no more than one spread over it (100 k destinations x 10, 526 k ids in 2 % of 111 M:
+// 265 us a call with every entry filled, 28 now; 561 k ids at the two ends 354, 33; spread over the range 38 either
+// way).  Buckets split the span of the list, not the id range, so that a list in one corner has as few ids per bucket
+// as any (2.75 M ids in 2 % of 250 M, 9.8 M x 5: 1490 us split by id range, 1075 by span).  shift >= 1: at most
+// V / 2 + 1 entries.
 struct Buckets {
-  int shift;
-  int32_t count;
+  int32_t first, last, shift, count;
 };
-__device__ __forceinline__ Buckets bucket_shape(int64_t num_vertices, int64_t n) {
-  const uint32_t q = uint32_t((num_vertices - 1) / (n > 0 ? n : 1));
-  const int shift = q > 3 ? 31 - __clz(int(q)) : 1;           // half an id to one id per bucket on average
-  return Buckets{shift, int32_t((num_vertices - 1) >> shift) + 1};
-}
-
-// start[first .. first + len) = value for every lane of a wave; the long stretches are filled by all lanes together.
-__device__ __forceinline__ void fill_stretches(int32_t* start, int32_t first, int32_t len, int32_t value) {
-  constexpr int32_t kAlone = 8;
-  for (int32_t k = 0; k < len && len <= kAlone; ++k) start[first + k] = value;
-  for (uint64_t todo = __ballot(len > kAlone); todo; todo &= todo - 1) {
-    const int from = __ffsll((unsigned long long)todo) - 1;
-    const int32_t f = __builtin_amdgcn_readlane(first, from), l = __builtin_amdgcn_readlane(len, from);
-    const int32_t v = __builtin_amdgcn_readlane(value, from);
-    for (int32_t k = threadIdx.x & 63; k < l; k += 64) start[f + k] = v;
+__device__ __forceinline__ Buckets bucket_shape(const int32_t* ids, int64_t num_vertices, int64_t n) {
+  uint32_t end = n > 0 ? uint32_t(n - 1) : 0;
+  asm("" : "+s"(end));                                         // a register of its own: a scalar load
+  int32_t first = n > 0 ? ids[0] : 0, last = n > 0 ? ids[end] : 0;
+  if (first < 0 || last < first || last >= num_vertices) {    // not ascending ids below V: any shape will do
+    first = 0;
+    last = int32_t(num_vertices - 1);
   }
+  const uint32_t q = uint32_t(last - first) / uint32_t(n > 0 ? n : 1);
+  const int shift = q > 3 ? 31 - __clz(int(q)) : 1;           // half an id to one id per bucket on average
+  return Buckets{first, last, shift, ((last - first) >> shift) + 1};
 }
 
 // Positions of N ids in the list, -1 for u < 0 (for an id that is not in the list: some value, from reads inside it).
@@ -107,8 +107,8 @@ __device__ __forceinline__ void positions(const int32_t* ids, int32_t n, const i
   int32_t hi[N];
 #pragma unroll
   for (int q = 0; q < N; ++q) {
-    const int32_t k = u[q] >> b.shift;
-    const bool ok = u[q] >= 0 && k < b.count;
+    const int32_t k = (u[q] - b.first) >> b.shift;
+    const bool ok = u[q] >= b.first && k < b.count;
     lo[q] = ok ? start[k] : -1;
     hi[q] = ok && k + 1 < b.count ? start[k + 1] : n;
   }
@@ -188,17 +188,18 @@ __global__ __launch_bounds__(256) void index_lists_kernel(BlocksArgs a, Ranges r
     const int32_t* ids = a.frontier[r];
     const int64_t n = clamped(a.n_frontier + r, a.cap[r]);
     int32_t* start = a.table + int64_t(r) * a.num_vertices;
-    const Buckets b = bucket_shape(a.num_vertices, n);
-    const int lane = threadIdx.x & 63;
-    for (int64_t base = int64_t(index) * 256 + (threadIdx.x - lane); base < n; base += int64_t(count) * 256) {
-      const int64_t k = base + lane;
-      const int32_t v = k < n ? ids[k] : 0, before = k > 0 && k < n ? ids[k - 1] : -1;
-      const bool ok = k < n && uint32_t(v) < uint64_t(a.num_vertices) && before < v;
-      if (k < n && !ok) a.unordered[r] = a.call;               // every writer stores the same value
-      const int32_t mine = v >> b.shift, prev = before < 0 ? -1 : before >> b.shift;
-      fill_stretches(start, prev + 1, ok ? mine - prev : 0, int32_t(k));
-      if (base + 64 >= n)                                      // this wave holds the last id
-        fill_stretches(start, mine + 1, ok && k == n - 1 ? b.count - 1 - mine : 0, int32_t(n));
+    const Buckets b = bucket_shape(ids, a.num_vertices, n);
+    for (int64_t k = int64_t(index) * 256 + threadIdx.x; k < n; k += int64_t(count) * 256) {
+      const int32_t v = ids[k], before = k > 0 ? ids[k - 1] : b.first - 1;
+      if (v < b.first || v > b.last || before < b.first - (k == 0) || before >= v) {
+        a.unordered[r] = a.call;                               // every writer stores the same value
+        continue;
+      }
+      const int32_t mine = (v - b.first) >> b.shift, prev = k > 0 ? (before - b.first) >> b.shift : -1;
+      if (mine != prev) {
+        start[prev + 1] = int32_t(k);
+        start[mine] = int32_t(k);
+      }
     }
     return;
   }
@@ -249,9 +250,13 @@ __global__ __launch_bounds__(256, 8) void lookup_relabel_kernel(BlocksArgs a, Ra
   const uint32_t inv_f = (1u << 20) / uint32_t(f) + 1;       // exact division of t < 1024 by f <= 64
   const int32_t* cnt = a.cnt[h];
   const int32_t* next = a.frontier[h + 1];
-  const int32_t n_next = int32_t(clamped(a.n_frontier + h + 1, a.cap[h + 1]));
+  // The two frontier sizes lie side by side; as one access they become a vector load in front of everything else, and
+  // apart they are scalar loads, hits for all workgroups but the first (kernel 25.0 -> 23.0 us at 111 M vertices).
+  int j = h + 1;
+  asm("" : "+s"(j));
+  const int32_t n_next = int32_t(clamped(a.n_frontier + j, a.cap[j]));
   const int32_t* start = a.table + int64_t(h + 1) * a.num_vertices;
-  const Buckets b = bucket_shape(a.num_vertices, n_next);
+  const Buckets b = bucket_shape(next, a.num_vertices, n_next);
   const bool ascending = a.unordered[h + 1] != a.call;
   const int64_t* tile_sums = a.tile_sums + a.tile_base[h];
   int64_t* indptr = a.blk_indptr[h];

@@ -242,3 +242,35 @@ def test_blocks_of_reordered_frontiers(V, n_seeds, fanouts, how):
             assert (gids[rows[h]] == fr[h]).all(), f"{how} {reordered} feat_row[{h}]"
     assert_blocks_equal(orc.sample_khop(seeds, fanouts, 21, blocks=True), (indptr, src, rows), "ascending")
     ctx.check()
+
+
+@pytest.mark.parametrize("V", [1, 2, 70, 100_000, 3_000_000])
+@pytest.mark.parametrize("where", ["first id", "last id", "both ends", "one run", "three runs", "all over"])
+def test_blocks_of_frontiers_in_parts_of_the_range(V, where):
+    """The frontiers' bucket index covers the span of the list and leaves the buckets of its gaps unset."""
+    from gpu_common import assert_batch_equal, assert_blocks_equal
+    import oracle
+    import paper_2305_16588_amd as lgp
+    rng = np.random.default_rng(V)
+    parts = {"first id": [(0, 1)], "last id": [(V - 1, V)], "both ends": [(0, 40), (V - 40, V)],
+             "one run": [(V // 3, V // 3 + 900)], "three runs": [(V // 9, V // 9 + 5), (V // 2, V // 2 + 300), (V - 7, V)],
+             "all over": [(0, V)]}[where]
+    pool = np.unique(np.concatenate([np.arange(max(lo, 0), min(hi, V)) for lo, hi in parts]))
+    d = rng.integers(0, 12, V)
+    indptr = np.zeros(V + 1, np.int32)
+    np.cumsum(d, out=indptr[1:])
+    indices = pool[rng.integers(0, pool.size, int(indptr[-1]))].astype(np.int32)
+    ctx = lgp.Context(lgp.pinned_copy(indptr), lgp.pinned_copy(indices))
+    orc = oracle.Oracle(indptr, indices, None)
+    seeds = np.sort(rng.permutation(V)[:700]).astype(np.int32)
+    seeds_dev = torch.from_numpy(seeds).cuda()
+    fanouts = (6, 3)
+    buf = lgp.SampleBuffers(V, seeds.size, fanouts, last_frontier=True)
+    blk = lgp.BlockBuffers(buf)
+    for rep in range(2):
+        ctx.sample_khop(seeds_dev, fanouts, 50 + rep, out=buf)
+        ctx.build_blocks(seeds_dev, fanouts, buf, out=blk)
+        ref = orc.sample_khop(seeds, fanouts, 50 + rep, blocks=True)
+        assert_batch_equal(ref, buf.to_host(seeds_dev), f"{V} {where}")
+        assert_blocks_equal(ref, blk.to_host(), f"{V} {where}")
+    ctx.check()
