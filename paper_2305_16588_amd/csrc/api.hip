@@ -1321,6 +1321,13 @@ int lgp_set_overlap(lgp_ctx* c, int enable) {
   return LGP_OK;
 }
 
+int lgp_set_wait_polls(lgp_ctx* c, int32_t polls) {
+  if (!c) return LGP_EINVAL;
+  if (polls < 0) return fail(c, LGP_EINVAL, "polls is negative");
+  c->maps.polls = polls;
+  return LGP_OK;
+}
+
 int lgp_set_profiling(lgp_ctx* c, int enable) {
   if (!c) return LGP_EINVAL;
   c->profiling = enable == 2 ? 2 : (enable != 0 ? 1 : 0);

@@ -57,6 +57,8 @@ inline MapGeom map_geometry(int64_t num_vertices, int shift) {
   return g;
 }
 
+constexpr int32_t kDefaultPolls = 1 << 12;   // about 4 ms of polling before a share is counted by the one who waits
+
 // The two dedup maps of a context and the status words of the compaction kernel (one per workgroup).  Both maps
 // are clear between calls; every hop kernel clears the status words for the compaction that follows it.
 struct DedupMaps {
@@ -64,6 +66,7 @@ struct DedupMaps {
   uint64_t* gather = nullptr;
   uint64_t* status = nullptr;
   MapGeom geom;
+  int32_t polls = kDefaultPolls;
 };
 
 struct DeviceInfo {
@@ -118,6 +121,7 @@ struct CompactArgs {
   int32_t* seg;
   uint32_t* d_err;
   int32_t shift, passes;
+  int32_t polls;      // looks at a status word before the share is counted instead
 };
 // Frontier map -> ascending id list out[0 .. *n_out); its marks are added to the gather map, the frontier map is
 // cleared.  Every compaction follows a launch_sample_hop on the same stream, which clears the status words.

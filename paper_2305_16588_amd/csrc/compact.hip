@@ -14,10 +14,10 @@
 //
 // Waiting: a workgroup publishes before it waits, so workgroups that run make progress
 // together.  One that has polled a predecessor for a long time without an answer (it may be
-// queued behind other work on the chip) counts that share itself, so no wait depends on when
-// another workgroup is scheduled.  The recount is sound because a workgroup clears its words
-// only after its status has reached memory: if the status is still missing after the words
-// were read, they were read untouched.
+// queued behind other work on the chip) counts that share itself, looking for the status
+// between a few words and the next, so no wait depends on when another workgroup is scheduled.
+// The recount is sound because a workgroup clears its words only after its status has reached
+// memory: if the status is still missing after the words were read, they were read untouched.
 #include "common.hpp"
 
 #include <algorithm>
@@ -28,7 +28,6 @@ namespace {
 constexpr int kWaves = kCompactThreads / 64;
 constexpr uint64_t kPublished = 1ull << 63;     // status word: published | second count << 32 | first count
 constexpr int kMaxSubs = kMaxPasses * 4;         // sub-passes of two words in a share of 8 * passes words per thread
-constexpr int kPolls = 1 << 12;                 // about 4 ms of polling before a share is counted by the one who waits
 
 // What a compaction produces besides the ascending list of the marks in `bits`.
 enum Mode {
@@ -71,32 +70,34 @@ __device__ __forceinline__ uint32_t count_of(uint64_t x, uint64_t y) {
 }
 __device__ __forceinline__ uint64_t widen(uint32_t c) { return uint64_t(c & 0xffffu) | (uint64_t(c >> 16) << 32); }
 
-// Counts of one workgroup's share, taken by a single thread (see the note on waiting above).
-template <Mode M>
-__device__ uint64_t recount(const uint64_t* bits, const uint64_t* other, int64_t first, int64_t words) {
-  uint64_t c = 0;
-#pragma unroll 1
-  for (int64_t k = first; k < first + words; ++k) {
-    const uint64_t x = __hip_atomic_load(bits + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const uint64_t y = M == kList ? 0ull : __hip_atomic_load(other + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    c += widen(count_of<M>(x, y));
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // the words are read before the status is looked at again
-  return c;
-}
-
+// Counts of one workgroup's share: its status if that appears, else its words, counted by this one thread (see the note
+// on waiting above).
 template <Mode M>
 __device__ __forceinline__ uint64_t wait_for(const uint64_t* status, const uint64_t* bits, const uint64_t* other,
-                                             int64_t first, int64_t words) {
+                                             int64_t first, int64_t words, int polls) {
 #pragma unroll 1
-  for (int it = 0; it < kPolls; ++it) {
+  for (int it = 0; it < polls; ++it) {
     const uint64_t s = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (s & kPublished) return s & ~kPublished;
     __builtin_amdgcn_s_sleep(2);
   }
-  const uint64_t c = recount<M>(bits, other, first, words);
-  const uint64_t s = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return (s & kPublished) ? (s & ~kPublished) : c;
+  constexpr int kBatch = M == kList ? 8 : 4;                // loads in flight; a share is a multiple of 2048 words
+  uint64_t c = 0;
+#pragma unroll 1
+  for (int64_t k = first; k < first + words; k += kBatch) {
+    uint64_t x[kBatch], y[kBatch];
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) {
+      x[j] = __hip_atomic_load(bits + k + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      y[j] = M == kList ? 0ull : __hip_atomic_load(other + k + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+    for (int j = 0; j < kBatch; ++j) c += widen(count_of<M>(x[j], y[j]));
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the words are read before the status is looked at
+    const uint64_t s = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (s & kPublished) return s & ~kPublished;
+  }
+  return c;
 }
 
 // The word (pair) at 32-bit word index k of a map of at most 2^25 words, so that an address is one register.
@@ -232,7 +233,8 @@ __global__ __launch_bounds__(kCompactThreads, 8) void compact_kernel(CompactArgs
         uint64_t before = 0;
 #pragma unroll 1
         for (int k = threadIdx.x; k < int(blockIdx.x); k += kCompactThreads)
-          before += wait_for<M>(&a.status[k], a.bits, a.other, int64_t(k) * share, int64_t(share));
+          before += wait_for<M>(&a.status[k], a.bits, a.other, int64_t(k) * share, int64_t(share),
+                                a.polls);
         const uint32_t b1 = wave_sum(uint32_t(before)), b2 = kDual ? wave_sum(uint32_t(before >> 32)) : 0;
         if (lane == 0) {
           wave_before[wave] = b1;
@@ -366,6 +368,7 @@ CompactArgs base_args(const DeviceInfo& di, const DedupMaps& m, int32_t* out, in
   a.bits = m.frontier;
   a.other = m.gather;
   a.status = m.status;
+  a.polls = m.polls;
   a.out = out;
   a.out_cap = capacity(out_cap);
   a.n_out = n_out;

@@ -274,3 +274,68 @@ def test_blocks_of_frontiers_in_parts_of_the_range(V, where):
         assert_batch_equal(ref, buf.to_host(seeds_dev), f"{V} {where}")
         assert_blocks_equal(ref, blk.to_host(), f"{V} {where}")
     ctx.check()
+
+
+@pytest.mark.parametrize("V", [1 << 20, (1 << 23) + 1, (1 << 26) + 3, (1 << 28) + 3])
+def test_compaction_that_counts_for_others(V):
+    """With no polls a workgroup counts every share before its own whose status is not there yet: all three kinds of
+    compaction, over byte maps, bit maps, wider shares and several passes, give the same lists."""
+    import oracle
+    import paper_2305_16588_amd as lgp
+    from gpu_common import assert_batch_equal
+    rng = np.random.default_rng(V + 2)
+    gap = max(1, V // 2_000_000)
+    sources = (V + gap - 1) // gap
+    indptr = lgp.pinned_empty(V + 1, np.int32)
+    d = np.zeros(V, np.int32)
+    d[::gap] = 4
+    indptr[0] = 0
+    np.cumsum(d, out=indptr[1:])
+    del d
+    indices = lgp.pinned_copy((rng.integers(0, sources, int(indptr[-1])) * gap).astype(np.int32))
+    indices[::5] = rng.integers(0, V, indices[::5].size)
+    feats = lgp.pinned_empty((V, 1), np.float16)
+    feats[:, 0] = np.arange(V, dtype=np.uint32).astype(np.uint16).view(np.float16)
+    ctx, orc = lgp.Context(indptr, indices, feats), oracle.Oracle(indptr, indices, feats)
+    seeds = (np.unique(rng.integers(0, sources, 9000)) * gap).astype(np.int32)
+    seeds_dev = torch.from_numpy(seeds).cuda()
+    fanouts = (3, 4)
+    both = lgp.SampleBuffers(V, seeds.size, fanouts, last_frontier=True)
+    plain = lgp.SampleBuffers(V, seeds.size, fanouts)
+    rows = torch.empty((both.gather_cap, 1), dtype=torch.float16, device="cuda")
+    ref = orc.sample_khop(seeds, fanouts, 31)
+    for polls in (0, 0, 1, 4096):
+        ctx.set_wait_polls(polls)
+        ctx.sample_khop(seeds_dev, fanouts, 31, out=plain)
+        assert_batch_equal(ref, plain.to_host(seeds_dev), f"{V} {polls}")
+        ctx.sample_khop(seeds_dev, fanouts, 31, out=both)
+        assert_batch_equal(ref, both.to_host(seeds_dev), f"{V} {polls} with the last frontier")
+        ctx.sample_extract(seeds_dev, fanouts, 31, both, rows)
+        fr, _, _, listing = both.to_host(seeds_dev)
+        assert (fr[2] == ref.frontier[2]).all() and listing.tolist() == ref.hop_order.tolist(), f"{V} {polls} listing"
+        assert rows[:listing.size].cpu().numpy().tobytes() == orc.gather(listing).tobytes()
+    with pytest.raises(lgp.LegionPrepError):
+        ctx.set_wait_polls(-1)
+    ctx.check()
+
+
+def test_two_contexts_sample_side_by_side():
+    """Compactions of two contexts wait for their own workgroups while both share the chip."""
+    from gpu_common import assert_batch_equal
+    import paper_2305_16588_amd as lgp
+    V, fanouts = 1 << 20, (5, 4)
+    sides = []
+    for k in range(2):
+        ctx, orc, rng = _workload(V, 6, 77 + k)
+        seeds = np.unique(rng.integers(0, V, 6000)).astype(np.int32)
+        sides.append((ctx, orc, seeds, torch.from_numpy(seeds).cuda(), torch.cuda.Stream(),
+                      [lgp.SampleBuffers(V, seeds.size, fanouts, last_frontier=True) for _ in range(8)]))
+    torch.cuda.synchronize()
+    for i in range(8):
+        for ctx, _, _, dev, stream, bufs in sides:
+            ctx.sample_khop(dev, fanouts, 60 + i, out=bufs[i], stream=stream)
+    torch.cuda.synchronize()
+    for ctx, orc, seeds, dev, _, bufs in sides:
+        for i in range(8):
+            assert_batch_equal(orc.sample_khop(seeds, fanouts, 60 + i), bufs[i].to_host(dev), f"pass {i}")
+        ctx.check()
