@@ -132,14 +132,47 @@ def test_rows_of_any_even_width_and_alignment(row_bytes, shift):
         ctx.build_cache(0, n_cached * row_bytes)
         flat = torch.full((ids.size * D + 16,), 21845, dtype=torch.int16, device="cuda")
         out = flat[shift:shift + ids.size * D].view(torch.float16).view(ids.size, D)
-        try:
-            ctx.gather_features(dev, out=out)
-        except lgp.LegionPrepError as e:
-            assert e.status == -4 and row_bytes // 2 > 4096       # refused widths stay refused
-            continue
+        ctx.gather_features(dev, out=out)
         got = flat.cpu().numpy().view(np.uint16)
         assert (got[shift:shift + want.size] == want).all(), f"{n_cached} rows cached"
         assert (got[:shift] == 21845).all() and (got[shift + want.size:] == 21845).all()
+    ctx.check()
+
+
+@pytest.mark.parametrize("row_bytes,shift,ok", [(8192, 1, True), (8194, 0, False), (8194, 1, False), (8196, 0, True), (8196, 1, False),
+                                                (8196, 2, True), (16384, 2, True), (16388, 0, False), (16392, 0, True),
+                                                (16392, 2, False), (32768, 4, True), (32776, 0, False), (65536, 0, True)])
+def test_widest_rows_of_each_alignment(row_bytes, shift, ok):
+    """A row may have 4096 of the widest chunks that divide it and its output address (2, 4, 8 or 16 bytes); wider ones
+    are refused, when the context is made if no output could do, else by the call."""
+    import paper_2305_16588_amd as lgp
+    V, D = 9, row_bytes // 2
+    rng = np.random.default_rng(row_bytes)
+    feats = lgp.pinned_empty((V, D), np.float16)
+    feats.view(np.uint16)[...] = rng.integers(0, 1 << 16, (V, D), dtype=np.uint16)
+    graph = lgp.pinned_copy(np.zeros(V + 1, np.int32)), lgp.pinned_empty(1, np.int32)[:0]
+    if not ok and row_bytes in (8194, 16388, 32776):
+        with pytest.raises(lgp.LegionPrepError) as e:
+            lgp.Context(*graph, feats)
+        assert e.value.status == -4
+        return
+    ctx = lgp.Context(*graph, feats)
+    ids = np.array([8, 0, 3, 3, 7], np.int32)
+    dev = torch.from_numpy(ids).cuda()
+    ctx.set_hotness(np.zeros(V, np.uint32), np.arange(V, dtype=np.uint32))
+    for n_cached in (0, 4, V):
+        ctx.build_cache(0, n_cached * row_bytes)
+        flat = torch.full((ids.size * D + 16,), 21845, dtype=torch.int16, device="cuda")
+        out = flat[shift:shift + ids.size * D].view(torch.float16).view(ids.size, D)
+        if not ok:
+            with pytest.raises(lgp.LegionPrepError) as e:
+                ctx.gather_features(dev, out=out)
+            assert e.value.status == -4
+            continue
+        ctx.gather_features(dev, out=out)
+        got = flat.cpu().numpy().view(np.uint16)
+        assert (got[shift:shift + ids.size * D] == feats.view(np.uint16)[ids].reshape(-1)).all()
+        assert (got[:shift] == 21845).all() and (got[shift + ids.size * D:] == 21845).all()
     ctx.check()
 
 
