@@ -265,12 +265,16 @@ def measure(inp: Inputs, steps: int, warmup: int, reps: int, topo_frac=None, fea
                          "rows_per_launch": round(miss_rows / prof_g.n_miss, 1), "bytes_per_row": row_bytes}
     # The sampler (whole lgp_sample_khop call: hop kernels + dedup compactions).  Algorithmic bytes per call:
     # per expanded vertex its id (4), its row-table entry (8) and the sampled column ids (4 each) are read, its
-    # nbr row (4 f) and cnt (4) written; every sample sets one bit of the dedup bitmap (an atomic, not counted as
-    # bytes); each of the L compactions reads the V/8-byte bitmap once and writes its id list (4 per id).
+    # nbr row (4 f) and cnt (4) written; every sample marks its vertex in a dedup map (not counted as bytes); each of
+    # the L compactions reads its map once and writes its id list (4 per id).  A map holds a word, a half-word or a byte
+    # per vertex, marked with a plain store, on graphs of up to 2^19, 2^20 and 2^23 vertices, and a bit set with an
+    # atomic beyond.
     roofline_sampler = None
     if prof.n_sample:
         f = np.asarray(spec.fanouts, np.int64)
-        sampler_bytes = int((n_front * (4 + 8 + 4 + 4 * f)).sum() + 4 * n_edges.sum() + 4 * n_lists) + steps * L * (V // 8)
+        bits = 32 if V <= 1 << 19 else 16 if V <= 1 << 20 else 8 if V <= 1 << 23 else 1
+        marks = float(n_edges.sum()) / steps + spec.batch
+        sampler_bytes = int((n_front * (4 + 8 + 4 + 4 * f)).sum() + 4 * n_edges.sum() + 4 * n_lists) + steps * L * (V * bits // 8)
         ms_call = prof.ms_sample / prof.n_sample
         ach = sampler_bytes / steps / (ms_call * 1e-3) / 1e9
         s_traffic = (prof_rec or {}).get("sampler_hbm_bytes_per_call")
@@ -281,7 +285,8 @@ def measure(inp: Inputs, steps: int, warmup: int, reps: int, topo_frac=None, fea
                             "occupancy_percent": (prof_rec or {}).get("sampler_occupancy_percent"),
                             "avg_call_ms": round(ms_call, 4), "bytes_per_call": round(sampler_bytes / steps),
                             "expanded_vertices_per_call": round(float(n_front.sum()) / steps, 1),
-                            "bitmap_atomics_per_call": round(float(n_edges.sum()) / steps + spec.batch, 1)}
+                            "mark": "atomic on a bit" if bits == 1 else f"store of {bits} bits",
+                            "bitmap_atomics_per_call": round(marks, 1)}   # marks of either kind
 
     rec = {
         "value": round(n_steps * spec.batch / elapsed, 1), "unit": "seeds/s", "steps": steps, "warmup": warmup,
