@@ -78,9 +78,9 @@ __device__ __forceinline__ int64_t block_exclusive_scan64(int64_t x, int64_t* to
 // Bucket index of an ascending list of n ids: bucket b holds the ids with (id - first) >> shift == b and begins at
 // start[b].  start[b] is set for every bucket that holds ids and for the one after it, which is where the bucket ends
 // (the last one ends at n): the ids looked up are in the list, so the entries of other empty buckets are never read, and
-// a list crowded into parts of the id range costs no more than one spread over it (100 k destinations x 10, 526 k ids in 2 % of 111 M:
-// 265 us a call with every entry filled, 28 now; 561 k ids at the two ends 354, 33; spread over the range 38 either
-// way).  Buckets split the span of the list, not the id range, so that a list in one corner has as few ids per bucket
+// a list crowded into parts of the id range costs no more than one spread over it (100 k destinations x 10, 526 k ids
+// in 2 % of 111 M: 265 us a call with every entry filled, 28 now; 561 k ids at the two ends 354, 33; spread over the
+// range 38 either way).  Buckets split the span of the list, not the id range, so that a list in one corner has as few ids per bucket
 // as any (2.75 M ids in 2 % of 250 M, 9.8 M x 5: 1490 us split by id range, 1075 by span).  There are at most V
 // buckets, the size of a table.
 struct Buckets {
@@ -222,8 +222,8 @@ __global__ __launch_bounds__(256) void index_lists_kernel(BlocksArgs a, Ranges r
 }
 
 // Range r < n_hops, hop h = n_hops - 1 - r (the longest first): blk_indptr[i] = cnt[0] + ... + cnt[i - 1] for i <= n
-// (64-bit sums), and blk_src of hop h = positions of its samples in frontier h + 1, packed at those offsets.  Range n_hops + k: feat_row of frontier j = n_hops - k, position of its vertex i in the extracted id list
-// (table 0).
+// (64-bit sums), and blk_src of hop h = positions of its samples in frontier h + 1, packed at those offsets.
+// Range n_hops + k: feat_row of frontier j = n_hops - k, position of its vertex i in the extracted id list (table 0).
 // A workgroup pass takes a power of two of destinations with at most kRelabelLoads samples per lane, all looked up
 // at once: a hop of few destinations and a wide fan-out would otherwise be a handful of workgroups in a long chain.
 constexpr int kRelabelLoads = 4;
