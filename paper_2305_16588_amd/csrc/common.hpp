@@ -26,6 +26,9 @@ enum : uint32_t { ERR_BAD_ID = 1u, ERR_OVERRUN = 2u };
 // 79 -> 49 us at 3 M vertices, 74 -> 64 at 6 M, 74 -> 77 at 12 M, 74 -> 94 at 25 M: bytes up to 2^23 vertices.
 // Words instead of bytes on the smallest graphs keep neighbours' marks on different lines (10 k vertices:
 // 2 us of a 33-us call).
+// Calls of few seeds pay the larger scan too, and are still faster than with atomics on spread bits and two launches per
+// compaction: 64 seeds (15, 10, 5) take 28.9 -> 21.8 us at 300 k vertices (words) and 700 k (half-words), 28.9
+// -> 22.4 at 2.4 M and 28.8 -> 25.5 at 8 M (bytes); 16 seeds (10, 5) 20.6 -> 15.7 at 1 M, 20.9 -> 16.1 at 8 M.
 constexpr int64_t kWordMapMaxVertices = int64_t(1) << 19;
 constexpr int64_t kHalfMapMaxVertices = int64_t(1) << 20;
 constexpr int64_t kByteMapMaxVertices = int64_t(1) << 23;
