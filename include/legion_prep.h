@@ -143,15 +143,20 @@ int lgp_shuffle_tablet(int device, const int32_t* in, int32_t* out, int64_t n, u
  * from CPU memory unless a topology cache was built before.  For every expanded vertex its topology hotness grows by
  * the number of edges sampled out of it; for every distinct vertex of a batch's
  * result (seeds included) its feature hotness grows by one.  Both vectors are reset
- * first.  max_batches < 0 processes the whole tablet once.  fanouts is [host]. */
+ * first.  max_batches < 0 processes the whole tablet once.  fanouts is [host].
+ * With many mini-batches the column ids may be copied to HBM after the first one, into
+ * 4 bytes per edge of stream-ordered memory that are given back at the end of the call (never more than half
+ * of what is free, and not after lgp_reserve, under stream capture or beside a topology cache: rows are then read in
+ * place).  The result does not depend on it. */
 int lgp_build_hotness(lgp_ctx* ctx, const int32_t* train_ids, int64_t n_train, int32_t batch,
                       const int32_t* fanouts, int32_t n_hops, uint64_t base_seed, int64_t max_batches,
                       void* stream);
 
 /* What the last lgp_build_hotness did: mini-batches processed and vertex expansions performed
- * (the sum of all frontier sizes).  During pre-sampling every expansion reads its column ids
+ * (the sum of all frontier sizes).  Without a cache every expansion reads its column ids
  * from CPU memory, so n_expansions is the exact count of row reads over PCIe -- on this GPU one
- * 128-byte line each for all but very long rows -- and serves as N_TSUM for
+ * 128-byte line each for all but very long rows -- that pre-sampling makes (unless it copies the
+ * topology to HBM) or would make without the copy, and serves as N_TSUM for
  * lgp_search_cache_plan (with cls_bytes = 128).  Synchronous. */
 int lgp_get_presample_stats(lgp_ctx* ctx, int64_t* n_batches, int64_t* n_expansions);
 

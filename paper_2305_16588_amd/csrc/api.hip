@@ -4,6 +4,7 @@
 #include "common.hpp"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -93,8 +94,10 @@ struct lgp_ctx {
   int32_t* hs_frontier[LGP_MAX_HOPS] = {};
   int64_t hs_cap[LGP_MAX_HOPS] = {};
   int32_t* hs_n = nullptr;
-  unsigned long long* hs_expansions = nullptr;   // device counter: sum of frontier sizes of the last pre-sampling
+  unsigned long long* hs_expansions = nullptr;   // device: sum of frontier sizes of the last pre-sampling, then whether
+                                                 // its topology was staged in HBM (launch_stage_topology)
   int64_t hs_batches = 0;
+  bool indices_on_host = false;                  // the column ids lie in CPU memory
 
   hipStream_t miss_stream = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -136,7 +139,7 @@ int fail_hip(lgp_ctx* ctx, hipError_t e, const char* what) {
   } while (0)
 
 // Resolve a caller pointer to an address kernels can use.
-int device_visible(lgp_ctx* ctx, const void* p, const void** out, const char* name) {
+int device_visible(lgp_ctx* ctx, const void* p, const void** out, const char* name, bool* on_host = nullptr) {
   hipPointerAttribute_t attr;
   std::memset(&attr, 0, sizeof(attr));
   hipError_t e = hipPointerGetAttributes(&attr, p);
@@ -144,6 +147,7 @@ int device_visible(lgp_ctx* ctx, const void* p, const void** out, const char* na
     (void)hipGetLastError();
     return fail(ctx, LGP_EINVAL, std::string(name) + " is not pinned host memory nor device memory");
   }
+  if (on_host) *on_host = attr.type == hipMemoryTypeHost;
   if (attr.type == hipMemoryTypeHost) {
     void* d = nullptr;
     e = hipHostGetDevicePointer(&d, const_cast<void*>(p), 0);
@@ -247,15 +251,20 @@ void prof_end(lgp_ctx* c, EvPair& p, hipStream_t s) {
   c->ev_used.push_back(p);
 }
 
-// Sampling of one mini-batch; out == nullptr is the pre-sampling mode (hotness only).
+// Sampling of one mini-batch; out == nullptr is the pre-sampling mode (hotness only), for which `staged` may hold room for
+// the column ids in HBM.
 int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops,
-                uint64_t rng_seed, const lgp_sample_out* out, hipStream_t s) {
+                uint64_t rng_seed, const lgp_sample_out* out, hipStream_t s, const int32_t* staged = nullptr) {
   const bool hot_mode = (out == nullptr);
   const int64_t V = c->g.num_vertices;
   uint32_t* fbits32 = reinterpret_cast<uint32_t*>(c->maps.frontier);
   uint32_t* gbits32 = reinterpret_cast<uint32_t*>(c->maps.gather);
   int32_t* n_frontier = hot_mode ? c->hs_n : out->n_frontier;
-  const TopoView tv = topo_view(c);
+  TopoView tv = topo_view(c);
+  if (staged) {
+    tv.staged = staged;
+    tv.use_staged = reinterpret_cast<const uint64_t*>(c->hs_expansions + 1);
+  }
 
   const int32_t* frontier = seeds;
   int64_t cap = n_seeds;
@@ -484,6 +493,38 @@ int gather_core(lgp_ctx* c, int32_t member, const int32_t* ids, int64_t n_max, c
   return LGP_OK;
 }
 
+// Room in HBM for the column ids while pre-sampling runs, or null if it is not worth having: launch_stage_topology decides
+// with the first batch's row count, and this estimate keeps calls that will hardly stage from paying for the room (10-40 us,
+// and up to 0.3 ms when it is given back): at least 24 MB, half a millisecond of the link, must be saved.  It takes the
+// expected distinct samples of uniformly popular vertices, halved: on graphs whose popularity falls with the rank (2.4 M
+// vertices, 8192 seeds, 15-10-5) it gives 530 k rows a batch where 263 k are read.  A topology cache that is in place
+// already serves the rows that are read often, so nothing is staged beside it.
+constexpr double kStageSaving = 24e6;
+int32_t* staging_room(const lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts, int32_t n_hops, int64_t n_batches,
+                      hipStream_t s, void** base) {
+  *base = nullptr;
+  if (!c->indices_on_host || c->reserved || c->plan.n_topo > 0 || n_batches < 2) return nullptr;
+  const double V = double(c->g.num_vertices), degree = double(c->g.num_edges) / V;
+  double n = double(n_seeds), rows = n;
+  for (int h = 0; h + 1 < n_hops; ++h) {
+    n = V * -std::expm1(-n * std::min(degree, double(fanouts[h])) / V);
+    rows += n;
+  }
+  if (0.5 * rows * double(n_batches - 1) * 128.0 - double(c->g.num_edges) * 4.0 < kStageSaving) return nullptr;
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  size_t free_bytes = 0, total_bytes = 0;
+  const size_t bytes = size_t(c->g.num_edges) * 4 + 16;
+  // no allocation under capture, and never more than half of the free memory; without room the rows are read in place
+  if (hipStreamIsCapturing(s, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone ||
+      hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess || bytes > free_bytes / 2 ||
+      hipMallocAsync(base, bytes, s) != hipSuccess) {
+    (void)hipGetLastError();
+    *base = nullptr;
+    return nullptr;
+  }
+  return static_cast<int32_t*>(*base) + ((uintptr_t(c->g.indices) >> 2) & 3);
+}
+
 }  // namespace
 
 extern "C" {
@@ -558,7 +599,7 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   if ((st = device_visible(c, g->indptr, &p, "indptr")) != LGP_OK) return bail(st);
   c->g.indptr = p;
   if (g->indices) {
-    if ((st = device_visible(c, g->indices, &p, "indices")) != LGP_OK) return bail(st);
+    if ((st = device_visible(c, g->indices, &p, "indices", &c->indices_on_host)) != LGP_OK) return bail(st);
     c->g.indices = static_cast<const int32_t*>(p);
   }
   if (g->features) {
@@ -588,7 +629,7 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   step(dev_alloc(&c->d_err, 1));
   step(dev_alloc(&c->counters, 3));
   step(dev_alloc(&c->hs_n, LGP_MAX_HOPS + 1));
-  step(dev_alloc(&c->hs_expansions, 1));
+  step(dev_alloc(&c->hs_expansions, 2));
   step(dev_alloc(&c->seg, LGP_MAX_HOPS + 2));
   step(dev_alloc(&c->unordered, LGP_MAX_HOPS + 1));
   step(dev_alloc(&c->seg_counters, (LGP_MAX_HOPS + 1) * 3));
@@ -600,7 +641,7 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   if (e == hipSuccess) e = hipMemset(c->d_err, 0, sizeof(uint32_t));
   if (e == hipSuccess) e = hipMemset(c->counters, 0, 3 * sizeof(int32_t));
   if (e == hipSuccess) e = hipMemset(c->unordered, 0, (LGP_MAX_HOPS + 1) * sizeof(uint32_t));
-  if (e == hipSuccess) e = hipMemset(c->hs_expansions, 0, sizeof(unsigned long long));
+  if (e == hipSuccess) e = hipMemset(c->hs_expansions, 0, 2 * sizeof(unsigned long long));
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->miss_stream, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming);
@@ -665,15 +706,24 @@ int lgp_build_hotness(lgp_ctx* c, const int32_t* train_ids, int64_t n_train, int
   if (st != LGP_OK) return st;
   launch_fill_i32(c->di, reinterpret_cast<int32_t*>(c->topo_hot), V, 0, s);
   launch_fill_i32(c->di, reinterpret_cast<int32_t*>(c->feat_hot), V, 0, s);
-  launch_fill_i32(c->di, reinterpret_cast<int32_t*>(c->hs_expansions), 2, 0, s);
+  launch_fill_i32(c->di, reinterpret_cast<int32_t*>(c->hs_expansions), 4, 0, s);
   int64_t n_batches = (n_train + batch - 1) / batch;
   if (max_batches >= 0 && max_batches < n_batches) n_batches = max_batches;
-  for (int64_t b = 0; b < n_batches; ++b) {
+  void* room = nullptr;
+  int32_t* const staged = staging_room(c, need[0], fanouts, n_hops, n_batches, s, &room);
+  for (int64_t b = 0; b < n_batches && st == LGP_OK; ++b) {
     const int64_t lo = b * batch;
     const int32_t nb = int32_t(std::min<int64_t>(batch, n_train - lo));
-    st = sample_core(c, train_ids + lo, nb, fanouts, n_hops, base_seed + uint64_t(b), nullptr, s);
-    if (st != LGP_OK) return st;
+    if (staged && b == 1)
+      launch_stage_topology(c->g.indices, staged, c->g.num_edges, c->hs_expansions, n_batches - 1,
+                            reinterpret_cast<uint64_t*>(c->hs_expansions + 1), s);
+    st = sample_core(c, train_ids + lo, nb, fanouts, n_hops, base_seed + uint64_t(b), nullptr, s, b > 0 ? staged : nullptr);
   }
+  if (room) {
+    const hipError_t e = hipFreeAsync(room, s);
+    if (e != hipSuccess && st == LGP_OK) st = fail_hip(c, e, "giving back the room of the staged topology");
+  }
+  if (st != LGP_OK) return st;
   c->hs_batches = n_batches;
   c->have_hot = true;
   return LGP_OK;

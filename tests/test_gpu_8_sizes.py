@@ -372,3 +372,32 @@ def test_two_contexts_sample_side_by_side():
         for i in range(8):
             assert_batch_equal(orc.sample_khop(seeds, fanouts, 60 + i), bufs[i].to_host(dev), f"pass {i}")
         ctx.check()
+
+
+@pytest.mark.parametrize("skip,V,n_edges,batch", [(0, 30_000, 240_000, 512), (1, 30_000, 240_001, 512),
+                                                  (2, 30_000, 240_003, 512), (3, 30_000, 240_002, 512),
+                                                  (1, 1_000_000, 6, 4096), (3, 1_000_000, 1, 4096), (0, 5000, 0, 64)])
+def test_pre_sampling_with_staged_topology(skip, V, n_edges, batch):
+    """Many mini-batches on a small graph, whose column ids are copied to HBM after the first one: arrays that begin at any
+    multiple of four bytes and end inside a 16-byte chunk, arrays shorter than a chunk; and calls that read in place (few
+    batches, no edges, after lgp_reserve)."""
+    import oracle
+    import paper_2305_16588_amd as lgp
+    fanouts = (10, 10, 2)
+    rng = np.random.default_rng(skip * 100_003 + n_edges)
+    indptr = lgp.pinned_copy(np.concatenate([[0], np.sort(rng.integers(0, n_edges + 1, V - 1)), [n_edges]]).astype(np.int32))
+    indices = lgp.pinned_empty(n_edges + 8, np.int32)[skip:skip + n_edges]
+    indices[:] = rng.integers(0, V, n_edges)
+    ctx, orc = lgp.Context(indptr, indices), oracle.Oracle(indptr, indices, None)
+    tablet = rng.permutation(V).astype(np.int32)
+    dev = torch.from_numpy(tablet).cuda()
+    for max_batches in (-1, 2, 1, -1):
+        ctx.build_hotness(dev, batch, fanouts, 5, max_batches=max_batches)
+        rt, rf, _ = orc.build_hotness(tablet, batch, fanouts, 5, max_batches=max_batches)
+        topo, feat = ctx.get_hotness()
+        assert (topo == rt).all() and (feat == rf).all(), f"{max_batches} batches"
+    ctx.reserve(batch, fanouts)                                  # nothing may be allocated now: rows are read in place
+    ctx.build_hotness(dev, batch, fanouts, 5)
+    topo, feat = ctx.get_hotness()
+    assert (topo == rt).all() and (feat == rf).all()
+    ctx.check()
