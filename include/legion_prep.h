@@ -324,13 +324,12 @@ int lgp_gather_features(lgp_ctx* ctx, const int32_t* ids, int64_t n_max, const i
 int lgp_gather_features_static(lgp_ctx* ctx, const int32_t* ids, int64_t n_max, const int32_t* n_dev, void* out,
                                int32_t* stats, void* stream);
 
-/* By default lgp_gather_features runs the hit gather and then the miss gather on
- * `stream`.  With overlap enabled the miss gather runs on a stream of the library's own
- * beside the hit gather, which is then launched a quarter as wide so that its requests do
- * not crowd the PCIe reads, and `stream` waits for both.  Measured on MI355X with misses
- * dominating (2.4 M vertices, 400-byte rows, 30 % of them cached): 2.49 ms per step instead
- * of 2.56 ms.  The hit gather itself takes many times longer that way (PCIe reads queued
- * ahead of it throttle it), so per-kernel timings are only meaningful with overlap off,
+/* By default lgp_gather_features copies hits and misses in one launch on `stream`, side by
+ * side (rows below 16 bytes, and calls timed by lgp_set_profiling: the hit gather, then the
+ * miss gather).  With overlap enabled the miss gather is a launch of its own on a stream of the
+ * library's own beside the hit gather, which is then launched a quarter as wide so that its requests do
+ * not crowd the PCIe reads, and `stream` waits for both.  The hit gather itself takes many times longer
+ * beside PCIe reads that are queued ahead of it, so per-kernel timings are only meaningful with overlap off,
  * which is the default.  A process has a few hardware queues (four by default) and HIP
  * spreads streams over them: if the library's stream and `stream` happen to share one, the
  * result is the same but the two gathers run one after the other.  The same holds for

@@ -459,6 +459,13 @@ int gather_core(lgp_ctx* c, int32_t member, const int32_t* ids, int64_t n_max, c
                      three ? int32_t(c->clique_fn[member]) : 0, three ? int32_t(c->clique_fn[member + 1]) : 0, counters,
                      c->d_err, s, window, window_items);
     prof_end(c, ev, s);
+    // Hits and misses in one launch, unless they are to be timed apart or run on two streams.
+    if (c->profiling == 0 && !c->overlap &&
+        launch_gather_split(c->di, c->fc, c->g.features, out, c->row_bytes, L, three, n_max, counters,
+                            window ? window_items : 0, s)) {
+      hipError_t e = hipGetLastError();
+      return e == hipSuccess ? LGP_OK : fail_hip(c, e, "gather kernel launch");
+    }
     // Hits first (HBM -> HBM, short), then misses (PCIe, long).  With overlap enabled the
     // misses run on a second stream beside the hits and rejoin `s` afterwards.
     hipStream_t ms = s;

@@ -200,6 +200,13 @@ void launch_gather_rows(const DeviceInfo& di, const void* src, void* dst, int64_
                         hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr, bool beside_pcie = false,
                         int64_t grid_items = 0);
 
+// Hits and misses of a partition in one launch, side by side: rows of lists[0] (and lists[2] with peers) from hit_src, rows
+// of lists[1] from miss_src in CPU memory; counters as launch_partition left them.  False, and nothing is launched, for rows
+// below 16 bytes.
+bool launch_gather_split(const DeviceInfo& di, const void* hit_src, const void* miss_src, void* dst, int64_t row_bytes,
+                         const PartLists& lists, bool peers, int64_t n_max, const int32_t* counters, int64_t grid_items,
+                         hipStream_t s);
+
 // ---- blocks.hip -----------------------------------------------------------
 constexpr int kScanTile = 1024;   // elements per workgroup of the counts -> offsets scan
 // Everything one graph-constructor call reads and writes.  cap[h] = 0 marks a frontier that

@@ -1,8 +1,9 @@
 // Feature extractor (Sec. 2.2 step 3; Sec. 5 "feature extractor") for gfx950:
-// cache lookup + hit/miss partition, then two row-gather launches -- hits move
-// HBM -> HBM, misses are read in place from CPU memory over PCIe.
+// cache lookup + hit/miss partition, then one row-gather launch for both -- hits move
+// HBM -> HBM, misses are read in place from CPU memory over PCIe beside them (gather_split_kernel),
+// or two launches where they are timed apart or run on two streams.
 //
-// Two row-gather kernels share the work.  The group kernel further down gives every row a
+// Two row-gather kernels share the work of calls with one kind of row.  The group kernel further down gives every row a
 // group of lanes: it serves the misses, the cache fill and the hits on rows that straddle
 // 128-byte lines.  The flat kernel serves hits on rows made of whole lines:
 // a wavefront takes 64 list entries (one coalesced load of the row / source
@@ -12,7 +13,7 @@
 // (row, source) pair a chunk belongs to is fetched from the owning lane by a
 // cross-lane read, the LDS-crossbar path (ds_bpermute) -- the rows themselves never
 // need to sit in LDS because a chunk is loaded and stored by the same lane.
-#include "common.hpp"
+#include "gather_dev.hpp"
 
 #include <hip/hip_ext.h>
 
@@ -21,33 +22,6 @@
 
 namespace lgp {
 namespace {
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-// A row is copied in chunks of sizeof(VecT) bytes.  RAGGED: row width or addresses are no multiple of that; the
-// chunks then start at any even address (global loads and stores of any width may), and the last one ends where
-// the row ends, overlapping the one before it with the same bytes.  Copying such rows in the widest chunk that
-// divides them instead leaves most of a lane's 16 bytes unused: cached rows of 150 bytes (238 k) took 74 us in
-// 2-byte chunks and take 20.5, of 602 bytes 296 and 72, of 200 bytes (8-byte chunks) 27.5 and 23.
-template <typename VecT, bool RAGGED>
-struct Chunk {
-  typedef VecT T;
-};
-template <typename VecT>
-struct Chunk<VecT, true> {
-  typedef VecT T __attribute__((aligned(2)));
-};
-struct RowShape {
-  uint32_t cpr;    // chunks per row
-  uint32_t bytes;  // row width
-  uint32_t last;   // where the last chunk starts: bytes - sizeof(VecT)
-};
-template <typename VecT, bool RAGGED>
-__device__ __forceinline__ uint32_t chunk_at(const RowShape& r, uint32_t col) {
-  const uint32_t at = col * uint32_t(sizeof(VecT));
-  return RAGGED ? (at < r.last ? at : r.last) : at;
-}
 
 __global__ void zero_counters_kernel(int32_t* counters, int n) {
   if (int(threadIdx.x) < n) counters[threadIdx.x] = 0;
@@ -133,23 +107,6 @@ __global__ __launch_bounds__(256) void partition_kernel(
   }
 }
 
-__device__ __forceinline__ void direct_stats(const DirectIds& dir, int64_t n) {
-  if (dir.stats && blockIdx.x == 0 && threadIdx.x == 0) {
-    dir.stats[dir.stats_slot] = int32_t(n > 0 ? n : 0);
-    dir.stats[1 - dir.stats_slot] = 0;
-  }
-}
-
-// Translate one entry of the source-row array; -1 = skip this row.
-__device__ __forceinline__ int32_t direct_source(const DirectIds& dir, int32_t entry, bool in_range) {
-  if (dir.num_vertices == 0 || !in_range) return in_range ? entry : -1;
-  if (uint32_t(entry) >= uint64_t(dir.num_vertices)) {
-    atomicOr(dir.d_err, ERR_BAD_ID);
-    return -1;
-  }
-  return dir.remap ? dir.remap[entry] : entry;
-}
-
 // ---- cache hits: HBM -> HBM ------------------------------------------------
 // A wavefront takes 64 list entries and walks their rows as one flat run of chunks:
 // all 64 lanes stay busy for any row width and UNROLL loads per lane are in flight
@@ -170,7 +127,7 @@ __global__ __launch_bounds__(256) void gather_rows_flat_kernel(const char* __res
     n = dir.window[1];
   }
   if (n > n_max) n = n_max;
-  direct_stats(dir, n - lo);
+  if (blockIdx.x == 0) direct_stats(dir, n - lo);
   const int lane = threadIdx.x & 63;
   const int64_t wave = (int64_t(blockIdx.x) * 256 + threadIdx.x) >> 6;
   const int64_t n_waves = int64_t(gridDim.x) * 4;
@@ -219,85 +176,46 @@ __global__ __launch_bounds__(256) void gather_rows_flat_kernel(const char* __res
 }
 
 // ---- cache misses and cache fill: CPU memory -> HBM over PCIe ---------------
-// Reads of CPU memory are not cached on the GPU and travel as whole 128-byte lines, so
-// a line requested by two different load instructions crosses the link twice.  Here a
-// group of G >= chunks-per-row lanes owns a whole row, so one instruction requests each
-// line of the row exactly once; UNROLL rows per group are in flight before the first
-// store.  Rows wider than 64 chunks are walked in 64-chunk pieces.  HBM_SOURCE selects the
-// variant used for cache hits on rows that straddle lines (cached loads, streaming stores).
+// One lane group per row (see group_rows).
 template <typename VecT, bool RAGGED, int G, int UNROLL, bool HBM_SOURCE>
 __global__ __launch_bounds__(256) void gather_rows_group_kernel(const char* __restrict__ src, char* __restrict__ dst,
                                                                 RowShape shape, const int32_t* __restrict__ row,
                                                                 const int32_t* __restrict__ srcrow, int64_t n_max,
                                                                 const int32_t* __restrict__ n_dev, DirectIds dir) {
-  // carried pointers keep their address space only if it is spelled out
-  typedef __attribute__((address_space(1))) char Global;
-  typedef __attribute__((address_space(1))) typename Chunk<VecT, RAGGED>::T GlobalMem;
-  int64_t n = n_dev ? int64_t(*n_dev) : n_max;
-  int64_t lo = 0;
-  if (dir.window) {
-    lo = dir.window[0] < 0 ? 0 : dir.window[0];
-    n = dir.window[1];
+  group_rows<VecT, RAGGED, UNROLL, HBM_SOURCE>(src, dst, shape, row, srcrow, n_max, n_dev, dir, G, blockIdx.x, gridDim.x);
+}
+
+// ---- hits and misses in one launch --------------------------------------------
+// The two lists of a partition (three for a clique member: list 2 is a second list of rows in HBM).  One after the other,
+// the link idles while the hits are copied and HBM while the misses arrive; here the first miss_blocks workgroups
+// take the misses and the others the hits, beside them.  Calls, one after the other -> beside each other: 400-byte rows of
+// 2.4 M vertices, 688 k ids, 30 / 70 / 95 / 99.5 % of the table cached 2925 -> 2844, 1208 -> 1100, 324 -> 231, 163 -> 148 us;
+// 2-KiB rows, 95 % 445 -> 310; 7 k ids of 10 k vertices (512-byte rows, 20 %) 76 -> 65.
+struct SplitArgs {
+  const char* hit_src;
+  const char* miss_src;
+  char* dst;
+  RowShape hit_shape, miss_shape;
+  PartLists lists;
+  const int32_t* counters;
+  int64_t n_max;
+  uint32_t hit_lanes, miss_lanes, miss_blocks;
+  bool peers;
+};
+constexpr int kSplitHitUnroll = 2;
+template <typename VecT, bool RAGGED>
+__global__ __launch_bounds__(256) void gather_split_kernel(SplitArgs a) {
+  const DirectIds listed{nullptr, 0, nullptr, 0, nullptr, nullptr};
+  if (blockIdx.x < a.miss_blocks) {
+    group_rows<VecT, RAGGED, 4, false>(a.miss_src, a.dst, a.miss_shape, a.lists.row[1], a.lists.src[1], a.n_max,
+                                       a.counters + 1, listed, a.miss_lanes, blockIdx.x, a.miss_blocks);
+    return;
   }
-  if (n > n_max) n = n_max;
-  direct_stats(dir, n - lo);
-  const uint32_t sub = threadIdx.x % G;
-  const int64_t group = (int64_t(blockIdx.x) * 256 + threadIdx.x) / G;
-  const int64_t n_groups = int64_t(gridDim.x) * (256 / G);
-  // The list entries of the next pass are loaded before the rows of this one, so that a pass waits
-  // for one round trip to memory (its rows), not two in a row (entries, then rows).
-  int32_t next_src[UNROLL], next_row[UNROLL];
-  const int64_t first = lo + group * UNROLL;
-#pragma unroll
-  for (int u = 0; u < UNROLL; ++u) {
-    const int64_t e = first + u;
-    next_src[u] = e < n ? (srcrow ? srcrow[e] : int32_t(e)) : 0;
-    next_row[u] = e < n ? (row ? row[e] : int32_t(e)) : 0;
-  }
-  for (int64_t e0 = first; e0 < n; e0 += n_groups * UNROLL) {
-    int64_t so[UNROLL], dof[UNROLL];
-#pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-      const bool ok = e0 + u < n;
-      const int32_t sr = direct_source(dir, next_src[u], ok);
-      so[u] = sr >= 0 ? int64_t(sr) * shape.bytes : -1;
-      dof[u] = int64_t(next_row[u]) * shape.bytes;
-      const int64_t e = e0 + n_groups * UNROLL + u;
-      next_src[u] = e < n ? (srcrow ? srcrow[e] : int32_t(e)) : 0;
-      next_row[u] = e < n ? (row ? row[e] : int32_t(e)) : 0;
-    }
-    // Addresses are carried from piece to piece: computed at the load they would share its registers and make it
-    // wait for the entries requested above (38 -> 44 us on 400-byte rows).
-    uint32_t at = chunk_at<VecT, RAGGED>(shape, sub);
-    const Global* from[UNROLL];
-    Global* to[UNROLL];
-#pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-      from[u] = (const Global*)(src) + (so[u] + at);
-      to[u] = (Global*)(dst) + (dof[u] + at);
-    }
-    for (uint32_t c0 = 0; c0 < shape.cpr; c0 += G) {
-      const bool in_row = c0 + sub < shape.cpr;
-      VecT val[UNROLL];
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u)
-        if (so[u] >= 0 && in_row)
-          val[u] = HBM_SOURCE ? *(const GlobalMem*)(from[u]) : __builtin_nontemporal_load((const GlobalMem*)(from[u]));
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u)
-        if (so[u] >= 0 && in_row) {
-          if (HBM_SOURCE) __builtin_nontemporal_store(val[u], (GlobalMem*)(to[u]));
-          else *(GlobalMem*)(to[u]) = val[u];
-        }
-      const uint32_t next = chunk_at<VecT, RAGGED>(shape, c0 + G + sub);
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
-        from[u] += next - at;
-        to[u] += next - at;
-      }
-      at = next;
-    }
-  }
+  const uint32_t block = blockIdx.x - a.miss_blocks, blocks = gridDim.x - a.miss_blocks;
+  for (int l = 0; l <= (a.peers ? 2 : 0); l += 2)
+    group_rows<u32x4, true, kSplitHitUnroll, true>(a.hit_src, a.dst, a.hit_shape, l ? a.lists.row[2] : a.lists.row[0],
+                                                   l ? a.lists.src[2] : a.lists.src[0], a.n_max, a.counters + l, listed,
+                                                   a.hit_lanes, block, blocks);
 }
 
 inline unsigned blocks_for(int64_t work_blocks, int64_t limit) {
@@ -415,6 +333,26 @@ void launch_group(const DeviceInfo& di, const char* src, char* dst, const RowSha
   else launch_group_g<VecT, RAGGED, 64>(di, src, dst, shape, row, srcrow, n_max, n_dev, dir, s);
 }
 
+// The widest chunk that fits the row; RAGGED (see Chunk) where rows or addresses are no multiple of it.  Over PCIe
+// a chunk that straddles two lines requests one of them a second time, so there a row that divides into at most
+// 32 aligned chunks of 4 or 8 bytes -- one load instruction of a 32-lane group -- keeps them (200-byte rows: 240 us
+// ragged, 233 aligned; 100-byte rows 181 / 179; but 50-byte rows of 2-byte chunks 150 ragged, 154 aligned, and
+// rows of more chunks 302 / 329 at 300 bytes, 509 / 1060 at 602).  align: addresses and row width, OR-ed.
+int64_t chunk_width(uintptr_t align, int64_t row_bytes, bool streaming) {
+  const int64_t whole = (align & 15) == 0 ? 16 : (align & 7) == 0 ? 8 : (align & 3) == 0 ? 4 : 2;
+  if (streaming && whole >= 4 && row_bytes / whole <= 32) return whole;
+  return row_bytes >= 16 ? 16 : row_bytes >= 8 ? 8 : row_bytes >= 4 ? 4 : 2;
+}
+RowShape row_shape(int64_t row_bytes, int64_t width) {
+  return RowShape{uint32_t((row_bytes + width - 1) / width), uint32_t(row_bytes), uint32_t(row_bytes - width)};
+}
+// Lanes of the group that owns a row: the power of two that covers its chunks, 4 to 64.
+uint32_t group_lanes(const RowShape& r) {
+  uint32_t g = 4;
+  while (g < r.cpr && g < 64) g *= 2;
+  return g;
+}
+
 }  // namespace
 
 void launch_partition(const DeviceInfo& di, const int32_t* ids, int64_t n_max, const int32_t* n_dev,
@@ -448,16 +386,9 @@ void launch_gather_rows(const DeviceInfo& di, const void* src, void* dst, int64_
   // gather, 2.24 ms beside a narrow one, and the step 2.49 ms instead of 2.66 ms).
   const Where s{stream, ev_start, ev_stop, int64_t(di.num_cus) * (beside_pcie ? 2 : 8),
                 (grid_items > 0 && grid_items < n_max) ? grid_items : n_max};
-  // The widest chunk that fits the row; RAGGED (see Chunk) where rows or addresses are no multiple of it.  Over PCIe
-  // a chunk that straddles two lines requests one of them a second time, so there a row that divides into at most
-  // 32 aligned chunks of 4 or 8 bytes -- one load instruction of a 32-lane group -- keeps them (200-byte rows: 240 us
-  // ragged, 233 aligned; 100-byte rows 181 / 179; but 50-byte rows of 2-byte chunks 150 ragged, 154 aligned, and
-  // rows of more chunks 302 / 329 at 300 bytes, 509 / 1060 at 602).
   const uintptr_t align = uintptr_t(src) | uintptr_t(dst) | uintptr_t(row_bytes);
-  int64_t width = row_bytes >= 16 ? 16 : row_bytes >= 8 ? 8 : row_bytes >= 4 ? 4 : 2;
-  const int64_t whole = (align & 15) == 0 ? 16 : (align & 7) == 0 ? 8 : (align & 3) == 0 ? 4 : 2;
-  if (streaming && whole >= 4 && row_bytes / whole <= 32) width = whole;
-  const RowShape shape{uint32_t((row_bytes + width - 1) / width), uint32_t(row_bytes), uint32_t(row_bytes - width)};
+  const int64_t width = chunk_width(align, row_bytes, streaming);
+  const RowShape shape = row_shape(row_bytes, width);
   const char* from = static_cast<const char*>(src);
   char* to = static_cast<char*>(dst);
   auto rows = [&](auto vec, auto ragged) {
@@ -476,6 +407,38 @@ void launch_gather_rows(const DeviceInfo& di, const void* src, void* dst, int64_
   else if (width == 8) width_of(u32x2{});
   else if (width == 4) width_of(uint32_t{});
   else rows(uint16_t{}, std::false_type{});
+}
+
+bool launch_gather_split(const DeviceInfo& di, const void* hit_src, const void* miss_src, void* dst, int64_t row_bytes,
+                         const PartLists& lists, bool peers, int64_t n_max, const int32_t* counters, int64_t grid_items,
+                         hipStream_t s) {
+  if (row_bytes < 16) return false;
+  const uintptr_t align = uintptr_t(miss_src) | uintptr_t(dst) | uintptr_t(row_bytes);
+  const int64_t width = chunk_width(align, row_bytes, true);
+  const int64_t items = (grid_items > 0 && grid_items < n_max) ? grid_items : n_max;
+  SplitArgs a = {};
+  a.hit_src = static_cast<const char*>(hit_src);
+  a.miss_src = static_cast<const char*>(miss_src);
+  a.dst = static_cast<char*>(dst);
+  a.hit_shape = row_shape(row_bytes, 16);
+  a.miss_shape = row_shape(row_bytes, width);
+  a.lists = lists;
+  a.counters = counters;
+  a.n_max = n_max;
+  a.hit_lanes = group_lanes(a.hit_shape);
+  a.miss_lanes = group_lanes(a.miss_shape);
+  a.peers = peers;
+  const int64_t miss_pass = 256 / a.miss_lanes * 4, hit_pass = 256 / a.hit_lanes * kSplitHitUnroll;
+  a.miss_blocks = blocks_for((items + miss_pass - 1) / miss_pass, std::max(1, di.num_cus / 4));
+  // Misses keep the width that suits the link; hits take six workgroups per CU with two rows per group in flight.  At 2 / 4 /
+  // 6 / 8 per CU: 512-byte rows, 688 k of 2.4 M ids with 95 % of the table cached 291 / 252 / 233 / 227 us a call, 30 % cached and
+  // 400-byte rows 2841 / 2843 / 2850 / 2845, 99.5 % cached 167 / 150 / 148 / 156.
+  const unsigned hit_blocks = blocks_for((items + hit_pass - 1) / hit_pass, int64_t(di.num_cus) * 6);
+  const dim3 grid{a.miss_blocks + hit_blocks}, block{256};
+  if (width == 16) hipLaunchKernelGGL((gather_split_kernel<u32x4, true>), grid, block, 0, s, a);
+  else if (width == 8) hipLaunchKernelGGL((gather_split_kernel<u32x2, false>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((gather_split_kernel<uint32_t, false>), grid, block, 0, s, a);
+  return true;
 }
 
 }  // namespace lgp

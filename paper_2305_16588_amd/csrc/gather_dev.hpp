@@ -1,0 +1,140 @@
+// Device code of the row gather that more than one kernel is built from.
+#pragma once
+
+#include "common.hpp"
+
+namespace lgp {
+namespace {
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// A row is copied in chunks of sizeof(VecT) bytes.  RAGGED: row width or addresses are no multiple of that; the
+// chunks then start at any even address (global loads and stores of any width may), and the last one ends where
+// the row ends, overlapping the one before it with the same bytes.  Copying such rows in the widest chunk that
+// divides them instead leaves most of a lane's 16 bytes unused: cached rows of 150 bytes (238 k) took 74 us in
+// 2-byte chunks and take 20.5, of 602 bytes 296 and 72, of 200 bytes (8-byte chunks) 27.5 and 23.
+template <typename VecT, bool RAGGED>
+struct Chunk {
+  typedef VecT T;
+};
+template <typename VecT>
+struct Chunk<VecT, true> {
+  typedef VecT T __attribute__((aligned(2)));
+};
+struct RowShape {
+  uint32_t cpr;    // chunks per row
+  uint32_t bytes;  // row width
+  uint32_t last;   // where the last chunk starts: bytes - sizeof(VecT)
+};
+template <typename VecT, bool RAGGED>
+__device__ __forceinline__ uint32_t chunk_at(const RowShape& r, uint32_t col) {
+  const uint32_t at = col * uint32_t(sizeof(VecT));
+  return RAGGED ? (at < r.last ? at : r.last) : at;
+}
+
+// Called by one workgroup.
+__device__ __forceinline__ void direct_stats(const DirectIds& dir, int64_t n) {
+  if (dir.stats && threadIdx.x == 0) {
+    dir.stats[dir.stats_slot] = int32_t(n > 0 ? n : 0);
+    dir.stats[1 - dir.stats_slot] = 0;
+  }
+}
+
+// Translate one entry of the source-row array; -1 = skip this row.
+__device__ __forceinline__ int32_t direct_source(const DirectIds& dir, int32_t entry, bool in_range) {
+  if (dir.num_vertices == 0 || !in_range) return in_range ? entry : -1;
+  if (uint32_t(entry) >= uint64_t(dir.num_vertices)) {
+    atomicOr(dir.d_err, ERR_BAD_ID);
+    return -1;
+  }
+  return dir.remap ? dir.remap[entry] : entry;
+}
+
+// ---- rows by lane groups -----------------------------------------------------
+// Reads of CPU memory are not cached on the GPU and travel as whole 128-byte lines, so
+// a line requested by two different load instructions crosses the link twice.  Here a
+// group of `lanes` >= chunks-per-row lanes (a power of two) owns a whole row, so one instruction requests each
+// line of the row exactly once; UNROLL rows per group are in flight before the first
+// store.  Rows wider than 64 chunks are walked in 64-chunk pieces.  HBM_SOURCE selects the
+// variant used for cache hits on rows that straddle lines (cached loads, streaming stores).
+// A workgroup pass takes consecutive entries, and so does each of its load instructions: where consecutive entries are
+// neighbouring rows, the line that two of them share is requested once.
+// The caller is workgroup `block` of `blocks` that share the entries.
+template <typename VecT, bool RAGGED, int UNROLL, bool HBM_SOURCE>
+__device__ __forceinline__ void group_rows(const char* __restrict__ src, char* __restrict__ dst, const RowShape& shape,
+                                           const int32_t* __restrict__ row, const int32_t* __restrict__ srcrow,
+                                           int64_t n_max, const int32_t* __restrict__ n_dev, const DirectIds& dir,
+                                           uint32_t lanes, uint32_t block, uint32_t blocks) {
+  // carried pointers keep their address space only if it is spelled out
+  typedef __attribute__((address_space(1))) char Global;
+  typedef __attribute__((address_space(1))) typename Chunk<VecT, RAGGED>::T GlobalMem;
+  int64_t n = n_dev ? int64_t(*n_dev) : n_max;
+  int64_t lo = 0;
+  if (dir.window) {
+    lo = dir.window[0] < 0 ? 0 : dir.window[0];
+    n = dir.window[1];
+  }
+  if (n > n_max) n = n_max;
+  if (block == 0) direct_stats(dir, n - lo);
+  const uint32_t groups = 256u / lanes;                       // rows per load instruction of the workgroup
+  const uint32_t sub = threadIdx.x & (lanes - 1);
+  const int64_t pass = int64_t(groups) * UNROLL;
+  // The list entries of the next pass are loaded before the rows of this one, so that a pass waits
+  // for one round trip to memory (its rows), not two in a row (entries, then rows).
+  int32_t next_src[UNROLL], next_row[UNROLL];
+  const int64_t first = lo + int64_t(block) * pass + threadIdx.x / lanes;
+#pragma unroll
+  for (int u = 0; u < UNROLL; ++u) {
+    const int64_t e = first + u * groups;
+    next_src[u] = e < n ? (srcrow ? srcrow[e] : int32_t(e)) : 0;
+    next_row[u] = e < n ? (row ? row[e] : int32_t(e)) : 0;
+  }
+  for (int64_t e0 = first; e0 < n; e0 += int64_t(blocks) * pass) {
+    int64_t so[UNROLL], dof[UNROLL];
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      const bool ok = e0 + u * groups < n;
+      const int32_t sr = direct_source(dir, next_src[u], ok);
+      so[u] = sr >= 0 ? int64_t(sr) * shape.bytes : -1;
+      dof[u] = int64_t(next_row[u]) * shape.bytes;
+      const int64_t e = e0 + int64_t(blocks) * pass + u * groups;
+      next_src[u] = e < n ? (srcrow ? srcrow[e] : int32_t(e)) : 0;
+      next_row[u] = e < n ? (row ? row[e] : int32_t(e)) : 0;
+    }
+    // Addresses are carried from piece to piece: computed at the load they would share its registers and make it
+    // wait for the entries requested above (38 -> 44 us on 400-byte rows).
+    uint32_t at = chunk_at<VecT, RAGGED>(shape, sub);
+    const Global* from[UNROLL];
+    Global* to[UNROLL];
+#pragma unroll
+    for (int u = 0; u < UNROLL; ++u) {
+      from[u] = (const Global*)(src) + (so[u] + at);
+      to[u] = (Global*)(dst) + (dof[u] + at);
+    }
+    for (uint32_t c0 = 0; c0 < shape.cpr; c0 += lanes) {
+      const bool in_row = c0 + sub < shape.cpr;
+      VecT val[UNROLL];
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u)
+        if (so[u] >= 0 && in_row)
+          val[u] = HBM_SOURCE ? *(const GlobalMem*)(from[u]) : __builtin_nontemporal_load((const GlobalMem*)(from[u]));
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u)
+        if (so[u] >= 0 && in_row) {
+          if (HBM_SOURCE) __builtin_nontemporal_store(val[u], (GlobalMem*)(to[u]));
+          else *(GlobalMem*)(to[u]) = val[u];
+        }
+      const uint32_t next = chunk_at<VecT, RAGGED>(shape, c0 + lanes + sub);
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) {
+        from[u] += next - at;
+        to[u] += next - at;
+      }
+      at = next;
+    }
+  }
+}
+
+}  // namespace
+}  // namespace lgp

@@ -401,3 +401,40 @@ def test_pre_sampling_with_staged_topology(skip, V, n_edges, batch):
     topo, feat = ctx.get_hotness()
     assert (topo == rt).all() and (feat == rf).all()
     ctx.check()
+
+
+@pytest.mark.parametrize("dim,dtype", [(7, np.float16), (8, np.float16), (9, np.float16), (25, np.float32), (50, np.float32),
+                                       (75, np.float16), (100, np.float32), (128, np.float32), (131, np.float16),
+                                       (260, np.float32)])
+def test_hits_and_misses_side_by_side(dim, dtype):
+    """Rows from both sources in one launch: every chunk width and lane-group size it is built for and the narrower rows it
+    leaves to two launches, with one row cached, half of them and all but one, at list lengths around a workgroup pass and
+    on both sides of the partition with one workgroup; timed apart (two launches) the bytes are the same."""
+    import oracle
+    import paper_2305_16588_amd as lgp
+    V = 6000
+    rng = np.random.default_rng(dim)
+    indptr = lgp.pinned_copy(np.zeros(V + 1, np.int32))
+    feats = lgp.pinned_empty((V, dim), dtype)
+    feats[:] = rng.integers(-2000, 2000, (V, dim))
+    ctx, orc = lgp.Context(indptr, np.empty(0, np.int32), feats), oracle.Oracle(indptr, np.empty(0, np.int32), feats)
+    ctx.set_hotness(np.zeros(V, np.uint32), rng.permutation(V).astype(np.uint32))
+    row = dim * np.dtype(dtype).itemsize
+    for n_cached in (1, V // 2, V - 1):
+        ctx.build_cache(0, n_cached * row)
+        cached = np.zeros(V, bool)
+        cached[ctx.get_cache(contents=False)[3]] = True
+        assert cached.sum() == n_cached
+        for n in (0, 1, 3, 64, 257, 4096, 4097, 12_000):
+            ids = np.sort(rng.integers(0, V, n)).astype(np.int32) if n % 2 else rng.integers(0, V, n).astype(np.int32)
+            dev = torch.from_numpy(ids).cuda()
+            want = orc.gather(ids).tobytes()
+            for mode in (0, 1):
+                ctx.set_profiling(mode)
+                out = torch.full((n + 1, dim), 7.0, dtype=ctx.feat_torch_dtype, device="cuda")
+                stats = torch.full((2,), -1, dtype=torch.int32, device="cuda")
+                ctx.gather_features(dev, out=out[:n], stats=stats)
+                assert out[:n].cpu().numpy().tobytes() == want, f"{n_cached} cached, {n} ids, mode {mode}"
+                assert (out[n] == 7.0).all() and stats.tolist() == [int(cached[ids].sum()), int((~cached[ids]).sum())]
+    ctx.set_profiling(0)
+    ctx.check()
