@@ -15,11 +15,10 @@ __device__ __forceinline__ uint64_t philox_draw64(uint32_t k0, uint32_t k1, uint
   uint32_t c0 = vertex, c1 = 0u, c2 = hop, c3 = slot;
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    const uint32_t hi0 = __umulhi(M0, c0), lo0 = M0 * c0;
-    const uint32_t hi1 = __umulhi(M1, c2), lo1 = M1 * c2;
-    const uint32_t n0 = hi1 ^ c1 ^ k0;
-    const uint32_t n2 = hi0 ^ c3 ^ k1;
-    c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
+    const uint64_t p0 = uint64_t(M0) * c0, p1 = uint64_t(M1) * c2;
+    const uint32_t n0 = uint32_t(p1 >> 32) ^ c1 ^ k0;
+    const uint32_t n2 = uint32_t(p0 >> 32) ^ c3 ^ k1;
+    c0 = n0; c1 = uint32_t(p1); c2 = n2; c3 = uint32_t(p0);
     k0 += W0; k1 += W1;
   }
   return uint64_t(c0) | (uint64_t(c1) << 32);

@@ -438,3 +438,27 @@ def test_hits_and_misses_side_by_side(dim, dtype):
                 assert (out[n] == 7.0).all() and stats.tolist() == [int(cached[ids].sum()), int((~cached[ids]).sum())]
     ctx.set_profiling(0)
     ctx.check()
+
+
+@pytest.mark.parametrize("f", [1, 2, 3, 5, 7, 9, 15, 16, 17, 21, 22, 31, 32, 33, 63, 64])
+def test_samples_of_rows_hardly_longer_than_the_fanout(f):
+    """Rows of f - 1 to 2 f ids in turn, where most draws collide and chains of moved slots are long, at fan-outs around
+    every number of vertices a wave takes; list lengths around a wave and a workgroup pass, and several passes."""
+    import oracle
+    import paper_2305_16588_amd as lgp
+    from gpu_common import assert_batch_equal
+    V = 9000
+    d = (f - 1 + np.arange(V) % (f + 2)).astype(np.int64)
+    indptr = np.concatenate([[0], np.cumsum(d)]).astype(np.int32)
+    rng = np.random.default_rng(f)
+    indices = rng.integers(0, V, int(indptr[-1])).astype(np.int32)
+    ctx, orc = lgp.Context(lgp.pinned_copy(indptr), lgp.pinned_copy(indices)), oracle.Oracle(indptr, indices, None)
+    per_wave = 64 // f
+    order = rng.permutation(V).astype(np.int32)
+    for n in (1, per_wave, per_wave + 1, 4 * per_wave - 1, 4 * per_wave + 1, V):
+        seeds = order[:n]
+        dev = torch.from_numpy(seeds).cuda()
+        buf = lgp.SampleBuffers(V, n, (f,))
+        ctx.sample_khop(dev, (f,), 70 + n, out=buf)
+        assert_batch_equal(orc.sample_khop(seeds, (f,), 70 + n), buf.to_host(dev), f"{n} seeds")
+    ctx.check()
