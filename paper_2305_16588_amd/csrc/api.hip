@@ -83,7 +83,7 @@ struct lgp_ctx {
   int64_t list_cap = 0;
 
   // graph-constructor scratch
-  int32_t* pos_table = nullptr;   // pos_tables tables of V entries: position of a vertex in one list of the batch
+  int32_t* pos_table = nullptr;   // pos_tables tables of table_stride() entries: positions of vertices in one list of the batch
   int32_t pos_tables = 0;
   int64_t* tile_sums = nullptr;
   int64_t tile_cap = 0;
@@ -354,6 +354,9 @@ int ensure_lists(lgp_ctx* c, int64_t n, hipStream_t s) {
   return LGP_OK;
 }
 
+// Entries of one of the graph constructor's tables: a rank index has eight-byte entries, also for a single vertex.
+int64_t table_stride(const lgp_ctx* c) { return (c->g.num_vertices + 1) / 2 * 2; }
+
 int ensure_block_scratch(lgp_ctx* c, int32_t tables, int64_t tiles, hipStream_t s) {
   if (c->pos_tables >= tables && c->tile_cap >= tiles) return LGP_OK;
   if (c->reserved) return fail(c, LGP_ECAPACITY, "more hops or seeds than lgp_reserve provided graph-constructor scratch for");
@@ -362,7 +365,7 @@ int ensure_block_scratch(lgp_ctx* c, int32_t tables, int64_t tiles, hipStream_t 
     if (c->pos_table) (void)hipFree(c->pos_table);
     c->pos_table = nullptr;
     c->pos_tables = 0;
-    LGP_HIP(c, dev_alloc(&c->pos_table, size_t(tables) * size_t(c->g.num_vertices)));
+    LGP_HIP(c, dev_alloc(&c->pos_table, size_t(tables) * size_t(table_stride(c))));
     c->pos_tables = tables;
   }
   if (c->tile_cap < tiles) {
@@ -1243,6 +1246,7 @@ int lgp_build_blocks(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const in
   st = ensure_block_scratch(c, n_hops + 1, tiles, s);
   if (st != LGP_OK) return st;
   a.table = c->pos_table;
+  a.table_stride = table_stride(c);
   a.tile_sums = c->tile_sums;
   a.unordered = c->unordered;
   a.call = ++c->blocks_calls;      // 0 marks no call: skipped after 2^32 of them
@@ -1348,7 +1352,7 @@ int lgp_workspace_bytes(const lgp_ctx* c, int32_t max_seeds, const int32_t* fano
     int64_t need[LGP_MAX_HOPS + 1], gather_need;
     worst_case(c, max_seeds, fanouts, n_hops, need, &gather_need);
     size_t total = size_t(gather_need) * 6 * 4;                 // hit / miss / peer lists
-    total += size_t(n_hops + 1) * V * 4;                        // graph constructor: one position table per list
+    total += size_t(n_hops + 1) * size_t(table_stride(c)) * 4;   // graph constructor: one table per list
     for (int h = 0; h < n_hops; ++h) total += (size_t(need[h]) / kScanTile + 1) * 8;
     for (int h = 1; h < n_hops; ++h) total += size_t(need[h]) * 4;   // pre-sampling frontiers
     *scratch = total;

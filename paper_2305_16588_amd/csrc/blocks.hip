@@ -4,12 +4,13 @@
 // 4-5 us; a workgroup of the second one adds up the tile counts before its own destinations
 // instead of reading offsets that a launch between the two would write.)
 //
-// "Position of vertex u in a frontier": frontiers are ascending unique id lists, so each gets a
-// bucket index -- where the ids of u >> s begin, with about one id per bucket -- and a lookup is
-// one load of the bucket and, for the minority of buckets with several ids, a search in it.  Index
-// and list together are a few MB, where a table with an entry per vertex made every write and
-// lookup a random access to hundreds of MB (2.2 M accesses of a 111 M-vertex graph: 70 us per call,
-// now 37; 630 k lookups of a 2.4 M-vertex graph 44 -> 37 us, four launches -> two).  A frontier
+// "Position of vertex u in a frontier": frontiers are ascending unique id lists, so each gets an
+// index by blocks of vertices (see Entry): a lookup is one load of eight bytes, and for lists of few
+// ids sometimes a search among the ids of a block.  Index and list together are a few MB, where a
+// table with an entry per vertex made every write and lookup a random access to hundreds of MB.
+// Calls, table -> where the ids of a bucket of vertices begin, two loads and a search a lookup -> now:
+// 2.2 M accesses of a 111 M-vertex graph 70 -> 34.4 -> 34.4 us; 8192 seeds (15, 10, 5) of 2.4 M vertices
+// 44 -> 41.5 -> 33.3; (25, 25) of 20 M 27.9 -> 27.0.  A frontier
 // that a caller has reordered is noticed while it is indexed, and its lookups take another path
 // (position_any_order).  The
 // extracted id list need not be ascending (the intra-batch pipeline lists in first-reach order),
@@ -75,18 +76,23 @@ __device__ __forceinline__ int64_t block_exclusive_scan64(int64_t x, int64_t* to
   return before + inc - x;
 }
 
-// Bucket index of an ascending list of n ids: bucket b holds the ids with (id - first) >> shift == b and begins at
-// start[b].  start[b] is set for every bucket that holds ids and for the one after it, which is where the bucket ends
-// (the last one ends at n): the ids looked up are in the list, so the entries of other empty buckets are never read, and
-// a list crowded into parts of the id range costs no more than one spread over it (100 k destinations x 10, 526 k ids
-// in 2 % of 111 M: 265 us a call with every entry filled, 28 now; 561 k ids at the two ends 354, 33; spread over the
-// range 38 either way).  Buckets split the span of the list, not the id range, so that a list in one corner has as few ids per bucket
-// as any (2.75 M ids in 2 % of 250 M, 9.8 M x 5: 1490 us split by id range, 1075 by span).  There are at most V
-// buckets, the size of a table.
-struct Buckets {
-  int32_t first, last, shift, count;
+// Index of an ascending list of n ids: block b holds the ids with (id - first) >> shift == b, and one eight-byte load says
+// where they are.  Shift 5: a bit for each of the block's 32 vertices that is in the list and where its ids begin; the
+// position of an id is that plus the bits below its own.  Wider blocks, of lists with fewer ids, hold half an id to one id
+// on average and have where they begin and end, for a search.
+// Only blocks that hold ids are set: the ids looked up are in the list, so the other entries are never read, and a list
+// crowded into parts of the id range costs no more than one spread over it.  Blocks split the span of the list, not the
+// id range, so that a list in one corner has as few ids per block as any.  A block has 32 vertices or more, so an index
+// fits the table of one entry per vertex.
+struct Entry {
+  uint32_t start, more;            // first position in the block; bits of its vertices, or the position after its last
 };
-__device__ __forceinline__ Buckets bucket_shape(const int32_t* ids, int64_t num_vertices, int64_t n) {
+struct Shape {
+  int32_t first, last, shift;
+};
+constexpr int kBitsShift = 5;
+constexpr uint32_t kBitsMaxGap = 64;      // vertices per id up to which a block is 32 vertices (calls are level at 16, 64, 128)
+__device__ __forceinline__ Shape index_shape(const int32_t* ids, int64_t num_vertices, int64_t n) {
   uint32_t end = n > 0 ? uint32_t(n - 1) : 0;
   asm("" : "+s"(end));                                         // a register of its own: a scalar load
   int32_t first = n > 0 ? ids[0] : 0, last = n > 0 ? ids[end] : 0;
@@ -95,29 +101,35 @@ __device__ __forceinline__ Buckets bucket_shape(const int32_t* ids, int64_t num_
     last = int32_t(num_vertices - 1);
   }
   const uint32_t q = uint32_t(last - first) / uint32_t(n > 0 ? n : 1);
-  // Half an id to one id per bucket on average; up to three vertices per id each vertex is a bucket of its own, and a
-  // lookup needs no search (2 M destinations x 64 into 6.6 M of 20 M vertices: 1750 us with buckets of two, 1433 now,
-  // a table with an entry per vertex 1460; 9.8 M x 5 into 2.75 M of a span of 5 M 1026, 873, 950).
-  const int shift = q > 3 ? 31 - __clz(int(q)) : 0;
-  return Buckets{first, last, shift, ((last - first) >> shift) + 1};
+  return Shape{first, last, q < kBitsMaxGap ? kBitsShift : 31 - __clz(int(q))};
 }
 
 // Positions of N ids in the list, -1 for u < 0 (for an id that is not in the list: some value, from reads inside it).
 // The searches run in step, so that the loads of all of them are in flight together.
 template <int N>
-__device__ __forceinline__ void positions(const int32_t* ids, int32_t n, const int32_t* start, const Buckets& b,
+__device__ __forceinline__ void positions(const int32_t* ids, int32_t n, const Entry* index, const Shape& sh,
                                           const int32_t (&u)[N], int32_t (&lo)[N]) {
+  Entry e[N];
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    const bool ok = u[q] >= sh.first && u[q] <= sh.last;
+    uint32_t at = ok ? uint32_t(u[q] - sh.first) >> sh.shift : 0;
+    asm("" : "+v"(at));                                        // one load each, which no branch sets apart from the others
+    e[q] = index[at];
+    lo[q] = ok ? int32_t(e[q].start) : -1;
+  }
+  if (sh.shift == kBitsShift) {
+#pragma unroll
+    for (int q = 0; q < N; ++q) {
+      const int before = __popc(e[q].more & ((1u << (uint32_t(u[q] - sh.first) & 31u)) - 1u));
+      if (lo[q] >= 0) lo[q] += before;
+    }
+    return;
+  }
   int32_t hi[N];
 #pragma unroll
   for (int q = 0; q < N; ++q) {
-    const int32_t k = (u[q] - b.first) >> b.shift;
-    const bool ok = u[q] >= b.first && k < b.count;
-    lo[q] = ok ? start[k] : -1;
-    hi[q] = ok && k + 1 < b.count ? start[k + 1] : n;
-  }
-#pragma unroll
-  for (int q = 0; q < N; ++q) {
-    hi[q] = uint32_t(hi[q]) < uint32_t(n) ? hi[q] : n;
+    hi[q] = e[q].more < uint32_t(n) ? int32_t(e[q].more) : n;
     if (lo[q] < 0 || lo[q] > hi[q]) hi[q] = lo[q];            // nothing to search
   }
   for (;;) {
@@ -130,19 +142,76 @@ __device__ __forceinline__ void positions(const int32_t* ids, int32_t n, const i
     }
     if (!__any(more)) break;
 #pragma unroll
-    for (int q = 0; q < N; ++q) at[q] = mid[q] != lo[q] ? ids[mid[q]] : u[q];
+    for (int q = 0; q < N; ++q) {
+      uint32_t k = mid[q] != lo[q] ? mid[q] : 0;
+      asm("" : "+v"(k));
+      at[q] = ids[k];
+    }
 #pragma unroll
-    for (int q = 0; q < N; ++q) {                             // closed searches keep lo: at == u, mid == lo
-      const bool right = at[q] <= u[q];
+    for (int q = 0; q < N; ++q) {                             // closed searches keep lo, which is mid
+      const bool right = mid[q] == lo[q] || at[q] <= u[q];
       lo[q] = right ? mid[q] : lo[q];
       hi[q] = right ? hi[q] : mid[q];
     }
   }
 }
 
+__device__ __forceinline__ uint32_t wave_inclusive_scan32(uint32_t x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);   // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);   // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);   // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);   // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
+// Entries of the blocks whose first id is among the 64 ids from `base` on (one wave; base < n, a multiple of 64).
+// Returns false in a lane that found its id out of order.
+__device__ __forceinline__ bool index_ids(const int32_t* ids, int64_t n, const Shape& sh, int64_t base, Entry* index) {
+  const int lane = threadIdx.x & 63;
+  const int64_t k = base + lane;
+  const bool in = k < n;
+  const int32_t v = in ? ids[k] : 0;
+  const int32_t before = in && k > 0 ? ids[k - 1] : -1;
+  const bool valid = v >= sh.first && v <= sh.last, valid_before = before >= sh.first && before <= sh.last;
+  const uint32_t o = uint32_t(v - sh.first), block = o >> sh.shift;
+  const uint32_t block_before = uint32_t(before - sh.first) >> sh.shift;
+  const bool leads = in && (k == 0 || block_before != block);
+  const bool ordered = !in || (valid && (k == 0 || (valid_before && before < v)));
+  if (sh.shift != kBitsShift) {
+    if (leads && valid) {
+      index[block].start = uint32_t(k);
+      if (k > 0 && valid_before) index[block_before].more = uint32_t(k);
+    }
+    if (k + 1 == n && valid) index[block].more = uint32_t(n);
+    return ordered;
+  }
+  // The bits of a block are those of a run of lanes, and of the ids behind the wave where the last run goes on: a block has
+  // at most 32 ids.  Ids differ, so the OR of their bits is their sum.
+  const bool behind = lane < 32 && base + 64 + lane < n;
+  const int32_t w = behind ? ids[base + 64 + lane] : 0;
+  const uint32_t bit = in ? 1u << (o & 31u) : 0u;
+  const uint32_t sum = wave_inclusive_scan32(bit);
+  const uint64_t lead = __ballot(leads);
+  const uint32_t last_block = uint32_t(__builtin_amdgcn_readlane(int(block), 63));
+  const uint32_t o_w = uint32_t(w - sh.first);
+  const bool goes_on = behind && o_w >> sh.shift == last_block;
+  uint32_t sum_behind = 0;
+  if (__any(goes_on))
+    sum_behind = uint32_t(__builtin_amdgcn_readlane(int(wave_inclusive_scan32(goes_on ? 1u << (o_w & 31u) : 0u)), 63));
+  const uint64_t mine = lead & (~0ull >> (63 - lane));         // the last of them is the first lane of this lane's run
+  const int leader = mine ? 63 - __clzll((long long)mine) : 0;
+  const uint32_t sum_before = uint32_t(__shfl(int(sum - bit), leader, 64));
+  const bool ends = in && (lane == 63 || k + 1 == n || ((lead >> (lane + 1)) & 1ull));
+  if (ends && mine && valid)
+    index[block] = Entry{uint32_t(base + leader), sum - sum_before + (lane == 63 ? sum_behind : 0u)};
+  return ordered;
+}
+
 // Position of one id per lane (-1 for u < 0 and for an id that is not in the list) in a list that is not ascending:
 // the workgroup's ids go into a hash table in LDS and the whole list passes by once.  The work grows with workgroups
-// times list, far beyond that of the bucket index, but a frontier comes out of the sampler ascending; only a caller
+// times list, far beyond that of the index, but a frontier comes out of the sampler ascending; only a caller
 // who reorders it comes here.
 constexpr int kJoinSlots = 512;                                // twice the ids of a workgroup: probing ends
 struct JoinTable {
@@ -174,7 +243,7 @@ __device__ __forceinline__ int32_t position_any_order(const int32_t* ids, int32_
   return pos;
 }
 
-// Range 0: positions inside the extracted id list go to table 0.  Range j = 1 .. n_hops: bucket index of frontier j, in
+// Range 0: positions inside the extracted id list go to table 0.  Range j = 1 .. n_hops: index of frontier j, in
 // table j.  Range n_hops + 1 + h: edge count of every tile of kScanTile destinations of hop h.
 __global__ __launch_bounds__(256) void index_lists_kernel(BlocksArgs a, Ranges rg) {
   int index, count;
@@ -190,20 +259,10 @@ __global__ __launch_bounds__(256) void index_lists_kernel(BlocksArgs a, Ranges r
   if (r <= a.n_hops) {
     const int32_t* ids = a.frontier[r];
     const int64_t n = clamped(a.n_frontier + r, a.cap[r]);
-    int32_t* start = a.table + int64_t(r) * a.num_vertices;
-    const Buckets b = bucket_shape(ids, a.num_vertices, n);
-    for (int64_t k = int64_t(index) * 256 + threadIdx.x; k < n; k += int64_t(count) * 256) {
-      const int32_t v = ids[k], before = k > 0 ? ids[k - 1] : b.first - 1;
-      if (v < b.first || v > b.last || before < b.first - (k == 0) || before >= v) {
-        a.unordered[r] = a.call;                               // every writer stores the same value
-        continue;
-      }
-      const int32_t mine = (v - b.first) >> b.shift, prev = k > 0 ? (before - b.first) >> b.shift : -1;
-      if (mine != prev) {
-        start[prev + 1] = int32_t(k);
-        start[mine] = int32_t(k);
-      }
-    }
+    Entry* entries = reinterpret_cast<Entry*>(a.table + int64_t(r) * a.table_stride);
+    const Shape sh = index_shape(ids, a.num_vertices, n);
+    for (int64_t k = int64_t(index) * 256 + (threadIdx.x & 192); k < n; k += int64_t(count) * 256)
+      if (!index_ids(ids, n, sh, k, entries)) a.unordered[r] = a.call;      // every writer stores the same value
     return;
   }
   const int h = r - a.n_hops - 1;
@@ -258,8 +317,8 @@ __global__ __launch_bounds__(256, 8) void lookup_relabel_kernel(BlocksArgs a, Ra
   int j = h + 1;
   asm("" : "+s"(j));
   const int32_t n_next = int32_t(clamped(a.n_frontier + j, a.cap[j]));
-  const int32_t* start = a.table + int64_t(h + 1) * a.num_vertices;
-  const Buckets b = bucket_shape(next, a.num_vertices, n_next);
+  const Entry* entries = reinterpret_cast<const Entry*>(a.table + int64_t(h + 1) * a.table_stride);
+  const Shape sh = index_shape(next, a.num_vertices, n_next);
   const bool ascending = a.unordered[h + 1] != a.call;
   const int64_t* tile_sums = a.tile_sums + a.tile_base[h];
   int64_t* indptr = a.blk_indptr[h];
@@ -289,7 +348,7 @@ __global__ __launch_bounds__(256, 8) void lookup_relabel_kernel(BlocksArgs a, Ra
     for (uint32_t k = tile * kScanTile + threadIdx.x; k < first; k += 256) part += cnt[k];
     const uint32_t i = first + threadIdx.x;
     const int32_t c = int(threadIdx.x) < dst ? cnt[i] : 0;
-    positions(next, n_next, start, b, u, pos);
+    positions(next, n_next, entries, sh, u, pos);
     int64_t before, mine;
     block_exclusive_scan64(part, &before);
     const int64_t at = before + block_exclusive_scan64(c, &mine);

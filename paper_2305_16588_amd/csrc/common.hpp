@@ -226,7 +226,8 @@ struct BlocksArgs {
   int64_t* blk_indptr[LGP_MAX_HOPS];
   int32_t* blk_src[LGP_MAX_HOPS];
   int32_t* feat_row[LGP_MAX_HOPS + 1];
-  int32_t* table;                              // n_hops + 1 tables of num_vertices entries each
+  int32_t* table;                              // n_hops + 1 tables of table_stride entries each (at least num_vertices, even)
+  int64_t table_stride;
   int64_t* tile_sums;                          // hop h owns cap[h] / kScanTile + 1 entries from tile_base[h]
   int64_t tile_base[LGP_MAX_HOPS];
   uint32_t* unordered;                         // [j] == call: frontier j is not ascending (n_hops + 1 words)

@@ -462,3 +462,31 @@ def test_samples_of_rows_hardly_longer_than_the_fanout(f):
         ctx.sample_khop(dev, (f,), 70 + n, out=buf)
         assert_batch_equal(orc.sample_khop(seeds, (f,), 70 + n), buf.to_host(dev), f"{n} seeds")
     ctx.check()
+
+
+@pytest.mark.parametrize("gap", [1, 2, 31, 32, 33, 63, 64, 65, 66, 129])
+@pytest.mark.parametrize("n", [1, 33, 64, 65, 96, 97, 1000])
+def test_blocks_of_evenly_spaced_frontiers(gap, n):
+    """Frontiers of n ids `gap` vertices apart: both kinds of index entries and the gap where they change over, blocks of 32
+    vertices whose ids lie in one wave and in two; a second list has gaps in it."""
+    import oracle
+    import paper_2305_16588_amd as lgp
+    from gpu_common import assert_blocks_equal
+    f, V = 8, max((n - 1) * gap + 1, 400)
+    pool = V - 1 - np.arange(n)[::-1] * gap
+    n_seeds = (n + f - 1) // f
+    indptr = np.zeros(V + 1, np.int64)
+    indptr[1:n_seeds + 1] = np.minimum(np.arange(1, n_seeds + 1) * f, n)
+    indptr[n_seeds + 1:] = n
+    for ids in (pool, np.where(np.arange(n) % 3 == 2, pool[0], pool)):
+        indices = ids.astype(np.int32)
+        ctx = lgp.Context(lgp.pinned_copy(indptr.astype(np.int32)), lgp.pinned_copy(indices))
+        orc = oracle.Oracle(indptr.astype(np.int32), indices, None)
+        seeds = np.arange(n_seeds, dtype=np.int32)
+        dev = torch.from_numpy(seeds).cuda()
+        buf = lgp.SampleBuffers(V, n_seeds, (f,), last_frontier=True)
+        blk = lgp.BlockBuffers(buf)
+        ctx.sample_khop(dev, (f,), 3, out=buf)
+        ctx.build_blocks(dev, (f,), buf, out=blk)
+        assert_blocks_equal(orc.sample_khop(seeds, (f,), 3, blocks=True), blk.to_host(), f"{gap} {n}")
+        ctx.check()
