@@ -243,6 +243,9 @@ __device__ __forceinline__ int32_t position_any_order(const int32_t* ids, int32_
   return pos;
 }
 
+// Ids of the extracted list that a thread has in flight, and that a workgroup takes per pass.
+constexpr int kScatterLoads = 4, kScatterTile = 256 * kScatterLoads;
+
 // Range 0: positions inside the extracted id list go to table 0.  Range j = 1 .. n_hops: index of frontier j, in
 // table j.  Range n_hops + 1 + h: edge count of every tile of kScanTile destinations of hop h.
 __global__ __launch_bounds__(256) void index_lists_kernel(BlocksArgs a, Ranges rg) {
@@ -250,9 +253,13 @@ __global__ __launch_bounds__(256) void index_lists_kernel(BlocksArgs a, Ranges r
   const int r = find_range(rg, 2 * a.n_hops + 1, &index, &count);
   if (r == 0) {
     const int64_t n = clamped(a.n_gather, a.gather_cap);
-    for (int64_t k = int64_t(index) * 256 + threadIdx.x; k < n; k += int64_t(count) * 256) {
-      const int32_t v = a.gather_ids[k];
-      if (uint32_t(v) < uint64_t(a.num_vertices)) a.table[v] = int32_t(k);
+    for (int64_t k = int64_t(index) * kScatterTile + threadIdx.x; k < n; k += int64_t(count) * kScatterTile) {
+      int32_t v[kScatterLoads];
+#pragma unroll
+      for (int q = 0; q < kScatterLoads; ++q) v[q] = k + q * 256 < n ? a.gather_ids[k + q * 256] : -1;
+#pragma unroll
+      for (int q = 0; q < kScatterLoads; ++q)
+        if (uint32_t(v[q]) < uint64_t(a.num_vertices)) a.table[v[q]] = int32_t(k + q * 256);
     }
     return;
   }
@@ -367,12 +374,16 @@ __global__ __launch_bounds__(256, 8) void lookup_relabel_kernel(BlocksArgs a, Ra
   }
 }
 
-// Workgroups for `items` of which one workgroup pass takes `per`: at most eight per CU and list (4 / 8: 41.3 / 39.1 us
-// at 111 M vertices, 35 / 36 us at 2.4 M).
-inline int32_t groups_for(const DeviceInfo& di, int64_t items, int64_t per) {
-  const int64_t most = int64_t(di.num_cus) * 8;
-  return int32_t(std::min(most, (items + per - 1) / per));
+// Workgroups for `items` of which one workgroup pass takes `per`: at most `per_cu` per CU and list.  The lists' sizes are only
+// known on the device, so most workgroups of a grid for the worst case find nothing to do, and 8000 of them take longer to
+// start than the indexing takes: 8 / 4 / 3 / 2 per CU and list 33.1 / 30.4 / 30.2 / 30.3 us a call at 2.4 M vertices, 34.7 / 33.2
+// / 33.1 / 33.1 at 111 M, 26.9 / 27.0 / 27.0 / 27.1 with 20 M.  The lookups wait for a chain of loads in each pass and need the
+// wider grid: 8 / 4 per CU in both launches 27.6 / 30.1 at 20 M, 36.1 / 35.4 at 111 M, 33.9 / 29.0 at 2.4 M; one grid of eight
+// workgroups per CU that shares out the tiles of all lists 28.2, 35.0 and 31.5.
+inline int32_t groups_for(const DeviceInfo& di, int64_t items, int64_t per, int64_t per_cu) {
+  return int32_t(std::min(int64_t(di.num_cus) * per_cu, (items + per - 1) / per));
 }
+constexpr int kIndexGroups = 4, kLookupGroups = 8;
 
 }  // namespace
 
@@ -380,15 +391,15 @@ void launch_build_blocks(const DeviceInfo& di, const BlocksArgs& a, hipStream_t 
   const int L = a.n_hops;
   Ranges scatter = {}, lookup = {};
   for (int j = 0; j <= L; ++j)
-    scatter.first[j + 1] = scatter.first[j] + groups_for(di, j == 0 ? a.gather_cap : a.cap[j], 256);
+    scatter.first[j + 1] = scatter.first[j] + groups_for(di, j == 0 ? a.gather_cap : a.cap[j], j == 0 ? kScatterTile : 256, kIndexGroups);
   for (int h = 0; h < L; ++h)        // one more tile than the destinations fill, so that indptr[n] is always written
-    scatter.first[L + h + 2] = scatter.first[L + h + 1] + groups_for(di, a.cap[h] / kScanTile + 1, 1);
+    scatter.first[L + h + 2] = scatter.first[L + h + 1] + groups_for(di, a.cap[h] / kScanTile + 1, 1, kIndexGroups);
   for (int r = 0; r < L; ++r) {
     const int h = L - 1 - r;
     lookup.tile[h] = relabel_tile(a.fanout[h]);
-    lookup.first[r + 1] = lookup.first[r] + groups_for(di, a.cap[h] / lookup.tile[h] + 1, 1);
+    lookup.first[r + 1] = lookup.first[r] + groups_for(di, a.cap[h] / lookup.tile[h] + 1, 1, kLookupGroups);
   }
-  for (int k = 0; k <= L; ++k) lookup.first[L + k + 1] = lookup.first[L + k] + groups_for(di, a.cap[L - k], 256);
+  for (int k = 0; k <= L; ++k) lookup.first[L + k + 1] = lookup.first[L + k] + groups_for(di, a.cap[L - k], 256, kLookupGroups);
   hipLaunchKernelGGL(index_lists_kernel, dim3(unsigned(scatter.first[2 * L + 1])), dim3(256), 0, s, a, scatter);
   hipLaunchKernelGGL(lookup_relabel_kernel, dim3(unsigned(lookup.first[2 * L + 1])), dim3(256), 0, s, a, lookup);
 }
