@@ -328,7 +328,7 @@ def measure(inp: Inputs, steps: int, warmup: int, reps: int, topo_frac=None, fea
             "value": round(steps * spec.batch / t_intra, 1), "unit": "seeds/s",
             "ms_per_step": round(t_intra * 1e3 / steps, 4),
             "how": "lgp_sample_extract: extraction of the seeds' rows beside hop 0, of each hop's newly reached rows "
-                   "beside the next hop, on a second stream"}
+                   "beside the next hop, in the same launches"}
     if extras:
         rec.update(secondary_figures(inp, spec, plan, buf, rows, stats, steps, warmup, ms_per_step, overlap, step))
     if clique_k > 0:

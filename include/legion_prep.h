@@ -266,7 +266,8 @@ int lgp_sample_khop(lgp_ctx* ctx, const int32_t* seeds, int32_t n_seeds, const i
 
 /* One mini-batch through the intra-batch pipeline of Sec. 5 (one batch's sampling runs beside its own
  * feature extraction): lgp_sample_khop and lgp_gather_features in one call, with the
- * extraction running on a stream of the library's own beside the sampling.  That is only possible if rows are
+ * extraction beside the sampling in the same launches (one after the other for rows below 16 bytes, and where
+ * hits and misses are timed apart or run on two streams).  That is only possible if rows are
  * extracted in the order in which the sampler reaches their vertices, so out->gather_ids is not the ascending
  * list here but the listing
  *     seeds as given | vertices first reached by hop 0, ascending | ... | first reached by hop n_hops-1, ascending
@@ -278,7 +279,7 @@ int lgp_sample_khop(lgp_ctx* ctx, const int32_t* seeds, int32_t n_seeds, const i
  * groups [device int32[n_hops + 2], may be NULL] receives the group bounds (groups[0] = 0, groups[1] = n_seeds,
  * group g = [groups[g], groups[g+1])); stats [device int32[2], may be NULL] = {n_hit, n_miss} over all groups.
  * Seeds must be distinct (a repeated seed is listed, and its row extracted, once per occurrence;
- * out->gather_cap must also be >= n_seeds).  `stream` waits for the extraction before later work on it runs.
+ * out->gather_cap must also be >= n_seeds).
  * lgp_build_blocks accepts the result (its feat_row then points into this listing).  Not to be overlapped with
  * lgp_sample_khop, lgp_gather_features or another lgp_sample_extract on the same context. */
 int lgp_sample_extract(lgp_ctx* ctx, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops,

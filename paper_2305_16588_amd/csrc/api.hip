@@ -102,11 +102,7 @@ struct lgp_ctx {
   hipStream_t miss_stream = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
 
-  // intra-batch pipeline (lgp_sample_extract): the extractor's stream, one event per group of rows,
-  // the groups' bounds and their hit / miss counts
-  hipStream_t extract_stream = nullptr;
-  hipEvent_t ev_group[LGP_MAX_HOPS + 2] = {};
-  hipEvent_t ev_extracted = nullptr;
+  // intra-batch pipeline (lgp_sample_extract): the groups' bounds and their hit / miss counts
   int32_t* seg = nullptr;            // int32[LGP_MAX_HOPS + 2]
   int32_t* seg_counters = nullptr;   // int32[(LGP_MAX_HOPS + 1) * 3]
 
@@ -398,6 +394,26 @@ int64_t scan_tiles(const int64_t* cap, int32_t n_hops) {
   return tiles;
 }
 
+// The lists of a partition: pairs of arrays of `cap` entries, one behind the other.
+PartLists part_lists(int32_t* lists, int64_t cap, int n) {
+  PartLists L = {};
+  for (int l = 0; l < n; ++l) {
+    L.row[l] = lists + (2 * l) * cap;
+    L.src[l] = lists + (2 * l + 1) * cap;
+  }
+  return L;
+}
+
+int check_rows(lgp_ctx* c, const int32_t* ids, int64_t n_max, const void* out) {
+  if (n_max < 0 || (n_max > 0 && (!ids || !out))) return fail(c, LGP_EINVAL, "ids / out / n_max");
+  if (!c->g.features) return fail(c, LGP_ESTATE, "the graph was created without a feature table");
+  if (n_max >= (int64_t(1) << 31)) return fail(c, LGP_EUNSUPPORTED, "more than 2^31 - 1 rows in one call");
+  const uintptr_t a = uintptr_t(out) | uintptr_t(c->row_bytes);
+  const int64_t vec = (a & 15u) == 0 ? 16 : (a & 7u) == 0 ? 8 : (a & 3u) == 0 ? 4 : (a & 1u) == 0 ? 2 : 0;
+  if (vec == 0 || c->row_bytes / vec > 4096) return fail(c, LGP_EUNSUPPORTED, "output alignment too small for this row width");
+  return LGP_OK;
+}
+
 // member < 0: plain two-way extraction; member >= 0: three-way, as that member of the clique cache.
 // fixed != nullptr: the counters and lists live in that caller-provided block (kStaticHeadWords words, then
 // 2 * n_lists lists of fixed_cap entries); nothing is allocated, created or timed on this path.
@@ -406,12 +422,8 @@ int64_t scan_tiles(const int64_t* cap, int32_t n_hops) {
 int gather_core(lgp_ctx* c, int32_t member, const int32_t* ids, int64_t n_max, const int32_t* n_dev, void* out,
                        int32_t* stats, void* stream, int32_t* fixed = nullptr, int64_t fixed_cap = 0,
                        const int32_t* window = nullptr, int64_t window_items = 0) {
-  if (n_max < 0 || (n_max > 0 && (!ids || !out))) return fail(c, LGP_EINVAL, "ids / out / n_max");
-  if (!c->g.features) return fail(c, LGP_ESTATE, "the graph was created without a feature table");
-  if (n_max >= (int64_t(1) << 31)) return fail(c, LGP_EUNSUPPORTED, "more than 2^31 - 1 rows in one call");
-  const uintptr_t a = uintptr_t(out) | uintptr_t(c->row_bytes);
-  const int64_t vec = (a & 15u) == 0 ? 16 : (a & 7u) == 0 ? 8 : (a & 3u) == 0 ? 4 : (a & 1u) == 0 ? 2 : 0;
-  if (vec == 0 || c->row_bytes / vec > 4096) return fail(c, LGP_EUNSUPPORTED, "output alignment too small for this row width");
+  const int checked = check_rows(c, ids, n_max, out);
+  if (checked != LGP_OK) return checked;
   hipStream_t s = static_cast<hipStream_t>(stream);
   LGP_HIP(c, hipSetDevice(c->di.device));
   const bool three = member >= 0;
@@ -451,21 +463,16 @@ int gather_core(lgp_ctx* c, int32_t member, const int32_t* ids, int64_t n_max, c
       const int st = ensure_lists(c, n_max, s);
       if (st != LGP_OK) return st;
     }
-    int32_t* const lists = fixed ? fixed + kStaticHeadWords : c->lists;
-    const int64_t cap = fixed ? fixed_cap : c->list_cap;
-    for (int l = 0; l < (three ? 3 : 2); ++l) {
-      L.row[l] = lists + (2 * l) * cap;
-      L.src[l] = lists + (2 * l + 1) * cap;
-    }
+    L = fixed ? part_lists(fixed + kStaticHeadWords, fixed_cap, 2) : part_lists(c->lists, c->list_cap, three ? 3 : 2);
     ev = prof_begin(c, PK_PARTITION, s);
     launch_partition(c->di, ids, n_max, n_dev, c->f_remap, V, L, three ? 3 : 2,
                      three ? int32_t(c->clique_fn[member]) : 0, three ? int32_t(c->clique_fn[member + 1]) : 0, counters,
                      c->d_err, s, window, window_items);
     prof_end(c, ev, s);
     // Hits and misses in one launch, unless they are to be timed apart or run on two streams.
-    if (c->profiling == 0 && !c->overlap &&
-        launch_gather_split(c->di, c->fc, c->g.features, out, c->row_bytes, L, three, n_max, counters,
-                            window ? window_items : 0, s)) {
+    const RowSources both{L, counters, DirectIds{nullptr, 0, nullptr, 0, nullptr, nullptr}, n_max, window ? window_items : 0,
+                          true, true, three};
+    if (c->profiling == 0 && !c->overlap && launch_gather_split(c->di, both, c->fc, c->g.features, out, c->row_bytes, s)) {
       hipError_t e = hipGetLastError();
       return e == hipSuccess ? LGP_OK : fail_hip(c, e, "gather kernel launch");
     }
@@ -655,10 +662,6 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->miss_stream, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming);
-  if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->extract_stream, hipStreamNonBlocking);
-  for (int k = 0; k < LGP_MAX_HOPS + 2 && e == hipSuccess; ++k)
-    e = hipEventCreateWithFlags(&c->ev_group[k], hipEventDisableTiming);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_extracted, hipEventDisableTiming);
   if (e == hipSuccess) {
     launch_init_row_table(c->di, c->g.indptr, c->g.indptr_bytes, V, c->row_tab, nullptr);
     e = hipGetLastError();
@@ -692,10 +695,6 @@ int lgp_destroy(lgp_ctx* c) {
   if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
   if (c->ev_join) (void)hipEventDestroy(c->ev_join);
   if (c->miss_stream) (void)hipStreamDestroy(c->miss_stream);
-  for (hipEvent_t ev : c->ev_group)
-    if (ev) (void)hipEventDestroy(ev);
-  if (c->ev_extracted) (void)hipEventDestroy(c->ev_extracted);
-  if (c->extract_stream) (void)hipStreamDestroy(c->extract_stream);
   (void)hipGetLastError();
   delete c;
   return LGP_OK;
@@ -1149,9 +1148,10 @@ int lgp_sample_extract(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const 
     return fail(c, LGP_ECAPACITY, "out->gather_cap is below the worst case");
   if (gather_need > 0 && (!out->gather_ids || !rows)) return fail(c, LGP_EINVAL, "out->gather_ids / rows is null");
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipStream_t x = c->extract_stream;
   LGP_HIP(c, hipSetDevice(c->di.device));
-  if (0 < c->plan.n_feat && c->plan.n_feat < c->g.num_vertices) {   // the partition lists must exist before anything is enqueued
+  if ((st = check_rows(c, out->gather_ids, out->gather_cap, rows)) != LGP_OK) return st;
+  const bool all = c->plan.n_feat == c->g.num_vertices, none = c->plan.n_feat == 0;
+  if (!all && !none) {   // the partition lists must exist before anything is enqueued
     st = ensure_lists(c, out->gather_cap, s);
     if (st != LGP_OK) return st;
   }
@@ -1159,40 +1159,56 @@ int lgp_sample_extract(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const 
   uint32_t* fbits32 = reinterpret_cast<uint32_t*>(c->maps.frontier);
   uint32_t* gbits32 = reinterpret_cast<uint32_t*>(c->maps.gather);
   const int n_groups = n_hops + 1;
-  // group 0: the seeds' rows, extracted while the first hop is being sampled
   launch_begin_listing(c->di, seeds, n_seeds, out->gather_ids, c->seg, c->seg_counters, n_groups * 3, s);
-  LGP_HIP(c, hipEventRecord(c->ev_group[0], s));
-  LGP_HIP(c, hipStreamWaitEvent(x, c->ev_group[0], 0));
-  // from here on a failed step stops the enqueueing but not the clean-up below: the bitmaps must be clear and
-  // `stream` must have joined the library's stream whatever the call returns
-  st = gather_core(c, -1, out->gather_ids, out->gather_cap, nullptr, rows, c->seg_counters, x, nullptr, 0, c->seg,
-                   std::max<int64_t>(n_seeds, 1));
+  // Group g of the listing -- the seeds, then what hop g - 1 reached first -- is extracted in the launch that samples hop g;
+  // the last one, and groups whose hits and misses are timed apart or run on two streams, by launches of their own.
+  // A failed step stops the enqueueing but not the clean-up below: the bitmaps must be clear whatever the call returns.
+  const bool beside = c->row_bytes >= 16 && c->profiling == 0 && !c->overlap;
+  auto extract = [&](int g) {
+    return gather_core(c, -1, out->gather_ids, out->gather_cap, nullptr, rows, c->seg_counters + 3 * g, s, nullptr, 0, c->seg + g,
+                       std::max<int64_t>(need[g], 1));
+  };
   const int32_t* frontier = seeds;
   int64_t cap = n_seeds;
   for (int h = 0; h < n_hops && st == LGP_OK; ++h) {
-    launch_sample_hop(c->di, tv, frontier, out->n_frontier + h, cap, fanouts[h], h, rng_seed, out->nbr[h], out->cnt[h],
-                      fbits32, h == 0 ? gbits32 : nullptr, nullptr, c->d_err, c->maps.status, c->maps.geom.groups, s);
+    uint32_t* const self = h == 0 ? gbits32 : nullptr;
+    if (beside) {
+      int32_t* const counters = c->seg_counters + 3 * h;
+      RowSources r = {};
+      r.n_max = out->gather_cap;
+      r.grid_items = std::max<int64_t>(need[h], 1);
+      r.hits = !none;
+      r.misses = !all;
+      if (all || none) {
+        r.lists.src[none] = out->gather_ids;
+        r.direct = DirectIds{all && !c->fc_identity ? c->f_remap : nullptr, c->g.num_vertices, counters, none, c->d_err, c->seg + h};
+      } else {
+        r.lists = part_lists(c->lists, c->list_cap, 2);
+        r.counters = counters;
+        launch_partition(c->di, out->gather_ids, r.n_max, nullptr, c->f_remap, c->g.num_vertices, r.lists, 2, 0, 0, counters,
+                         c->d_err, s, c->seg + h, r.grid_items);
+      }
+      launch_hop_and_rows(c->di, tv, frontier, out->n_frontier + h, cap, fanouts[h], h, rng_seed, out->nbr[h], out->cnt[h],
+                          fbits32, self, c->d_err, c->maps.status, c->maps.geom.groups, r, c->fc, c->g.features, rows,
+                          c->row_bytes, s);
+    } else {
+      if ((st = extract(h)) != LGP_OK) break;
+      launch_sample_hop(c->di, tv, frontier, out->n_frontier + h, cap, fanouts[h], h, rng_seed, out->nbr[h], out->cnt[h],
+                        fbits32, self, nullptr, c->d_err, c->maps.status, c->maps.geom.groups, s);
+    }
     // next frontier (if anyone needs it as a list) and the vertices this hop reached first, appended to the listing
-    const bool want = (h + 1 < n_hops) || out->frontier[n_hops] != nullptr;
-    int32_t* next = want ? out->frontier[h + 1] : nullptr;
     const bool last = h + 1 == n_hops;
+    const bool want = !last || out->frontier[n_hops] != nullptr;
+    int32_t* next = want ? out->frontier[h + 1] : nullptr;
     launch_compact_new(c->di, c->maps, next, next ? out->cap[h + 1] : 0, want ? out->n_frontier + h + 1 : nullptr,
                        out->gather_ids, out->gather_cap, c->seg + h + 1, last ? out->n_gather : nullptr, c->d_err, s);
-    LGP_HIP(c, hipEventRecord(c->ev_group[h + 1], s));
-    LGP_HIP(c, hipStreamWaitEvent(x, c->ev_group[h + 1], 0));
-    st = gather_core(c, -1, out->gather_ids, out->gather_cap, nullptr, rows, c->seg_counters + 3 * (h + 1), x, nullptr, 0,
-                     c->seg + h + 1, std::max<int64_t>(need[h + 1], 1));
     frontier = next;
     cap = next ? out->cap[h + 1] : 0;
   }
-  // the "seen" bitmap of this batch is not compacted (the listing replaces the ascending list), so clear it whole
-  launch_fill_i32(c->di, reinterpret_cast<int32_t*>(c->maps.gather), c->maps.geom.words() * 2, 0, s);
-  if (st == LGP_OK && stats) launch_sum_stats(c->seg_counters, n_groups, stats, x);
-  if (st == LGP_OK && groups) {
-    LGP_HIP(c, hipMemcpyAsync(groups, c->seg, sizeof(int32_t) * size_t(n_hops + 2), hipMemcpyDeviceToDevice, x));
-  }
-  LGP_HIP(c, hipEventRecord(c->ev_extracted, x));
-  LGP_HIP(c, hipStreamWaitEvent(s, c->ev_extracted, 0));
+  if (st == LGP_OK) st = extract(n_hops);
+  // the "seen" bitmap of this batch is not compacted (the listing replaces the ascending list), so it is cleared whole
+  launch_end_listing(c->di, c->maps.gather, c->maps.geom.words(), c->seg, c->seg_counters, n_groups, st == LGP_OK ? groups : nullptr,
+                     st == LGP_OK ? stats : nullptr, s);
   if (st != LGP_OK) return st;
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail_hip(c, e, "intra-batch pipeline launch");

@@ -157,11 +157,6 @@ void launch_compact_new(const DeviceInfo& di, const DedupMaps& m, int32_t* out, 
 // frontier sizes of the batch).
 void launch_bump(const DeviceInfo& di, const DedupMaps& m, uint32_t* bump, const int32_t* sizes, int32_t n_sizes,
                  unsigned long long* acc, hipStream_t s);
-// seg[0] = 0, seg[1] = n_seeds, listed[0 .. n_seeds) = seeds, counters[0 .. n_counters) = 0.
-void launch_begin_listing(const DeviceInfo& di, const int32_t* seeds, int64_t n_seeds, int32_t* listed, int32_t* seg,
-                          int32_t* counters, int32_t n_counters, hipStream_t s);
-// stats[0 .. 2) = column sums of the n_seg x 3 matrix seg_counters (first two columns), one thread.
-void launch_sum_stats(const int32_t* seg_counters, int32_t n_seg, int32_t* stats, hipStream_t s);
 
 // ---- gather.hip -----------------------------------------------------------
 // Look up every id in the feature remap and append (row, slot) to the hit list (list 0) or
@@ -200,12 +195,38 @@ void launch_gather_rows(const DeviceInfo& di, const void* src, void* dst, int64_
                         hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr, bool beside_pcie = false,
                         int64_t grid_items = 0);
 
-// Hits and misses of a partition in one launch, side by side: rows of lists[0] (and lists[2] with peers) from hit_src, rows
-// of lists[1] from miss_src in CPU memory; counters as launch_partition left them.  False, and nothing is launched, for rows
+// Rows to copy from their two sources side by side.  With counters: the lists of a partition, counters as launch_partition
+// left them (lists[2] with peers; rows of lists[1] are misses).  Without: the caller's list of ids is lists.src[0] (hits) or
+// lists.src[1] (misses), and direct.window says which entries.
+struct RowSources {
+  PartLists lists;
+  const int32_t* counters;
+  DirectIds direct;
+  int64_t n_max, grid_items;   // as for launch_gather_rows
+  bool hits, misses, peers;
+};
+// One launch for both, hits from hit_src and misses from miss_src in CPU memory.  False, and nothing is launched, for rows
 // below 16 bytes.
-bool launch_gather_split(const DeviceInfo& di, const void* hit_src, const void* miss_src, void* dst, int64_t row_bytes,
-                         const PartLists& lists, bool peers, int64_t n_max, const int32_t* counters, int64_t grid_items,
-                         hipStream_t s);
+bool launch_gather_split(const DeviceInfo& di, const RowSources& r, const void* hit_src, const void* miss_src, void* dst,
+                         int64_t row_bytes, hipStream_t s);
+// Arguments of the device code for that; returns the width of a miss's chunks, 0 for rows below 16 bytes.
+struct SplitArgs;
+int split_args(const DeviceInfo& di, const RowSources& r, const void* hit_src, const void* miss_src, void* dst,
+               int64_t row_bytes, SplitArgs* out);
+
+// ---- extract.hip ----------------------------------------------------------
+// A sampling hop (arguments as launch_sample_hop) and, beside it in the same launch, the rows r; not for rows below 16 bytes.
+void launch_hop_and_rows(const DeviceInfo& di, const TopoView& tv, const int32_t* frontier, int32_t* n_frontier, int64_t cap,
+                         int32_t fanout, int32_t hop, uint64_t rng_seed, int32_t* nbr, int32_t* cnt, uint32_t* mark_bits,
+                         uint32_t* self_bits, uint32_t* d_err, uint64_t* status, int64_t n_status, const RowSources& r,
+                         const void* hit_src, const void* miss_src, void* dst, int64_t row_bytes, hipStream_t s);
+// seg[0] = 0, seg[1] = n_seeds, listed[0 .. n_seeds) = seeds, counters[0 .. n_counters) = 0.
+void launch_begin_listing(const DeviceInfo& di, const int32_t* seeds, int64_t n_seeds, int32_t* listed, int32_t* seg,
+                          int32_t* counters, int32_t n_counters, hipStream_t s);
+// Clears words 64-bit words of a map; groups[0 .. n_seg] = seg[0 .. n_seg], stats[0 .. 2) = column sums of the n_seg x 3 matrix
+// seg_counters (first two columns); either may be null.
+void launch_end_listing(const DeviceInfo& di, uint64_t* map, int64_t words, const int32_t* seg, const int32_t* seg_counters,
+                        int32_t n_seg, int32_t* groups, int32_t* stats, hipStream_t s);
 
 // ---- blocks.hip -----------------------------------------------------------
 constexpr int kScanTile = 1024;   // elements per workgroup of the counts -> offsets scan

@@ -323,30 +323,6 @@ __global__ __launch_bounds__(256) void bump_kernel(uint64_t* __restrict__ bits, 
   }
 }
 
-__global__ __launch_bounds__(256) void begin_listing_kernel(const int32_t* __restrict__ seeds, int64_t n_seeds,
-                                                            int32_t* __restrict__ listed, int32_t* __restrict__ seg,
-                                                            int32_t* __restrict__ counters, int32_t n_counters) {
-  const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (t == 0) {
-    seg[0] = 0;
-    seg[1] = int32_t(n_seeds);
-  }
-  if (t < n_counters) counters[t] = 0;
-  for (int64_t i = t; i < n_seeds; i += int64_t(gridDim.x) * 256) listed[i] = seeds[i];
-}
-
-__global__ void sum_stats_kernel(const int32_t* __restrict__ seg_counters, int32_t n_seg, int32_t* __restrict__ stats) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    int32_t hit = 0, miss = 0;
-    for (int32_t k = 0; k < n_seg; ++k) {
-      hit += seg_counters[3 * k];
-      miss += seg_counters[3 * k + 1];
-    }
-    stats[0] = hit;
-    stats[1] = miss;
-  }
-}
-
 template <Mode M>
 void launch_mode(const MapGeom& g, CompactArgs a, hipStream_t s) {
   const dim3 grid{unsigned(g.groups)}, block{unsigned(kCompactThreads)};
@@ -418,19 +394,6 @@ void launch_bump(const DeviceInfo& di, const DedupMaps& m, uint32_t* bump, const
   if (blocks > di.num_cus * 8) blocks = di.num_cus * 8;
   hipLaunchKernelGGL(bump_kernel, dim3(unsigned(blocks)), dim3(256), 0, s, m.gather, m.geom.words(), di.spread_shift,
                      bump, sizes, n_sizes, acc);
-}
-
-void launch_begin_listing(const DeviceInfo& di, const int32_t* seeds, int64_t n_seeds, int32_t* listed, int32_t* seg,
-                          int32_t* counters, int32_t n_counters, hipStream_t s) {
-  int64_t blocks = (n_seeds + 255) / 256;
-  if (blocks > di.num_cus * 4) blocks = di.num_cus * 4;
-  if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(begin_listing_kernel, dim3(unsigned(blocks)), dim3(256), 0, s, seeds, n_seeds, listed, seg,
-                     counters, n_counters);
-}
-
-void launch_sum_stats(const int32_t* seg_counters, int32_t n_seg, int32_t* stats, hipStream_t s) {
-  hipLaunchKernelGGL(sum_stats_kernel, dim3(1), dim3(64), 0, s, seg_counters, n_seg, stats);
 }
 
 }  // namespace lgp

@@ -197,37 +197,10 @@ __global__ __launch_bounds__(256) void gather_rows_group_kernel(const char* __re
   group_rows<VecT, RAGGED, UNROLL, HBM_SOURCE>(src, dst, shape, row, srcrow, n_max, n_dev, dir, G, blockIdx.x, gridDim.x);
 }
 
-// ---- hits and misses in one launch --------------------------------------------
-// The two lists of a partition (three for a clique member: list 2 is a second list of rows in HBM).  One after the other,
-// the link idles while the hits are copied and HBM while the misses arrive; here the first miss_blocks workgroups
-// take the misses and the others the hits, beside them.  Calls, one after the other -> beside each other: 400-byte rows of
-// 2.4 M vertices, 688 k ids, 30 / 70 / 95 / 99.5 % of the table cached 2925 -> 2844, 1208 -> 1100, 324 -> 231, 163 -> 148 us;
-// 2-KiB rows, 95 % 445 -> 310; 7 k ids of 10 k vertices (512-byte rows, 20 %) 76 -> 65.
-struct SplitArgs {
-  const char* hit_src;
-  const char* miss_src;
-  char* dst;
-  RowShape hit_shape, miss_shape;
-  PartLists lists;
-  const int32_t* counters;
-  int64_t n_max;
-  uint32_t hit_lanes, miss_lanes, miss_blocks;
-  bool peers;
-};
-constexpr int kSplitHitUnroll = 2;
 template <typename VecT, bool RAGGED>
 __global__ __launch_bounds__(256) void gather_split_kernel(SplitArgs a) {
-  const DirectIds listed{nullptr, 0, nullptr, 0, nullptr, nullptr};
-  if (blockIdx.x < a.miss_blocks) {
-    group_rows<VecT, RAGGED, 4, false>(a.miss_src, a.dst, a.miss_shape, a.lists.row[1], a.lists.src[1], a.n_max,
-                                       a.counters + 1, listed, a.miss_lanes, blockIdx.x, a.miss_blocks);
-    return;
-  }
-  const uint32_t block = blockIdx.x - a.miss_blocks, blocks = gridDim.x - a.miss_blocks;
-  for (int l = 0; l <= (a.peers ? 2 : 0); l += 2)
-    group_rows<u32x4, true, kSplitHitUnroll, true>(a.hit_src, a.dst, a.hit_shape, l ? a.lists.row[2] : a.lists.row[0],
-                                                   l ? a.lists.src[2] : a.lists.src[0], a.n_max, a.counters + l, listed,
-                                                   a.hit_lanes, block, blocks);
+  if (blockIdx.x < a.miss_blocks) split_misses<VecT, RAGGED>(a, blockIdx.x);
+  else split_hits(a, blockIdx.x - a.miss_blocks);
 }
 
 inline unsigned blocks_for(int64_t work_blocks, int64_t limit) {
@@ -427,32 +400,41 @@ void launch_gather_rows(const DeviceInfo& di, const void* src, void* dst, int64_
   else rows(uint16_t{}, std::false_type{});
 }
 
-bool launch_gather_split(const DeviceInfo& di, const void* hit_src, const void* miss_src, void* dst, int64_t row_bytes,
-                         const PartLists& lists, bool peers, int64_t n_max, const int32_t* counters, int64_t grid_items,
-                         hipStream_t s) {
-  if (row_bytes < 16) return false;
+int split_args(const DeviceInfo& di, const RowSources& r, const void* hit_src, const void* miss_src, void* dst,
+               int64_t row_bytes, SplitArgs* out) {
+  if (row_bytes < 16) return 0;
   const uintptr_t align = uintptr_t(miss_src) | uintptr_t(dst) | uintptr_t(row_bytes);
   const int64_t width = chunk_width(align, row_bytes, true);
-  const int64_t items = (grid_items > 0 && grid_items < n_max) ? grid_items : n_max;
   SplitArgs a = {};
   a.hit_src = static_cast<const char*>(hit_src);
   a.miss_src = static_cast<const char*>(miss_src);
   a.dst = static_cast<char*>(dst);
   a.hit_shape = row_shape(row_bytes, 16);
   a.miss_shape = row_shape(row_bytes, width);
-  a.lists = lists;
-  a.counters = counters;
-  a.n_max = n_max;
+  a.lists = r.lists;
+  a.counters = r.counters;
+  a.direct = r.direct;
+  a.n_max = r.n_max;
   a.hit_lanes = group_lanes(a.hit_shape);
   a.miss_lanes = group_lanes(a.miss_shape);
-  a.peers = peers;
-  const int64_t miss_pass = 256 / a.miss_lanes * 4, hit_pass = 256 / a.hit_lanes * kSplitHitUnroll;
-  a.miss_blocks = blocks_for((items + miss_pass - 1) / miss_pass, std::max(1, di.num_cus / 4));
+  a.peers = r.peers;
+  const int64_t items = (r.grid_items > 0 && r.grid_items < r.n_max) ? r.grid_items : r.n_max;
+  const int64_t miss_pass = 256 / a.miss_lanes * kSplitMissUnroll, hit_pass = 256 / a.hit_lanes * kSplitHitUnroll;
   // Misses keep the width that suits the link; hits take six workgroups per CU with two rows per group in flight.  At 2 / 4 /
   // 6 / 8 per CU: 512-byte rows, 688 k of 2.4 M ids with 95 % of the table cached 291 / 252 / 233 / 227 us a call, 30 % cached and
   // 400-byte rows 2841 / 2843 / 2850 / 2845, 99.5 % cached 167 / 150 / 148 / 156.
-  const unsigned hit_blocks = blocks_for((items + hit_pass - 1) / hit_pass, int64_t(di.num_cus) * 6);
-  const dim3 grid{a.miss_blocks + hit_blocks}, block{256};
+  if (r.misses) a.miss_blocks = blocks_for((items + miss_pass - 1) / miss_pass, std::max(1, di.num_cus / 4));
+  if (r.hits) a.hit_blocks = blocks_for((items + hit_pass - 1) / hit_pass, int64_t(di.num_cus) * 6);
+  *out = a;
+  return int(width);
+}
+
+bool launch_gather_split(const DeviceInfo& di, const RowSources& r, const void* hit_src, const void* miss_src, void* dst,
+                         int64_t row_bytes, hipStream_t s) {
+  SplitArgs a;
+  const int width = split_args(di, r, hit_src, miss_src, dst, row_bytes, &a);
+  if (width == 0) return false;
+  const dim3 grid{a.miss_blocks + a.hit_blocks}, block{256};
   if (width == 16) hipLaunchKernelGGL((gather_split_kernel<u32x4, true>), grid, block, 0, s, a);
   else if (width == 8) hipLaunchKernelGGL((gather_split_kernel<u32x2, false>), grid, block, 0, s, a);
   else hipLaunchKernelGGL((gather_split_kernel<uint32_t, false>), grid, block, 0, s, a);

@@ -116,3 +116,32 @@ def test_mid_workload_full_size():
         ref = _run_and_check(M, seeds, seeds_dev, spec.fanouts, spec.base_seed + 100 + b, plan.n_feat, f"mid batch {b}",
                              blocks=(b == 0))
     assert ref.hop_seg[-1] == ref.gather_ids.size
+
+
+@pytest.mark.parametrize("V,dim,dtype", [(3000, 7, np.float16), (3000, 25, np.float32), (3000, 260, np.float32),
+                                         (600_000, 10, np.float32), (1_200_000, 75, np.float16), ((1 << 23) + 5, 8, np.float16)])
+def test_rows_beside_a_hop(V, dim, dtype):
+    """Every chunk width and dedup-map layout that a hop shares a launch with, and rows too narrow for it: nothing, half and
+    everything cached, groups of one row up to many passes, hits and misses timed apart."""
+    import types
+
+    import oracle
+    import paper_2305_16588_amd as lgp
+    rng = np.random.default_rng(V + dim)
+    indptr = np.concatenate([[0], np.cumsum(rng.integers(0, 7, V))]).astype(np.int32)
+    indices = rng.integers(0, V, int(indptr[-1])).astype(np.int32)
+    feats = lgp.pinned_empty((V, dim), dtype)
+    feats[:] = rng.integers(-2000, 2000, (V, dim), dtype=np.int16)
+    hot = rng.integers(0, 9, V).astype(np.uint32)
+    orc = oracle.Oracle(indptr, indices, feats)
+    w = types.SimpleNamespace(ctx=lgp.Context(lgp.pinned_copy(indptr), lgp.pinned_copy(indices), feats), orc=orc, V=V,
+                              qf=orc.rank_by_hotness(hot), spec=types.SimpleNamespace(feat_dim=dim))
+    w.ctx.set_hotness(np.zeros(V, np.uint32), hot)
+    for n_feat in (0, V // 2, V):
+        w.ctx.build_cache(0, n_feat * orc.row_bytes)
+        for n_seeds, fanouts in ((1, (1, 1)), (700, (5, 3, 2)), (2900, (4,))):
+            seeds = rng.permutation(V)[:n_seeds].astype(np.int32)
+            for mode in (0, 1) if n_seeds == 700 else (0,):
+                w.ctx.set_profiling(mode)
+                _run_and_check(w, seeds, torch.from_numpy(seeds).cuda(), fanouts, 31 + n_seeds, n_feat, f"{n_feat} {fanouts} {mode}")
+    w.ctx.set_profiling(0)
