@@ -275,9 +275,11 @@ template <typename VecT, bool RAGGED, int G>
 void launch_group_hbm_g(const DeviceInfo& di, const char* src, char* dst, const RowShape& shape, const int32_t* row,
                         const int32_t* srcrow, int64_t n_max, const int32_t* n_dev, const DirectIds& dir,
                         const Where& s) {
-  // one row per group in flight needs more waves than the flat walk: 6 workgroups per CU (400-byte rows,
-  // 512 k hits: 138.7 / 107.6 / 95.6 / 90.7 / 91.4 us at 2 / 3 / 4 / 6 / 8 workgroups per CU)
-  const unsigned blocks = blocks_for((s.items + 256 / G - 1) / (256 / G), std::min<int64_t>(s.hbm_blocks, int64_t(di.num_cus) * 6));
+  // one row per group in flight needs more waves than the flat walk: 8 workgroups per CU (2 / 3 / 4 / 6 / 8: 512 k rows of 400
+  // bytes 138.7 / 107.6 / 95.6 / 90.7 / 91.4 us; 6 / 8: 400 bytes 43.9 / 43.5, 150 bytes 25.0 / 23.2 and, of 30 M vertices, 52.5 /
+  // 48.6, 602 bytes 82.3 / 78.1, 66 bytes 14.4 / 13.2, 80 bytes 14.1 / 13.4).  Two rows in flight are level or slower below
+  // 150 bytes (66 bytes 14.2) and on rows of multiples of 4 (250 bytes 30.0 / 30.5), and ahead on 150 (22.5) and 602 (76.6).
+  const unsigned blocks = blocks_for((s.items + 256 / G - 1) / (256 / G), std::min<int64_t>(s.hbm_blocks, int64_t(di.num_cus) * 8));
   launch_on(s, gather_rows_group_kernel<VecT, RAGGED, G, 1, true>, blocks, src, dst, shape, row, srcrow, n_max, n_dev, dir);
 }
 
