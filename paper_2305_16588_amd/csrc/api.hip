@@ -60,6 +60,8 @@ struct lgp_ctx {
   uint32_t* feat_hot = nullptr;
   bool have_hot = false;
   DedupMaps maps;              // frontier and gather-set dedup maps
+  bool either_map = false;     // a call may lay the maps out as bytes instead (kEitherMapMaxVertices), with this geometry
+  MapGeom byte_geom;
   uint32_t* d_err = nullptr;
   int32_t* counters = nullptr;  // {n_hit, n_miss, n_peer}
 
@@ -247,14 +249,42 @@ void prof_end(lgp_ctx* c, EvPair& p, hipStream_t s) {
   c->ev_used.push_back(p);
 }
 
+// 64-bit words of a dedup map.
+size_t map_words(const lgp_ctx* c) {
+  return size_t(c->either_map ? std::max(c->maps.geom.words(), c->byte_geom.words()) : c->maps.geom.words());
+}
+
+// Marks of a mini-batch on a graph whose vertices all have the mean degree and are equally popular: more than where
+// popularity and degrees are skewed.  *rows, if given: vertices expanded.
+double expected_marks(const lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts, int32_t n_hops, double* rows = nullptr) {
+  const double V = double(c->g.num_vertices), degree = double(c->g.num_edges) / V;
+  double n = double(n_seeds), marks = 0;
+  if (rows) *rows = 0;
+  for (int h = 0; h < n_hops; ++h) {
+    if (rows) *rows += n;
+    const double m = n * std::min(degree, double(fanouts[h]));
+    marks += m;
+    n = V * -std::expm1(-m / V);
+  }
+  return marks;
+}
+
 // Sampling of one mini-batch; out == nullptr is the pre-sampling mode (hotness only), for which `staged` may hold room for
 // the column ids in HBM.
 int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops,
                 uint64_t rng_seed, const lgp_sample_out* out, hipStream_t s, const int32_t* staged = nullptr) {
   const bool hot_mode = (out == nullptr);
   const int64_t V = c->g.num_vertices;
-  uint32_t* fbits32 = reinterpret_cast<uint32_t*>(c->maps.frontier);
-  uint32_t* gbits32 = reinterpret_cast<uint32_t*>(c->maps.gather);
+  const bool want_last = !hot_mode && out->frontier[n_hops] != nullptr;
+  DeviceInfo di = c->di;
+  DedupMaps maps = c->maps;
+  if (c->either_map && expected_marks(c, n_seeds, fanouts, n_hops) >=
+                                     (want_last ? kByteMarksPerVertexBoth : kByteMarksPerVertex) * double(V)) {
+    di.spread_shift = 3;
+    maps.geom = c->byte_geom;
+  }
+  uint32_t* fbits32 = reinterpret_cast<uint32_t*>(maps.frontier);
+  uint32_t* gbits32 = reinterpret_cast<uint32_t*>(maps.gather);
   int32_t* n_frontier = hot_mode ? c->hs_n : out->n_frontier;
   TopoView tv = topo_view(c);
   if (staged) {
@@ -264,29 +294,28 @@ int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t
 
   const int32_t* frontier = seeds;
   int64_t cap = n_seeds;
-  const bool want_last = !hot_mode && out->frontier[n_hops] != nullptr;
   for (int h = 0; h < n_hops; ++h) {
     // the last hop's samples only feed the gather set, so they are marked there directly -- unless
     // the caller wants the last frontier as a list of its own
     const bool final_hop = h + 1 == n_hops;
-    launch_sample_hop(c->di, tv, frontier, n_frontier + h, cap, fanouts[h], h, rng_seed,
+    launch_sample_hop(di, tv, frontier, n_frontier + h, cap, fanouts[h], h, rng_seed,
                       hot_mode ? nullptr : out->nbr[h], hot_mode ? nullptr : out->cnt[h],
                       final_hop && !want_last ? gbits32 : fbits32, h == 0 ? gbits32 : nullptr,
-                      hot_mode ? c->topo_hot : nullptr, c->d_err, c->maps.status, c->maps.geom.groups, s);
+                      hot_mode ? c->topo_hot : nullptr, c->d_err, maps.status, maps.geom.groups, s);
     if (final_hop) break;
     int32_t* next = hot_mode ? c->hs_frontier[h + 1] : out->frontier[h + 1];
     const int64_t next_cap = hot_mode ? c->hs_cap[h + 1] : out->cap[h + 1];
-    launch_compact(c->di, c->maps, next, next_cap, n_frontier + h + 1, c->d_err, s);
+    launch_compact(di, maps, next, next_cap, n_frontier + h + 1, c->d_err, s);
     frontier = next;
     cap = next_cap;
   }
   if (hot_mode)
-    launch_bump(c->di, c->maps, c->feat_hot, c->hs_n, n_hops, c->hs_expansions, s);
+    launch_bump(di, maps, c->feat_hot, c->hs_n, n_hops, c->hs_expansions, s);
   else if (want_last)
-    launch_compact_both(c->di, c->maps, out->frontier[n_hops], out->cap[n_hops], n_frontier + n_hops, out->gather_ids,
+    launch_compact_both(di, maps, out->frontier[n_hops], out->cap[n_hops], n_frontier + n_hops, out->gather_ids,
                         out->gather_cap, out->n_gather, c->d_err, s);
   else
-    launch_compact_gather(c->di, c->maps, out->gather_ids, out->gather_cap, out->n_gather, c->d_err, s);
+    launch_compact_gather(di, maps, out->gather_ids, out->gather_cap, out->n_gather, c->d_err, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail_hip(c, e, "sampling kernel launch");
   return LGP_OK;
@@ -521,12 +550,8 @@ int32_t* staging_room(const lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts,
                       hipStream_t s, void** base) {
   *base = nullptr;
   if (!c->indices_on_host || c->reserved || c->plan.n_topo > 0 || n_batches < 2) return nullptr;
-  const double V = double(c->g.num_vertices), degree = double(c->g.num_edges) / V;
-  double n = double(n_seeds), rows = n;
-  for (int h = 0; h + 1 < n_hops; ++h) {
-    n = V * -std::expm1(-n * std::min(degree, double(fanouts[h])) / V);
-    rows += n;
-  }
+  double rows = 0;
+  expected_marks(c, n_seeds, fanouts, n_hops, &rows);
   if (0.5 * rows * double(n_batches - 1) * 128.0 - double(c->g.num_edges) * 4.0 < kStageSaving) return nullptr;
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
   size_t free_bytes = 0, total_bytes = 0;
@@ -631,7 +656,9 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   const int64_t V = g->num_vertices;
   c->di.spread_shift = mark_shift(V);
   c->maps.geom = map_geometry(V, c->di.spread_shift);
-  const size_t words = size_t(c->maps.geom.words());
+  c->either_map = V > kByteMapMaxVertices && V <= kEitherMapMaxVertices;
+  if (c->either_map) c->byte_geom = map_geometry(V, 3);
+  const size_t words = map_words(c);
   hipError_t e = hipSuccess;
   auto step = [&](hipError_t r) {
     if (e == hipSuccess) e = r;
@@ -642,7 +669,7 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   step(dev_alloc(&c->feat_hot, size_t(V)));
   step(dev_alloc(&c->maps.frontier, words));
   step(dev_alloc(&c->maps.gather, words));
-  step(dev_alloc(&c->maps.status, size_t(c->maps.geom.groups)));
+  step(dev_alloc(&c->maps.status, size_t(std::max(c->maps.geom.groups, c->byte_geom.groups))));
   step(dev_alloc(&c->d_err, 1));
   step(dev_alloc(&c->counters, 3));
   step(dev_alloc(&c->hs_n, LGP_MAX_HOPS + 1));
@@ -1360,9 +1387,9 @@ int lgp_workspace_bytes(const lgp_ctx* c, int32_t max_seeds, const int32_t* fano
   }
   const size_t V = size_t(c->g.num_vertices);
   if (fixed) {
-    const size_t map = size_t(c->maps.geom.words()) * 8;
+    const size_t map = map_words(c) * 8;
     // row table 8 + remap 4 + two hotness vectors 4 + 4 + two rankings 4 + 4 bytes per vertex
-    *fixed = V * 28 + 2 * map + size_t(c->maps.geom.groups) * 8 + 64;
+    *fixed = V * 28 + 2 * map + size_t(std::max(c->maps.geom.groups, c->byte_geom.groups)) * 8 + 64;
   }
   if (scratch) {
     int64_t need[LGP_MAX_HOPS + 1], gather_need;

@@ -32,6 +32,15 @@ enum : uint32_t { ERR_BAD_ID = 1u, ERR_OVERRUN = 2u };
 constexpr int64_t kWordMapMaxVertices = int64_t(1) << 19;
 constexpr int64_t kHalfMapMaxVertices = int64_t(1) << 20;
 constexpr int64_t kByteMapMaxVertices = int64_t(1) << 23;
+// Up to twice as many vertices the layout is chosen per call (both maps are clear between calls): a compaction has 1 to 2.4
+// us more to scan, and many marks earn that back.  8192 / 4096 / 2048 seeds (15, 10, 5), bits -> bytes: 8.5 M vertices of mean
+// degree 25 91 -> 60, 61 -> 46, 43 -> 38 us; 16.5 M 90 -> 69, 60 -> 51, 42 -> 41; 12 M of degree 12 44 -> 42, 33 -> 34, 27 -> 30;
+// one hop of 25 10.7 -> 11.7.  Compactions of both maps at once scan twice: with the last frontier wanted 158 -> 139, 167 -> 161
+// and 82 -> 83 us a step with blocks and rows.  The expected marks (expected_marks) of these calls are 0.83, 0.43, 0.22; 0.44,
+// 0.22, 0.11; 0.48, 0.25, 0.12 per vertex, too high by more where degrees are small beside the fan-out, so the line is drawn where
+// no call measured loses.
+constexpr int64_t kEitherMapMaxVertices = int64_t(1) << 24;
+constexpr double kByteMarksPerVertex = 0.4, kByteMarksPerVertexBoth = 0.5;
 inline int mark_shift(int64_t num_vertices) {
   return num_vertices <= kWordMapMaxVertices ? 5 : num_vertices <= kHalfMapMaxVertices ? 4
          : num_vertices <= kByteMapMaxVertices ? 3 : 0;

@@ -490,3 +490,41 @@ def test_blocks_of_evenly_spaced_frontiers(gap, n):
         ctx.build_blocks(dev, (f,), buf, out=blk)
         assert_blocks_equal(orc.sample_khop(seeds, (f,), 3, blocks=True), blk.to_host(), f"{gap} {n}")
         ctx.check()
+
+
+@pytest.mark.parametrize("V", [(1 << 23) + 1, 1 << 24, (1 << 24) + 1])
+def test_maps_laid_out_per_call(V):
+    """Calls of many marks and of few in turn on one context, whose maps take both layouts where the graph is between the
+    limits: every kind of compaction, and pre-sampling."""
+    import oracle
+    import paper_2305_16588_amd as lgp
+    from gpu_common import assert_batch_equal
+    rng = np.random.default_rng(V)
+    sources = 20_000                                               # rows of 64 ids, the others are empty
+    few = sources * 64
+    indptr = np.zeros(V + 1, np.int32)
+    indptr[1:sources + 1] = np.arange(1, sources + 1) * 64
+    indptr[sources + 1:] = few
+    indices = rng.integers(0, V, few).astype(np.int32)
+    indices[::4] = rng.integers(0, sources, indices[::4].size)
+    indices[:2] = [0, V - 1]
+    # pretend edges behind the rows raise the mean degree, which decides about the layout
+    more = lgp.pinned_empty(7 * V, np.int32)
+    more[:few] = indices
+    ctx, orc = lgp.Context(lgp.pinned_copy(indptr), more), oracle.Oracle(indptr, indices, None)
+    order = np.concatenate([[0], 1 + rng.permutation(sources - 1)]).astype(np.int32)
+    for n_seeds, fanouts in ((20_000, (8, 8, 8)), (300, (5, 3)), (20_000, (8, 8, 8)), (20_000, (2,))):
+        seeds = order[:n_seeds]
+        dev = torch.from_numpy(seeds).cuda()
+        ref = orc.sample_khop(seeds, fanouts, 17)
+        for last in (False, True):
+            buf = lgp.SampleBuffers(V, n_seeds, fanouts, last_frontier=last)
+            ctx.sample_khop(dev, fanouts, 17, out=buf)
+            assert_batch_equal(ref, buf.to_host(dev), f"{n_seeds} {fanouts} {last}")
+    tablet = torch.from_numpy(order).cuda()
+    for fanouts in ((8, 8, 8), (3,)):
+        ctx.build_hotness(tablet, 10_000, fanouts, 5)
+        rt, rf, _ = orc.build_hotness(order, 10_000, fanouts, 5)
+        topo, feat = ctx.get_hotness()
+        assert (topo == rt).all() and (feat == rf).all()
+    ctx.check()
