@@ -121,8 +121,8 @@ int lgp_host_free(void* ptr);
  * (LGP_EINVAL if an array is not GPU-addressable) and allocates the per-vertex
  * lookup state in HBM: a row table (offset + degree + "cached" flag, 8 bytes per
  * vertex, filled from indptr), the feature remap, two hotness vectors and the dedup
- * maps -- about 20.3 bytes per vertex (22 to 28 on graphs of up to 2^23 vertices, whose maps
- * hold a byte or more per vertex), outside the cache budgets.  It starts with
+ * maps -- about 20.3 bytes per vertex (22 to 28 on graphs of up to 2^24 vertices, whose maps
+ * have room for a byte or more per vertex), outside the cache budgets.  It starts with
  * empty caches, so sampling and gathering already work, with every column id and
  * feature row read from CPU memory (Sec. 3.2's mode with the topology kept in CPU memory).
  * Synchronous. */
@@ -144,10 +144,10 @@ int lgp_shuffle_tablet(int device, const int32_t* in, int32_t* out, int64_t n, u
  * the number of edges sampled out of it; for every distinct vertex of a batch's
  * result (seeds included) its feature hotness grows by one.  Both vectors are reset
  * first.  max_batches < 0 processes the whole tablet once.  fanouts is [host].
- * With many mini-batches the column ids may be copied to HBM after the first one, into
- * 4 bytes per edge of stream-ordered memory that are given back at the end of the call (never more than half
- * of what is free, and not after lgp_reserve, under stream capture or beside a topology cache: rows are then read in
- * place).  The result does not depend on it. */
+ * With many mini-batches the call may wait until the frontier sizes of the first one are known and, if they say
+ * that this saves time, copy the column ids to HBM, into 4 bytes per edge of stream-ordered memory that are given back at the
+ * end of the call (never more than half of what is free, and not after lgp_reserve, under stream capture or beside a
+ * topology cache: rows are then read in place and nothing is waited for).  The result does not depend on it. */
 int lgp_build_hotness(lgp_ctx* ctx, const int32_t* train_ids, int64_t n_train, int32_t batch,
                       const int32_t* fanouts, int32_t n_hops, uint64_t base_seed, int64_t max_batches,
                       void* stream);
@@ -344,7 +344,8 @@ int lgp_set_overlap(lgp_ctx* ctx, int enable);
  * was made); scratch [host] = what pre-sampling, lgp_gather_features(_clique) with up to the
  * worst-case number of ids and lgp_build_blocks allocate on first use for batches of up to
  * max_seeds seeds with these fan-outs.  The caches themselves are reported by lgp_plan_cache /
- * lgp_get_cache_plan.  Either pointer may be NULL.  Nothing is allocated or launched. */
+ * lgp_get_cache_plan.  The column ids that lgp_build_hotness may hold in HBM while it runs are in
+ * neither figure: it does without them where memory is short.  Either pointer may be NULL.  Nothing is allocated or launched. */
 int lgp_workspace_bytes(const lgp_ctx* ctx, int32_t max_seeds, const int32_t* fanouts, int32_t n_hops, size_t* fixed,
                         size_t* scratch);
 

@@ -96,9 +96,10 @@ struct lgp_ctx {
   int32_t* hs_frontier[LGP_MAX_HOPS] = {};
   int64_t hs_cap[LGP_MAX_HOPS] = {};
   int32_t* hs_n = nullptr;
-  unsigned long long* hs_expansions = nullptr;   // device: sum of frontier sizes of the last pre-sampling, then whether
-                                                 // its topology was staged in HBM (launch_stage_topology)
+  unsigned long long* hs_expansions = nullptr;   // device counter: sum of frontier sizes of the last pre-sampling
   int64_t hs_batches = 0;
+  int32_t* hs_seen = nullptr;                    // pinned host copy of hs_n, complete when ev_seen is (stage_topology)
+  hipEvent_t ev_seen = nullptr;
   bool indices_on_host = false;                  // the column ids lie in CPU memory
 
   hipStream_t miss_stream = nullptr;
@@ -269,10 +270,11 @@ double expected_marks(const lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts,
   return marks;
 }
 
-// Sampling of one mini-batch; out == nullptr is the pre-sampling mode (hotness only), for which `staged` may hold room for
-// the column ids in HBM.
+// Sampling of one mini-batch; out == nullptr is the pre-sampling mode (hotness only), for which `staged` may hold the
+// column ids in HBM, and `show` sends the frontier sizes to hs_seen as soon as all are known.
 int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops,
-                uint64_t rng_seed, const lgp_sample_out* out, hipStream_t s, const int32_t* staged = nullptr) {
+                uint64_t rng_seed, const lgp_sample_out* out, hipStream_t s, const int32_t* staged = nullptr,
+                bool show = false) {
   const bool hot_mode = (out == nullptr);
   const int64_t V = c->g.num_vertices;
   const bool want_last = !hot_mode && out->frontier[n_hops] != nullptr;
@@ -287,10 +289,7 @@ int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t
   uint32_t* gbits32 = reinterpret_cast<uint32_t*>(maps.gather);
   int32_t* n_frontier = hot_mode ? c->hs_n : out->n_frontier;
   TopoView tv = topo_view(c);
-  if (staged) {
-    tv.staged = staged;
-    tv.use_staged = reinterpret_cast<const uint64_t*>(c->hs_expansions + 1);
-  }
+  if (staged) tv.h_indices = staged;
 
   const int32_t* frontier = seeds;
   int64_t cap = n_seeds;
@@ -298,6 +297,10 @@ int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t
     // the last hop's samples only feed the gather set, so they are marked there directly -- unless
     // the caller wants the last frontier as a list of its own
     const bool final_hop = h + 1 == n_hops;
+    if (final_hop && show) {
+      LGP_HIP(c, hipMemcpyAsync(c->hs_seen, c->hs_n, sizeof(int32_t) * size_t(n_hops), hipMemcpyDeviceToHost, s));
+      LGP_HIP(c, hipEventRecord(c->ev_seen, s));
+    }
     launch_sample_hop(di, tv, frontier, n_frontier + h, cap, fanouts[h], h, rng_seed,
                       hot_mode ? nullptr : out->nbr[h], hot_mode ? nullptr : out->cnt[h],
                       final_hop && !want_last ? gbits32 : fbits32, h == 0 ? gbits32 : nullptr,
@@ -539,32 +542,50 @@ int gather_core(lgp_ctx* c, int32_t member, const int32_t* ids, int64_t n_max, c
   return LGP_OK;
 }
 
-// Room in HBM for the column ids while pre-sampling runs, or null if it is not worth having: launch_stage_topology decides
-// with the first batch's row count, and this estimate keeps calls that will hardly stage from paying for the room (10-40 us,
-// and up to 0.3 ms when it is given back): at least 24 MB, half a millisecond of the link, must be saved.  It takes the
-// expected distinct samples of uniformly popular vertices, halved: on graphs whose popularity falls with the rank (2.4 M
-// vertices, 8192 seeds, 15-10-5) it gives 530 k rows a batch where 263 k are read.  A topology cache that is in place
-// already serves the rows that are read often, so nothing is staged beside it.
+// Whether lgp_build_hotness may copy the column ids to HBM after its first mini-batch: 24 MB, half a millisecond of the
+// link, are to be saved.  expected_marks gives more rows than are read where popularity is skewed (2.4 M vertices, 8192 seeds,
+// 15-10-5: 530 k, 263 k), so half of what it says is taken.  A topology cache that is in place already serves the rows that
+// are read often, so nothing is copied beside it; nor is anything waited for or allocated under capture, nor more than half of
+// the free memory taken (asked before anything is enqueued: beside running kernels hipMemGetInfo took up to 0.6 ms).
 constexpr double kStageSaving = 24e6;
-int32_t* staging_room(const lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts, int32_t n_hops, int64_t n_batches,
-                      hipStream_t s, void** base) {
-  *base = nullptr;
-  if (!c->indices_on_host || c->reserved || c->plan.n_topo > 0 || n_batches < 2) return nullptr;
+size_t stage_bytes(const lgp_ctx* c) { return size_t(c->g.num_edges) * 4 + 16; }
+double stage_saving(const lgp_ctx* c, double rows, int64_t remaining) {   // bytes over PCIe, a 128-byte line per row
+  return rows * double(remaining) * 128.0 - double(c->g.num_edges) * 4.0;
+}
+bool may_stage(const lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts, int32_t n_hops, int64_t n_batches, hipStream_t s) {
+  if (!c->indices_on_host || c->reserved || c->plan.n_topo > 0 || n_batches < 2) return false;
   double rows = 0;
   expected_marks(c, n_seeds, fanouts, n_hops, &rows);
-  if (0.5 * rows * double(n_batches - 1) * 128.0 - double(c->g.num_edges) * 4.0 < kStageSaving) return nullptr;
+  if (stage_saving(c, 0.5 * rows, n_batches - 1) < kStageSaving) return false;
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
   size_t free_bytes = 0, total_bytes = 0;
-  const size_t bytes = size_t(c->g.num_edges) * 4 + 16;
-  // no allocation under capture, and never more than half of the free memory; without room the rows are read in place
-  if (hipStreamIsCapturing(s, &capturing) != hipSuccess || capturing != hipStreamCaptureStatusNone ||
-      hipMemGetInfo(&free_bytes, &total_bytes) != hipSuccess || bytes > free_bytes / 2 ||
-      hipMallocAsync(base, bytes, s) != hipSuccess) {
+  if (hipStreamIsCapturing(s, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone &&
+      hipMemGetInfo(&free_bytes, &total_bytes) == hipSuccess)
+    return stage_bytes(c) <= free_bytes / 2;
+  (void)hipGetLastError();
+  return false;
+}
+
+// The copy, if the rows that the first mini-batch reads say that it saves time; else, and where memory is short, *staged
+// stays null and rows are read in place.  The host waits for the frontier sizes, which are known before the last hop: what
+// follows is enqueued while that runs.  With the room taken beforehand and the decision on the device, calls on skewed graphs
+// left the room unused (8 M vertices, 115 M edges, 8 batches, rows in place: 460 MB and 5090 us a call; now none and 5020, and
+// 5000 with no question asked).
+int stage_topology(lgp_ctx* c, int64_t n_seeds, int32_t n_hops, int64_t remaining, hipStream_t s, void** room,
+                   const int32_t** staged) {
+  LGP_HIP(c, hipEventSynchronize(c->ev_seen));
+  double rows = double(n_seeds);
+  for (int h = 1; h < n_hops; ++h) rows += double(c->hs_seen[h]);
+  if (stage_saving(c, rows, remaining) <= 0) return LGP_OK;
+  if (hipMallocAsync(room, stage_bytes(c), s) != hipSuccess) {
     (void)hipGetLastError();
-    *base = nullptr;
-    return nullptr;
+    *room = nullptr;
+    return LGP_OK;
   }
-  return static_cast<int32_t*>(*base) + ((uintptr_t(c->g.indices) >> 2) & 3);
+  int32_t* const to = static_cast<int32_t*>(*room) + ((uintptr_t(c->g.indices) >> 2) & 3);
+  launch_stage_topology(c->g.indices, to, c->g.num_edges, s);
+  *staged = to;
+  return LGP_OK;
 }
 
 }  // namespace
@@ -673,7 +694,7 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   step(dev_alloc(&c->d_err, 1));
   step(dev_alloc(&c->counters, 3));
   step(dev_alloc(&c->hs_n, LGP_MAX_HOPS + 1));
-  step(dev_alloc(&c->hs_expansions, 2));
+  step(dev_alloc(&c->hs_expansions, 1));
   step(dev_alloc(&c->seg, LGP_MAX_HOPS + 2));
   step(dev_alloc(&c->unordered, LGP_MAX_HOPS + 1));
   step(dev_alloc(&c->seg_counters, (LGP_MAX_HOPS + 1) * 3));
@@ -685,10 +706,12 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   if (e == hipSuccess) e = hipMemset(c->d_err, 0, sizeof(uint32_t));
   if (e == hipSuccess) e = hipMemset(c->counters, 0, 3 * sizeof(int32_t));
   if (e == hipSuccess) e = hipMemset(c->unordered, 0, (LGP_MAX_HOPS + 1) * sizeof(uint32_t));
-  if (e == hipSuccess) e = hipMemset(c->hs_expansions, 0, 2 * sizeof(unsigned long long));
+  if (e == hipSuccess) e = hipMemset(c->hs_expansions, 0, sizeof(unsigned long long));
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->miss_stream, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_seen, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&c->hs_seen), LGP_MAX_HOPS * sizeof(int32_t), hipHostMallocDefault);
   if (e == hipSuccess) {
     launch_init_row_table(c->di, c->g.indptr, c->g.indptr_bytes, V, c->row_tab, nullptr);
     e = hipGetLastError();
@@ -721,6 +744,8 @@ int lgp_destroy(lgp_ctx* c) {
     }
   if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
   if (c->ev_join) (void)hipEventDestroy(c->ev_join);
+  if (c->ev_seen) (void)hipEventDestroy(c->ev_seen);
+  if (c->hs_seen) (void)hipHostFree(c->hs_seen);
   if (c->miss_stream) (void)hipStreamDestroy(c->miss_stream);
   (void)hipGetLastError();
   delete c;
@@ -740,20 +765,19 @@ int lgp_build_hotness(lgp_ctx* c, const int32_t* train_ids, int64_t n_train, int
   worst_case(c, std::min<int64_t>(batch, std::max<int64_t>(n_train, 1)), fanouts, n_hops, need, &gather_need);
   st = ensure_presample_frontiers(c, need, n_hops, s);
   if (st != LGP_OK) return st;
-  launch_fill_i32(c->di, reinterpret_cast<int32_t*>(c->topo_hot), V, 0, s);
-  launch_fill_i32(c->di, reinterpret_cast<int32_t*>(c->feat_hot), V, 0, s);
-  launch_fill_i32(c->di, reinterpret_cast<int32_t*>(c->hs_expansions), 4, 0, s);
   int64_t n_batches = (n_train + batch - 1) / batch;
   if (max_batches >= 0 && max_batches < n_batches) n_batches = max_batches;
+  const bool may = may_stage(c, need[0], fanouts, n_hops, n_batches, s);
+  launch_fill_i32(c->di, reinterpret_cast<int32_t*>(c->topo_hot), V, 0, s);
+  launch_fill_i32(c->di, reinterpret_cast<int32_t*>(c->feat_hot), V, 0, s);
+  launch_fill_i32(c->di, reinterpret_cast<int32_t*>(c->hs_expansions), 2, 0, s);
   void* room = nullptr;
-  int32_t* const staged = staging_room(c, need[0], fanouts, n_hops, n_batches, s, &room);
+  const int32_t* staged = nullptr;
   for (int64_t b = 0; b < n_batches && st == LGP_OK; ++b) {
     const int64_t lo = b * batch;
     const int32_t nb = int32_t(std::min<int64_t>(batch, n_train - lo));
-    if (staged && b == 1)
-      launch_stage_topology(c->g.indices, staged, c->g.num_edges, c->hs_expansions, n_batches - 1,
-                            reinterpret_cast<uint64_t*>(c->hs_expansions + 1), s);
-    st = sample_core(c, train_ids + lo, nb, fanouts, n_hops, base_seed + uint64_t(b), nullptr, s, b > 0 ? staged : nullptr);
+    if (may && b == 1 && (st = stage_topology(c, need[0], n_hops, n_batches - 1, s, &room, &staged)) != LGP_OK) break;
+    st = sample_core(c, train_ids + lo, nb, fanouts, n_hops, base_seed + uint64_t(b), nullptr, s, staged, may && b == 0);
   }
   if (room) {
     const hipError_t e = hipFreeAsync(room, s);

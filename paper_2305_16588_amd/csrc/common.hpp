@@ -105,9 +105,6 @@ struct TopoView {
   const int32_t* t_indices;  // cached column ids (HBM)
   int32_t indptr_bytes;
   int64_t num_vertices;
-  // Pre-sampling: where *use_staged is not 0, `staged` holds all of h_indices in HBM (both null otherwise).
-  const int32_t* staged = nullptr;
-  const uint64_t* use_staged = nullptr;
 };
 
 // ---- sampler.hip ----------------------------------------------------------
@@ -122,12 +119,8 @@ void launch_sample_hop(const DeviceInfo& di, const TopoView& tv, const int32_t* 
                        uint32_t* mark_bits, uint32_t* self_bits, uint32_t* topo_hot, uint32_t* d_err, uint64_t* status,
                        int64_t n_status, hipStream_t s);
 
-// Pre-sampling, between the first mini-batch and the others: decide on the device whether the row reads of the
-// `remaining` mini-batches, each like the *rows of the first one, would move more bytes over PCIe (a 128-byte line each)
-// than all n_edges column ids, and if so copy h_indices to staged[0 .. n_edges) and set *use_staged to 1.
-// The two addresses are equal modulo 16.
-void launch_stage_topology(const int32_t* h_indices, int32_t* staged, int64_t n_edges, const unsigned long long* rows,
-                           int64_t remaining, uint64_t* use_staged, hipStream_t s);
+// Pre-sampling: staged[0 .. n_edges) = h_indices[0 .. n_edges), from CPU memory to HBM.  The two addresses are equal modulo 16.
+void launch_stage_topology(const int32_t* h_indices, int32_t* staged, int64_t n_edges, hipStream_t s);
 
 // ---- compact.hip ----------------------------------------------------------
 struct CompactArgs {

@@ -19,20 +19,15 @@ __global__ __launch_bounds__(256) void sample_hop_kernel(HopArgs a) {
 
 // Pre-sampling reads rows of a few column ids at random places of CPU memory, a 128-byte line of the link each (340 M
 // lines/s = 43.5 GB/s when every line stands alone), and comes back to the same rows batch after batch; all column ids in
-// order cross the link at 57 GB/s, once.  The first batch tells how many rows a batch reads, so the choice is made here on
-// the device, without the host waiting for the count.  16 batches of 8192 seeds (15, 10, 5) on 2.4 M vertices and 62 M edges:
+// order cross the link at 57 GB/s, once.  16 batches of 8192 seeds (15, 10, 5) on 2.4 M vertices and 62 M edges:
 // 0.79 ms a batch over PCIe, 4.4 ms for the copy and 0.08 ms a batch from HBM; the call with the vectors' copy to the host
 // 15.8 -> 8.5 ms, 8 batches of 4555 seeds (11, 11, 11) on 0.87 M vertices and 30 M edges 5.6 -> 3.7.
 // 64 workgroups keep the link full (57.5 GB/s; 55.5 at 1024).
 constexpr int kStageGroups = 64;
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(256) void stage_topology_kernel(const int32_t* __restrict__ src, int32_t* __restrict__ dst,
-                                                             int64_t n, const unsigned long long* __restrict__ rows,
-                                                             int64_t remaining, uint64_t* __restrict__ use_staged) {
-  constexpr uint64_t kIdsPerLine = 128 / sizeof(int32_t);
-  if (*rows * uint64_t(remaining) <= uint64_t(n) / kIdsPerLine) return;
+                                                             int64_t n) {
   const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x, threads = int64_t(gridDim.x) * 256;
-  if (t == 0) *use_staged = 1;
   // whole 16-byte chunks from the first aligned id on; fewer than four ids are left over at either end
   const int64_t head = int64_t((0 - (uintptr_t(src) >> 2)) & 3) < n ? int64_t((0 - (uintptr_t(src) >> 2)) & 3) : n;
   const int64_t chunks = (n - head) / 4, tail = head + chunks * 4;
@@ -54,10 +49,8 @@ __global__ __launch_bounds__(256) void stage_topology_kernel(const int32_t* __re
 
 }  // namespace
 
-void launch_stage_topology(const int32_t* h_indices, int32_t* staged, int64_t n_edges, const unsigned long long* rows,
-                           int64_t remaining, uint64_t* use_staged, hipStream_t s) {
-  hipLaunchKernelGGL(stage_topology_kernel, dim3(kStageGroups), dim3(256), 0, s, h_indices, staged, n_edges, rows,
-                     remaining, use_staged);
+void launch_stage_topology(const int32_t* h_indices, int32_t* staged, int64_t n_edges, hipStream_t s) {
+  hipLaunchKernelGGL(stage_topology_kernel, dim3(kStageGroups), dim3(256), 0, s, h_indices, staged, n_edges);
 }
 
 void launch_sample_hop(const DeviceInfo& di, const TopoView& tv, const int32_t* frontier, int32_t* n_frontier,

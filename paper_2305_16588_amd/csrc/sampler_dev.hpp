@@ -85,7 +85,6 @@ __device__ __forceinline__ void sample_hop(const HopArgs& a, uint32_t block, uin
   if (self_bits && block == 0 && threadIdx.x == 0) *a.n_frontier = int32_t(a.cap);
   if (block == 0)
     for (int k = threadIdx.x; k < a.n_status; k += 256) a.status[k] = 0;
-  if (a.tv.use_staged && *a.tv.use_staged) h_indices = a.tv.staged;
   int64_t n = self_bits ? a.cap : int64_t(*a.n_frontier);
   if (n > a.cap) n = a.cap;                           // never trust a count beyond the buffer
   const int per_wave = 64 / f;                    // vertices per wave pass

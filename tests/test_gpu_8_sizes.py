@@ -528,3 +528,36 @@ def test_maps_laid_out_per_call(V):
         topo, feat = ctx.get_hotness()
         assert (topo == rt).all() and (feat == rf).all()
     ctx.check()
+
+
+@pytest.mark.parametrize("sources,reserve,copied", [(100_000, False, True), (2000, False, False), (100_000, True, False)])
+def test_topology_is_copied_only_where_batches_read_it(sources, reserve, copied):
+    """HBM that pre-sampling takes: all column ids where the first batch's reads say that a copy pays, and nothing where a
+    few vertices own all edges, so that batches read far fewer rows than the mean degree suggests, or after lgp_reserve."""
+    import ctypes
+    import oracle
+    import paper_2305_16588_amd as lgp
+    V, batch, fanouts, degree = 100_000, 256, (8, 8), 4_000_000 // sources
+    rng = np.random.default_rng(sources)
+    order = rng.permutation(V)
+    d = np.zeros(V, np.int64)
+    d[order[:sources]] = degree
+    indptr = np.concatenate([[0], np.cumsum(d)]).astype(np.int32)
+    indices = order[rng.integers(sources, V, 4_000_000) if sources < V else rng.integers(0, V, 4_000_000)].astype(np.int32)
+    ctx, orc = lgp.Context(lgp.pinned_copy(indptr), lgp.pinned_copy(indices)), oracle.Oracle(indptr, indices, None)
+    if reserve:
+        ctx.reserve(batch, fanouts)
+    hip = lgp.load_library()                                       # symbols of the runtime that the library is linked to
+    used_high, pool, value = 8, ctypes.c_void_p(), ctypes.c_uint64(0)           # hipMemPoolAttrUsedMemHigh
+    assert hip.hipDeviceGetDefaultMemPool(ctypes.byref(pool), 0) == 0
+    tablet = rng.permutation(V).astype(np.int32)
+    dev = torch.from_numpy(tablet).cuda()
+    torch.cuda.synchronize()
+    assert hip.hipMemPoolSetAttribute(pool, used_high, ctypes.byref(value)) == 0
+    ctx.build_hotness(dev, batch, fanouts, 5)
+    topo, feat = ctx.get_hotness()
+    assert hip.hipMemPoolGetAttribute(pool, used_high, ctypes.byref(value)) == 0
+    assert (value.value >= 4 * indices.size) if copied else value.value == 0, f"{value.value} bytes taken"
+    rt, rf, _ = orc.build_hotness(tablet, batch, fanouts, 5)
+    assert (topo == rt).all() and (feat == rf).all()
+    ctx.check()
