@@ -189,6 +189,7 @@ TopoView topo_view(const lgp_ctx* c) {
   tv.t_indices = c->t_indices;
   tv.indptr_bytes = c->g.indptr_bytes;
   tv.num_vertices = c->g.num_vertices;
+  tv.over_pcie = c->indices_on_host && c->plan.n_topo < c->g.num_vertices;
   return tv;
 }
 
@@ -289,7 +290,10 @@ int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t
   uint32_t* gbits32 = reinterpret_cast<uint32_t*>(maps.gather);
   int32_t* n_frontier = hot_mode ? c->hs_n : out->n_frontier;
   TopoView tv = topo_view(c);
-  if (staged) tv.h_indices = staged;
+  if (staged) {
+    tv.h_indices = staged;
+    tv.over_pcie = false;
+  }
 
   const int32_t* frontier = seeds;
   int64_t cap = n_seeds;

@@ -105,6 +105,7 @@ struct TopoView {
   const int32_t* t_indices;  // cached column ids (HBM)
   int32_t indptr_bytes;
   int64_t num_vertices;
+  bool over_pcie;            // h_indices lies in CPU memory, and not all rows are cached
 };
 
 // ---- sampler.hip ----------------------------------------------------------

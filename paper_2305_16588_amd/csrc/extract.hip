@@ -54,11 +54,11 @@ void launch_hop_and_rows(const DeviceInfo& di, const TopoView& tv, const int32_t
                          int32_t fanout, int32_t hop, uint64_t rng_seed, int32_t* nbr, int32_t* cnt, uint32_t* mark_bits,
                          uint32_t* self_bits, uint32_t* d_err, uint64_t* status, int64_t n_status, const RowSources& r,
                          const void* hit_src, const void* miss_src, void* dst, int64_t row_bytes, hipStream_t s) {
-  const HopArgs h{tv,        frontier,  n_frontier, cap,   fanout, hop,    uint32_t(rng_seed), uint32_t(rng_seed >> 32), nbr, cnt,
-                  mark_bits, self_bits, nullptr,    d_err, status, int32_t(n_status)};
+  const HopArgs h{tv,  frontier, n_frontier, cap,       fanout,  hop_lanes(tv, fanout), hop,    uint32_t(rng_seed), uint32_t(rng_seed >> 32),
+                  nbr, cnt,      mark_bits,  self_bits, nullptr, d_err,                 status, int32_t(n_status)};
   SplitArgs a;
   const int width = split_args(di, r, hit_src, miss_src, dst, row_bytes, &a);
-  const uint32_t hop_groups = hop_blocks(di, cap, fanout);
+  const uint32_t hop_groups = hop_blocks(di, cap, h.lanes);
   const dim3 grid{a.miss_blocks + hop_groups + a.hit_blocks}, block{256};
   auto launch = [&](auto shift, auto vec, auto ragged) {
     hipLaunchKernelGGL((hop_and_rows_kernel<decltype(shift)::value, decltype(vec), decltype(ragged)::value>), grid, block, 0, s,

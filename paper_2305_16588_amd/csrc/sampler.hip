@@ -1,12 +1,12 @@
 // Neighbour sampler (Sec. 2.2 step 2; Sec. 5 "neighbor sampler") for gfx950.
 //
-// A wave takes 64 / fanout frontier vertices, `fanout` lanes each; a lane is a sample
+// A wave takes 64 / fanout frontier vertices, `fanout` lanes each (see hop_lanes); a lane is a sample
 // slot.  One load of the HBM row table gives the row's offset and degree and says
 // whether its column ids sit in the HBM topology cache or in the CPU-resident CSR (read
 // in place over PCIe), so an uncached vertex costs one PCIe round trip, not two.  All slots draw their
 // Philox number at once, and Floyd's sequential "already taken?" test becomes one that needs
-// no order (floyd_moves).  The kernel is bound by dependent loads and, on large graphs, by the bitmap
-// atomics, not by issue slots, so the grid is capped at six workgroups per CU (see launch_one).
+// no order (floyd_moves).  What bounds the kernel stands at sample_hop, the width of its grid at
+// hop_blocks.
 #include "sampler_dev.hpp"
 
 namespace lgp {
@@ -57,9 +57,9 @@ void launch_sample_hop(const DeviceInfo& di, const TopoView& tv, const int32_t* 
                        int64_t cap, int32_t fanout, int32_t hop, uint64_t rng_seed, int32_t* nbr, int32_t* cnt,
                        uint32_t* mark_bits, uint32_t* self_bits, uint32_t* topo_hot, uint32_t* d_err, uint64_t* status,
                        int64_t n_status, hipStream_t s) {
-  const HopArgs a{tv,        frontier,  n_frontier, cap,   fanout, hop,    uint32_t(rng_seed), uint32_t(rng_seed >> 32), nbr, cnt,
-                  mark_bits, self_bits, topo_hot,   d_err, status, int32_t(n_status)};
-  const dim3 grid{hop_blocks(di, cap, fanout)}, block{256};
+  const HopArgs a{tv,  frontier, n_frontier, cap,       fanout,   hop_lanes(tv, fanout), hop,    uint32_t(rng_seed), uint32_t(rng_seed >> 32),
+                  nbr, cnt,      mark_bits,  self_bits, topo_hot, d_err,                 status, int32_t(n_status)};
+  const dim3 grid{hop_blocks(di, cap, a.lanes)}, block{256};
   switch (di.spread_shift) {
     case 0: hipLaunchKernelGGL((sample_hop_kernel<0>), grid, block, 0, s, a); break;
     case 3: hipLaunchKernelGGL((sample_hop_kernel<3>), grid, block, 0, s, a); break;

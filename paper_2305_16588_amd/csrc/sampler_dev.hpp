@@ -52,7 +52,7 @@ struct HopArgs {
   const int32_t* frontier;
   int32_t* n_frontier;
   int64_t cap;
-  int32_t f, hop;
+  int32_t f, lanes, hop;   // fan-out, lanes of a vertex (hop_lanes)
   uint32_t k0, k1;
   int32_t* nbr;
   int32_t* cnt;
@@ -65,10 +65,10 @@ struct HopArgs {
 };
 
 // Marks bound this kernel (last hop of 190 k vertices x 5 at 2.4 M vertices: 23 us with its 950 k byte marks, 11 without;
-// 490 k atomic marks at 250 M: 24 and 9); what is left is loads and issue slots, so lanes are packed without gaps.  Against
-// a power of two of lanes per vertex and a chain of fanout - 1 broadcasts for Floyd's test, calls on 2.4 M vertices from
-// 8192 seeds: fan-outs 17, 17 28.2 -> 25.1 us, 64 17.5 -> 15.4, 9, 9 21.2 -> 20.2, 15, 10, 5 with blocks and gather
-// 190 -> 186; 25 or 3, 3, 3 and graphs with atomic marks are level.
+// 490 k atomic marks at 250 M: 24 and 9); what is left is loads and issue slots, so lanes are packed without gaps (but see
+// hop_lanes).  Against a power of two of lanes per vertex and a chain of fanout - 1 broadcasts for Floyd's test, calls on
+// 2.4 M vertices from 8192 seeds: fan-outs 17, 17 28.2 -> 25.1 us, 64 17.5 -> 15.4, 9, 9 21.2 -> 20.2, 15, 10, 5 with blocks
+// and gather 190 -> 186; 25 or 3, 3, 3 and graphs with atomic marks are level.
 // The caller is workgroup `block` of `blocks` that share the frontier.
 template <int SHIFT>
 __device__ __forceinline__ void sample_hop(const HopArgs& a, uint32_t block, uint32_t blocks) {
@@ -79,7 +79,7 @@ __device__ __forceinline__ void sample_hop(const HopArgs& a, uint32_t block, uin
   int32_t* __restrict__ cnt = a.cnt;
   uint32_t* __restrict__ mark_bits = a.mark_bits;
   uint32_t* __restrict__ self_bits = a.self_bits;
-  const int32_t f = a.f;
+  const int32_t f = a.f, lanes = a.lanes;
   // self_bits != nullptr: this is the first hop; the frontier is the caller's seed list of `cap`
   // ids, whose size is published here and whose members are marked in the gather set.
   if (self_bits && block == 0 && threadIdx.x == 0) *a.n_frontier = int32_t(a.cap);
@@ -87,9 +87,9 @@ __device__ __forceinline__ void sample_hop(const HopArgs& a, uint32_t block, uin
     for (int k = threadIdx.x; k < a.n_status; k += 256) a.status[k] = 0;
   int64_t n = self_bits ? a.cap : int64_t(*a.n_frontier);
   if (n > a.cap) n = a.cap;                           // never trust a count beyond the buffer
-  const int per_wave = 64 / f;                    // vertices per wave pass
+  const int per_wave = 64 / lanes;                // vertices per wave pass
   const int lane = threadIdx.x & 63;
-  const int sub = lane / f, slot = lane - sub * f;   // vertex of this lane in the pass, sample slot
+  const int sub = lane / lanes, slot = lane - sub * lanes;   // vertex of this lane in the pass, sample slot (below f)
   // Three loads depend on one another (frontier id -> row-table entry -> column id).  The id is loaded two passes ahead
   // and the row-table entry one pass ahead, so that a pass waits for its column ids only (two hops of 17 from 8192 seeds
   // of 2.4 M vertices 25.8 -> 25.1 us, one hop of 64 16.0 -> 15.4).
@@ -138,10 +138,10 @@ __device__ __forceinline__ void sample_hop(const HopArgs& a, uint32_t block, uin
       const int32_t j = d - f + slot;
       const int32_t t = int32_t(
           __umul64hi(philox_draw64(a.k0, a.k1, uint32_t(v), uint32_t(a.hop), uint32_t(slot)), uint64_t(uint32_t(j)) + 1));
-      const bool moves = floyd_moves(big, t, d, f, slot, lane - slot);
+      const bool moves = floyd_moves(big && slot < f, t, d, f, slot, lane - slot);
       if (big) p = moves ? j : t;
     }
-    if (active) {
+    if (active && slot < f) {
       int32_t u = -1;
       if (big || slot < d) {
         u = colbase[s + p];
@@ -152,7 +152,7 @@ __device__ __forceinline__ void sample_hop(const HopArgs& a, uint32_t block, uin
           mark_vertex<SHIFT>(mark_bits, u);
         }
       }
-      if (nbr) nbr[g0 * f + lane] = u;
+      if (nbr) nbr[g * f + slot] = u;
       if (slot == 0) {
         if (self_bits && !bad) mark_vertex<SHIFT>(self_bits, v);
         const int32_t c = d < f ? d : f;
@@ -163,14 +163,24 @@ __device__ __forceinline__ void sample_hop(const HopArgs& a, uint32_t block, uin
   }
 }
 
+// Lanes of a vertex: as many as samples, but a power of two of them where rows cross PCIe.  The link bounds the hop there, and
+// lanes packed without gaps cost it up to 4 %.  Calls, packed / power of two: 4096 seeds of 8 M vertices 9, 9 169.5 / 162.4 us,
+// 11, 11 185.9 / 180.7, 5, 5 116.6 / 113.5, 20, 20 236.3 / 237.0; 8192 seeds (15, 10, 5) of 2.4 M 931 / 915, with half of the
+// topology cached 504 / 499 (where the cached half serves most rows 275.7 / 276.9).
+inline int32_t hop_lanes(const TopoView& tv, int32_t f) {
+  if (!tv.over_pcie) return f;
+  int32_t lanes = 1;
+  while (lanes < f) lanes *= 2;
+  return lanes;
+}
+
 // Workgroups for a hop over at most `cap` vertices.
-// Six workgroups (24 waves) per CU: the kernel is bound by scattered marks and dependent loads, not by issue slots.
-// Calls at 4 / 6 / 8 per CU: 2.4 M vertices, half of the topology over PCIe 279.9 / 276.3 / 276.4 us, 111 M vertices
-// 67.7 / 64.8 / 67.0, 250 M 63.3 / 61.7 / 63.4; sampling server step at 2.4 M 194.6 / 189.9 / 192.6.  Sampling a batch
-// beside the extraction of the one before, 2.4 M vertices, at 4 / 6: half of the topology and 30 % of the features
+// Six workgroups (24 waves) per CU: more waves do not make scattered marks faster.  Calls at 4 / 6 / 8 per CU: 2.4 M
+// vertices, half of the topology over PCIe 279.9 / 276.3 / 276.4 us, 111 M vertices 67.7 / 64.8 / 67.0, 250 M 63.3 / 61.7 /
+// 63.4; sampling server step at 2.4 M 194.6 / 189.9 / 192.6.  Sampling a batch beside the extraction of the one before, 2.4 M vertices, at 4 / 6: half of the topology and 30 % of the features
 // cached 1869 / 1870 us a step, half and 90 % 574 / 575, everything 148.7 / 145.0.
-inline uint32_t hop_blocks(const DeviceInfo& di, int64_t cap, int32_t f) {
-  const int64_t per_block = 4 * (64 / f), full = int64_t(di.num_cus) * 6;       // vertices of a workgroup pass
+inline uint32_t hop_blocks(const DeviceInfo& di, int64_t cap, int32_t lanes) {
+  const int64_t per_block = 4 * (64 / lanes), full = int64_t(di.num_cus) * 6;       // vertices of a workgroup pass
   const int64_t blocks = (cap + per_block - 1) / per_block;
   return uint32_t(blocks > full ? full : blocks < 1 ? 1 : blocks);
 }

@@ -561,3 +561,30 @@ def test_topology_is_copied_only_where_batches_read_it(sources, reserve, copied)
     rt, rf, _ = orc.build_hotness(tablet, batch, fanouts, 5)
     assert (topo == rt).all() and (feat == rf).all()
     ctx.check()
+
+
+@pytest.mark.parametrize("f", [1, 3, 5, 8, 9, 16, 17, 21, 22, 32, 33, 64])
+def test_samples_of_resident_and_host_topology(f):
+    """Lanes of a vertex: as many as samples where all rows are in HBM (arrays there to begin with, or all cached), a power
+    of two of them where some are read over PCIe."""
+    import oracle
+    import paper_2305_16588_amd as lgp
+    from gpu_common import assert_batch_equal
+    V, n = 5000, 700
+    rng = np.random.default_rng(f)
+    indptr = np.concatenate([[0], np.cumsum(rng.integers(0, 2 * f + 2, V))]).astype(np.int32)
+    indices = rng.integers(0, V, int(indptr[-1])).astype(np.int32)
+    orc = oracle.Oracle(indptr, indices, None)
+    seeds = rng.permutation(V)[:n].astype(np.int32)
+    dev = torch.from_numpy(seeds).cuda()
+    hot = rng.integers(0, 9, V).astype(np.uint32)
+    ref = orc.sample_khop(seeds, (f, 2), 41)
+    for resident, budget in ((True, 0), (False, 0), (False, 2 * indices.size), (False, 1 << 40)):
+        arrays = [torch.from_numpy(a).cuda() if resident else lgp.pinned_copy(a) for a in (indptr, indices)]
+        ctx = lgp.Context(*arrays)
+        ctx.set_hotness(hot, hot)
+        ctx.build_cache(budget, 0)
+        buf = lgp.SampleBuffers(V, n, (f, 2))
+        ctx.sample_khop(dev, (f, 2), 41, out=buf)
+        assert_batch_equal(ref, buf.to_host(dev), f"{resident} {budget}")
+        ctx.check()
