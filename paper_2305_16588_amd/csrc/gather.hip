@@ -188,13 +188,20 @@ __global__ __launch_bounds__(256) void gather_rows_flat_kernel(const char* __res
 }
 
 // ---- cache misses and cache fill: CPU memory -> HBM over PCIe ---------------
-// One lane group per row (see group_rows).
+// One lane group per row (see group_rows).  A call of more than `most` rows is left to the first `narrow` workgroups.
 template <typename VecT, bool RAGGED, int G, int UNROLL, bool HBM_SOURCE>
 __global__ __launch_bounds__(256) void gather_rows_group_kernel(const char* __restrict__ src, char* __restrict__ dst,
                                                                 RowShape shape, const int32_t* __restrict__ row,
                                                                 const int32_t* __restrict__ srcrow, int64_t n_max,
-                                                                const int32_t* __restrict__ n_dev, DirectIds dir) {
-  group_rows<VecT, RAGGED, UNROLL, HBM_SOURCE>(src, dst, shape, row, srcrow, n_max, n_dev, dir, G, blockIdx.x, gridDim.x);
+                                                                const int32_t* __restrict__ n_dev, DirectIds dir,
+                                                                int64_t most, uint32_t narrow) {
+  uint32_t blocks = gridDim.x;
+  if (blocks > narrow) {
+    const int64_t n = dir.window ? int64_t(dir.window[1]) - dir.window[0] : n_dev ? int64_t(*n_dev) : n_max;
+    if (n > most) blocks = narrow;
+    if (blockIdx.x >= blocks) return;
+  }
+  group_rows<VecT, RAGGED, UNROLL, HBM_SOURCE>(src, dst, shape, row, srcrow, n_max, n_dev, dir, G, blockIdx.x, blocks);
 }
 
 template <typename VecT, bool RAGGED>
@@ -265,7 +272,8 @@ void launch_group_g(const DeviceInfo& di, const char* src, char* dst, const RowS
   // (400-B rows 44.9 -> 44.0 GB/s, 2-KiB rows 57.5 -> 55.7 GB/s from 64 to 512 workgroups), because the
   // excess requests only queue up in front of the link.
   const unsigned blocks = blocks_for((s.items + (256 / G) * U - 1) / ((256 / G) * U), std::max(1, di.num_cus / 4));
-  launch_on(s, gather_rows_group_kernel<VecT, RAGGED, G, U, false>, blocks, src, dst, shape, row, srcrow, n_max, n_dev, dir);
+  launch_on(s, gather_rows_group_kernel<VecT, RAGGED, G, U, false>, blocks, src, dst, shape, row, srcrow, n_max, n_dev, dir,
+            n_max, blocks);
 }
 
 // Cache hits whose rows straddle 128-byte lines (e.g. 400-byte rows): one lane group per row, one
@@ -275,12 +283,19 @@ template <typename VecT, bool RAGGED, int G>
 void launch_group_hbm_g(const DeviceInfo& di, const char* src, char* dst, const RowShape& shape, const int32_t* row,
                         const int32_t* srcrow, int64_t n_max, const int32_t* n_dev, const DirectIds& dir,
                         const Where& s) {
-  // one row per group in flight needs more waves than the flat walk: 8 workgroups per CU (2 / 3 / 4 / 6 / 8: 512 k rows of 400
-  // bytes 138.7 / 107.6 / 95.6 / 90.7 / 91.4 us; 6 / 8: 400 bytes 43.9 / 43.5, 150 bytes 25.0 / 23.2 and, of 30 M vertices, 52.5 /
-  // 48.6, 602 bytes 82.3 / 78.1, 66 bytes 14.4 / 13.2, 80 bytes 14.1 / 13.4).  Two rows in flight are level or slower below
-  // 150 bytes (66 bytes 14.2) and on rows of multiples of 4 (250 bytes 30.0 / 30.5), and ahead on 150 (22.5) and 602 (76.6).
+  // One row per group in flight needs more waves than the flat walk: 8 workgroups per CU (2 / 3 / 4 / 6 / 8: 512 k rows of 400
+  // bytes 138.7 / 107.6 / 95.6 / 90.7 / 91.4 us), but 6 for a call whose rows leave little of the 256-MB last-level cache,
+  // unless so many lanes of a group have no chunk that 8 workgroups keep no more requests in flight than 6 full ones.
+  // 6 / 8 with 300 k, 500 k, 1 M and 2 M rows of 20 M vertices: 250 bytes 31.2 / 29.7, 52.3 / 49.4, 109 / 114, 221 / 246, 352 bytes 40.1 / 38.5,
+  // 77.0 / 71.8, 140 / 144, 278 / 292, 400 bytes of 2.4 M 42.9 / 42.5, 80.6 / 72.0, 152 / 155, 280 / 312, 700 bytes 81.3 / 78.1, 141 / 151, 280 /
+  // 306, 562 / 617; with few busy lanes 66 bytes 14.2 / 13.2, 21.9 / 20.4, 43.1 / 40.3, 85.8 / 82.1, 150 bytes 24.9 / 23.0, 40.3 / 37.0, 79.1 /
+  // 71.2, 164 / 154, 520 bytes 66.9 / 67.0, 116 / 104, 234 / 214, 464 / 425.  Two rows in flight are level or slower below 150 bytes
+  // and on rows of multiples of 4.
+  const bool few = G <= 16 ? shape.cpr * 8 <= G * 5 : shape.cpr * 16 <= G * 9;
+  const int64_t most = few ? n_max : (int64_t(224) << 20) / shape.bytes;
   const unsigned blocks = blocks_for((s.items + 256 / G - 1) / (256 / G), std::min<int64_t>(s.hbm_blocks, int64_t(di.num_cus) * 8));
-  launch_on(s, gather_rows_group_kernel<VecT, RAGGED, G, 1, true>, blocks, src, dst, shape, row, srcrow, n_max, n_dev, dir);
+  launch_on(s, gather_rows_group_kernel<VecT, RAGGED, G, 1, true>, blocks, src, dst, shape, row, srcrow, n_max, n_dev, dir, most,
+            uint32_t(di.num_cus) * 6);
 }
 
 template <typename VecT, bool RAGGED>

@@ -588,3 +588,27 @@ def test_samples_of_resident_and_host_topology(f):
         ctx.sample_khop(dev, (f, 2), 41, out=buf)
         assert_batch_equal(ref, buf.to_host(dev), f"{resident} {budget}")
         ctx.check()
+
+
+@pytest.mark.parametrize("row_bytes", [74, 500, 700, 2056])
+def test_cached_rows_by_lane_groups_of_small_and_large_calls(row_bytes):
+    """Calls on both sides of the size from which a narrower grid takes the rows (224 MiB of them), counts below the length
+    of the list included."""
+    import paper_2305_16588_amd as lgp
+    V, most = 9000, (224 << 20) // row_bytes
+    feats = torch.randint(-9, 9, (V, row_bytes // 2), dtype=torch.int16, device="cuda").view(torch.float16)
+    ctx = lgp.Context(torch.zeros(V + 1, dtype=torch.int32, device="cuda"), np.empty(0, np.int32), feats)
+    ctx.set_hotness(np.zeros(V, np.uint32), np.zeros(V, np.uint32))
+    ctx.build_cache(0, V * row_bytes)
+    ids = torch.randint(0, V, (most + 1500,), dtype=torch.int32, device="cuda")
+    out = torch.empty((ids.numel(), row_bytes // 2), dtype=torch.float16, device="cuda")
+    want = feats.view(torch.int16)
+    for n in (ids.numel(), most + 1, most, 900, 0):
+        out.view(torch.int16).fill_(99)
+        ctx.gather_features(ids, n_dev=torch.tensor([n], dtype=torch.int32, device="cuda"), out=out)
+        got = out.view(torch.int16)
+        for lo in range(0, n, 1 << 18):                            # by parts: the reference is as large as the result
+            hi = min(n, lo + (1 << 18))
+            assert torch.equal(got[lo:hi], want[ids[lo:hi].long()]), f"{n} rows"
+        assert bool((got[n:] == 99).all())
+    ctx.check()
