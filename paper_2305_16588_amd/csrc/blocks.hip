@@ -78,16 +78,19 @@ __device__ __forceinline__ int64_t block_exclusive_scan64(int64_t x, int64_t* to
 
 // Index of an ascending list of n ids: block b holds the ids with (id - first) >> shift == b, and one eight-byte load says
 // where they are.  Shift 5: a bit for each of the block's 32 vertices that is in the list and where its ids begin; the
-// position of an id is that plus the bits below its own.  Wider blocks, of lists with fewer ids, hold one to two ids
-// on average and have where they begin and end, for a search (half as many ids per block and twice the index: 23.1 -> 24.4 us
-// a call with 300 k ids in 111 M, 18.9 -> 19.4 with 200 k in 20 M, three hops of 111 M 32.3 -> 33.2).
+// position of an id is that plus the bits below its own.  Wider blocks, of lists with fewer ids, hold one to two ids on
+// average; an entry is four bytes, where its ids begin, the entry after it then says where they end, and a search finds the
+// id.  With both in an entry of eight bytes the index outgrows the L2 cache earlier: calls with 0.55, 0.92, 1.2 and 1.6 M ids in
+// 111 M vertices 33.8 / 54.5 / 73.0 / 96.3 us, now 31.7 / 49.9 / 66.9 / 89.5.  Half as many ids per block (twice the index) is slower up
+// to about 1.5 M ids (the same four 33.5 / 52.4 / 68.6 / 89.0) and ahead beyond (250 M vertices, 2.1 M ids 132.4 / 129.7, 2.8 M
+// 189.6 / 184.1).
 // Only blocks that hold ids are set: the ids looked up are in the list, so the other entries are never read, and a list
 // crowded into parts of the id range costs no more than one spread over it.  Blocks split the span of the list, not the
 // id range, so that a list in one corner has as few ids per block as any (calls, two loads and a search -> now: 2 M
 // destinations x 16 of 20 M vertices, 16 M sources 772 -> 390 us, 400 k sources in one corner 265 -> 181, at both ends 795 ->
-// 181; 1 M x 5 of 111 M 339 -> 295, 85 -> 48, 243 -> 47; 100 k x 10, 1 M sources 55 -> 58, corner 33 -> 23, both ends 48 -> 48).
+// 181; 1 M x 5 of 111 M 339 -> 295, 85 -> 48, 243 -> 47; 100 k x 10, 1 M sources 55 -> 53, corner 33 -> 23, both ends 48 -> 48).
 // A block has 32 vertices or more, so an index fits the table of one entry per vertex.
-struct Entry {
+struct __attribute__((packed, aligned(4))) Entry {             // one load, also at an odd word
   uint32_t start, more;            // first position in the block; bits of its vertices, or the position after its last
 };
 struct Shape {
@@ -95,6 +98,7 @@ struct Shape {
 };
 constexpr int kBitsShift = 5;
 constexpr uint32_t kBitsMaxGap = 64;      // vertices per id up to which a block is 32 vertices (calls are level at 16, 64, 128)
+constexpr int64_t kManyIds = int64_t(1) << 21;   // from here on blocks that need a search hold half as many ids
 __device__ __forceinline__ Shape index_shape(const int32_t* ids, int64_t num_vertices, int64_t n) {
   uint32_t end = n > 0 ? uint32_t(n - 1) : 0;
   asm("" : "+s"(end));                                         // a register of its own: a scalar load
@@ -104,21 +108,22 @@ __device__ __forceinline__ Shape index_shape(const int32_t* ids, int64_t num_ver
     last = int32_t(num_vertices - 1);
   }
   const uint32_t q = uint32_t(last - first) / uint32_t(n > 0 ? n : 1);
-  return Shape{first, last, q < kBitsMaxGap ? kBitsShift : 32 - __clz(int(q))};
+  return Shape{first, last, q < kBitsMaxGap ? kBitsShift : (n < kManyIds ? 32 : 31) - __clz(int(q))};
 }
 
 // Positions of N ids in the list, -1 for u < 0 (for an id that is not in the list: some value, from reads inside it).
 // The searches run in step, so that the loads of all of them are in flight together.
 template <int N>
-__device__ __forceinline__ void positions(const int32_t* ids, int32_t n, const Entry* index, const Shape& sh,
+__device__ __forceinline__ void positions(const int32_t* ids, int32_t n, const uint32_t* index, const Shape& sh,
                                           const int32_t (&u)[N], int32_t (&lo)[N]) {
   Entry e[N];
+  const int entry_words = sh.shift == kBitsShift ? 1 : 0;     // as a power of two
 #pragma unroll
   for (int q = 0; q < N; ++q) {
     const bool ok = u[q] >= sh.first && u[q] <= sh.last;
     uint32_t at = ok ? uint32_t(u[q] - sh.first) >> sh.shift : 0;
     asm("" : "+v"(at));                                        // one load each, which no branch sets apart from the others
-    e[q] = index[at];
+    e[q] = *reinterpret_cast<const Entry*>(index + (size_t(at) << entry_words));
     lo[q] = ok ? int32_t(e[q].start) : -1;
   }
   if (sh.shift == kBitsShift) {
@@ -171,7 +176,7 @@ __device__ __forceinline__ uint32_t wave_inclusive_scan32(uint32_t x) {
 
 // Entries of the blocks whose first id is among the 64 ids from `base` on (one wave; base < n, a multiple of 64).
 // Returns false in a lane that found its id out of order.
-__device__ __forceinline__ bool index_ids(const int32_t* ids, int64_t n, const Shape& sh, int64_t base, Entry* index) {
+__device__ __forceinline__ bool index_ids(const int32_t* ids, int64_t n, const Shape& sh, int64_t base, uint32_t* index) {
   const int lane = threadIdx.x & 63;
   const int64_t k = base + lane;
   const bool in = k < n;
@@ -184,10 +189,10 @@ __device__ __forceinline__ bool index_ids(const int32_t* ids, int64_t n, const S
   const bool ordered = !in || (valid && (k == 0 || (valid_before && before < v)));
   if (sh.shift != kBitsShift) {
     if (leads && valid) {
-      index[block].start = uint32_t(k);
-      if (k > 0 && valid_before) index[block_before].more = uint32_t(k);
+      index[block] = uint32_t(k);
+      if (k > 0 && valid_before) index[block_before + 1] = uint32_t(k);
     }
-    if (k + 1 == n && valid) index[block].more = uint32_t(n);
+    if (k + 1 == n && valid) index[block + 1] = uint32_t(n);
     return ordered;
   }
   // The bits of a block are those of a run of lanes, and of the ids behind the wave where the last run goes on: a block has
@@ -208,7 +213,8 @@ __device__ __forceinline__ bool index_ids(const int32_t* ids, int64_t n, const S
   const uint32_t sum_before = uint32_t(__shfl(int(sum - bit), leader, 64));
   const bool ends = in && (lane == 63 || k + 1 == n || ((lead >> (lane + 1)) & 1ull));
   if (ends && mine && valid)
-    index[block] = Entry{uint32_t(base + leader), sum - sum_before + (lane == 63 ? sum_behind : 0u)};
+    *reinterpret_cast<Entry*>(index + 2 * size_t(block)) =
+        Entry{uint32_t(base + leader), sum - sum_before + (lane == 63 ? sum_behind : 0u)};
   return ordered;
 }
 
@@ -269,7 +275,7 @@ __global__ __launch_bounds__(256) void index_lists_kernel(BlocksArgs a, Ranges r
   if (r <= a.n_hops) {
     const int32_t* ids = a.frontier[r];
     const int64_t n = clamped(a.n_frontier + r, a.cap[r]);
-    Entry* entries = reinterpret_cast<Entry*>(a.table + int64_t(r) * a.table_stride);
+    uint32_t* entries = reinterpret_cast<uint32_t*>(a.table + int64_t(r) * a.table_stride);
     const Shape sh = index_shape(ids, a.num_vertices, n);
     for (int64_t k = int64_t(index) * 256 + (threadIdx.x & 192); k < n; k += int64_t(count) * 256)
       if (!index_ids(ids, n, sh, k, entries)) a.unordered[r] = a.call;      // every writer stores the same value
@@ -327,7 +333,7 @@ __global__ __launch_bounds__(256, 8) void lookup_relabel_kernel(BlocksArgs a, Ra
   int j = h + 1;
   asm("" : "+s"(j));
   const int32_t n_next = int32_t(clamped(a.n_frontier + j, a.cap[j]));
-  const Entry* entries = reinterpret_cast<const Entry*>(a.table + int64_t(h + 1) * a.table_stride);
+  const uint32_t* entries = reinterpret_cast<const uint32_t*>(a.table + int64_t(h + 1) * a.table_stride);
   const Shape sh = index_shape(next, a.num_vertices, n_next);
   const bool ascending = a.unordered[h + 1] != a.call;
   const int64_t* tile_sums = a.tile_sums + a.tile_base[h];

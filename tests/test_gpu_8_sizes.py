@@ -612,3 +612,27 @@ def test_cached_rows_by_lane_groups_of_small_and_large_calls(row_bytes):
             assert torch.equal(got[lo:hi], want[ids[lo:hi].long()]), f"{n} rows"
         assert bool((got[n:] == 99).all())
     ctx.check()
+
+
+@pytest.mark.parametrize("V,n_seeds", [(146_000_000, 230_000), (146_000_000, 200_000), (100_000_000, 230_000)])
+def test_blocks_of_sparse_frontiers_of_millions_of_ids(V, n_seeds):
+    """More and fewer ids than the number from which blocks hold half as many, and a list whose blocks have bits: each
+    position has to lead back to the id that was looked up."""
+    import paper_2305_16588_amd as lgp
+    f, gen = 10, torch.Generator(device="cuda").manual_seed(n_seeds)
+    indptr = torch.full((V + 1,), n_seeds * f, dtype=torch.int32, device="cuda")
+    indptr[:n_seeds + 1] = torch.arange(n_seeds + 1, dtype=torch.int32, device="cuda") * f
+    indices = torch.randint(0, V, (n_seeds * f,), device="cuda", generator=gen, dtype=torch.int32)
+    ctx = lgp.Context(indptr, indices)
+    seeds = torch.arange(n_seeds, dtype=torch.int32, device="cuda")
+    buf = lgp.SampleBuffers(V, n_seeds, (f,), last_frontier=True)
+    blk = lgp.BlockBuffers(buf)
+    ctx.sample_khop(seeds, (f,), 3, out=buf)
+    ctx.build_blocks(seeds, (f,), buf, out=blk)
+    ctx.check()
+    n, sources = buf.n_frontier.tolist()
+    assert n == n_seeds and sources == torch.unique(indices).numel()
+    assert torch.equal(blk.blk_indptr[0], torch.arange(n + 1, dtype=torch.int64, device="cuda") * f)
+    assert torch.equal(buf.frontier[1][blk.blk_src[0].long()], buf.nbr[0].flatten())
+    rows = blk.feat_row[1][:sources].long()
+    assert torch.equal(buf.gather_ids[rows], buf.frontier[1][:sources]) and torch.equal(buf.gather_ids[blk.feat_row[0].long()], seeds)
