@@ -18,7 +18,7 @@ template <int SHIFT, typename VecT, bool RAGGED>
 __global__ __launch_bounds__(256) void hop_and_rows_kernel(HopArgs h, SplitArgs a, uint32_t hop_groups) {
   if (blockIdx.x < a.miss_blocks) split_misses<VecT, RAGGED>(a, blockIdx.x);
   else if (blockIdx.x < a.miss_blocks + hop_groups) sample_hop<SHIFT>(h, blockIdx.x - a.miss_blocks, hop_groups);
-  else split_hits(a, blockIdx.x - a.miss_blocks - hop_groups);
+  else split_hits<HitWalk::kGroups>(a, blockIdx.x - a.miss_blocks - hop_groups, a.hit_blocks);
 }
 
 __global__ __launch_bounds__(256) void begin_listing_kernel(const int32_t* __restrict__ seeds, int64_t n_seeds,

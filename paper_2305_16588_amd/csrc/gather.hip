@@ -120,10 +120,7 @@ __global__ __launch_bounds__(THREADS) void partition_kernel(
 }
 
 // ---- cache hits: HBM -> HBM ------------------------------------------------
-// A wavefront takes 64 list entries and walks their rows as one flat run of chunks:
-// all 64 lanes stay busy for any row width and UNROLL loads per lane are in flight
-// before the first store.  Output rows are written once and not read again by this
-// path, so they are stored non-temporally.
+// Rows as flat runs of chunks (see flat_rows).
 template <typename VecT, bool RAGGED, int UNROLL, bool NT_LOAD>
 __global__ __launch_bounds__(256) void gather_rows_flat_kernel(const char* __restrict__ src, char* __restrict__ dst,
                                                                RowShape shape, uint64_t inv_cpr,
@@ -131,60 +128,7 @@ __global__ __launch_bounds__(256) void gather_rows_flat_kernel(const char* __res
                                                                const int32_t* __restrict__ srcrow, int64_t n_max,
                                                                const int32_t* __restrict__ n_dev, DirectIds dir,
                                                                int epw) {
-  typedef typename Chunk<VecT, RAGGED>::T Mem;
-  int64_t n = n_dev ? int64_t(*n_dev) : n_max;
-  int64_t lo = 0;
-  if (dir.window) {                                 // entries [window[0], window[1]) only
-    lo = dir.window[0] < 0 ? 0 : dir.window[0];
-    n = dir.window[1];
-  }
-  if (n > n_max) n = n_max;
-  if (blockIdx.x == 0) direct_stats(dir, n - lo);
-  const int lane = threadIdx.x & 63;
-  const int64_t wave = (int64_t(blockIdx.x) * 256 + threadIdx.x) >> 6;
-  const int64_t n_waves = int64_t(gridDim.x) * 4;
-  // epw (<= 64) list entries per wave and pass: fewer for wide rows, so that a pass moves a few tens of
-  // KiB and the passes spread evenly over the waves whatever the (device-side) number of entries is
-  for (int64_t e0 = lo + wave * epw; e0 < n; e0 += n_waves * epw) {
-    const int64_t e = e0 + lane;
-    const bool mine = lane < epw && e < n;
-    const int32_t my_row = mine ? (row ? row[e] : int32_t(e)) : 0;
-    const int32_t my_src = direct_source(dir, mine ? (srcrow ? srcrow[e] : int32_t(e)) : 0, mine);
-    const uint32_t entries = uint32_t(n - e0 < epw ? n - e0 : epw);
-    const uint32_t cpr = shape.cpr;
-    const uint32_t total = entries * cpr;          // chunks in this wave's 64 rows
-    for (uint32_t f0 = 0; f0 < total; f0 += 64 * UNROLL) {
-      VecT val[UNROLL];
-      int64_t doff[UNROLL];
-      bool ok[UNROLL];
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u) {
-        const uint32_t flat = f0 + u * 64 + lane;
-        ok[u] = flat < total;
-        const uint32_t k = ok[u] ? uint32_t((uint64_t(flat) * inv_cpr) >> 32) : 0u;   // flat / cpr
-        const uint32_t col = flat - k * cpr;
-        const int32_t r = __shfl(my_row, int(k), 64);
-        const int32_t sr = __shfl(my_src, int(k), 64);
-        ok[u] = ok[u] && sr >= 0;
-        if (RAGGED) {
-          const uint32_t at = chunk_at<VecT, true>(shape, col);
-          doff[u] = int64_t(r) * shape.bytes + at;
-          const Mem* from = reinterpret_cast<const Mem*>(src + (int64_t(sr) * shape.bytes + at));
-          if (ok[u]) val[u] = NT_LOAD ? __builtin_nontemporal_load(from) : *from;
-        } else {                                   // whole chunks: indexes, not bytes (1 % at 256-byte rows)
-          doff[u] = int64_t(r) * cpr + col;
-          const VecT* from = reinterpret_cast<const VecT*>(src);
-          if (ok[u])
-            val[u] = NT_LOAD ? __builtin_nontemporal_load(from + int64_t(sr) * cpr + col) : from[int64_t(sr) * cpr + col];
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < UNROLL; ++u)
-        if (ok[u])
-          __builtin_nontemporal_store(val[u], RAGGED ? reinterpret_cast<Mem*>(dst + doff[u])
-                                                     : reinterpret_cast<Mem*>(reinterpret_cast<VecT*>(dst) + doff[u]));
-    }
-  }
+  flat_rows<VecT, RAGGED, UNROLL, NT_LOAD>(src, dst, shape, inv_cpr, row, srcrow, n_max, n_dev, dir, epw, blockIdx.x, gridDim.x);
 }
 
 // ---- cache misses and cache fill: CPU memory -> HBM over PCIe ---------------
@@ -204,10 +148,25 @@ __global__ __launch_bounds__(256) void gather_rows_group_kernel(const char* __re
   group_rows<VecT, RAGGED, UNROLL, HBM_SOURCE>(src, dst, shape, row, srcrow, n_max, n_dev, dir, G, blockIdx.x, blocks);
 }
 
-template <typename VecT, bool RAGGED>
+// Hits by lane groups, but rows of 2 KiB and more by the flat walk, as in a launch of their own; with six workgroups per CU
+// while the link is the last to finish, and with two where there are 200 hits and more to a miss.  Lane groups / flat with two / with six, at 95, 99, 99.5 and 99.99 % cached: 257 k rows of 1792 bytes 350 / 380 / 330,
+// 200 / 218 / 204, 193 / 204 / 200, 178 / 191 / 195 us a call, of 2048 396 / 434 / 379, 231 / 233 / 222, 225 / 214 / 215, 209 / 198 / 205, of 4096
+// 778 / 849 / 752, 451 / 450 / 431, 437 / 414 / 415, 405 / 390 / 407; 278 k of 3080 718 / 785 / 689, 450 / 449 / 434, 439 / 419 / 422,
+// 417 / 373 / 405 (one launch after the other 954, 495, 438, 388).  Beside a hop (launch_hop_and_rows) lane groups are ahead or
+// level: all rows cached and 4096 seeds of 400 k vertices, 2048 bytes 125 / 152 / 147, 4096 211 / 236 / 227.
+constexpr int64_t kFlatHitBytes = 2048, kNarrowHitsPerMiss = 200;
+template <typename VecT, bool RAGGED, HitWalk W>
 __global__ __launch_bounds__(256) void gather_split_kernel(SplitArgs a) {
   if (blockIdx.x < a.miss_blocks) split_misses<VecT, RAGGED>(a, blockIdx.x);
-  else split_hits(a, blockIdx.x - a.miss_blocks);
+  else {
+    const uint32_t block = blockIdx.x - a.miss_blocks;
+    uint32_t blocks = a.hit_blocks;
+    if (W != HitWalk::kGroups && blocks > a.hit_narrow) {
+      const int64_t hits = int64_t(a.counters[0]) + (a.peers ? a.counters[2] : 0);
+      if (int64_t(a.counters[1]) * kNarrowHitsPerMiss <= hits) blocks = a.hit_narrow;
+    }
+    if (block < blocks) split_hits<W>(a, block, blocks);
+  }
 }
 
 inline unsigned blocks_for(int64_t work_blocks, int64_t limit) {
@@ -231,13 +190,20 @@ void launch_on(const Where& w, K kernel, unsigned blocks, Args... args) {
   else hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, w.s, args...);
 }
 
+inline uint64_t inverse(uint32_t cpr) { return (uint64_t(1) << 32) / cpr + 1; }   // exact for flat < 64 * cpr, cpr <= 4096
+inline int entries_per_wave(const RowShape& r, bool wide) {
+  int epw = 64;
+  while (epw > 4 && int64_t(epw) * r.bytes > (wide ? 8192 : 32768)) epw >>= 1;
+  return epw;
+}
+
 constexpr uint32_t kWideChunks = 160;   // ragged cached rows of more chunks go through the flat kernel (see by_lane_group)
 
 template <typename VecT, bool RAGGED>
 void launch_flat(const DeviceInfo& di, const char* src, char* dst, const RowShape& shape, const int32_t* row,
                  const int32_t* srcrow, int64_t n_max, const int32_t* n_dev, const DirectIds& dir, const Where& s) {
   const int64_t row_bytes = shape.bytes;
-  const uint64_t inv = (uint64_t(1) << 32) / shape.cpr + 1;          // exact for flat < 64 * cpr, cpr <= 4096
+  const uint64_t inv = inverse(shape.cpr);
   // Three workgroups (12 waves) per CU: the flat walk keeps 4 x 16 bytes per lane in flight, and more
   // waves than that only add concurrent streams for the memory system to interleave -- measured hit
   // gather at 8 / 4 / 3 / 2 workgroups per CU: 51.3 / 48.9 / 48.3 / 49.0 us on 505 k 256-byte rows,
@@ -250,8 +216,7 @@ void launch_flat(const DeviceInfo& di, const char* src, char* dst, const RowShap
   // still in L2 when its other part arrives (3080 bytes, 187 k rows: 248 -> 225 us, 4100 bytes, 175 k: 295 -> 281; but
   // 264 bytes, 584 k rows: 61 -> 68).
   const bool wide = RAGGED && shape.cpr > kWideChunks;
-  int epw = 64;
-  while (epw > 4 && int64_t(epw) * row_bytes > (wide ? 8192 : 32768)) epw >>= 1;
+  const int epw = entries_per_wave(shape, wide);
   const unsigned blocks = blocks_for((s.items + 4 * epw - 1) / (4 * epw),
                                      std::min<int64_t>(s.hbm_blocks, int64_t(di.num_cus) * (wide ? 2 : 3)));
   // Rows made of whole 128-byte lines are read once: stream them past L2 (+2.5 % at 512-B and 2-KiB
@@ -451,10 +416,20 @@ bool launch_gather_split(const DeviceInfo& di, const RowSources& r, const void* 
   SplitArgs a;
   const int width = split_args(di, r, hit_src, miss_src, dst, row_bytes, &a);
   if (width == 0) return false;
+  const bool lines = row_bytes % 128 == 0, flat = width == 16 && row_bytes >= kFlatHitBytes;
+  if (flat) {
+    a.hit_inv = inverse(a.hit_shape.cpr);
+    a.hit_epw = entries_per_wave(a.hit_shape, !lines && a.hit_shape.cpr > kWideChunks);
+    a.hit_narrow = uint32_t(di.num_cus) * 2;
+    const int64_t items = (r.grid_items > 0 && r.grid_items < r.n_max) ? r.grid_items : r.n_max;
+    a.hit_blocks = blocks_for((items + 4 * a.hit_epw - 1) / (4 * a.hit_epw), int64_t(di.num_cus) * 6);
+  }
   const dim3 grid{a.miss_blocks + a.hit_blocks}, block{256};
-  if (width == 16) hipLaunchKernelGGL((gather_split_kernel<u32x4, true>), grid, block, 0, s, a);
-  else if (width == 8) hipLaunchKernelGGL((gather_split_kernel<u32x2, false>), grid, block, 0, s, a);
-  else hipLaunchKernelGGL((gather_split_kernel<uint32_t, false>), grid, block, 0, s, a);
+  if (flat && lines) hipLaunchKernelGGL((gather_split_kernel<u32x4, true, HitWalk::kFlatLines>), grid, block, 0, s, a);
+  else if (flat) hipLaunchKernelGGL((gather_split_kernel<u32x4, true, HitWalk::kFlat>), grid, block, 0, s, a);
+  else if (width == 16) hipLaunchKernelGGL((gather_split_kernel<u32x4, true, HitWalk::kGroups>), grid, block, 0, s, a);
+  else if (width == 8) hipLaunchKernelGGL((gather_split_kernel<u32x2, false, HitWalk::kGroups>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((gather_split_kernel<uint32_t, false, HitWalk::kGroups>), grid, block, 0, s, a);
   return true;
 }
 

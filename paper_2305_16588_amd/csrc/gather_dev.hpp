@@ -11,6 +11,9 @@ struct RowShape {
   uint32_t last;   // where the last chunk starts: bytes - size of a chunk
 };
 
+// How hits beside misses are copied: group_rows, or flat_rows, which streams rows of whole lines past L2.
+enum class HitWalk { kGroups, kFlat, kFlatLines };
+
 // Both kinds of rows in one launch (see split_hits, split_misses).
 struct SplitArgs {
   const char* hit_src;
@@ -22,6 +25,9 @@ struct SplitArgs {
   DirectIds direct;
   int64_t n_max;
   uint32_t hit_lanes, miss_lanes, hit_blocks, miss_blocks;     // 0 blocks: no such rows
+  uint64_t hit_inv;           // of flat_rows
+  int32_t hit_epw;
+  uint32_t hit_narrow;        // workgroups that take hits where misses are few
   bool peers;
 };
 
@@ -152,6 +158,74 @@ __device__ __forceinline__ void group_rows(const char* __restrict__ src, char* _
   }
 }
 
+// ---- rows as flat runs of chunks ------------------------------------------------
+// A wavefront takes 64 list entries and walks their rows as one flat run of chunks:
+// all 64 lanes stay busy for any row width and UNROLL loads per lane are in flight
+// before the first store.  Output rows are written once and not read again by this
+// path, so they are stored non-temporally.
+// The caller is workgroup `block` of `blocks` that share the entries.
+template <typename VecT, bool RAGGED, int UNROLL, bool NT_LOAD>
+__device__ __forceinline__ void flat_rows(const char* __restrict__ src, char* __restrict__ dst, const RowShape& shape,
+                                          uint64_t inv_cpr, const int32_t* __restrict__ row,
+                                          const int32_t* __restrict__ srcrow, int64_t n_max,
+                                          const int32_t* __restrict__ n_dev, const DirectIds& dir, int epw, uint32_t block,
+                                          uint32_t blocks) {
+  typedef typename Chunk<VecT, RAGGED>::T Mem;
+  int64_t n = n_dev ? int64_t(*n_dev) : n_max;
+  int64_t lo = 0;
+  if (dir.window) {                                 // entries [window[0], window[1]) only
+    lo = dir.window[0] < 0 ? 0 : dir.window[0];
+    n = dir.window[1];
+  }
+  if (n > n_max) n = n_max;
+  if (block == 0) direct_stats(dir, n - lo);
+  const int lane = threadIdx.x & 63;
+  const int64_t wave = int64_t(block) * 4 + (threadIdx.x >> 6);
+  const int64_t n_waves = int64_t(blocks) * 4;
+  // epw (<= 64) list entries per wave and pass: fewer for wide rows, so that a pass moves a few tens of
+  // KiB and the passes spread evenly over the waves whatever the (device-side) number of entries is
+  for (int64_t e0 = lo + wave * epw; e0 < n; e0 += n_waves * epw) {
+    const int64_t e = e0 + lane;
+    const bool mine = lane < epw && e < n;
+    const int32_t my_row = mine ? (row ? row[e] : int32_t(e)) : 0;
+    const int32_t my_src = direct_source(dir, mine ? (srcrow ? srcrow[e] : int32_t(e)) : 0, mine);
+    const uint32_t entries = uint32_t(n - e0 < epw ? n - e0 : epw);
+    const uint32_t cpr = shape.cpr;
+    const uint32_t total = entries * cpr;          // chunks in this wave's 64 rows
+    for (uint32_t f0 = 0; f0 < total; f0 += 64 * UNROLL) {
+      VecT val[UNROLL];
+      int64_t doff[UNROLL];
+      bool ok[UNROLL];
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u) {
+        const uint32_t flat = f0 + u * 64 + lane;
+        ok[u] = flat < total;
+        const uint32_t k = ok[u] ? uint32_t((uint64_t(flat) * inv_cpr) >> 32) : 0u;   // flat / cpr
+        const uint32_t col = flat - k * cpr;
+        const int32_t r = __shfl(my_row, int(k), 64);
+        const int32_t sr = __shfl(my_src, int(k), 64);
+        ok[u] = ok[u] && sr >= 0;
+        if (RAGGED) {
+          const uint32_t at = chunk_at<VecT, true>(shape, col);
+          doff[u] = int64_t(r) * shape.bytes + at;
+          const Mem* from = reinterpret_cast<const Mem*>(src + (int64_t(sr) * shape.bytes + at));
+          if (ok[u]) val[u] = NT_LOAD ? __builtin_nontemporal_load(from) : *from;
+        } else {                                   // whole chunks: indexes, not bytes (1 % at 256-byte rows)
+          doff[u] = int64_t(r) * cpr + col;
+          const VecT* from = reinterpret_cast<const VecT*>(src);
+          if (ok[u])
+            val[u] = NT_LOAD ? __builtin_nontemporal_load(from + int64_t(sr) * cpr + col) : from[int64_t(sr) * cpr + col];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < UNROLL; ++u)
+        if (ok[u])
+          __builtin_nontemporal_store(val[u], RAGGED ? reinterpret_cast<Mem*>(dst + doff[u])
+                                                     : reinterpret_cast<Mem*>(reinterpret_cast<VecT*>(dst) + doff[u]));
+    }
+  }
+}
+
 // ---- hits and misses in one launch --------------------------------------------
 // The two lists of a partition (three for a clique member: list 2 is a second list of rows in HBM), or the caller's list of
 // ids where all rows have the same source.  One after the other,
@@ -167,13 +241,20 @@ __device__ __forceinline__ void split_misses(const SplitArgs& a, uint32_t block)
                                                     a.counters ? a.counters + 1 : nullptr, a.direct, a.miss_lanes, block,
                                                     a.miss_blocks);
 }
-// Called by workgroup `block` of a.hit_blocks.
-__device__ __forceinline__ void split_hits(const SplitArgs& a, uint32_t block) {
-  for (int l = 0; l <= (a.peers ? 2 : 0); l += 2)
-    group_rows<u32x4, true, kSplitHitUnroll, true>(a.hit_src, a.dst, a.hit_shape, l ? a.lists.row[2] : a.lists.row[0],
-                                                   l ? a.lists.src[2] : a.lists.src[0], a.n_max,
-                                                   a.counters ? a.counters + l : nullptr, a.direct, a.hit_lanes, block,
-                                                   a.hit_blocks);
+// Called by workgroup `block` of `blocks`.
+template <HitWalk W>
+__device__ __forceinline__ void split_hits(const SplitArgs& a, uint32_t block, uint32_t blocks) {
+  for (int l = 0; l <= (a.peers ? 2 : 0); l += 2) {
+    const int32_t* const row = l ? a.lists.row[2] : a.lists.row[0];
+    const int32_t* const src = l ? a.lists.src[2] : a.lists.src[0];
+    const int32_t* const n = a.counters ? a.counters + l : nullptr;
+    if constexpr (W == HitWalk::kGroups)
+      group_rows<u32x4, true, kSplitHitUnroll, true>(a.hit_src, a.dst, a.hit_shape, row, src, a.n_max, n, a.direct, a.hit_lanes,
+                                                     block, blocks);
+    else
+      flat_rows<u32x4, true, 4, W == HitWalk::kFlatLines>(a.hit_src, a.dst, a.hit_shape, a.hit_inv, row, src, a.n_max, n,
+                                                          a.direct, a.hit_epw, block, blocks);
+  }
 }
 
 }  // namespace

@@ -636,3 +636,34 @@ def test_blocks_of_sparse_frontiers_of_millions_of_ids(V, n_seeds):
     assert torch.equal(buf.frontier[1][blk.blk_src[0].long()], buf.nbr[0].flatten())
     rows = blk.feat_row[1][:sources].long()
     assert torch.equal(buf.gather_ids[rows], buf.frontier[1][:sources]) and torch.equal(buf.gather_ids[blk.feat_row[0].long()], seeds)
+
+
+@pytest.mark.parametrize("row_bytes,skew", [(2046, 0), (2048, 0), (2048, 2), (2050, 2), (2570, 0), (4096, 4), (16_384, 0)])
+def test_wide_rows_from_both_sources(row_bytes, skew):
+    """Rows around the width from which hits beside misses are walked as runs of chunks, of whole lines and ragged, written
+    to any even address; few misses, for which fewer workgroups take the hits, many, none and only misses, in lists of
+    hardly any rows and of several passes."""
+    import paper_2305_16588_amd as lgp
+    V, dim = 40_000 if row_bytes < 4096 else 10_000, row_bytes // 2
+    rng = np.random.default_rng(row_bytes + skew)
+    feats = lgp.pinned_empty((V, dim), np.float16)
+    feats.view(np.int16)[:] = np.arange(dim, dtype=np.int16) * np.int16(3) + np.arange(V, dtype=np.int32)[:, None].astype(np.int16)
+    want = torch.from_numpy(feats.view(np.int16)).cuda()
+    ctx = lgp.Context(lgp.pinned_copy(np.zeros(V + 1, np.int32)), np.empty(0, np.int32), feats)
+    ctx.set_hotness(np.zeros(V, np.uint32), rng.permutation(V).astype(np.uint32))
+    room = torch.empty(V * dim + 8, dtype=torch.int16, device="cuda")
+    for n_cached in (1, V // 2, V - 60, V - 1):
+        ctx.build_cache(0, n_cached * row_bytes)
+        cached = np.zeros(V, bool)
+        cached[ctx.get_cache(contents=False)[3]] = True
+        everything = rng.permutation(V).astype(np.int32)
+        for ids in (everything if n_cached > V // 2 else everything[:3000], everything[:5], everything[:0],
+                    np.flatnonzero(cached)[:700].astype(np.int32), np.flatnonzero(~cached)[:700].astype(np.int32)):
+            room.fill_(99)
+            out = room[skew // 2:skew // 2 + ids.size * dim].view(ids.size, dim)
+            stats = torch.full((2,), -1, dtype=torch.int32, device="cuda")
+            ctx.gather_features(torch.from_numpy(ids).cuda(), out=out.view(torch.float16), stats=stats)
+            assert torch.equal(out, want[torch.from_numpy(ids).cuda().long()]), f"{n_cached} cached, {ids.size} ids"
+            assert bool((room[skew // 2 + ids.size * dim:] == 99).all()) and bool((room[:skew // 2] == 99).all())
+            assert stats.tolist() == [int(cached[ids].sum()), int((~cached[ids]).sum())]
+    ctx.check()
