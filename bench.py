@@ -192,21 +192,40 @@ def measure(inp: Inputs, steps: int, warmup: int, reps: int, topo_frac=None, fea
         b.copy_(a)
         torch.cuda.synchronize()
         del a, b
-    # Timed regions: R x K steps, HIP events only on the two row gathers (hits: the kernel of `roofline`; misses:
-    # `roofline_pcie`), which those launches record themselves.  The full breakdown of `per_step` and the sampler's
-    # work counts come from an untimed pass over the first region's K steps with events around every kernel group.
-    ctx.set_profiling(2)
+    # Timed regions: R x K steps, made exactly as a caller makes them.  Kernel times come from untimed passes over steps
+    # of those regions: with events on the two row gathers (hits: the kernel of `roofline`; misses: `roofline_pcie`),
+    # which then run one after the other, where the timed calls copy hits and misses in one launch; with events around
+    # every kernel group (`per_step`, the sampler); and with events around gather_features as the timed calls make it
+    # (`roofline_both`).
     if reps <= 0:                                       # auto: at least 0.5 s of timed work, at least 5 regions
         probe = timed_regions(step, warmup, steps, 1)[0]
         reps = max(5, min(400, int(0.5 / max(probe, 1e-6)) + 1))
-        ctx.get_profile()                               # the probe region's events are not part of the figures
         if warmup + reps * steps > stats.shape[0]:
             stats = torch.zeros((warmup + reps * steps, 2), dtype=torch.int32, device="cuda")
             for i in range(warmup):                     # `step` writes into the new tensor from here on
                 step(i)
             torch.cuda.synchronize()
     regions = timed_regions(step, warmup, steps, reps)
+    ctx.check()
+    n_prof = steps * min(reps, 5)
+    ctx.set_profiling(2)
+    for i in range(warmup, warmup + n_prof):
+        step(i)
+    torch.cuda.synchronize()
     prof_g = ctx.get_profile()
+    ctx.set_profiling(0)
+    both = 0 < plan.n_feat < V and not overlap
+    ms_both = 0.0                          # gather_features with hits and misses, sum over n_prof steps
+    if both:
+        ev = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)) for _ in range(n_prof)]
+        for k, (e0, e1) in enumerate(ev):
+            i = warmup + k
+            ctx.sample_khop(inp.seeds(i), spec.fanouts, step_seed(spec, i), out=buf)
+            e0.record()
+            ctx.gather_features(buf.gather_ids, n_dev=buf.n_gather, out=rows, stats=stats[i])
+            e1.record()
+        torch.cuda.synchronize()
+        ms_both = sum(e0.elapsed_time(e1) for e0, e1 in ev)
     ctx.check()
     ctx.set_profiling(1)
     n_front = np.zeros(L, np.int64)        # frontier vertices expanded per hop, summed over the K steps
@@ -233,6 +252,7 @@ def measure(inp: Inputs, steps: int, warmup: int, reps: int, topo_frac=None, fea
     st = stats[warmup:].cpu().numpy().astype(np.int64)
     hit_rows, miss_rows = int(st[:, 0].sum()), int(st[:, 1].sum())
     gathered = hit_rows + miss_rows
+    prof_hits, prof_misses = int(st[:n_prof, 0].sum()), int(st[:n_prof, 1].sum())      # of the steps of prof_g
     shape_key = (f"{inp.spec.name}@B{cache_bytes}" if cache_bytes
                  else f"{inp.spec.name}@topo{spec.topo_frac:g},feat{spec.feat_frac:g}")
     prof_rec, prof_why = measured_traffic(shape_key)
@@ -247,32 +267,47 @@ def measure(inp: Inputs, steps: int, warmup: int, reps: int, topo_frac=None, fea
                   else f"gather_rows_flat_kernel<u32x4, false, 4, {'true' if row_bytes % 128 == 0 else 'false'}>")
     miss_kernel = f"gather_rows_group_kernel<u32x4, false, {grp}, 4, false>"
     roofline = None
-    if prof_g.n_hit and hit_rows:
-        ach = hit_rows * hit_bytes_per_row / (prof_g.ms_hit * 1e-3) / 1e9
+    if prof_g.n_hit and prof_hits:
+        ach = prof_hits * hit_bytes_per_row / (prof_g.ms_hit * 1e-3) / 1e9
         per_row = (prof_rec or {}).get("hit_gather_hbm_bytes_per_row")
         roofline = {"bound": "hbm", "kernel": hit_kernel + " (cache hits, HBM->HBM)", "achieved": round(ach, 1),
                     "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 4),
-                    "traffic": round(per_row * hit_rows / prof_g.n_hit) if per_row else None,
+                    "traffic": round(per_row * prof_hits / prof_g.n_hit) if per_row else None,
                     "traffic_source": (prof_rec or {}).get("source") if per_row else prof_why or "no hit-gather figure",
                     "avg_launch_ms": round(prof_g.ms_hit / prof_g.n_hit, 4),
-                    "rows_per_launch": round(hit_rows / prof_g.n_hit, 1), "bytes_per_row": hit_bytes_per_row}
+                    "rows_per_launch": round(prof_hits / prof_g.n_hit, 1), "bytes_per_row": hit_bytes_per_row}
+    # hits and misses of a call in one launch (rows of 16 bytes and more), with the partition before it
+    roofline_both = None
+    if both and prof_misses:
+        ach = prof_misses * row_bytes / (ms_both * 1e-3) / 1e9
+        roofline_both = {"bound": "pcie", "kernel": "lgp_gather_features (partition_kernel, gather_split_kernel)",
+                         "achieved": round(ach, 2), "peak": PCIE_PEAK_GBS, "unit": "GB/s",
+                         "frac": round(ach / PCIE_PEAK_GBS, 4), "avg_call_ms": round(ms_both / n_prof, 4),
+                         "hits_per_call": round(prof_hits / n_prof, 1), "misses_per_call": round(prof_misses / n_prof, 1)}
     roofline_pcie = None
-    if prof_g.n_miss and miss_rows:
-        ach = miss_rows * row_bytes / (prof_g.ms_miss * 1e-3) / 1e9
+    if prof_g.n_miss and prof_misses:
+        ach = prof_misses * row_bytes / (prof_g.ms_miss * 1e-3) / 1e9
         roofline_pcie = {"bound": "pcie", "kernel": miss_kernel + " (cache misses, CPU memory->HBM)",
                          "achieved": round(ach, 2), "peak": PCIE_PEAK_GBS, "unit": "GB/s",
                          "frac": round(ach / PCIE_PEAK_GBS, 4), "avg_launch_ms": round(prof_g.ms_miss / prof_g.n_miss, 4),
-                         "rows_per_launch": round(miss_rows / prof_g.n_miss, 1), "bytes_per_row": row_bytes}
+                         "rows_per_launch": round(prof_misses / prof_g.n_miss, 1), "bytes_per_row": row_bytes}
     # The sampler (whole lgp_sample_khop call: hop kernels + dedup compactions).  Algorithmic bytes per call:
     # per expanded vertex its id (4), its row-table entry (8) and the sampled column ids (4 each) are read, its
     # nbr row (4 f) and cnt (4) written; every sample marks its vertex in a dedup map (not counted as bytes); each of
     # the L compactions reads its map once and writes its id list (4 per id).  A map holds a word, a half-word or a byte
-    # per vertex, marked with a plain store, on graphs of up to 2^19, 2^20 and 2^23 vertices, and a bit set with an
-    # atomic beyond.
+    # per vertex, marked with a plain store, on graphs of up to 2^19, 2^20 and 2^23 vertices (and a byte up to 2^24 for
+    # calls whose seeds, mean degree and fan-outs promise a mark for 0.4 of the vertices), and a bit set with an atomic
+    # otherwise.
     roofline_sampler = None
     if prof.n_sample:
         f = np.asarray(spec.fanouts, np.int64)
         bits = 32 if V <= 1 << 19 else 16 if V <= 1 << 20 else 8 if V <= 1 << 23 else 1
+        if 1 << 23 < V <= 1 << 24:
+            n, expected = float(spec.batch), 0.0
+            for fan in spec.fanouts:
+                expected += n * min(E / V, fan)
+                n = V * -np.expm1(-n * min(E / V, fan) / V)
+            bits = 8 if expected >= 0.4 * V else 1
         marks = float(n_edges.sum()) / steps + spec.batch
         sampler_bytes = int((n_front * (4 + 8 + 4 + 4 * f)).sum() + 4 * n_edges.sum() + 4 * n_lists) + steps * L * (V * bits // 8)
         ms_call = prof.ms_sample / prof.n_sample
@@ -300,7 +335,7 @@ def measure(inp: Inputs, steps: int, warmup: int, reps: int, topo_frac=None, fea
                                   if inp.on_device else ""),
                    "cached_topo_rows": plan.n_topo, "cached_feat_rows": plan.n_feat, "cache_plan": auto_plan,
                    "batches_in_tablet": inp.n_batches},
-        "roofline": roofline, "roofline_pcie": roofline_pcie, "roofline_sampler": roofline_sampler,
+        "roofline": roofline, "roofline_pcie": roofline_pcie, "roofline_both": roofline_both, "roofline_sampler": roofline_sampler,
         "per_step": {"gather_rows": round(gathered / n_steps, 1), "hit_rate": round(hit_rows / max(gathered, 1), 4),
                      "ms_sample": round(prof.ms_sample / max(prof.n_sample, 1), 4),
                      "ms_partition": round(prof.ms_partition / max(prof.n_partition, 1), 4),
@@ -353,9 +388,8 @@ def secondary_figures(inp, spec, plan, buf, rows, stats, steps, warmup, ms_per_s
         ctx.check()
         return {"value": round(steps * spec.batch / t, 1), "unit": "seeds/s", "ms_per_step": round(t * 1e3 / steps, 4)}
 
-    # the library's hit / miss overlap (the miss gather on a stream of its own beside a narrower hit gather):
-    # faster whenever both gathers have work, but the hit gather's own duration then says nothing about the
-    # kernel, so the headline and the rooflines stay with overlap off
+    # the library's hit / miss overlap (the miss gather on a stream of its own beside a narrower hit gather), against
+    # the headline, whose calls copy both kinds of rows in one launch; the pipelines below run with whichever is faster
     overlapped = None
     if not overlap and 0 < plan.n_feat < V:
         ctx.set_overlap(True)
@@ -681,6 +715,7 @@ def main() -> int:
             "share is the largest single-GPU workload of the five (250 M vertices, 8 B edges); the others are "
             "under `configs`" if head_spec.name == "share" else "chosen with --workload")),
         "roofline": head["roofline"], "roofline_pcie": head["roofline_pcie"],
+        "roofline_both": head["roofline_both"],
         "roofline_sampler": head["roofline_sampler"], "cpu_baseline": cpu, "cpu_baseline_all_cores": cpu_all,
         "per_step": head["per_step"], "setup_s": head["setup_s"],
     }

@@ -234,8 +234,8 @@ int lgp_get_clique_plan(lgp_ctx* ctx, int32_t member, lgp_cache_plan* plan);
 
 /* Feature extraction as member `member` of the clique sees it: like lgp_gather_features, but
  * the ids are split three ways -- rows in the member's own cache, rows in a peer's cache (both
- * HBM reads here, gathered by separate launches) and rows in no cache (read in place from CPU
- * memory).  stats [device int32[3], may be NULL] receives {n_local, n_miss, n_peer}.
+ * HBM reads here) and rows in no cache (read in place from CPU memory) -- and copied in one launch
+ * where lgp_gather_features does so, else in three.  stats [device int32[3], may be NULL] receives {n_local, n_miss, n_peer}.
  * LGP_ESTATE without a clique cache. */
 int lgp_gather_features_clique(lgp_ctx* ctx, int32_t member, const int32_t* ids, int64_t n_max, const int32_t* n_dev,
                                void* out, int32_t* stats, void* stream);
@@ -333,8 +333,8 @@ int lgp_gather_features_static(lgp_ctx* ctx, const int32_t* ids, int64_t n_max, 
  * beside PCIe reads that are queued ahead of it, so per-kernel timings are only meaningful with overlap off,
  * which is the default.  A process has a few hardware queues (four by default) and HIP
  * spreads streams over them: if the library's stream and `stream` happen to share one, the
- * result is the same but the two gathers run one after the other.  The same holds for
- * lgp_sample_extract's stream. */
+ * result is the same but the two gathers run one after the other.  lgp_sample_extract then copies a
+ * group's rows before it samples the next hop, not beside it. */
 int lgp_set_overlap(lgp_ctx* ctx, int enable);
 
 /* HBM the library holds or will allocate on its own for calls of one shape, in bytes, so that a
@@ -372,7 +372,9 @@ int lgp_check(lgp_ctx* ctx, void* stream);
  * (hits, misses).  The gather launches record their own start and stop times; the groups
  * of several launches (sampling, partition) are bracketed by two recorded events, each of
  * which costs a few microseconds of stream time -- visible in steps that take a fraction of
- * a millisecond, hence mode 2.  Keep profiling off while calls are captured into a HIP
+ * a millisecond, hence mode 2.  In either mode hits and misses are copied in launches of their own, one after
+ * the other, and lgp_sample_extract runs its steps one after the other: the time of a step as it is made
+ * with profiling off is to be measured with profiling off.  Keep profiling off while calls are captured into a HIP
  * graph: timed launches are not capturable.  lgp_get_profile waits for the recorded events, adds
  * them up and resets. */
 int lgp_set_profiling(lgp_ctx* ctx, int mode);

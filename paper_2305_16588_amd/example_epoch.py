@@ -6,7 +6,7 @@ Shows the call sequence a training loop would use: pre-sampling, automatic split
 cache budget between topology and features, cache build, then per batch: epoch shuffle,
 k-hop sampling, graph construction and feature extraction on three streams -- the graph
 constructor beside the feature extractor of the same batch, the sampling of the next batch
-beside both -- with the miss gather overlapping the hit gather.  The feature matrix and
+beside both -- with the misses of a batch copied beside its hits.  The feature matrix and
 the per-hop blocks of every batch are what a GNN layer stack would consume.
 """
 from __future__ import annotations
@@ -47,7 +47,6 @@ def main() -> None:
     print(f"cache plan: alpha = {best / 100:.2f} -> {plan.n_topo} topology rows ({plan.topo_bytes / 1e6:.0f} MB), "
           f"{plan.n_feat} feature rows ({plan.feat_bytes / 1e6:.0f} MB)")
 
-    ctx.set_overlap(0 < plan.n_feat < spec.num_vertices)        # both gathers have work: run them side by side
     n_batches = tablet.numel() // spec.batch
     # streams that share a hardware queue would run one after the other, so pick three that do not
     (s_sample, s_gather, s_blocks), _ = lgp.concurrent_streams(3)
