@@ -296,18 +296,19 @@ def measure(inp: Inputs, steps: int, warmup: int, reps: int, topo_frac=None, fea
     # nbr row (4 f) and cnt (4) written; every sample marks its vertex in a dedup map (not counted as bytes); each of
     # the L compactions reads its map once and writes its id list (4 per id).  A map holds a word, a half-word or a byte
     # per vertex, marked with a plain store, on graphs of up to 2^19, 2^20 and 2^23 vertices (and a byte up to 2^24 for
-    # calls whose seeds, mean degree and fan-outs promise a mark for 0.4 of the vertices), and a bit set with an atomic
+    # calls whose seeds, degrees and fan-outs promise a mark for 0.04 of the vertices), and a bit set with an atomic
     # otherwise.
     roofline_sampler = None
     if prof.n_sample:
         f = np.asarray(spec.fanouts, np.int64)
         bits = 32 if V <= 1 << 19 else 16 if V <= 1 << 20 else 8 if V <= 1 << 23 else 1
         if 1 << 23 < V <= 1 << 24:
-            n, expected = float(spec.batch), 0.0
+            degrees, n, expected = np.diff(inp.indptr), float(spec.batch), 0.0
             for fan in spec.fanouts:
-                expected += n * min(E / V, fan)
-                n = V * -np.expm1(-n * min(E / V, fan) / V)
-            bits = 8 if expected >= 0.4 * V else 1
+                sampled = n * float(np.minimum(degrees, fan).mean())
+                expected += sampled
+                n = V * -np.expm1(-sampled / V)
+            bits = 8 if expected >= 0.04 * V else 1
         marks = float(n_edges.sum()) / steps + spec.batch
         sampler_bytes = int((n_front * (4 + 8 + 4 + 4 * f)).sum() + 4 * n_edges.sum() + 4 * n_lists) + steps * L * (V * bits // 8)
         ms_call = prof.ms_sample / prof.n_sample

@@ -62,6 +62,7 @@ struct lgp_ctx {
   DedupMaps maps;              // frontier and gather-set dedup maps
   bool either_map = false;     // a call may lay the maps out as bytes instead (kEitherMapMaxVertices), with this geometry
   MapGeom byte_geom;
+  std::vector<double> mean_samples;   // with either_map, [f]: samples of a vertex at fan-out f, mean over the graph
   uint32_t* d_err = nullptr;
   int32_t* counters = nullptr;  // {n_hit, n_miss, n_peer}
 
@@ -256,19 +257,44 @@ size_t map_words(const lgp_ctx* c) {
   return size_t(c->either_map ? std::max(c->maps.geom.words(), c->byte_geom.words()) : c->maps.geom.words());
 }
 
-// Marks of a mini-batch on a graph whose vertices all have the mean degree and are equally popular: more than where
-// popularity and degrees are skewed.  *rows, if given: vertices expanded.
-double expected_marks(const lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts, int32_t n_hops, double* rows = nullptr) {
-  const double V = double(c->g.num_vertices), degree = double(c->g.num_edges) / V;
+// Marks of a mini-batch on a graph whose vertices are equally popular: more than where popularity is skewed.  samples(f): of a
+// vertex at fan-out f.  *rows, if given: vertices expanded.
+template <typename Samples>
+double expected_marks(const lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts, int32_t n_hops, Samples samples,
+                      double* rows = nullptr) {
+  const double V = double(c->g.num_vertices);
   double n = double(n_seeds), marks = 0;
   if (rows) *rows = 0;
   for (int h = 0; h < n_hops; ++h) {
     if (rows) *rows += n;
-    const double m = n * std::min(degree, double(fanouts[h]));
+    const double m = n * samples(fanouts[h]);
     marks += m;
     n = V * -std::expm1(-m / V);
   }
   return marks;
+}
+
+// Whether the sampler lays the maps out as bytes for a mini-batch.
+bool marks_bytes(const lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts, int32_t n_hops) {
+  return c->either_map && expected_marks(c, n_seeds, fanouts, n_hops, [&](int32_t f) { return c->mean_samples[size_t(f)]; }) >=
+                              kByteMarksPerVertex * double(c->g.num_vertices);
+}
+
+// mean_samples, once the row table is there; counts in a hotness vector, which is all zero before and after.  Synchronous.
+hipError_t count_samples(lgp_ctx* c) {
+  uint32_t host[LGP_MAX_FANOUT + 1];
+  launch_count_degrees(c->di, c->row_tab, c->g.num_vertices, c->topo_hot, nullptr);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = hipMemcpy(host, c->topo_hot, sizeof(host), hipMemcpyDeviceToHost);
+  if (e == hipSuccess) e = hipMemset(c->topo_hot, 0, sizeof(host));
+  if (e != hipSuccess) return e;
+  c->mean_samples.assign(LGP_MAX_FANOUT + 1, 0.0);
+  double more = double(c->g.num_vertices);            // vertices of degree f and more
+  for (int f = 1; f <= LGP_MAX_FANOUT; ++f) {
+    more -= double(host[f - 1]);
+    c->mean_samples[size_t(f)] = c->mean_samples[size_t(f - 1)] + more / double(c->g.num_vertices);
+  }
+  return hipSuccess;
 }
 
 // Sampling of one mini-batch; out == nullptr is the pre-sampling mode (hotness only), for which `staged` may hold the
@@ -281,8 +307,7 @@ int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t
   const bool want_last = !hot_mode && out->frontier[n_hops] != nullptr;
   DeviceInfo di = c->di;
   DedupMaps maps = c->maps;
-  if (c->either_map && expected_marks(c, n_seeds, fanouts, n_hops) >=
-                                     (want_last ? kByteMarksPerVertexBoth : kByteMarksPerVertex) * double(V)) {
+  if (marks_bytes(c, n_seeds, fanouts, n_hops)) {
     di.spread_shift = 3;
     maps.geom = c->byte_geom;
   }
@@ -559,7 +584,8 @@ double stage_saving(const lgp_ctx* c, double rows, int64_t remaining) {   // byt
 bool may_stage(const lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts, int32_t n_hops, int64_t n_batches, hipStream_t s) {
   if (!c->indices_on_host || c->reserved || c->plan.n_topo > 0 || n_batches < 2) return false;
   double rows = 0;
-  expected_marks(c, n_seeds, fanouts, n_hops, &rows);
+  const double degree = double(c->g.num_edges) / double(c->g.num_vertices);
+  expected_marks(c, n_seeds, fanouts, n_hops, [&](int32_t f) { return std::min(degree, double(f)); }, &rows);
   if (stage_saving(c, 0.5 * rows, n_batches - 1) < kStageSaving) return false;
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
   size_t free_bytes = 0, total_bytes = 0;
@@ -720,6 +746,7 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
     launch_init_row_table(c->di, c->g.indptr, c->g.indptr_bytes, V, c->row_tab, nullptr);
     e = hipGetLastError();
   }
+  if (e == hipSuccess && c->either_map) e = count_samples(c);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     (void)hipGetLastError();

@@ -177,6 +177,20 @@ __global__ void init_row_table_kernel(const IdxT* __restrict__ indptr, int64_t n
   }
 }
 
+__global__ __launch_bounds__(256) void count_degrees_kernel(const uint64_t* __restrict__ row_tab, int64_t num_vertices,
+                                                            uint32_t* __restrict__ counts) {
+  __shared__ uint32_t mine[LGP_MAX_FANOUT + 1];
+  for (int k = threadIdx.x; k <= LGP_MAX_FANOUT; k += 256) mine[k] = 0;
+  __syncthreads();
+  for (int64_t v = int64_t(blockIdx.x) * 256 + threadIdx.x; v < num_vertices; v += int64_t(gridDim.x) * 256) {
+    const uint32_t d = uint32_t(row_tab[v]) & kRowDegOverflow;
+    atomicAdd(&mine[d < LGP_MAX_FANOUT ? d : LGP_MAX_FANOUT], 1u);
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k <= LGP_MAX_FANOUT; k += 256)
+    if (mine[k]) atomicAdd(&counts[k], mine[k]);
+}
+
 __global__ void set_cached_rows_kernel(const int32_t* __restrict__ order, int64_t n_topo,
                                        const int64_t* __restrict__ t_indptr, uint64_t* __restrict__ row_tab) {
   for (int64_t r = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; r < n_topo; r += int64_t(gridDim.x) * blockDim.x) {
@@ -370,6 +384,10 @@ void launch_init_row_table(const DeviceInfo& di, const void* h_indptr, int32_t i
   else
     hipLaunchKernelGGL(init_row_table_kernel<int32_t>, dim3(grid_for(di, num_vertices)), dim3(256), 0, s,
                        static_cast<const int32_t*>(h_indptr), num_vertices, row_tab);
+}
+
+void launch_count_degrees(const DeviceInfo& di, const uint64_t* row_tab, int64_t num_vertices, uint32_t* counts, hipStream_t s) {
+  hipLaunchKernelGGL(count_degrees_kernel, dim3(grid_for(di, num_vertices)), dim3(256), 0, s, row_tab, num_vertices, counts);
 }
 
 void launch_set_cached_rows(const DeviceInfo& di, const int32_t* order, int64_t n_topo, const int64_t* t_indptr,

@@ -32,15 +32,15 @@ enum : uint32_t { ERR_BAD_ID = 1u, ERR_OVERRUN = 2u };
 constexpr int64_t kWordMapMaxVertices = int64_t(1) << 19;
 constexpr int64_t kHalfMapMaxVertices = int64_t(1) << 20;
 constexpr int64_t kByteMapMaxVertices = int64_t(1) << 23;
-// Up to twice as many vertices the layout is chosen per call (both maps are clear between calls): a compaction has 1 to 2.4
-// us more to scan, and many marks earn that back.  8192 / 4096 / 2048 seeds (15, 10, 5), bits -> bytes: 8.5 M vertices of mean
-// degree 25 91 -> 60, 61 -> 46, 43 -> 38 us; 16.5 M 90 -> 69, 60 -> 51, 42 -> 41; 12 M of degree 12 44 -> 42, 33 -> 34, 27 -> 30;
-// one hop of 25 10.7 -> 11.7.  Compactions of both maps at once scan twice: with the last frontier wanted 158 -> 139, 167 -> 161
-// and 82 -> 83 us a step with blocks and rows.  The expected marks (expected_marks) of these calls are 0.83, 0.43, 0.22; 0.44,
-// 0.22, 0.11; 0.48, 0.25, 0.12 per vertex, too high by more where degrees are small beside the fan-out, so the line is drawn where
-// no call measured loses.
+// Up to twice as many vertices the layout is chosen per call of the sampler (both maps are clear between calls; the pipeline
+// inside a batch always marks bits): a compaction has 1 to 2.4 us more to scan, and many marks earn that back.  Bits -> bytes,
+// 8192 seeds (15, 10, 5), and expected marks per vertex (expected_marks with the graph's own degrees): 8.5 M vertices of power-law
+// degrees, mean 25, 91 -> 60 us, 0.18; 12 M, mean 12, 43.9 -> 42.3 and with the last frontier, which scans two maps at once, 46.0 ->
+// 46.0, 0.053; 12 M of which a quarter own 40 edges per vertex 32.9 -> 38.1 and 34.8 -> 41.3, 0.017; 9 M of which 2 % own them 23.4 ->
+// 24.4, below 0.001.  Of 480 calls on such graphs none that lies beyond the line is slower in bytes.  The mean degree alone cannot
+// tell: by it the last two lie beyond the second (0.60, 0.78; 0.48).
 constexpr int64_t kEitherMapMaxVertices = int64_t(1) << 24;
-constexpr double kByteMarksPerVertex = 0.4, kByteMarksPerVertexBoth = 0.5;
+constexpr double kByteMarksPerVertex = 0.04;
 inline int mark_shift(int64_t num_vertices) {
   return num_vertices <= kWordMapMaxVertices ? 5 : num_vertices <= kHalfMapMaxVertices ? 4
          : num_vertices <= kByteMapMaxVertices ? 3 : 0;
@@ -301,6 +301,8 @@ hipError_t shuffle_by_key(const DeviceInfo& di, const int32_t* in, int32_t* out,
 hipError_t cslp_rank(const DeviceInfo& di, int32_t k_g, int64_t num_vertices, const uint32_t* hot, uint64_t* acc,
                      int32_t* order, int32_t* owner, int32_t* queues, unsigned long long* counts, hipStream_t s);
 // row_tab[v] = (not cached, CPU offset, degree) for every vertex, streamed from the CPU-resident offsets.
+// counts[k] += vertices of degree k, counts[LGP_MAX_FANOUT] += those of that degree and more.
+void launch_count_degrees(const DeviceInfo& di, const uint64_t* row_tab, int64_t num_vertices, uint32_t* counts, hipStream_t s);
 void launch_init_row_table(const DeviceInfo& di, const void* h_indptr, int32_t indptr_bytes, int64_t num_vertices,
                            uint64_t* row_tab, hipStream_t s);
 // row_tab[order[r]] = (cached, t_indptr[r], degree) for r < n_topo (rows too long to pack keep their CPU entry).

@@ -494,8 +494,8 @@ def test_blocks_of_evenly_spaced_frontiers(gap, n):
 
 @pytest.mark.parametrize("V", [(1 << 23) + 1, 1 << 24, (1 << 24) + 1])
 def test_maps_laid_out_per_call(V):
-    """Calls of many marks and of few in turn on one context, whose maps take both layouts where the graph is between the
-    limits: every kind of compaction, and pre-sampling."""
+    """Calls of many marks and of few in turn on graphs around the limits between which maps have room for both layouts, few of
+    whose vertices have edges: every kind of compaction, and pre-sampling."""
     import oracle
     import paper_2305_16588_amd as lgp
     from gpu_common import assert_batch_equal
@@ -508,7 +508,7 @@ def test_maps_laid_out_per_call(V):
     indices = rng.integers(0, V, few).astype(np.int32)
     indices[::4] = rng.integers(0, sources, indices[::4].size)
     indices[:2] = [0, V - 1]
-    # pretend edges behind the rows raise the mean degree, which decides about the layout
+    # pretend edges behind the rows raise the mean degree, but not the marks to be expected
     more = lgp.pinned_empty(7 * V, np.int32)
     more[:few] = indices
     ctx, orc = lgp.Context(lgp.pinned_copy(indptr), more), oracle.Oracle(indptr, indices, None)
@@ -666,4 +666,43 @@ def test_wide_rows_from_both_sources(row_bytes, skew):
             assert torch.equal(out, want[torch.from_numpy(ids).cuda().long()]), f"{n_cached} cached, {ids.size} ids"
             assert bool((room[skew // 2 + ids.size * dim:] == 99).all()) and bool((room[:skew // 2] == 99).all())
             assert stats.tolist() == [int(cached[ids].sum()), int((~cached[ids]).sum())]
+    ctx.check()
+
+
+@pytest.mark.parametrize("V,share", [((1 << 23) + 1, 1.0), (1 << 24, 1.0), ((1 << 24) + 1, 1.0), ((1 << 23) + 1, 0.3)])
+def test_maps_of_calls_with_many_marks_and_few(V, share):
+    """Edges at all vertices or at a part of them, degrees below, at and beyond the fan-outs: calls that mark bytes between the
+    limits and calls that mark bits in turn on one context, the pipeline inside a batch (always bits) between them."""
+    import oracle
+    import paper_2305_16588_amd as lgp
+    from gpu_common import assert_batch_equal
+    rng = np.random.default_rng(V + int(10 * share))
+    degrees = rng.integers(1, 8, V, dtype=np.int32)
+    degrees[rng.random(V) >= share] = 0
+    indptr = np.concatenate([[0], np.cumsum(degrees)]).astype(np.int32)
+    indices = rng.integers(0, V, int(indptr[-1]), dtype=np.int32)
+    indices[:2] = [0, V - 1]
+    feats = lgp.pinned_empty((V, 8), np.float16)
+    feats.view(np.int16)[:] = np.arange(V, dtype=np.int32)[:, None].astype(np.int16)
+    ctx, orc = lgp.Context(lgp.pinned_copy(indptr), lgp.pinned_copy(indices), feats), oracle.Oracle(indptr, indices, feats)
+    order = np.concatenate([[0, V - 1], 1 + rng.permutation(V - 2)[:120_000]]).astype(np.int32)
+    for n_seeds, fanouts in ((120_000, (6, 5)), (300, (5, 3)), (120_000, (6, 5)), (2000, (7,))):
+        seeds = order[:n_seeds]
+        dev = torch.from_numpy(seeds).cuda()
+        ref = orc.sample_khop(seeds, fanouts, 19)
+        for last in (False, True):
+            buf = lgp.SampleBuffers(V, n_seeds, fanouts, last_frontier=last)
+            ctx.sample_khop(dev, fanouts, 19, out=buf)
+            assert_batch_equal(ref, buf.to_host(dev), f"{n_seeds} {fanouts} {last}")
+            rows = torch.empty((buf.gather_cap, 8), dtype=torch.float16, device="cuda")
+            ctx.sample_extract(dev, fanouts, 19, buf, rows)
+            n = int(buf.n_gather)
+            listed = buf.gather_ids[:n].cpu().numpy()
+            assert np.array_equal(np.sort(listed), np.sort(ref.gather_ids)), f"{n_seeds} {fanouts} {last}"
+            assert np.array_equal(rows[:n].cpu().numpy().view(np.int16), feats.view(np.int16)[listed])
+    tablet = torch.from_numpy(order).cuda()
+    ctx.build_hotness(tablet, 60_000, (6, 5), 5)
+    rt, rf, _ = orc.build_hotness(order, 60_000, (6, 5), 5)
+    topo, feat = ctx.get_hotness()
+    assert (topo == rt).all() and (feat == rf).all()
     ctx.check()
