@@ -99,7 +99,8 @@ struct lgp_ctx {
   int32_t* hs_n = nullptr;
   unsigned long long* hs_expansions = nullptr;   // device counter: sum of frontier sizes of the last pre-sampling
   int64_t hs_batches = 0;
-  int32_t* hs_seen = nullptr;                    // pinned host copy of hs_n, complete when ev_seen is (stage_topology)
+  int32_t* hs_seen = nullptr;                    // pinned host copy of hs_n, complete when ev_seen is (stage_topology);
+                                                 // both from the first call that may stage
   hipEvent_t ev_seen = nullptr;
   bool indices_on_host = false;                  // the column ids lie in CPU memory
 
@@ -581,7 +582,7 @@ size_t stage_bytes(const lgp_ctx* c) { return size_t(c->g.num_edges) * 4 + 16; }
 double stage_saving(const lgp_ctx* c, double rows, int64_t remaining) {   // bytes over PCIe, a 128-byte line per row
   return rows * double(remaining) * 128.0 - double(c->g.num_edges) * 4.0;
 }
-bool may_stage(const lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts, int32_t n_hops, int64_t n_batches, hipStream_t s) {
+bool may_stage(lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts, int32_t n_hops, int64_t n_batches, hipStream_t s) {
   if (!c->indices_on_host || c->reserved || c->plan.n_topo > 0 || n_batches < 2) return false;
   double rows = 0;
   const double degree = double(c->g.num_edges) / double(c->g.num_vertices);
@@ -590,8 +591,10 @@ bool may_stage(const lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts, int32_
   hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
   size_t free_bytes = 0, total_bytes = 0;
   if (hipStreamIsCapturing(s, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone &&
-      hipMemGetInfo(&free_bytes, &total_bytes) == hipSuccess)
-    return stage_bytes(c) <= free_bytes / 2;
+      hipMemGetInfo(&free_bytes, &total_bytes) == hipSuccess && stage_bytes(c) <= free_bytes / 2 &&
+      (c->ev_seen || hipEventCreateWithFlags(&c->ev_seen, hipEventDisableTiming) == hipSuccess) &&
+      (c->hs_seen || hipHostMalloc(reinterpret_cast<void**>(&c->hs_seen), LGP_MAX_HOPS * sizeof(int32_t), hipHostMallocDefault) == hipSuccess))
+    return true;
   (void)hipGetLastError();
   return false;
 }
@@ -740,8 +743,6 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->miss_stream, hipStreamNonBlocking);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_seen, hipEventDisableTiming);
-  if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&c->hs_seen), LGP_MAX_HOPS * sizeof(int32_t), hipHostMallocDefault);
   if (e == hipSuccess) {
     launch_init_row_table(c->di, c->g.indptr, c->g.indptr_bytes, V, c->row_tab, nullptr);
     e = hipGetLastError();
