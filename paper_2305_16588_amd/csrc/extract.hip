@@ -1,6 +1,6 @@
 // The pipeline inside one mini-batch (Sec. 5): while a hop is sampled, the rows of the vertices that the hop before it
 // reached are extracted beside it, in the same launch.  On two streams every group of rows cost an event and a wait
-// between them (10-25 us each).  8192 seeds (15, 10, 5) on 2.4 M vertices, 400-byte rows, all cached: 178 -> 145 us a call (sampling
+// between them (10-25 us each).  8192 seeds (15, 10, 5) on 2.4 M vertices, 400-byte rows, all cached: 181 -> 146 us a call (sampling
 // takes 60 of that and extraction 80 by themselves: both are bound by requests to HBM); 64 seeds (15, 10) 76 -> 24; 8000 seeds
 // (15, 10) on 1 M vertices in CPU memory, a fifth cached 871 -> 839; 128-byte rows of which 95 % are cached 196 -> 168.
 #include "gather_dev.hpp"

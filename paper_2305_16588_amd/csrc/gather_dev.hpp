@@ -232,7 +232,7 @@ __device__ __forceinline__ void flat_rows(const char* __restrict__ src, char* __
 // the link idles while the hits are copied and HBM while the misses arrive; here the first miss_blocks workgroups
 // take the misses and others the hits, beside them.  Calls, one after the other -> beside each other: 400-byte rows of
 // 2.4 M vertices, 688 k ids, 30 / 70 / 95 / 99.5 % of the table cached 2925 -> 2844, 1208 -> 1100, 324 -> 231, 163 -> 148 us;
-// 2-KiB rows, 95 % 445 -> 310; 7 k ids of 10 k vertices (512-byte rows, 20 %) 76 -> 65.
+// 2-KiB rows, 95 % 654 -> 428 (356 k of 1.2 M); 7 k ids of 10 k vertices (512-byte rows, 20 %) 76 -> 65.
 constexpr int kSplitHitUnroll = 2, kSplitMissUnroll = 4;
 // Called by workgroup `block` of a.miss_blocks.
 template <typename VecT, bool RAGGED>

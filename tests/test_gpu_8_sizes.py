@@ -204,8 +204,8 @@ def test_cached_rows_on_both_sides_of_a_kernel_choice(row_bytes, list_len):
                                                (200_000, (3, 2), 700), (200_000, (1, 1, 1), 256), (200_000, (25, 10), 1025)])
 @pytest.mark.parametrize("span", [1.0, 0.02])
 def test_blocks_of_dense_sparse_and_clustered_frontiers(V, fanouts, n_seeds, span):
-    """The frontiers' bucket index: more and fewer ids than vertices to spread them over, ids in one corner of the
-    range (long empty stretches, full buckets), hops whose destinations are and are not whole tiles."""
+    """The frontiers' index: more and fewer ids than vertices to spread them over, ids in one corner of the
+    range (long empty stretches, full blocks), hops whose destinations are and are not whole tiles."""
     from gpu_common import assert_batch_equal, assert_blocks_equal
     import oracle
     import paper_2305_16588_amd as lgp
@@ -280,7 +280,7 @@ def test_blocks_of_reordered_frontiers(V, n_seeds, fanouts, how):
 @pytest.mark.parametrize("V", [1, 2, 70, 100_000, 3_000_000])
 @pytest.mark.parametrize("where", ["first id", "last id", "both ends", "one run", "three runs", "all over"])
 def test_blocks_of_frontiers_in_parts_of_the_range(V, where):
-    """The frontiers' bucket index covers the span of the list and leaves the buckets of its gaps unset."""
+    """The frontiers' index covers the span of the list and leaves the blocks of its gaps unset."""
     from gpu_common import assert_batch_equal, assert_blocks_equal
     import oracle
     import paper_2305_16588_amd as lgp
