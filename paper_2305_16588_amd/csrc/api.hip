@@ -593,7 +593,8 @@ bool may_stage(lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts, int32_t n_ho
   if (hipStreamIsCapturing(s, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone &&
       hipMemGetInfo(&free_bytes, &total_bytes) == hipSuccess && stage_bytes(c) <= free_bytes / 2 &&
       (c->ev_seen || hipEventCreateWithFlags(&c->ev_seen, hipEventDisableTiming) == hipSuccess) &&
-      (c->hs_seen || hipHostMalloc(reinterpret_cast<void**>(&c->hs_seen), LGP_MAX_HOPS * sizeof(int32_t), hipHostMallocDefault) == hipSuccess))
+      (c->hs_seen || hipHostMalloc(reinterpret_cast<void**>(&c->hs_seen), LGP_MAX_HOPS * sizeof(int32_t), hipHostMallocDefault) ==
+                         hipSuccess))
     return true;
   (void)hipGetLastError();
   return false;

@@ -177,8 +177,9 @@ inline int32_t hop_lanes(const TopoView& tv, int32_t f) {
 // Workgroups for a hop over at most `cap` vertices.
 // Six workgroups (24 waves) per CU: more waves do not make scattered marks faster.  Calls at 4 / 6 / 8 per CU: 2.4 M
 // vertices, half of the topology over PCIe 279.9 / 276.3 / 276.4 us, 111 M vertices 67.7 / 64.8 / 67.0, 250 M 63.3 / 61.7 /
-// 63.4; sampling server step at 2.4 M 194.6 / 189.9 / 192.6.  Sampling a batch beside the extraction of the one before, 2.4 M vertices, at 4 / 6: half of the topology and 30 % of the features
-// cached 1869 / 1870 us a step, half and 90 % 574 / 575, everything 148.7 / 145.0.
+// 63.4; sampling server step at 2.4 M 194.6 / 189.9 / 192.6.  Sampling a batch beside the extraction of the one before, 2.4 M
+// vertices, at 4 / 6: half of the topology and 30 % of the features cached 1869 / 1870 us a step, half and 90 % 574 / 575,
+// everything 148.7 / 145.0.
 inline uint32_t hop_blocks(const DeviceInfo& di, int64_t cap, int32_t lanes) {
   const int64_t per_block = 4 * (64 / lanes), full = int64_t(di.num_cus) * 6;       // vertices of a workgroup pass
   const int64_t blocks = (cap + per_block - 1) / per_block;
