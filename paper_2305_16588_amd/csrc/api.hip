@@ -62,7 +62,8 @@ struct lgp_ctx {
   DedupMaps maps;              // frontier and gather-set dedup maps
   bool either_map = false;     // a call may lay the maps out as bytes instead (kEitherMapMaxVertices), with this geometry
   MapGeom byte_geom;
-  std::vector<double> mean_samples;   // with either_map, [f]: samples of a vertex at fan-out f, mean over the graph
+  BinMaps bins;
+  std::vector<double> mean_samples;   // where a rule asks for it, [f]: samples of a vertex at fan-out f, mean over the graph
   uint32_t* d_err = nullptr;
   int32_t* counters = nullptr;  // {n_hit, n_miss, n_peer}
 
@@ -253,10 +254,17 @@ void prof_end(lgp_ctx* c, EvPair& p, hipStream_t s) {
   c->ev_used.push_back(p);
 }
 
-// 64-bit words of a dedup map.
+// 64-bit words of a dedup map: whole shares of a compaction, of either layout, and whole bins.
 size_t map_words(const lgp_ctx* c) {
-  return size_t(c->either_map ? std::max(c->maps.geom.words(), c->byte_geom.words()) : c->maps.geom.words());
+  const int64_t words = c->either_map ? std::max(c->maps.geom.words(), c->byte_geom.words()) : c->maps.geom.words();
+  return size_t(std::max(words, c->bins.bins ? int64_t(c->bins.bins) << (c->bins.shift - 6) : 0));
 }
+// 64-bit status words of the sampler's kernels.
+size_t status_words(const lgp_ctx* c) {
+  return size_t(std::max<int64_t>({c->maps.geom.groups, c->byte_geom.groups, c->bins.bins ? kBinStatusWords / 2 : 0}));
+}
+// Room for the segments of a context with binned marks, in words.
+size_t segment_words(const lgp_ctx* c) { return size_t(c->bins.bins) * kBinWriters * kBinWords; }
 
 // Marks of a mini-batch on a graph whose vertices are equally popular: more than where popularity is skewed.  samples(f): of a
 // vertex at fan-out f.  *rows, if given: vertices expanded.
@@ -296,6 +304,83 @@ hipError_t count_samples(lgp_ctx* c) {
     c->mean_samples[size_t(f)] = c->mean_samples[size_t(f - 1)] + more / double(c->g.num_vertices);
   }
   return hipSuccess;
+}
+
+// Whether lgp_sample_khop bins its samples (kBinMarksPerSeed).  Every bin's workgroup looks through all seeds, and reads its share of
+// the inner frontiers again after all of them were written, so these must not share memory with anything the call writes.  Where rows
+// cross PCIe the link bounds the hops, and its two workgroups of 1024 threads per CU serve it a little worse (20 M vertices, 8192 seeds
+// (15, 10, 5), none and half of the topology cached 618 -> 621 and 225 -> 231 us).
+constexpr int32_t kBinMaxSeeds = 1 << 17;
+bool binned(const lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops, const int64_t* need,
+            int64_t gather_need, const lgp_sample_out* out) {
+  if (c->bins.bins == 0 || n_seeds > kBinMaxSeeds || topo_view(c).over_pcie) return false;
+  const double enough = bin_marks(c->g.num_vertices);
+  if (enough > 0 && expected_marks(c, n_seeds, fanouts, n_hops, [&](int32_t f) { return c->mean_samples[size_t(f)]; }) <
+                        enough + kBinMarksPerSeed * double(n_seeds))
+    return false;
+  struct Span {
+    uintptr_t at, end;
+  };
+  auto span = [](const int32_t* p, int64_t n) { return Span{uintptr_t(p), uintptr_t(p) + (p ? size_t(n) * 4 : 0)}; };
+  Span read[LGP_MAX_HOPS], written[3 * LGP_MAX_HOPS + 2];
+  int n_read = 0, n_written = 0;
+  read[n_read++] = span(seeds, n_seeds);
+  for (int h = 0; h < n_hops; ++h) {
+    if (h > 0) read[n_read++] = span(out->frontier[h], need[h]);
+    written[n_written++] = span(out->nbr[h], need[h] * fanouts[h]);
+    written[n_written++] = span(out->cnt[h], need[h]);
+    written[n_written++] = span(out->frontier[h + 1], need[h + 1]);
+  }
+  written[n_written++] = span(out->gather_ids, gather_need);
+  for (int r = 0; r < n_read; ++r) {
+    int meets = 0;
+    for (int w = 0; w < n_written; ++w) meets += read[r].at < written[w].end && written[w].at < read[r].end;
+    if (meets > (r > 0)) return false;             // an inner frontier meets itself
+  }
+  return true;
+}
+
+int binned_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops, uint64_t rng_seed,
+                const lgp_sample_out* out, hipStream_t s) {
+  const TopoView tv = topo_view(c);
+  BinArgs a = {};
+  a.maps = c->bins;
+  a.spill = c->maps.frontier;
+  a.status = reinterpret_cast<uint32_t*>(c->maps.status);
+  a.polls = c->maps.polls;
+  a.d_err = c->d_err;
+  a.seeds = seeds;
+  a.n_seeds = n_seeds;
+  a.first = c->bins.first;
+  a.tv = tv;
+  const int32_t* frontier = seeds;
+  int64_t cap = n_seeds;
+  for (int h = 0; h < n_hops; ++h) {
+    a.writers = launch_sample_hop_binned(c->di, tv, frontier, out->n_frontier + h, cap, fanouts[h], h, rng_seed, out->nbr[h],
+                                         out->cnt[h], c->bins, reinterpret_cast<uint32_t*>(c->maps.frontier), c->d_err,
+                                         c->maps.status, s);
+    const bool last = h + 1 == n_hops;
+    const bool want = out->frontier[h + 1] != nullptr;      // given, but for the last one
+    a.list = out->frontier[h + 1];
+    a.list_cap = out->cap[h + 1];
+    a.n_list = want ? out->n_frontier + h + 1 : nullptr;
+    if (last) {
+      a.list_first = nullptr;
+      a.inner = n_hops - 1;
+      a.all = out->gather_ids;
+      a.all_cap = out->gather_cap;
+      a.n_all = out->n_gather;
+    } else {
+      a.list_first = c->bins.first + (h + 1) * (kMaxBins + 1);
+      a.frontier[h + 1] = out->frontier[h + 1];
+    }
+    launch_list_bins(a, s);
+    frontier = out->frontier[h + 1];
+    cap = out->cap[h + 1];
+  }
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return fail_hip(c, e, "sampling kernel launch");
+  return LGP_OK;
 }
 
 // Sampling of one mini-batch; out == nullptr is the pre-sampling mode (hotness only), for which `staged` may hold the
@@ -713,6 +798,10 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   c->maps.geom = map_geometry(V, c->di.spread_shift);
   c->either_map = V > kByteMapMaxVertices && V <= kEitherMapMaxVertices;
   if (c->either_map) c->byte_geom = map_geometry(V, 3);
+  if (V > kBinMinVertices && V <= kBinMaxVertices) {
+    c->bins.shift = bin_shift(V);
+    c->bins.bins = int32_t((V + (int64_t(1) << c->bins.shift) - 1) >> c->bins.shift);
+  }
   const size_t words = map_words(c);
   hipError_t e = hipSuccess;
   auto step = [&](hipError_t r) {
@@ -724,7 +813,13 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   step(dev_alloc(&c->feat_hot, size_t(V)));
   step(dev_alloc(&c->maps.frontier, words));
   step(dev_alloc(&c->maps.gather, words));
-  step(dev_alloc(&c->maps.status, size_t(std::max(c->maps.geom.groups, c->byte_geom.groups))));
+  step(dev_alloc(&c->maps.status, status_words(c)));
+  if (c->bins.bins) {
+    step(dev_alloc(&c->bins.heads, segment_words(c) / kBinWords * kHeadWords));
+    step(dev_alloc(&c->bins.tails, segment_words(c) / kBinWords * (kBinWords - kHeadWords)));
+    step(dev_alloc(&c->bins.spilled, kMaxBins));
+    step(dev_alloc(&c->bins.first, LGP_MAX_HOPS * (kMaxBins + 1)));
+  }
   step(dev_alloc(&c->d_err, 1));
   step(dev_alloc(&c->counters, 3));
   step(dev_alloc(&c->hs_n, LGP_MAX_HOPS + 1));
@@ -737,6 +832,7 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   if (e == hipSuccess) e = hipMemset(c->feat_hot, 0, sizeof(uint32_t) * size_t(V));
   if (e == hipSuccess) e = hipMemset(c->maps.frontier, 0, sizeof(uint64_t) * words);
   if (e == hipSuccess) e = hipMemset(c->maps.gather, 0, sizeof(uint64_t) * words);
+  if (e == hipSuccess && c->bins.bins) e = hipMemset(c->bins.spilled, 0, sizeof(uint32_t) * kMaxBins);
   if (e == hipSuccess) e = hipMemset(c->d_err, 0, sizeof(uint32_t));
   if (e == hipSuccess) e = hipMemset(c->counters, 0, 3 * sizeof(int32_t));
   if (e == hipSuccess) e = hipMemset(c->unordered, 0, (LGP_MAX_HOPS + 1) * sizeof(uint32_t));
@@ -748,7 +844,7 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
     launch_init_row_table(c->di, c->g.indptr, c->g.indptr_bytes, V, c->row_tab, nullptr);
     e = hipGetLastError();
   }
-  if (e == hipSuccess && c->either_map) e = count_samples(c);
+  if (e == hipSuccess && (c->either_map || (c->bins.bins && bin_marks(V) > 0))) e = count_samples(c);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     (void)hipGetLastError();
@@ -765,7 +861,8 @@ int lgp_destroy(lgp_ctx* c) {
   free_cache(c);
   void* ptrs[] = {c->row_tab, c->f_remap, c->topo_hot, c->feat_hot, c->maps.frontier, c->maps.gather, c->maps.status,
                   c->d_err,   c->counters, c->order_t, c->order_f,  c->lists, c->hs_n, c->pos_table, c->tile_sums, c->hs_expansions,
-                  c->seg, c->seg_counters, c->unordered};
+                  c->seg, c->seg_counters, c->unordered, c->bins.heads, c->bins.tails,
+                  c->bins.spilled, c->bins.first};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (int h = 0; h < LGP_MAX_HOPS; ++h)
@@ -1204,7 +1301,9 @@ int lgp_sample_khop(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int
   hipStream_t s = static_cast<hipStream_t>(stream);
   LGP_HIP(c, hipSetDevice(c->di.device));
   EvPair ev = prof_begin(c, PK_SAMPLE, s);
-  st = sample_core(c, seeds, n_seeds, fanouts, n_hops, rng_seed, out, s);
+  st = binned(c, seeds, n_seeds, fanouts, n_hops, need, gather_need, out)
+           ? binned_core(c, seeds, n_seeds, fanouts, n_hops, rng_seed, out, s)
+           : sample_core(c, seeds, n_seeds, fanouts, n_hops, rng_seed, out, s);
   prof_end(c, ev, s);
   return st;
 }
@@ -1446,7 +1545,7 @@ int lgp_workspace_bytes(const lgp_ctx* c, int32_t max_seeds, const int32_t* fano
   if (fixed) {
     const size_t map = map_words(c) * 8;
     // row table 8 + remap 4 + two hotness vectors 4 + 4 + two rankings 4 + 4 bytes per vertex
-    *fixed = V * 28 + 2 * map + size_t(std::max(c->maps.geom.groups, c->byte_geom.groups)) * 8 + 64;
+    *fixed = V * 28 + 2 * map + status_words(c) * 8 + segment_words(c) * 4 + 64;
   }
   if (scratch) {
     int64_t need[LGP_MAX_HOPS + 1], gather_need;

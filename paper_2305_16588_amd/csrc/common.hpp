@@ -81,6 +81,46 @@ struct DedupMaps {
   int32_t polls = kDefaultPolls;
 };
 
+// Binned marks, for large graphs.  A sample is not marked in a map but appended to a segment of its workgroup and its bin
+// (2^shift consecutive vertices), at a place that a counter in LDS hands out: a plain store, where an atomic on a bit runs at
+// 26 G/s.  The workgroup of a bin then sets the bits in LDS (bins.hip), so the map in HBM is neither read nor cleared.  Samples
+// beyond a segment's room are marked in the frontier map, and the bin is flagged: a list crowded into few bins costs what marks cost.
+constexpr int kBinThreads = 1024;     // of a workgroup of either kernel
+constexpr int kBinWriters = 512;      // workgroups of a hop: two per CU
+constexpr int kBinWords = 128;        // words of a segment
+constexpr int kHeadWords = 16;        // of them in its head
+constexpr int kMaxBins = 256;         // a workgroup each, one per CU
+constexpr int kStatusCopies = 8;      // of the status words: one channel of memory does not answer all workgroups at once
+constexpr int kBinStatusWords = 2 * kStatusCopies * kMaxBins;      // of 32 bits: for the list of a hop, and for the union
+// Which calls: a hop saves about 25 us per million samples, a list from bins costs 1 to 3 us more than the compaction of a map
+// of up to 2^26 bits and less than that of one of more than 2^27.  So from expected_marks on that grow with the seeds, which every
+// bin's workgroup looks through.  Calls of lgp_sample_khop, map -> bins, and thousands of expected marks: 17 M vertices of power-law
+// degrees, 120000 seeds (10, 5) 103 -> 76 us, 2426; 8192 (15, 10, 5) 55.5 -> 44.8, 919; 16000 (10, 10) 32.6 -> 32.5, 410; 8000 (25, 10)
+// 28.0 -> 28.7, 272; 64 (15, 10, 5) 25.0 -> 32.5, 7.  60 M 90 -> 72, 1750; 49.4 -> 45.3, 540; 32.0 -> 33.0, 284; 25.9 -> 29.7, 183;
+// 29.4 -> 31.8, 4.  111 M 111 -> 84, 2087; 61.6 -> 48.5, 713; 36.5 -> 33.4, 343; 31.5 -> 30.2, 225; 28.8 -> 34.0, 6.  140 M 117 -> 83,
+// 1994; 67.5 -> 50.7, 663; 41.3 -> 36.7, 327; 35.5 -> 31.9, 213; 38.0 -> 36.2 and 33.9 -> 35.6, 5.  250 M 137 -> 97, 2248; 83.1 -> 55.5,
+// 802; 48.3 -> 36.7, 372; 41.8 -> 33.3, 245; 45.2 -> 36.4, 6.  Degrees of 12 everywhere, 111 M: 8192 (15, 10, 5) 308 -> 195, 5972; 64000
+// (10, 10) 342 -> 204, 7022.  Up to 2^24 vertices bytes or bits are as fast or faster (8192 seeds at 12 M, 8 M and 2.4 M vertices 43.6
+// -> 44.6, 49.4 -> 59.8 and 45.0 -> 60.8).
+constexpr int64_t kBinMinVertices = int64_t(1) << 24, kBinMaxVertices = int64_t(1) << 28;
+constexpr double kBinMarksPerSeed = 4.0;
+inline double bin_marks(int64_t num_vertices) {
+  return num_vertices <= int64_t(1) << 26 ? 600e3 : num_vertices <= int64_t(1) << 27 ? 200e3 : num_vertices <= int64_t(5) << 25 ? 60e3 : 0.0;
+}
+inline int bin_shift(int64_t num_vertices) {
+  int shift = 17;
+  while ((num_vertices - 1) >> shift >= kMaxBins) ++shift;
+  return shift;
+}
+struct BinMaps {
+  // Segments [bin][workgroup of the hop]; word 0 of a segment is its count, which may be larger than its room.
+  uint32_t* heads = nullptr;          // the first kHeadWords words of each, which are always read
+  uint32_t* tails = nullptr;          // the others
+  uint32_t* spilled = nullptr;        // [bin]: the frontier map has taken something; all zero between calls
+  int32_t* first = nullptr;           // [hop][kMaxBins + 1]: where the ids of each bin begin in frontier `hop`
+  int32_t shift = 0, bins = 0;        // bins == 0: this context marks maps
+};
+
 struct DeviceInfo {
   int device = 0;
   int num_cus = 256;
@@ -119,6 +159,12 @@ void launch_sample_hop(const DeviceInfo& di, const TopoView& tv, const int32_t* 
                        int64_t cap, int32_t fanout, int32_t hop, uint64_t rng_seed, int32_t* nbr, int32_t* cnt,
                        uint32_t* mark_bits, uint32_t* self_bits, uint32_t* topo_hot, uint32_t* d_err, uint64_t* status,
                        int64_t n_status, hipStream_t s);
+
+// The same for binned marks: no hotness, and seeds are not marked; what finds no room is marked in mark_bits.  status[0 ..
+// kBinStatusWords) of 32 bits is cleared.  Returns the number of workgroups, which is the number of segments of a bin.
+int32_t launch_sample_hop_binned(const DeviceInfo& di, const TopoView& tv, const int32_t* frontier, int32_t* n_frontier,
+                                 int64_t cap, int32_t fanout, int32_t hop, uint64_t rng_seed, int32_t* nbr, int32_t* cnt,
+                                 const BinMaps& m, uint32_t* mark_bits, uint32_t* d_err, uint64_t* status, hipStream_t s);
 
 // Pre-sampling: staged[0 .. n_edges) = h_indices[0 .. n_edges), from CPU memory to HBM.  The two addresses are equal modulo 16.
 void launch_stage_topology(const int32_t* h_indices, int32_t* staged, int64_t n_edges, hipStream_t s);
@@ -160,6 +206,31 @@ void launch_compact_new(const DeviceInfo& di, const DedupMaps& m, int32_t* out, 
 // frontier sizes of the batch).
 void launch_bump(const DeviceInfo& di, const DedupMaps& m, uint32_t* bump, const int32_t* sizes, int32_t n_sizes,
                  unsigned long long* acc, hipStream_t s);
+
+// ---- bins.hip -------------------------------------------------------------
+// What the samples of one binned hop are turned into.  With n_list: their ascending list, and in list_first (optional) where the ids
+// of each bin begin in it.  With n_all: the ascending union of them, the seeds and frontiers 1 .. inner, whose bins begin where
+// `first` says.  Every launch follows a launch_sample_hop_binned on the same stream, which clears the status words.
+struct BinArgs {
+  BinMaps maps;
+  int32_t writers;          // segments of a bin
+  uint64_t* spill;          // the frontier map
+  uint32_t* status;         // kBinStatusWords
+  int32_t polls;
+  uint32_t* d_err;
+  int32_t* list;
+  int64_t list_cap;
+  int32_t *n_list, *list_first;
+  int32_t* all;
+  int64_t all_cap;
+  int32_t* n_all;
+  const int32_t* seeds;
+  int32_t n_seeds, inner;
+  const int32_t* frontier[LGP_MAX_HOPS];
+  const int32_t* first;
+  TopoView tv;
+};
+void launch_list_bins(const BinArgs& a, hipStream_t s);
 
 // ---- gather.hip -----------------------------------------------------------
 // Look up every id in the feature remap and append (row, slot) to the hit list (list 0) or

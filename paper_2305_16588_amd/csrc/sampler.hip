@@ -9,12 +9,24 @@
 // hop_blocks.
 #include "sampler_dev.hpp"
 
+#include <algorithm>
+
 namespace lgp {
 namespace {
 
 template <int SHIFT>
 __global__ __launch_bounds__(256) void sample_hop_kernel(HopArgs a) {
   sample_hop<SHIFT>(a, blockIdx.x, gridDim.x);
+}
+
+__global__ __launch_bounds__(kBinThreads, 8) void sample_hop_binned_kernel(HopArgs a) {
+  __shared__ uint32_t used[kMaxBins];
+  if (threadIdx.x < kMaxBins) used[threadIdx.x] = 0;
+  __syncthreads();
+  sample_hop<kBinned, kBinThreads / 64>(a, blockIdx.x, gridDim.x, used);
+  __syncthreads();
+  if (int(threadIdx.x) < a.bins.bins)
+    a.bins.heads[(threadIdx.x * gridDim.x + blockIdx.x) * uint32_t(kHeadWords)] = used[threadIdx.x];
 }
 
 // Pre-sampling reads rows of a few column ids at random places of CPU memory, a 128-byte line of the link each (340 M
@@ -66,6 +78,17 @@ void launch_sample_hop(const DeviceInfo& di, const TopoView& tv, const int32_t* 
     case 4: hipLaunchKernelGGL((sample_hop_kernel<4>), grid, block, 0, s, a); break;
     default: hipLaunchKernelGGL((sample_hop_kernel<5>), grid, block, 0, s, a); break;
   }
+}
+
+int32_t launch_sample_hop_binned(const DeviceInfo& di, const TopoView& tv, const int32_t* frontier, int32_t* n_frontier,
+                                 int64_t cap, int32_t fanout, int32_t hop, uint64_t rng_seed, int32_t* nbr, int32_t* cnt,
+                                 const BinMaps& m, uint32_t* mark_bits, uint32_t* d_err, uint64_t* status, hipStream_t s) {
+  const HopArgs a{tv,  frontier, n_frontier, cap,     fanout,  hop_lanes(tv, fanout), hop,    uint32_t(rng_seed), uint32_t(rng_seed >> 32),
+                  nbr, cnt,      mark_bits,  nullptr, nullptr, d_err,                 status, kBinStatusWords / 2, m};
+  const int64_t per_block = kBinThreads / 64 * (64 / a.lanes), blocks = (cap + per_block - 1) / per_block;
+  const int32_t writers = int32_t(std::max<int64_t>(1, std::min<int64_t>(blocks, kBinWriters)));
+  hipLaunchKernelGGL(sample_hop_binned_kernel, dim3(unsigned(writers)), dim3(unsigned(kBinThreads)), 0, s, a);
+  return writers;
 }
 
 }  // namespace lgp

@@ -62,7 +62,22 @@ struct HopArgs {
   uint32_t* d_err;
   uint64_t* status;
   int32_t n_status;
+  BinMaps bins;            // of a binned hop
 };
+
+// Append vertex u to this workgroup's segment of its bin; used = entries of those segments, by bin (LDS).
+constexpr int kBinned = -1;               // in the place of a map's shift
+__device__ __forceinline__ void append_to_bin(const HopArgs& a, uint32_t* used, uint32_t block, uint32_t blocks, int32_t u) {
+  const uint32_t bin = uint32_t(u) >> a.bins.shift, at = atomicAdd(&used[bin], 1u) + 1u, segment = bin * blocks + block;
+  if (at < uint32_t(kHeadWords)) {
+    a.bins.heads[segment * uint32_t(kHeadWords) + at] = uint32_t(u);
+  } else if (at < uint32_t(kBinWords)) {
+    a.bins.tails[segment * uint32_t(kBinWords - kHeadWords) + at - kHeadWords] = uint32_t(u);
+  } else {
+    mark_vertex<0>(a.mark_bits, u);
+    a.bins.spilled[bin] = 1;
+  }
+}
 
 // Marks bound this kernel (last hop of 190 k vertices x 5 at 2.4 M vertices: 23 us with its 950 k byte marks, 11 without;
 // 490 k atomic marks at 250 M: 24 and 9); what is left is loads and issue slots, so lanes are packed without gaps (but see
@@ -70,8 +85,8 @@ struct HopArgs {
 // 2.4 M vertices from 8192 seeds: fan-outs 17, 17 28.2 -> 25.1 us, 64 17.5 -> 15.4, 9, 9 21.2 -> 20.2, 15, 10, 5 with blocks
 // and gather 190 -> 186; 25 or 3, 3, 3 and graphs with atomic marks are level.
 // The caller is workgroup `block` of `blocks` that share the frontier.
-template <int SHIFT>
-__device__ __forceinline__ void sample_hop(const HopArgs& a, uint32_t block, uint32_t blocks) {
+template <int SHIFT, int WAVES = 4>
+__device__ __forceinline__ void sample_hop(const HopArgs& a, uint32_t block, uint32_t blocks, uint32_t* used = nullptr) {
   const uint64_t* __restrict__ row_tab = a.tv.row_tab;
   const int32_t* __restrict__ h_indices = a.tv.h_indices;
   const int32_t* __restrict__ frontier = a.frontier;
@@ -82,10 +97,11 @@ __device__ __forceinline__ void sample_hop(const HopArgs& a, uint32_t block, uin
   const int32_t f = a.f, lanes = a.lanes;
   // self_bits != nullptr: this is the first hop; the frontier is the caller's seed list of `cap`
   // ids, whose size is published here and whose members are marked in the gather set.
-  if (self_bits && block == 0 && threadIdx.x == 0) *a.n_frontier = int32_t(a.cap);
+  const bool seeds = SHIFT == kBinned ? a.hop == 0 : self_bits != nullptr;
+  if (seeds && block == 0 && threadIdx.x == 0) *a.n_frontier = int32_t(a.cap);
   if (block == 0)
-    for (int k = threadIdx.x; k < a.n_status; k += 256) a.status[k] = 0;
-  int64_t n = self_bits ? a.cap : int64_t(*a.n_frontier);
+    for (int k = threadIdx.x; k < a.n_status; k += WAVES * 64) a.status[k] = 0;
+  int64_t n = seeds ? a.cap : int64_t(*a.n_frontier);
   if (n > a.cap) n = a.cap;                           // never trust a count beyond the buffer
   const int per_wave = 64 / lanes;                // vertices per wave pass
   const int lane = threadIdx.x & 63;
@@ -93,8 +109,8 @@ __device__ __forceinline__ void sample_hop(const HopArgs& a, uint32_t block, uin
   // Three loads depend on one another (frontier id -> row-table entry -> column id).  The id is loaded two passes ahead
   // and the row-table entry one pass ahead, so that a pass waits for its column ids only (two hops of 17 from 8192 seeds
   // of 2.4 M vertices 25.8 -> 25.1 us, one hop of 64 16.0 -> 15.4).
-  const int64_t wave = int64_t(block) * 4 + (threadIdx.x >> 6);
-  const int64_t stride = int64_t(blocks) * 4 * per_wave;
+  const int64_t wave = int64_t(block) * WAVES + (threadIdx.x >> 6);
+  const int64_t stride = int64_t(blocks) * WAVES * per_wave;
   const uint64_t nv = uint64_t(a.tv.num_vertices);
   auto id_at = [&](int64_t g) { return sub < per_wave && g < n ? frontier[g] : -1; };
   auto row_of = [&](int32_t v) { return uint32_t(v) < nv ? row_tab[v] : 0; };
@@ -148,13 +164,15 @@ __device__ __forceinline__ void sample_hop(const HopArgs& a, uint32_t block, uin
         if (uint32_t(u) >= nv) {
           atomicOr(a.d_err, ERR_BAD_ID);
           u = -1;
+        } else if (SHIFT == kBinned) {
+          append_to_bin(a, used, block, blocks, u);
         } else {
           mark_vertex<SHIFT>(mark_bits, u);
         }
       }
       if (nbr) nbr[g * f + slot] = u;
       if (slot == 0) {
-        if (self_bits && !bad) mark_vertex<SHIFT>(self_bits, v);
+        if (SHIFT != kBinned && self_bits && !bad) mark_vertex<SHIFT>(self_bits, v);
         const int32_t c = d < f ? d : f;
         if (cnt) cnt[g] = c;
         if (a.topo_hot && c > 0) atomicAdd(&a.topo_hot[v], uint32_t(c));

@@ -706,3 +706,74 @@ def test_maps_of_calls_with_many_marks_and_few(V, share):
     topo, feat = ctx.get_hotness()
     assert (topo == rt).all() and (feat == rf).all()
     ctx.check()
+
+
+@pytest.mark.parametrize("V,deg", [((1 << 24) + 1, 8), (1 << 25, 8), ((1 << 25) + 1, 8), ((1 << 26) + 1, 4), ((1 << 27) + 1, 2), (1 << 28, 0)])
+def test_samples_sorted_into_bins(V, deg):
+    """Calls with many samples on a large graph sort them by ranges of vertices into segments of limited room.  Samples spread over the
+    graph, at the edges of the ranges, in one range and on one vertex (segments overflow), with polls and without, with more seeds and
+    more inner frontiers than the kernel loads ahead, and calls that mark maps between them; a caller who uses one buffer for two
+    frontiers gets the marks in maps."""
+    import oracle
+    import paper_2305_16588_amd as lgp
+    from gpu_common import assert_batch_equal
+    rng = np.random.default_rng(V)
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    gap = 1 if deg else 61                                     # every vertex has `deg` edges, or every 61st has 7
+    deg = deg or 7
+    indptr = lgp.pinned_empty(V + 1, np.int32)
+    rows = (V + gap - 1) // gap
+    np.multiply((np.arange(V + 1, dtype=np.int64) + gap - 1) // gap, deg, out=indptr, casting="unsafe")
+    step = 1 << 17
+    edges = torch.arange(0, V, step, device="cuda")
+    edges = torch.unique(torch.cat([edges, edges[1:] - 1, torch.tensor([V - 1], device="cuda")]))
+
+    def draw(kind, n):
+        r = torch.randint(0, V, (n,), generator=gen, device="cuda")
+        if kind == "spread":
+            return r // gap * gap
+        if kind == "edges":
+            return edges[r % edges.numel()]
+        return r % step // gap * gap if kind == "crowd" else torch.full((n,), V - 1, device="cuda")
+
+    indices = lgp.pinned_empty(rows * deg, np.int32)
+    for lists in (("spread", "edges", "crowd", "one"), ("crowd",), ("one",)) if V <= 1 << 25 else (("spread", "edges", "spread", "one"),):
+        part = 1 << 24
+        for lo in range(0, indices.size, part):
+            n = min(part, indices.size - lo)
+            pick = torch.randint(0, len(lists), (n,), generator=gen, device="cuda")
+            got = torch.zeros(n, dtype=torch.int64, device="cuda")
+            for k, kind in enumerate(lists):
+                got = torch.where(pick == k, draw(kind, n), got)
+            torch.from_numpy(indices[lo:lo + n]).copy_(got.to(torch.int32))
+        ctx, orc = lgp.Context(indptr, indices), oracle.Oracle(indptr, indices, None)
+        order = (rng.permutation(min(rows, 1 << 20))[:140_000] * gap).astype(np.int32)
+        for n_seeds, fanouts in ((30_000, (7, 6, 3)), (1, (9, 9, 2)), (60_001, (2, 2, 2, 2, 2)), (8192, (5,)), (131_073, (3, 2))):
+            seeds = order[:n_seeds]
+            dev = torch.from_numpy(seeds).cuda()
+            ref = orc.sample_khop(seeds, fanouts, 23)
+            for last in (False, True):
+                buf = lgp.SampleBuffers(V, seeds.size, fanouts, last_frontier=last)
+                for polls in (4096, 0, 4096):
+                    ctx.set_wait_polls(polls)
+                    ctx.sample_khop(dev, fanouts, 23, out=buf)
+                    assert_batch_equal(ref, buf.to_host(dev), f"{V} {lists} {n_seeds} {fanouts} {polls} {last}")
+        seeds = order[:40_000]
+        dev = torch.from_numpy(seeds).cuda()
+        ref = orc.sample_khop(seeds, (4, 4, 4), 29)
+        buf = lgp.SampleBuffers(V, seeds.size, (4, 4, 4))
+        buf.c_struct.frontier[1] = buf.frontier[2].data_ptr()
+        ctx.sample_khop(dev, (4, 4, 4), 29, out=buf)
+        fr, nbr, _, ids = buf.to_host(dev)
+        assert (ids == ref.gather_ids).all() and (fr[2] == ref.frontier[2]).all()
+        assert all((nbr[h] == ref.nbr[h]).all() for h in range(3))
+        ctx.check()
+        bad = seeds.copy()
+        bad[[3, 77]] = [-1, V]
+        ctx.sample_khop(torch.from_numpy(bad).cuda(), (4, 4, 4), 29)
+        with pytest.raises(lgp.LegionPrepError):
+            ctx.check()
+        ctx.sample_khop(dev, (4, 4, 4), 29, out=buf)
+        assert (buf.to_host(dev)[3] == ref.gather_ids).all()
+        ctx.check()
+        del ctx, orc
