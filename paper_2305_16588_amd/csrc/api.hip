@@ -340,8 +340,8 @@ bool binned(const lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32
   return true;
 }
 
-int binned_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops, uint64_t rng_seed,
-                const lgp_sample_out* out, hipStream_t s) {
+int binned_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops, const int64_t* need,
+                uint64_t rng_seed, const lgp_sample_out* out, hipStream_t s) {
   const TopoView tv = topo_view(c);
   BinArgs a = {};
   a.maps = c->bins;
@@ -376,7 +376,7 @@ int binned_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t
     }
     launch_list_bins(a, s);
     frontier = out->frontier[h + 1];
-    cap = out->cap[h + 1];
+    cap = need[h + 1];
   }
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail_hip(c, e, "sampling kernel launch");
@@ -385,7 +385,8 @@ int binned_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t
 
 // Sampling of one mini-batch; out == nullptr is the pre-sampling mode (hotness only), for which `staged` may hold the
 // column ids in HBM, and `show` sends the frontier sizes to hs_seen as soon as all are known.
-int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops,
+// need: the worst-case frontier sizes.
+int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops, const int64_t* need,
                 uint64_t rng_seed, const lgp_sample_out* out, hipStream_t s, const int32_t* staged = nullptr,
                 bool show = false) {
   const bool hot_mode = (out == nullptr);
@@ -425,7 +426,7 @@ int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t
     const int64_t next_cap = hot_mode ? c->hs_cap[h + 1] : out->cap[h + 1];
     launch_compact(di, maps, next, next_cap, n_frontier + h + 1, c->d_err, s);
     frontier = next;
-    cap = next_cap;
+    cap = need[h + 1];                             // a buffer has that much room, whatever its capacity is said to be
   }
   if (hot_mode)
     launch_bump(di, maps, c->feat_hot, c->hs_n, n_hops, c->hs_expansions, s);
@@ -907,7 +908,7 @@ int lgp_build_hotness(lgp_ctx* c, const int32_t* train_ids, int64_t n_train, int
     const int64_t lo = b * batch;
     const int32_t nb = int32_t(std::min<int64_t>(batch, n_train - lo));
     if (may && b == 1 && (st = stage_topology(c, need[0], n_hops, n_batches - 1, s, &room, &staged)) != LGP_OK) break;
-    st = sample_core(c, train_ids + lo, nb, fanouts, n_hops, base_seed + uint64_t(b), nullptr, s, staged, may && b == 0);
+    st = sample_core(c, train_ids + lo, nb, fanouts, n_hops, need, base_seed + uint64_t(b), nullptr, s, staged, may && b == 0);
   }
   if (room) {
     const hipError_t e = hipFreeAsync(room, s);
@@ -1302,8 +1303,8 @@ int lgp_sample_khop(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int
   LGP_HIP(c, hipSetDevice(c->di.device));
   EvPair ev = prof_begin(c, PK_SAMPLE, s);
   st = binned(c, seeds, n_seeds, fanouts, n_hops, need, gather_need, out)
-           ? binned_core(c, seeds, n_seeds, fanouts, n_hops, rng_seed, out, s)
-           : sample_core(c, seeds, n_seeds, fanouts, n_hops, rng_seed, out, s);
+           ? binned_core(c, seeds, n_seeds, fanouts, n_hops, need, rng_seed, out, s)
+           : sample_core(c, seeds, n_seeds, fanouts, n_hops, need, rng_seed, out, s);
   prof_end(c, ev, s);
   return st;
 }
@@ -1386,7 +1387,7 @@ int lgp_sample_extract(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const 
     launch_compact_new(c->di, c->maps, next, next ? out->cap[h + 1] : 0, want ? out->n_frontier + h + 1 : nullptr,
                        out->gather_ids, out->gather_cap, c->seg + h + 1, last ? out->n_gather : nullptr, c->d_err, s);
     frontier = next;
-    cap = next ? out->cap[h + 1] : 0;
+    cap = need[h + 1];
   }
   if (st == LGP_OK) st = extract(n_hops);
   // the "seen" bitmap of this batch is not compacted (the listing replaces the ascending list), so it is cleared whole

@@ -149,7 +149,7 @@ struct TopoView {
 };
 
 // ---- sampler.hip ----------------------------------------------------------
-// Expand frontier[0 .. *n_frontier) with fan-out f at hop `hop`.  Writes nbr / cnt
+// Expand frontier[0 .. *n_frontier) with fan-out f at hop `hop`; the array has room for `cap` ids.  Writes nbr / cnt
 // (either may be null), marks every sampled neighbour in `mark_bits` (bit v << di.spread_shift),
 // adds cnt to topo_hot[v] if topo_hot is given.  With self_bits given (first hop) the
 // frontier is the seed list: exactly `cap` ids, *n_frontier is written (= cap) instead of
