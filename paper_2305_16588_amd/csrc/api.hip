@@ -306,6 +306,65 @@ hipError_t count_samples(lgp_ctx* c) {
   return hipSuccess;
 }
 
+// Whether lgp_build_hotness may copy the column ids to HBM within its first mini-batch: 24 MB, half a millisecond of the
+// link, are to be saved.  expected_marks gives more rows than are read where popularity is skewed (2.4 M vertices, 8192 seeds,
+// 15-10-5: 530 k, 263 k), so half of what it says is taken.  A topology cache that is in place already serves the rows that
+// are read often, so nothing is copied beside it; nor is anything waited for or allocated under capture, nor more than half of
+// the free memory taken (asked before anything is enqueued: beside running kernels hipMemGetInfo took up to 0.6 ms).
+constexpr double kStageSaving = 24e6;
+size_t stage_bytes(const lgp_ctx* c) { return size_t(c->g.num_edges) * 4 + 16; }
+double stage_saving(const lgp_ctx* c, double rows, int64_t remaining) {   // bytes over PCIe, a 128-byte line per row
+  return rows * double(remaining) * 128.0 - double(c->g.num_edges) * 4.0;
+}
+bool may_stage(lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts, int32_t n_hops, int64_t n_batches, hipStream_t s) {
+  if (!c->indices_on_host || c->reserved || c->plan.n_topo > 0 || n_batches < 2) return false;
+  double rows = 0;
+  const double degree = double(c->g.num_edges) / double(c->g.num_vertices);
+  expected_marks(c, n_seeds, fanouts, n_hops, [&](int32_t f) { return std::min(degree, double(f)); }, &rows);
+  if (stage_saving(c, 0.5 * rows, n_batches - 1) < kStageSaving) return false;
+  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+  size_t free_bytes = 0, total_bytes = 0;
+  if (hipStreamIsCapturing(s, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone &&
+      hipMemGetInfo(&free_bytes, &total_bytes) == hipSuccess && stage_bytes(c) <= free_bytes / 2 &&
+      (c->ev_seen || hipEventCreateWithFlags(&c->ev_seen, hipEventDisableTiming) == hipSuccess) &&
+      (c->hs_seen || hipHostMalloc(reinterpret_cast<void**>(&c->hs_seen), LGP_MAX_HOPS * sizeof(int32_t), hipHostMallocDefault) ==
+                         hipSuccess))
+    return true;
+  (void)hipGetLastError();
+  return false;
+}
+
+// The column ids in HBM, for the rest of a pre-sampling.
+struct Staging {
+  int64_t remaining = 0;             // mini-batches after the first
+  void* room = nullptr;
+  const int32_t* ids = nullptr;      // null: rows are read in place
+};
+
+// The copy, if the rows that the first mini-batch reads say that it saves time; else, and where memory is short, rows are read in
+// place.  The frontier sizes are known before the last hop, which reads most rows, so the host waits for them there and that hop
+// reads the copy already (decided beside that hop, for the batches after it: 16 batches of 8192 seeds (15, 10, 5) on 2.4 M vertices
+// 6.04 ms, now 5.56; 8 of 4555 (11, 11, 11) on 0.87 M 3.09, 2.67; where nothing is copied calls are level).  With the room taken beforehand and the decision on the device, calls on skewed graphs
+// left the room unused (8 M vertices, 115 M edges, 8 batches, rows in place: 460 MB and 5090 us a call; now none and 5020, and
+// 5000 with no question asked).
+int stage_topology(lgp_ctx* c, int64_t n_seeds, int32_t n_hops, hipStream_t s, Staging* st) {
+  LGP_HIP(c, hipMemcpyAsync(c->hs_seen, c->hs_n, sizeof(int32_t) * size_t(n_hops), hipMemcpyDeviceToHost, s));
+  LGP_HIP(c, hipEventRecord(c->ev_seen, s));
+  LGP_HIP(c, hipEventSynchronize(c->ev_seen));
+  double rows = double(n_seeds);
+  for (int h = 1; h < n_hops; ++h) rows += double(c->hs_seen[h]);
+  if (stage_saving(c, rows, st->remaining) <= 0) return LGP_OK;
+  if (hipMallocAsync(&st->room, stage_bytes(c), s) != hipSuccess) {
+    (void)hipGetLastError();
+    st->room = nullptr;
+    return LGP_OK;
+  }
+  int32_t* const to = static_cast<int32_t*>(st->room) + ((uintptr_t(c->g.indices) >> 2) & 3);
+  launch_stage_topology(c->g.indices, to, c->g.num_edges, s);
+  st->ids = to;
+  return LGP_OK;
+}
+
 // Whether lgp_sample_khop bins its samples (kBinMarksPerSeed).  Every bin's workgroup looks through all seeds, and reads its share of
 // the inner frontiers again after all of them were written, so these must not share memory with anything the call writes.  Where rows
 // cross PCIe the link bounds the hops, and its two workgroups of 1024 threads per CU serve it a little worse (20 M vertices, 8192 seeds
@@ -383,12 +442,12 @@ int binned_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t
   return LGP_OK;
 }
 
-// Sampling of one mini-batch; out == nullptr is the pre-sampling mode (hotness only), for which `staged` may hold the
-// column ids in HBM, and `show` sends the frontier sizes to hs_seen as soon as all are known.
+// Sampling of one mini-batch; out == nullptr is the pre-sampling mode (hotness only), for which `staging` may hold the
+// column ids in HBM, and with `ask` gets them before the last hop if that saves time.
 // need: the worst-case frontier sizes.
 int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops, const int64_t* need,
-                uint64_t rng_seed, const lgp_sample_out* out, hipStream_t s, const int32_t* staged = nullptr,
-                bool show = false) {
+                uint64_t rng_seed, const lgp_sample_out* out, hipStream_t s, Staging* staging = nullptr,
+                bool ask = false) {
   const bool hot_mode = (out == nullptr);
   const int64_t V = c->g.num_vertices;
   const bool want_last = !hot_mode && out->frontier[n_hops] != nullptr;
@@ -402,20 +461,23 @@ int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t
   uint32_t* gbits32 = reinterpret_cast<uint32_t*>(maps.gather);
   int32_t* n_frontier = hot_mode ? c->hs_n : out->n_frontier;
   TopoView tv = topo_view(c);
-  if (staged) {
-    tv.h_indices = staged;
+  auto use_staged = [&] {
+    if (!staging || !staging->ids) return;
+    tv.h_indices = staging->ids;
     tv.over_pcie = false;
-  }
+  };
+  use_staged();
 
   const int32_t* frontier = seeds;
   int64_t cap = n_seeds;
+  int asked = LGP_OK;                              // a failure there ends the call when the maps are clear again
   for (int h = 0; h < n_hops; ++h) {
     // the last hop's samples only feed the gather set, so they are marked there directly -- unless
     // the caller wants the last frontier as a list of its own
     const bool final_hop = h + 1 == n_hops;
-    if (final_hop && show) {
-      LGP_HIP(c, hipMemcpyAsync(c->hs_seen, c->hs_n, sizeof(int32_t) * size_t(n_hops), hipMemcpyDeviceToHost, s));
-      LGP_HIP(c, hipEventRecord(c->ev_seen, s));
+    if (final_hop && ask) {
+      asked = stage_topology(c, n_seeds, n_hops, s, staging);
+      use_staged();
     }
     launch_sample_hop(di, tv, frontier, n_frontier + h, cap, fanouts[h], h, rng_seed,
                       hot_mode ? nullptr : out->nbr[h], hot_mode ? nullptr : out->cnt[h],
@@ -437,7 +499,7 @@ int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t
     launch_compact_gather(di, maps, out->gather_ids, out->gather_cap, out->n_gather, c->d_err, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail_hip(c, e, "sampling kernel launch");
-  return LGP_OK;
+  return asked;
 }
 
 // Ranking + Eq. 3 / Eq. 6 sizes.  Leaves order_t / order_f filled; returns the
@@ -658,56 +720,6 @@ int gather_core(lgp_ctx* c, int32_t member, const int32_t* ids, int64_t n_max, c
   return LGP_OK;
 }
 
-// Whether lgp_build_hotness may copy the column ids to HBM after its first mini-batch: 24 MB, half a millisecond of the
-// link, are to be saved.  expected_marks gives more rows than are read where popularity is skewed (2.4 M vertices, 8192 seeds,
-// 15-10-5: 530 k, 263 k), so half of what it says is taken.  A topology cache that is in place already serves the rows that
-// are read often, so nothing is copied beside it; nor is anything waited for or allocated under capture, nor more than half of
-// the free memory taken (asked before anything is enqueued: beside running kernels hipMemGetInfo took up to 0.6 ms).
-constexpr double kStageSaving = 24e6;
-size_t stage_bytes(const lgp_ctx* c) { return size_t(c->g.num_edges) * 4 + 16; }
-double stage_saving(const lgp_ctx* c, double rows, int64_t remaining) {   // bytes over PCIe, a 128-byte line per row
-  return rows * double(remaining) * 128.0 - double(c->g.num_edges) * 4.0;
-}
-bool may_stage(lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts, int32_t n_hops, int64_t n_batches, hipStream_t s) {
-  if (!c->indices_on_host || c->reserved || c->plan.n_topo > 0 || n_batches < 2) return false;
-  double rows = 0;
-  const double degree = double(c->g.num_edges) / double(c->g.num_vertices);
-  expected_marks(c, n_seeds, fanouts, n_hops, [&](int32_t f) { return std::min(degree, double(f)); }, &rows);
-  if (stage_saving(c, 0.5 * rows, n_batches - 1) < kStageSaving) return false;
-  hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-  size_t free_bytes = 0, total_bytes = 0;
-  if (hipStreamIsCapturing(s, &capturing) == hipSuccess && capturing == hipStreamCaptureStatusNone &&
-      hipMemGetInfo(&free_bytes, &total_bytes) == hipSuccess && stage_bytes(c) <= free_bytes / 2 &&
-      (c->ev_seen || hipEventCreateWithFlags(&c->ev_seen, hipEventDisableTiming) == hipSuccess) &&
-      (c->hs_seen || hipHostMalloc(reinterpret_cast<void**>(&c->hs_seen), LGP_MAX_HOPS * sizeof(int32_t), hipHostMallocDefault) ==
-                         hipSuccess))
-    return true;
-  (void)hipGetLastError();
-  return false;
-}
-
-// The copy, if the rows that the first mini-batch reads say that it saves time; else, and where memory is short, *staged
-// stays null and rows are read in place.  The host waits for the frontier sizes, which are known before the last hop: what
-// follows is enqueued while that runs.  With the room taken beforehand and the decision on the device, calls on skewed graphs
-// left the room unused (8 M vertices, 115 M edges, 8 batches, rows in place: 460 MB and 5090 us a call; now none and 5020, and
-// 5000 with no question asked).
-int stage_topology(lgp_ctx* c, int64_t n_seeds, int32_t n_hops, int64_t remaining, hipStream_t s, void** room,
-                   const int32_t** staged) {
-  LGP_HIP(c, hipEventSynchronize(c->ev_seen));
-  double rows = double(n_seeds);
-  for (int h = 1; h < n_hops; ++h) rows += double(c->hs_seen[h]);
-  if (stage_saving(c, rows, remaining) <= 0) return LGP_OK;
-  if (hipMallocAsync(room, stage_bytes(c), s) != hipSuccess) {
-    (void)hipGetLastError();
-    *room = nullptr;
-    return LGP_OK;
-  }
-  int32_t* const to = static_cast<int32_t*>(*room) + ((uintptr_t(c->g.indices) >> 2) & 3);
-  launch_stage_topology(c->g.indices, to, c->g.num_edges, s);
-  *staged = to;
-  return LGP_OK;
-}
-
 }  // namespace
 
 extern "C" {
@@ -902,16 +914,15 @@ int lgp_build_hotness(lgp_ctx* c, const int32_t* train_ids, int64_t n_train, int
   launch_fill_i32(c->di, reinterpret_cast<int32_t*>(c->topo_hot), V, 0, s);
   launch_fill_i32(c->di, reinterpret_cast<int32_t*>(c->feat_hot), V, 0, s);
   launch_fill_i32(c->di, reinterpret_cast<int32_t*>(c->hs_expansions), 2, 0, s);
-  void* room = nullptr;
-  const int32_t* staged = nullptr;
+  Staging staging;
+  staging.remaining = n_batches - 1;
   for (int64_t b = 0; b < n_batches && st == LGP_OK; ++b) {
     const int64_t lo = b * batch;
     const int32_t nb = int32_t(std::min<int64_t>(batch, n_train - lo));
-    if (may && b == 1 && (st = stage_topology(c, need[0], n_hops, n_batches - 1, s, &room, &staged)) != LGP_OK) break;
-    st = sample_core(c, train_ids + lo, nb, fanouts, n_hops, need, base_seed + uint64_t(b), nullptr, s, staged, may && b == 0);
+    st = sample_core(c, train_ids + lo, nb, fanouts, n_hops, need, base_seed + uint64_t(b), nullptr, s, &staging, may && b == 0);
   }
-  if (room) {
-    const hipError_t e = hipFreeAsync(room, s);
+  if (staging.room) {
+    const hipError_t e = hipFreeAsync(staging.room, s);
     if (e != hipSuccess && st == LGP_OK) st = fail_hip(c, e, "giving back the room of the staged topology");
   }
   if (st != LGP_OK) return st;

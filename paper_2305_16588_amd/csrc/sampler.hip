@@ -33,7 +33,7 @@ __global__ __launch_bounds__(kBinThreads, 8) void sample_hop_binned_kernel(HopAr
 // lines/s = 43.5 GB/s when every line stands alone), and comes back to the same rows batch after batch; all column ids in
 // order cross the link at 57 GB/s, once.  16 batches of 8192 seeds (15, 10, 5) on 2.4 M vertices and 62 M edges:
 // 0.79 ms a batch over PCIe, 4.4 ms for the copy and 0.08 ms a batch from HBM; the call with the vectors' copy to the host
-// 16.1 -> 7.9 ms, 8 batches of 4555 seeds (11, 11, 11) on 0.87 M vertices and 30 M edges 5.6 -> 3.7.
+// 16.1 -> 6.8 ms, 8 batches of 4555 seeds (11, 11, 11) on 0.87 M vertices and 30 M edges 5.6 -> 3.2.
 // 64 workgroups keep the link full (57.5 GB/s; 55.5 at 1024).
 constexpr int kStageGroups = 64;
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
