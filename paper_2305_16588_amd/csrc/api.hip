@@ -628,10 +628,10 @@ int check_rows(lgp_ctx* c, const int32_t* ids, int64_t n_max, const void* out) {
 // fixed != nullptr: the counters and lists live in that caller-provided block (kStaticHeadWords words, then
 // 2 * n_lists lists of fixed_cap entries); nothing is allocated, created or timed on this path.
 // window != nullptr (device {begin, end}): only those entries of ids are extracted, into the output rows of the
-// same numbers; window_items bounds their count (for sizing the grids).
+// same numbers; window_items bounds their count (for sizing the grids).  zeroed: the counters are zero.
 int gather_core(lgp_ctx* c, int32_t member, const int32_t* ids, int64_t n_max, const int32_t* n_dev, void* out,
                        int32_t* stats, void* stream, int32_t* fixed = nullptr, int64_t fixed_cap = 0,
-                       const int32_t* window = nullptr, int64_t window_items = 0) {
+                       const int32_t* window = nullptr, int64_t window_items = 0, bool zeroed = false) {
   const int checked = check_rows(c, ids, n_max, out);
   if (checked != LGP_OK) return checked;
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -677,7 +677,7 @@ int gather_core(lgp_ctx* c, int32_t member, const int32_t* ids, int64_t n_max, c
     ev = prof_begin(c, PK_PARTITION, s);
     launch_partition(c->di, ids, n_max, n_dev, c->f_remap, V, L, three ? 3 : 2,
                      three ? int32_t(c->clique_fn[member]) : 0, three ? int32_t(c->clique_fn[member + 1]) : 0, counters,
-                     c->d_err, s, window, window_items);
+                     c->d_err, s, window, window_items, zeroed);
     prof_end(c, ev, s);
     // Hits and misses in one launch, unless they are to be timed apart or run on two streams.
     const RowSources both{L, counters, DirectIds{nullptr, 0, nullptr, 0, nullptr, nullptr}, n_max, window ? window_items : 0,
@@ -1354,15 +1354,23 @@ int lgp_sample_extract(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const 
   uint32_t* fbits32 = reinterpret_cast<uint32_t*>(c->maps.frontier);
   uint32_t* gbits32 = reinterpret_cast<uint32_t*>(c->maps.gather);
   const int n_groups = n_hops + 1;
-  launch_begin_listing(c->di, seeds, n_seeds, out->gather_ids, c->seg, c->seg_counters, n_groups * 3, s);
+  int32_t* const seg = groups ? groups : c->seg;
   // Group g of the listing -- the seeds, then what hop g - 1 reached first -- is extracted in the launch that samples hop g;
   // the last one, and groups whose hits and misses are timed apart or run on two streams, by launches of their own.
+  // The first group is the seeds themselves, which the first hop lists.
   // A failed step stops the enqueueing but not the clean-up below: the bitmaps must be clear whatever the call returns.
   const bool beside = c->row_bytes >= 16 && c->profiling == 0 && !c->overlap;
   auto extract = [&](int g) {
-    return gather_core(c, -1, out->gather_ids, out->gather_cap, nullptr, rows, c->seg_counters + 3 * g, s, nullptr, 0, c->seg + g,
-                       std::max<int64_t>(need[g], 1));
+    if (g == 0) return gather_core(c, -1, seeds, n_seeds, nullptr, rows, c->seg_counters, s);
+    return gather_core(c, -1, out->gather_ids, out->gather_cap, nullptr, rows, c->seg_counters + 3 * g, s, nullptr, 0, seg + g,
+                       std::max<int64_t>(need[g], 1), true);
   };
+  FirstGroup first;
+  first.listed = out->gather_ids;
+  first.seg = seg;
+  first.zeroed = c->seg_counters + 3;
+  first.n_zeroed = n_hops * 3;
+  bool cleared = false;
   const int32_t* frontier = seeds;
   int64_t cap = n_seeds;
   for (int h = 0; h < n_hops && st == LGP_OK; ++h) {
@@ -1370,40 +1378,44 @@ int lgp_sample_extract(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const 
     if (beside) {
       int32_t* const counters = c->seg_counters + 3 * h;
       RowSources r = {};
-      r.n_max = out->gather_cap;
+      const int32_t* const ids = h == 0 ? seeds : out->gather_ids;
+      const int32_t* const window = h == 0 ? nullptr : seg + h;
+      r.n_max = h == 0 ? n_seeds : out->gather_cap;
       r.grid_items = std::max<int64_t>(need[h], 1);
       r.hits = !none;
       r.misses = !all;
       if (all || none) {
-        r.lists.src[none] = out->gather_ids;
-        r.direct = DirectIds{all && !c->fc_identity ? c->f_remap : nullptr, c->g.num_vertices, counters, none, c->d_err, c->seg + h};
+        r.lists.src[none] = const_cast<int32_t*>(ids);       // only read
+        r.direct = DirectIds{all && !c->fc_identity ? c->f_remap : nullptr, c->g.num_vertices, counters, none, c->d_err, window};
       } else {
         r.lists = part_lists(c->lists, c->list_cap, 2);
         r.counters = counters;
-        launch_partition(c->di, out->gather_ids, r.n_max, nullptr, c->f_remap, c->g.num_vertices, r.lists, 2, 0, 0, counters,
-                         c->d_err, s, c->seg + h, r.grid_items);
+        launch_partition(c->di, ids, r.n_max, nullptr, c->f_remap, c->g.num_vertices, r.lists, 2, 0, 0, counters,
+                         c->d_err, s, window, r.grid_items, h > 0);
       }
       launch_hop_and_rows(c->di, tv, frontier, out->n_frontier + h, cap, fanouts[h], h, rng_seed, out->nbr[h], out->cnt[h],
                           fbits32, self, c->d_err, c->maps.status, c->maps.geom.groups, r, c->fc, c->g.features, rows,
-                          c->row_bytes, s);
+                          c->row_bytes, s, h == 0 ? first : FirstGroup{});
     } else {
       if ((st = extract(h)) != LGP_OK) break;
       launch_sample_hop(c->di, tv, frontier, out->n_frontier + h, cap, fanouts[h], h, rng_seed, out->nbr[h], out->cnt[h],
-                        fbits32, self, nullptr, c->d_err, c->maps.status, c->maps.geom.groups, s);
+                        fbits32, self, nullptr, c->d_err, c->maps.status, c->maps.geom.groups, s,
+                        h == 0 ? first : FirstGroup{});
     }
     // next frontier (if anyone needs it as a list) and the vertices this hop reached first, appended to the listing
     const bool last = h + 1 == n_hops;
     const bool want = !last || out->frontier[n_hops] != nullptr;
     int32_t* next = want ? out->frontier[h + 1] : nullptr;
     launch_compact_new(c->di, c->maps, next, next ? out->cap[h + 1] : 0, want ? out->n_frontier + h + 1 : nullptr,
-                       out->gather_ids, out->gather_cap, c->seg + h + 1, last ? out->n_gather : nullptr, c->d_err, s);
+                       out->gather_ids, out->gather_cap, seg + h + 1, last ? out->n_gather : nullptr, last,
+                       all || none ? stats : nullptr, none, c->d_err, s);
+    cleared = last;
     frontier = next;
     cap = need[h + 1];
   }
   if (st == LGP_OK) st = extract(n_hops);
-  // the "seen" bitmap of this batch is not compacted (the listing replaces the ascending list), so it is cleared whole
-  launch_end_listing(c->di, c->maps.gather, c->maps.geom.words(), c->seg, c->seg_counters, n_groups, st == LGP_OK ? groups : nullptr,
-                     st == LGP_OK ? stats : nullptr, s);
+  if (!cleared) launch_clear_map(c->di, c->maps.gather, c->maps.geom.words(), s);
+  else if (st == LGP_OK && stats && !all && !none) launch_sum_counters(c->seg_counters, n_groups, stats, s);
   if (st != LGP_OK) return st;
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail_hip(c, e, "intra-batch pipeline launch");

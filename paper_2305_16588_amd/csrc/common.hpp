@@ -149,16 +149,27 @@ struct TopoView {
 };
 
 // ---- sampler.hip ----------------------------------------------------------
+// What the first hop of the intra-batch pipeline does beside: listed[0 .. n_seeds) = the seeds, seg[0] = 0, seg[1] = n_seeds, and
+// zeroed[0 .. n_zeroed) = 0 (at most 256), the counters of the groups behind the seeds.  A launch ahead of the pipeline for that, one
+// behind it that cleared the map and copied the bounds, and one per partition that zeroed its counters were small ones of 4 to 5 us:
+// calls with them -> without, 8192 seeds (15, 10, 5) of 2.4 M vertices, 400-byte rows, all cached 143.7 -> 138, (10) 23.9 -> 19.2;
+// (25, 10) of 10 M, 256-byte rows 64.7 -> 60.0; 4000 (10, 10, 5) of 1 M, 256-byte rows, 90 % cached 113.5 -> 103.6.
+struct FirstGroup {
+  int32_t* listed = nullptr;
+  int32_t* seg = nullptr;
+  int32_t* zeroed = nullptr;
+  int32_t n_zeroed = 0;
+};
 // Expand frontier[0 .. *n_frontier) with fan-out f at hop `hop`; the array has room for `cap` ids.  Writes nbr / cnt
 // (either may be null), marks every sampled neighbour in `mark_bits` (bit v << di.spread_shift),
 // adds cnt to topo_hot[v] if topo_hot is given.  With self_bits given (first hop) the
 // frontier is the seed list: exactly `cap` ids, *n_frontier is written (= cap) instead of
-// read, and every valid seed is marked in self_bits.  status[0 .. n_status) is cleared for the compaction
+// read, and every valid seed is marked in self_bits (and listed as `first` says).  status[0 .. n_status) is cleared for the compaction
 // that follows.
 void launch_sample_hop(const DeviceInfo& di, const TopoView& tv, const int32_t* frontier, int32_t* n_frontier,
                        int64_t cap, int32_t fanout, int32_t hop, uint64_t rng_seed, int32_t* nbr, int32_t* cnt,
                        uint32_t* mark_bits, uint32_t* self_bits, uint32_t* topo_hot, uint32_t* d_err, uint64_t* status,
-                       int64_t n_status, hipStream_t s);
+                       int64_t n_status, hipStream_t s, const FirstGroup& first = FirstGroup{});
 
 // The same for binned marks: no hotness, and seeds are not marked; what finds no room is marked in mark_bits.  status[0 ..
 // kBinStatusWords) of 32 bits is cleared.  Returns the number of workgroups, which is the number of segments of a bin.
@@ -181,6 +192,8 @@ struct CompactArgs {
   int64_t out2_cap;
   int32_t* n_out2;
   int32_t* seg;
+  int32_t* stats;     // last listing: stats[stats_slot] = its length, the other one of the two = 0; may be null
+  int32_t stats_slot;
   uint32_t* d_err;
   int32_t shift, passes;
   int32_t polls;      // looks at a status word before the share is counted instead
@@ -198,10 +211,10 @@ void launch_compact_both(const DeviceInfo& di, const DedupMaps& m, int32_t* out,
 // Compaction for the intra-batch pipeline: like launch_compact, and in addition the vertices not yet in the gather
 // map -- the ones this hop reached first -- are appended, ascending, to listed[seg[0] ..], and seg[1] = seg[0] +
 // their number (seg: device int32 pair).  With out == nullptr no frontier list is written; n_listed, if given, also
-// receives seg[1].
+// receives seg[1].  last: no hop follows; both maps are cleared, and stats, if given, receives {0, 0} but for seg[1] at stats_slot.
 void launch_compact_new(const DeviceInfo& di, const DedupMaps& m, int32_t* out, int64_t out_cap, int32_t* n_out,
-                        int32_t* listed, int64_t listed_cap, int32_t* seg, int32_t* n_listed, uint32_t* d_err,
-                        hipStream_t s);
+                        int32_t* listed, int64_t listed_cap, int32_t* seg, int32_t* n_listed, bool last, int32_t* stats,
+                        int32_t stats_slot, uint32_t* d_err, hipStream_t s);
 // Pre-sampling: bump[id] += 1 for every id of the gather map, which is cleared; acc[0] += sizes[0] + ... (the
 // frontier sizes of the batch).
 void launch_bump(const DeviceInfo& di, const DedupMaps& m, uint32_t* bump, const int32_t* sizes, int32_t n_sizes,
@@ -236,7 +249,7 @@ void launch_list_bins(const BinArgs& a, hipStream_t s);
 // Look up every id in the feature remap and append (row, slot) to the hit list (list 0) or
 // (row, id) to the miss list (list 1).  With n_lists = 3, hits whose slot lies outside
 // [local_lo, local_hi) go to list 2 instead: rows cached by another member of a clique.
-// counters[l] = entries of list l, l < n_lists (zeroed here).
+// counters[l] = entries of list l, l < n_lists (zeroed here, unless the caller says that they are zero).
 struct PartLists {
   int32_t* row[3];
   int32_t* src[3];
@@ -244,7 +257,7 @@ struct PartLists {
 void launch_partition(const DeviceInfo& di, const int32_t* ids, int64_t n_max, const int32_t* n_dev,
                       const int32_t* f_remap, int64_t num_vertices, const PartLists& out, int n_lists,
                       int32_t local_lo, int32_t local_hi, int32_t* counters, uint32_t* d_err, hipStream_t s,
-                      const int32_t* window = nullptr, int64_t grid_items = 0);
+                      const int32_t* window = nullptr, int64_t grid_items = 0, bool zeroed = false);
 // "Direct" launches skip the partition: when every row is cached (or none is) the source-row
 // array is the caller's id list itself.
 struct DirectIds {
@@ -293,14 +306,12 @@ int split_args(const DeviceInfo& di, const RowSources& r, const void* hit_src, c
 void launch_hop_and_rows(const DeviceInfo& di, const TopoView& tv, const int32_t* frontier, int32_t* n_frontier, int64_t cap,
                          int32_t fanout, int32_t hop, uint64_t rng_seed, int32_t* nbr, int32_t* cnt, uint32_t* mark_bits,
                          uint32_t* self_bits, uint32_t* d_err, uint64_t* status, int64_t n_status, const RowSources& r,
-                         const void* hit_src, const void* miss_src, void* dst, int64_t row_bytes, hipStream_t s);
-// seg[0] = 0, seg[1] = n_seeds, listed[0 .. n_seeds) = seeds, counters[0 .. n_counters) = 0.
-void launch_begin_listing(const DeviceInfo& di, const int32_t* seeds, int64_t n_seeds, int32_t* listed, int32_t* seg,
-                          int32_t* counters, int32_t n_counters, hipStream_t s);
-// Clears words 64-bit words of a map; groups[0 .. n_seg] = seg[0 .. n_seg], stats[0 .. 2) = column sums of the n_seg x 3 matrix
-// seg_counters (first two columns); either may be null.
-void launch_end_listing(const DeviceInfo& di, uint64_t* map, int64_t words, const int32_t* seg, const int32_t* seg_counters,
-                        int32_t n_seg, int32_t* groups, int32_t* stats, hipStream_t s);
+                         const void* hit_src, const void* miss_src, void* dst, int64_t row_bytes, hipStream_t s,
+                         const FirstGroup& first = FirstGroup{});
+// stats[0 .. 2) = column sums of the n_seg x 3 matrix seg_counters, first two columns.
+void launch_sum_counters(const int32_t* seg_counters, int32_t n_seg, int32_t* stats, hipStream_t s);
+// Clears words 64-bit words of a map.
+void launch_clear_map(const DeviceInfo& di, uint64_t* map, int64_t words, hipStream_t s);
 
 // ---- blocks.hip -----------------------------------------------------------
 constexpr int kScanTile = 1024;   // elements per workgroup of the counts -> offsets scan

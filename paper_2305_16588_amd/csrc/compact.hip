@@ -33,7 +33,8 @@ constexpr int kMaxSubs = kMaxPasses * 4;         // sub-passes of two words in a
 enum Mode {
   kList,      // `other`, if given, receives the marks (OR)
   kListUnion, // second list: marks of `bits` or `other`; both maps are cleared
-  kListNew    // second list, appended at seg[0]: marks not yet in `other`; `other` receives the marks (OR)
+  kListNew,   // second list, appended at seg[0]: marks not yet in `other`; `other` receives the marks (OR)
+  kListLast   // the same, but both maps are cleared
 };
 
 struct Words {
@@ -58,7 +59,7 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
 // Marks of one word that go to the second list.
 template <Mode M>
 __device__ __forceinline__ uint64_t second(uint64_t x, uint64_t y) {
-  return M == kListUnion ? (x | y) : M == kListNew ? (x & ~y) : 0ull;
+  return M == kListUnion ? (x | y) : M == kListNew || M == kListLast ? (x & ~y) : 0ull;
 }
 
 // Marks of one word, both lists' counts in one register (low and high half).
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(kCompactThreads, 8) void compact_kernel(CompactArgs
   constexpr int S = M == kList && W >= 4 ? 4 : 2;
   constexpr int NS = W / S;
   constexpr int kEntries = S * kCompactThreads;
-  constexpr bool kDual = M != kList;
+  constexpr bool kDual = M != kList, kNew = M == kListNew || M == kListLast, kClear = M == kListUnion || M == kListLast;
   // counts per wave and sub-pass: at most 64 * S * 64 <= 16384 marks per list, both lists in one word
   __shared__ uint32_t wave_count[REREAD ? kMaxSubs : NS][kWaves];
   __shared__ uint32_t wave_total[kWaves], wave_total2[kWaves], wave_before[kWaves], wave_before2[kWaves];
@@ -173,7 +174,7 @@ __global__ __launch_bounds__(kCompactThreads, 8) void compact_kernel(CompactArgs
   if (threadIdx.x == 0)
     __hip_atomic_store(&a.status[blockIdx.x], mine | kPublished, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
-  const uint32_t base2 = M == kListNew ? uint32_t(a.seg[0]) : 0;
+  const uint32_t base2 = kNew ? uint32_t(a.seg[0]) : 0;
   const uint32_t cap = uint32_t(a.out ? a.out_cap : 0), cap2 = uint32_t(a.out2_cap);      // below 2^31 (capacity())
   uint32_t pos = 0, pos2 = 0;                 // where the ids of the sub-pass begin
   for (int p = 0; p < passes; ++p) {
@@ -207,7 +208,7 @@ __global__ __launch_bounds__(kCompactThreads, 8) void compact_kernel(CompactArgs
       int n_wave = 0;
 #pragma unroll
       for (int j = 0; j < S; ++j) {
-        filled[j] = __ballot((x[s][j] | (M == kListUnion ? y[s][j] : 0)) != 0);
+        filled[j] = __ballot((x[s][j] | (kClear ? y[s][j] : 0)) != 0);
         n_wave += __popcll(filled[j]);
       }
       int slot = 0;
@@ -258,7 +259,11 @@ __global__ __launch_bounds__(kCompactThreads, 8) void compact_kernel(CompactArgs
               atomicOr(a.d_err, ERR_OVERRUN);
               end = a.out2_cap;
             }
-            if (M == kListNew) a.seg[1] = int32_t(end);
+            if (kNew) a.seg[1] = int32_t(end);
+            if (M == kListLast && a.stats) {
+              a.stats[a.stats_slot] = int32_t(end);
+              a.stats[1 - a.stats_slot] = 0;
+            }
             if (a.n_out2) *a.n_out2 = int32_t(end);
           }
         }
@@ -288,7 +293,7 @@ __global__ __launch_bounds__(kCompactThreads, 8) void compact_kernel(CompactArgs
             ++at2;
           }
         }
-        if (M == kListUnion) {
+        if (kClear) {
           if (yw) *word_at(a.other, wi) = 0;
         } else if (kDual || a.other) {
           *word_at(a.other, wi) = yw | xw;
@@ -378,14 +383,17 @@ void launch_compact_both(const DeviceInfo& di, const DedupMaps& m, int32_t* out,
 }
 
 void launch_compact_new(const DeviceInfo& di, const DedupMaps& m, int32_t* out, int64_t out_cap, int32_t* n_out,
-                        int32_t* listed, int64_t listed_cap, int32_t* seg, int32_t* n_listed, uint32_t* d_err,
-                        hipStream_t s) {
+                        int32_t* listed, int64_t listed_cap, int32_t* seg, int32_t* n_listed, bool last, int32_t* stats,
+                        int32_t stats_slot, uint32_t* d_err, hipStream_t s) {
   CompactArgs a = base_args(di, m, out, out_cap, n_out, d_err);
   a.out2 = listed;
   a.out2_cap = capacity(listed_cap);
   a.n_out2 = n_listed;
   a.seg = seg;
-  launch_mode<kListNew>(m.geom, a, s);
+  a.stats = stats;
+  a.stats_slot = stats_slot;
+  if (last) launch_mode<kListLast>(m.geom, a, s);
+  else launch_mode<kListNew>(m.geom, a, s);
 }
 
 void launch_bump(const DeviceInfo& di, const DedupMaps& m, uint32_t* bump, const int32_t* sizes, int32_t n_sizes,

@@ -21,29 +21,16 @@ __global__ __launch_bounds__(256) void hop_and_rows_kernel(HopArgs h, SplitArgs 
   else split_hits<HitWalk::kGroups>(a, blockIdx.x - a.miss_blocks - hop_groups, a.hit_blocks);
 }
 
-__global__ __launch_bounds__(256) void begin_listing_kernel(const int32_t* __restrict__ seeds, int64_t n_seeds,
-                                                            int32_t* __restrict__ listed, int32_t* __restrict__ seg,
-                                                            int32_t* __restrict__ counters, int32_t n_counters) {
-  const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (t == 0) {
-    seg[0] = 0;
-    seg[1] = int32_t(n_seeds);
-  }
-  if (t < n_counters) counters[t] = 0;
-  for (int64_t i = t; i < n_seeds; i += int64_t(gridDim.x) * 256) listed[i] = seeds[i];
+__global__ __launch_bounds__(64) void sum_counters_kernel(const int32_t* __restrict__ seg_counters, int32_t n_seg,
+                                                          int32_t* __restrict__ stats) {
+  if (threadIdx.x >= 2) return;
+  int32_t sum = 0;
+  for (int32_t k = 0; k < n_seg; ++k) sum += seg_counters[3 * k + threadIdx.x];
+  stats[threadIdx.x] = sum;
 }
 
-__global__ __launch_bounds__(256) void end_listing_kernel(uint64_t* __restrict__ map, int64_t words,
-                                                          const int32_t* __restrict__ seg,
-                                                          const int32_t* __restrict__ seg_counters, int32_t n_seg,
-                                                          int32_t* __restrict__ groups, int32_t* __restrict__ stats) {
+__global__ __launch_bounds__(256) void clear_map_kernel(uint64_t* __restrict__ map, int64_t words) {
   const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  if (groups && t <= n_seg) groups[t] = seg[t];
-  if (stats && t < 2) {
-    int32_t sum = 0;
-    for (int32_t k = 0; k < n_seg; ++k) sum += seg_counters[3 * k + t];
-    stats[t] = sum;
-  }
   for (int64_t k = t * 2; k < words; k += int64_t(gridDim.x) * 512)       // a map has a multiple of 2048 words
     *reinterpret_cast<ulonglong2*>(map + k) = make_ulonglong2(0, 0);
 }
@@ -53,9 +40,14 @@ __global__ __launch_bounds__(256) void end_listing_kernel(uint64_t* __restrict__
 void launch_hop_and_rows(const DeviceInfo& di, const TopoView& tv, const int32_t* frontier, int32_t* n_frontier, int64_t cap,
                          int32_t fanout, int32_t hop, uint64_t rng_seed, int32_t* nbr, int32_t* cnt, uint32_t* mark_bits,
                          uint32_t* self_bits, uint32_t* d_err, uint64_t* status, int64_t n_status, const RowSources& r,
-                         const void* hit_src, const void* miss_src, void* dst, int64_t row_bytes, hipStream_t s) {
-  const HopArgs h{tv,  frontier, n_frontier, cap,       fanout,  hop_lanes(tv, fanout), hop,    uint32_t(rng_seed), uint32_t(rng_seed >> 32),
+                         const void* hit_src, const void* miss_src, void* dst, int64_t row_bytes, hipStream_t s,
+                         const FirstGroup& first) {
+  HopArgs h{tv,  frontier, n_frontier, cap,       fanout,  hop_lanes(tv, fanout), hop,    uint32_t(rng_seed), uint32_t(rng_seed >> 32),
                   nbr, cnt,      mark_bits,  self_bits, nullptr, d_err,                 status, int32_t(n_status)};
+  h.listed = first.listed;
+  h.seg = first.seg;
+  h.zeroed = first.zeroed;
+  h.n_zeroed = first.n_zeroed;
   SplitArgs a;
   const int width = split_args(di, r, hit_src, miss_src, dst, row_bytes, &a);
   const uint32_t hop_groups = hop_blocks(di, cap, h.lanes);
@@ -77,21 +69,14 @@ void launch_hop_and_rows(const DeviceInfo& di, const TopoView& tv, const int32_t
   }
 }
 
-void launch_begin_listing(const DeviceInfo& di, const int32_t* seeds, int64_t n_seeds, int32_t* listed, int32_t* seg,
-                          int32_t* counters, int32_t n_counters, hipStream_t s) {
-  int64_t blocks = (n_seeds + 255) / 256;
-  if (blocks > di.num_cus * 4) blocks = di.num_cus * 4;
-  if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(begin_listing_kernel, dim3(unsigned(blocks)), dim3(256), 0, s, seeds, n_seeds, listed, seg,
-                     counters, n_counters);
+void launch_sum_counters(const int32_t* seg_counters, int32_t n_seg, int32_t* stats, hipStream_t s) {
+  hipLaunchKernelGGL(sum_counters_kernel, dim3(1), dim3(64), 0, s, seg_counters, n_seg, stats);
 }
 
-void launch_end_listing(const DeviceInfo& di, uint64_t* map, int64_t words, const int32_t* seg, const int32_t* seg_counters,
-                        int32_t n_seg, int32_t* groups, int32_t* stats, hipStream_t s) {
+void launch_clear_map(const DeviceInfo& di, uint64_t* map, int64_t words, hipStream_t s) {
   int64_t blocks = (words + 511) / 512;
   if (blocks > di.num_cus * 8) blocks = di.num_cus * 8;
-  hipLaunchKernelGGL(end_listing_kernel, dim3(unsigned(blocks)), dim3(256), 0, s, map, words, seg, seg_counters, n_seg, groups,
-                     stats);
+  hipLaunchKernelGGL(clear_map_kernel, dim3(unsigned(blocks)), dim3(256), 0, s, map, words);
 }
 
 }  // namespace lgp

@@ -325,7 +325,7 @@ uint32_t group_lanes(const RowShape& r) {
 void launch_partition(const DeviceInfo& di, const int32_t* ids, int64_t n_max, const int32_t* n_dev,
                       const int32_t* f_remap, int64_t num_vertices, const PartLists& out, int n_lists,
                       int32_t local_lo, int32_t local_hi, int32_t* counters, uint32_t* d_err, hipStream_t s,
-                      const int32_t* window, int64_t grid_items) {
+                      const int32_t* window, int64_t grid_items, bool zeroed) {
   const bool three = n_lists == 3;
   const int64_t items = (window && grid_items > 0 && grid_items < n_max) ? grid_items : n_max;
   auto launch = [&](auto two_lists, auto three_lists, int64_t blocks, int threads) {
@@ -340,7 +340,7 @@ void launch_partition(const DeviceInfo& di, const int32_t* ids, int64_t n_max, c
            kAloneThreads);
     return;
   }
-  hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, s, counters, three ? 3 : 2);
+  if (!zeroed) hipLaunchKernelGGL(zero_counters_kernel, dim3(1), dim3(64), 0, s, counters, three ? 3 : 2);
   int64_t blocks = (items + 256 * kPartItems - 1) / (256 * kPartItems);
   const int64_t full = int64_t(di.num_cus) * 8;
   if (blocks > full) blocks = full;

@@ -68,9 +68,13 @@ void launch_stage_topology(const int32_t* h_indices, int32_t* staged, int64_t n_
 void launch_sample_hop(const DeviceInfo& di, const TopoView& tv, const int32_t* frontier, int32_t* n_frontier,
                        int64_t cap, int32_t fanout, int32_t hop, uint64_t rng_seed, int32_t* nbr, int32_t* cnt,
                        uint32_t* mark_bits, uint32_t* self_bits, uint32_t* topo_hot, uint32_t* d_err, uint64_t* status,
-                       int64_t n_status, hipStream_t s) {
-  const HopArgs a{tv,  frontier, n_frontier, cap,       fanout,   hop_lanes(tv, fanout), hop,    uint32_t(rng_seed), uint32_t(rng_seed >> 32),
+                       int64_t n_status, hipStream_t s, const FirstGroup& first) {
+  HopArgs a{tv,  frontier, n_frontier, cap,       fanout,   hop_lanes(tv, fanout), hop,    uint32_t(rng_seed), uint32_t(rng_seed >> 32),
                   nbr, cnt,      mark_bits,  self_bits, topo_hot, d_err,                 status, int32_t(n_status)};
+  a.listed = first.listed;
+  a.seg = first.seg;
+  a.zeroed = first.zeroed;
+  a.n_zeroed = first.n_zeroed;
   const dim3 grid{hop_blocks(di, cap, a.lanes)}, block{256};
   switch (di.spread_shift) {
     case 0: hipLaunchKernelGGL((sample_hop_kernel<0>), grid, block, 0, s, a); break;

@@ -63,6 +63,10 @@ struct HopArgs {
   uint64_t* status;
   int32_t n_status;
   BinMaps bins;            // of a binned hop
+  int32_t* listed;         // first hop of the intra-batch pipeline: the seeds are listed there as given, and
+  int32_t* seg;            // seg[0], seg[1] are the bounds of that group,
+  int32_t* zeroed;         // and the n_zeroed counters of the groups behind it are cleared
+  int32_t n_zeroed;
 };
 
 // Append vertex u to this workgroup's segment of its bin; used = entries of those segments, by bin (LDS).
@@ -98,9 +102,17 @@ __device__ __forceinline__ void sample_hop(const HopArgs& a, uint32_t block, uin
   // self_bits != nullptr: this is the first hop; the frontier is the caller's seed list of `cap`
   // ids, whose size is published here and whose members are marked in the gather set.
   const bool seeds = SHIFT == kBinned ? a.hop == 0 : self_bits != nullptr;
-  if (seeds && block == 0 && threadIdx.x == 0) *a.n_frontier = int32_t(a.cap);
-  if (block == 0)
+  if (seeds && block == 0 && threadIdx.x == 0) {
+    *a.n_frontier = int32_t(a.cap);
+    if (a.seg) {
+      a.seg[0] = 0;
+      a.seg[1] = int32_t(a.cap);
+    }
+  }
+  if (block == 0) {
     for (int k = threadIdx.x; k < a.n_status; k += WAVES * 64) a.status[k] = 0;
+    if (int(threadIdx.x) < a.n_zeroed) a.zeroed[threadIdx.x] = 0;
+  }
   const int per_wave = 64 / lanes;                // vertices per wave pass
   const int lane = threadIdx.x & 63;
   const int sub = lane / lanes, slot = lane - sub * lanes;   // vertex of this lane in the pass, sample slot (below f)
@@ -176,7 +188,10 @@ __device__ __forceinline__ void sample_hop(const HopArgs& a, uint32_t block, uin
       }
       if (nbr) nbr[g * f + slot] = u;
       if (slot == 0) {
-        if (SHIFT != kBinned && self_bits && !bad) mark_vertex<SHIFT>(self_bits, v);
+        if (SHIFT != kBinned && self_bits) {
+          if (!bad) mark_vertex<SHIFT>(self_bits, v);
+          if (a.listed) a.listed[g] = v;
+        }
         const int32_t c = d < f ? d : f;
         if (cnt) cnt[g] = c;
         if (a.topo_hot && c > 0) atomicAdd(&a.topo_hot[v], uint32_t(c));
