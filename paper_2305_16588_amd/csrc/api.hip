@@ -365,14 +365,13 @@ int stage_topology(lgp_ctx* c, int64_t n_seeds, int32_t n_hops, hipStream_t s, S
   return LGP_OK;
 }
 
-// Whether lgp_sample_khop bins its samples (kBinMarksPerSeed).  Every bin's workgroup looks through all seeds, and reads its share of
+// Whether lgp_sample_khop bins its samples (bin_marks).  Every bin's workgroup looks through all seeds, and reads its share of
 // the inner frontiers again after all of them were written, so these must not share memory with anything the call writes.  Where rows
 // cross PCIe the link bounds the hops, and its two workgroups of 1024 threads per CU serve it a little worse (20 M vertices, 8192 seeds
 // (15, 10, 5), none and half of the topology cached 618 -> 621 and 225 -> 231 us).
-constexpr int32_t kBinMaxSeeds = 1 << 17;
 bool binned(const lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops, const int64_t* need,
             int64_t gather_need, const lgp_sample_out* out) {
-  if (c->bins.bins == 0 || n_seeds > kBinMaxSeeds || topo_view(c).over_pcie) return false;
+  if (c->bins.bins == 0 || n_seeds > bin_max_seeds(c->g.num_vertices) || topo_view(c).over_pcie) return false;
   const double enough = bin_marks(c->g.num_vertices);
   if (enough > 0 && expected_marks(c, n_seeds, fanouts, n_hops, [&](int32_t f) { return c->mean_samples[size_t(f)]; }) <
                         enough + kBinMarksPerSeed * double(n_seeds))

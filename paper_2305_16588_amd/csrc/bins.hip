@@ -50,8 +50,10 @@ typedef int32_t i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 
 template <int B>
 struct Lds {
-  static constexpr int kGroups = 1 << (B - 8);              // of 256 vertices, eight words of bits
-  uint4 bits[kGroups * 2];                                   // the groups' first halves, then their second halves
+  // The bits: 1 << B of them.  A thread ranks a span of up to 256; spans of 256 lie in halves, the first halves of all of them
+  // before the second halves, so that a wave reads either without gaps.
+  static constexpr int kSpan = B >= 18 ? 256 : 1 << (B - 10);   // 17: all threads take part (256 bits each: 17 M 44.7 -> 42.8 us a call)
+  uint4 bits[1 << (B - 7)];
   uint32_t wave_count[64], wave_ahead[kWaves];
   uint64_t late[kMaxBins / 64];
   uint32_t again, total, late_any;
@@ -62,22 +64,23 @@ enum Mode { kList = 1, kUnion = 2, kBoth = 3 };
 
 template <int B>
 struct Lister {
-  static constexpr int kGroups = Lds<B>::kGroups;
-  static constexpr int kPasses = kGroups > kBinThreads ? kGroups / kBinThreads : 1;   // groups of a thread
-  static_assert(kPasses * kWaves <= 64, "one lane per wave and pass");
+  static constexpr int kSpan = Lds<B>::kSpan, kSpans = (1 << B) / kSpan, kPasses = kSpans / kBinThreads;   // spans of a thread
+  static constexpr int kWords = kSpan / 64;
+  static_assert(kWords >= 1 && kPasses * kWaves <= 64, "one lane per wave and pass");
   const BinArgs a;                                           // by value: by reference the compiler keeps the arguments in scratch memory
   Lds<B>& m;
   uint32_t fresh;                                            // bits set by this thread and not yet counted
-  uint64_t word[kPasses][4];                                 // the bits of this thread's groups
+  uint64_t word[kPasses][kWords];                            // the bits of this thread's spans
   uint32_t rank[kPasses];                                    // ids of the bin before them
   const int t = threadIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 
   __device__ __forceinline__ void clear() const {
-    for (int k = t; k < kGroups * 2; k += kBinThreads) m.bits[k] = make_uint4(0, 0, 0, 0);
+    for (int k = t; k < 1 << (B - 7); k += kBinThreads) m.bits[k] = make_uint4(0, 0, 0, 0);
   }
   __device__ __forceinline__ void set(uint32_t x) {
     const uint32_t o = x & ((1u << B) - 1u);
-    const uint32_t old = atomicOr(reinterpret_cast<uint32_t*>(&m.bits[(o >> 8) + ((o >> 7) & 1u) * kGroups]) + ((o >> 5) & 3u), 1u << (o & 31u));
+    const uint32_t chunk = kSpan == 256 ? (o >> 8) + ((o >> 7) & 1u) * uint32_t(kSpans) : o >> 7;
+    const uint32_t old = atomicOr(reinterpret_cast<uint32_t*>(&m.bits[chunk]) + ((o >> 5) & 3u), 1u << (o & 31u));
     fresh += 1u - ((old >> (o & 31u)) & 1u);
   }
   // Whether a seed is a member of the bin; one whose offsets make no sense is no member of the batch (the hop has reported it).
@@ -177,16 +180,21 @@ struct Lister {
 #pragma unroll
     for (int p = 0; p < kPasses; ++p) {
       const int g = p * kBinThreads + t;
-      uint4 x = make_uint4(0, 0, 0, 0), y = x;
-      if (g < kGroups) {
-        x = m.bits[g];
-        y = m.bits[g + kGroups];
+      if constexpr (kSpan >= 128) {
+        const uint4 x = m.bits[g];
+        word[p][0] = x.x | uint64_t(x.y) << 32;
+        word[p][1] = x.z | uint64_t(x.w) << 32;
+        if constexpr (kSpan == 256) {
+          const uint4 y = m.bits[g + kSpans];
+          word[p][2] = y.x | uint64_t(y.y) << 32;
+          word[p][3] = y.z | uint64_t(y.w) << 32;
+        }
+      } else {
+        word[p][0] = reinterpret_cast<const uint64_t*>(m.bits)[g];
       }
-      word[p][0] = x.x | uint64_t(x.y) << 32;
-      word[p][1] = x.z | uint64_t(x.w) << 32;
-      word[p][2] = y.x | uint64_t(y.y) << 32;
-      word[p][3] = y.z | uint64_t(y.w) << 32;
-      c[p] = uint32_t(__popcll(word[p][0]) + __popcll(word[p][1]) + __popcll(word[p][2]) + __popcll(word[p][3]));
+      c[p] = 0;
+#pragma unroll
+      for (int w = 0; w < kWords; ++w) c[p] += uint32_t(__popcll(word[p][w]));
       up_to[p] = wave_inclusive_scan(c[p]);
       if (lane == 63) m.wave_count[p * kWaves + wave] = up_to[p];
     }
@@ -260,13 +268,13 @@ struct Lister {
     const uint32_t at = place(bin, others, early, with_earlier), end = at + n;
 #pragma unroll
     for (int p = 0; p < kPasses; ++p) {
-      const uint32_t id0 = (bin << B) + uint32_t(p * kBinThreads + t) * 256u;
+      const uint32_t id0 = (bin << B) + uint32_t(p * kBinThreads + t) * uint32_t(kSpan);
       uint32_t k = at + rank[p];
 #pragma unroll
-      for (uint32_t w = 0; w < 4; ++w) {
+      for (int w = 0; w < kWords; ++w) {
 #pragma unroll 1
         for (uint64_t x = word[p][w]; x; x &= x - 1, ++k)
-          if (k < cap) out[k] = int32_t(id0 + w * 64u + uint32_t(__ffsll((unsigned long long)x) - 1));
+          if (k < cap) out[k] = int32_t(id0 + uint32_t(w) * 64u + uint32_t(__ffsll((unsigned long long)x) - 1));
       }
     }
     if (t != 0) return;
@@ -338,6 +346,7 @@ template <int M>
 void launch_mode(const BinArgs& a, hipStream_t s) {
   const dim3 grid{unsigned(a.maps.bins)}, block{unsigned(kBinThreads)};
   switch (a.maps.shift) {
+    case 16: hipLaunchKernelGGL((list_bins_kernel<16, M>), grid, block, 0, s, a); break;
     case 17: hipLaunchKernelGGL((list_bins_kernel<17, M>), grid, block, 0, s, a); break;
     case 18: hipLaunchKernelGGL((list_bins_kernel<18, M>), grid, block, 0, s, a); break;
     case 19: hipLaunchKernelGGL((list_bins_kernel<19, M>), grid, block, 0, s, a); break;

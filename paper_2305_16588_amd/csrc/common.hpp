@@ -92,23 +92,26 @@ constexpr int kHeadWords = 16;        // of them in its head
 constexpr int kMaxBins = 256;         // a workgroup each, one per CU
 constexpr int kStatusCopies = 8;      // of the status words: one channel of memory does not answer all workgroups at once
 constexpr int kBinStatusWords = 2 * kStatusCopies * kMaxBins;      // of 32 bits: for the list of a hop, and for the union
-// Which calls: a hop saves about 25 us per million samples, a list from bins costs 1 to 3 us more than the compaction of a map
-// of up to 2^26 bits and less than that of one of more than 2^27.  So from expected_marks on that grow with the seeds, which every
-// bin's workgroup looks through.  Calls of lgp_sample_khop, map -> bins, and thousands of expected marks: 17 M vertices of power-law
-// degrees, 120000 seeds (10, 5) 103 -> 76 us, 2426; 8192 (15, 10, 5) 55.5 -> 44.8, 919; 16000 (10, 10) 32.6 -> 32.5, 410; 8000 (25, 10)
-// 28.0 -> 28.7, 272; 64 (15, 10, 5) 25.0 -> 32.5, 7.  60 M 90 -> 72, 1750; 49.4 -> 45.3, 540; 32.0 -> 33.0, 284; 25.9 -> 29.7, 183;
-// 29.4 -> 31.8, 4.  111 M 111 -> 84, 2087; 61.6 -> 48.5, 713; 36.5 -> 33.4, 343; 31.5 -> 30.2, 225; 28.8 -> 34.0, 6.  140 M 117 -> 83,
-// 1994; 67.5 -> 50.7, 663; 41.3 -> 36.7, 327; 35.5 -> 31.9, 213; 38.0 -> 36.2 and 33.9 -> 35.6, 5.  250 M 137 -> 97, 2248; 83.1 -> 55.5,
-// 802; 48.3 -> 36.7, 372; 41.8 -> 33.3, 245; 45.2 -> 36.4, 6.  Degrees of 12 everywhere, 111 M: 8192 (15, 10, 5) 308 -> 195, 5972; 64000
-// (10, 10) 342 -> 204, 7022.  Up to 2^24 vertices bytes or bits are as fast or faster (8192 seeds at 12 M, 8 M and 2.4 M vertices 43.6
-// -> 44.6, 49.4 -> 59.8 and 45.0 -> 60.8).
-constexpr int64_t kBinMinVertices = int64_t(1) << 24, kBinMaxVertices = int64_t(1) << 28;
+// Which calls: a hop saves about 25 us per million samples against atomics, and less against bytes; a list from bins costs 1 to 3 us
+// more than the compaction of a map of up to 2^26 bits and less than that of one of more than 2^27.  So from expected_marks on, and a
+// little more where every bin's workgroup has many seeds to look through.  Calls of lgp_sample_khop, map -> bins, and thousands of
+// expected marks: 12 M vertices of power-law degrees, 8192 seeds (15, 10, 5) 42.4 -> 40.6 us, 634; 16000 (10, 10) 27.8 -> 27.6, 317; 8000
+// (25, 10) 24.3 -> 25.9, 207.  16.5 M 63.9 -> 51.5, 1518; 38.4 -> 30.8, 582; 30.0 -> 27.0, 398; 4096 (15, 10) 23.3 -> 24.4, 173.  40 M
+// 32000 (10, 10) 46.4 -> 36.7, 709; 31.3 -> 28.7, 355; 25.5 -> 27.4, 233; 64 (15, 10, 5) 25 -> 32 whatever the size.  111 M 61.6 -> 48.5,
+// 713; 36.5 -> 33.4, 343; 31.5 -> 30.2, 225.  140 M 67.5 -> 50.7, 663; 41.3 -> 36.7, 327; 35.5 -> 31.9, 213; 64 (15, 10, 5) 33.9 -> 35.6, 5.
+// 250 M 83.1 -> 55.5, 802; 48.3 -> 36.7, 372; 41.8 -> 33.3, 245; 45.2 -> 36.4, 6.  Degrees of 12 everywhere: 12 M, 8192 (15, 10, 5) 211 ->
+// 175, 5778; 111 M 308 -> 195, 5972.  Fewer than 144 bins hold so many ids each that bytes are ahead (8.5 M vertices, 130 bins, 16000 (10,
+// 10) 31.0 -> 33.3, 8192 (15, 10, 5) 59.1 -> 57.0), as they are on small graphs (2.4 M, 44.1 -> 49.9), and with 120000 seeds (10, 5) of
+// 16.5 M vertices, degrees of 12 and the last frontier (230 -> 237; 250 M and power-law degrees 137 -> 97).
+constexpr int64_t kBinMinVertices = int64_t(9) << 20, kBinMaxVertices = int64_t(1) << 28;
 constexpr double kBinMarksPerSeed = 4.0;
+inline int32_t bin_max_seeds(int64_t num_vertices) { return num_vertices <= int64_t(1) << 24 ? 1 << 16 : 1 << 17; }
 inline double bin_marks(int64_t num_vertices) {
-  return num_vertices <= int64_t(1) << 26 ? 600e3 : num_vertices <= int64_t(1) << 27 ? 200e3 : num_vertices <= int64_t(5) << 25 ? 60e3 : 0.0;
+  return num_vertices <= int64_t(1) << 24 ? 510e3 : num_vertices <= int64_t(1) << 26 ? 400e3
+         : num_vertices <= int64_t(1) << 27 ? 200e3 : num_vertices <= int64_t(5) << 25 ? 60e3 : 0.0;
 }
 inline int bin_shift(int64_t num_vertices) {
-  int shift = 17;
+  int shift = 16;
   while ((num_vertices - 1) >> shift >= kMaxBins) ++shift;
   return shift;
 }

@@ -708,7 +708,7 @@ def test_maps_of_calls_with_many_marks_and_few(V, share):
     ctx.check()
 
 
-@pytest.mark.parametrize("V,deg", [((1 << 24) + 1, 8), (1 << 25, 8), ((1 << 25) + 1, 8), ((1 << 26) + 1, 4), ((1 << 27) + 1, 2), (1 << 28, 0)])
+@pytest.mark.parametrize("V,deg", [((9 << 20) + 1, 8), (1 << 24, 8), ((1 << 24) + 1, 8), (1 << 25, 8), ((1 << 25) + 1, 8), ((1 << 26) + 1, 4), ((1 << 27) + 1, 2), (1 << 28, 0)])
 def test_samples_sorted_into_bins(V, deg):
     """Calls with many samples on a large graph sort them by ranges of vertices into segments of limited room.  Samples spread over the
     graph, at the edges of the ranges, in one range and on one vertex (segments overflow), with polls and without, with more seeds and
