@@ -86,7 +86,7 @@ struct DedupMaps {
 // 26 G/s.  The workgroup of a bin then sets the bits in LDS (bins.hip), so the map in HBM is neither read nor cleared.  Samples
 // beyond a segment's room are marked in the frontier map, and the bin is flagged: a list crowded into few bins costs what marks cost.
 constexpr int kBinThreads = 1024;     // of a workgroup of either kernel
-constexpr int kBinWriters = 512;      // workgroups of a hop: two per CU
+constexpr int kBinWriters = 512;      // most workgroups of a hop: two per CU
 constexpr int kBinWords = 128;        // words of a segment
 constexpr int kHeadWords = 16;        // of them in its head
 constexpr int kMaxBins = 256;         // a workgroup each, one per CU
