@@ -341,7 +341,8 @@ int lgp_set_overlap(lgp_ctx* ctx, int enable);
  * caller can budget device memory before building caches (Sec. 4.3.1: B is what is left after
  * everything else is reserved).  fixed [host] = the per-context tables that exist since
  * lgp_create (row table, feature remap, hotness vectors, dedup maps, the sampler's segments on
- * graphs of more than 9 * 2^20 vertices, rankings once a plan was made); scratch [host] = what pre-sampling, lgp_gather_features(_clique) with up to the
+ * graphs of more than 9 * 2^20 vertices whose column ids are spread, rankings once a plan was
+ * made); scratch [host] = what pre-sampling, lgp_gather_features(_clique) with up to the
  * worst-case number of ids and lgp_build_blocks allocate on first use for batches of up to
  * max_seeds seeds with these fan-outs.  The caches themselves are reported by lgp_plan_cache /
  * lgp_get_cache_plan.  The column ids that lgp_build_hotness may hold in HBM while it runs are in

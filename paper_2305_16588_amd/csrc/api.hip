@@ -63,6 +63,7 @@ struct lgp_ctx {
   bool either_map = false;     // a call may lay the maps out as bytes instead (kEitherMapMaxVertices), with this geometry
   MapGeom byte_geom;
   BinMaps bins;
+  size_t map_words = 0, status_words = 0;   // 64-bit words of each map, and of its status
   std::vector<double> mean_samples;   // where a rule asks for it, [f]: samples of a vertex at fan-out f, mean over the graph
   uint32_t* d_err = nullptr;
   int32_t* counters = nullptr;  // {n_hit, n_miss, n_peer}
@@ -306,6 +307,21 @@ hipError_t count_samples(lgp_ctx* c) {
   return hipSuccess;
 }
 
+// Gives up the bins of a context whose column ids are crowded (columns_spread).  As count_samples does.
+hipError_t count_columns(lgp_ctx* c) {
+  uint32_t host[2 * kMaxBins];
+  launch_count_columns(c->di, c->row_tab, c->g.indices, c->g.num_vertices, c->g.num_edges, c->bins.shift, c->topo_hot, nullptr);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = hipMemcpy(host, c->topo_hot, sizeof(host), hipMemcpyDeviceToHost);
+  if (e == hipSuccess) e = hipMemset(c->topo_hot, 0, sizeof(host));
+  if (e != hipSuccess || columns_spread(host, c->bins.bins)) return e;
+  for (void* p : {static_cast<void*>(c->bins.heads), static_cast<void*>(c->bins.tails), static_cast<void*>(c->bins.spilled),
+                  static_cast<void*>(c->bins.first)})
+    if (e == hipSuccess) e = hipFree(p);
+  c->bins = BinMaps{};
+  return e;
+}
+
 // Whether lgp_build_hotness may copy the column ids to HBM within its first mini-batch: 24 MB, half a millisecond of the
 // link, are to be saved.  expected_marks gives more rows than are read where popularity is skewed (2.4 M vertices, 8192 seeds,
 // 15-10-5: 530 k, 263 k), so half of what it says is taken.  A topology cache that is in place already serves the rows that
@@ -344,9 +360,9 @@ struct Staging {
 // The copy, if the rows that the first mini-batch reads say that it saves time; else, and where memory is short, rows are read in
 // place.  The frontier sizes are known before the last hop, which reads most rows, so the host waits for them there and that hop
 // reads the copy already (decided beside that hop, for the batches after it: 16 batches of 8192 seeds (15, 10, 5) on 2.4 M vertices
-// 6.04 ms, now 5.56; 8 of 4555 (11, 11, 11) on 0.87 M 3.09, 2.67; where nothing is copied calls are level).  With the room taken beforehand and the decision on the device, calls on skewed graphs
-// left the room unused (8 M vertices, 115 M edges, 8 batches, rows in place: 460 MB and 5090 us a call; now none and 5020, and
-// 5000 with no question asked).
+// 6.04 ms, now 5.56; 8 of 4555 (11, 11, 11) on 0.87 M 3.09, 2.67; where nothing is copied calls are level).  With the room taken
+// beforehand and the decision on the device, calls on skewed graphs left the room unused (8 M vertices, 115 M edges, 8 batches,
+// rows in place: 460 MB and 5090 us a call; now none and 5020, and 5000 with no question asked).
 int stage_topology(lgp_ctx* c, int64_t n_seeds, int32_t n_hops, hipStream_t s, Staging* st) {
   LGP_HIP(c, hipMemcpyAsync(c->hs_seen, c->hs_n, sizeof(int32_t) * size_t(n_hops), hipMemcpyDeviceToHost, s));
   LGP_HIP(c, hipEventRecord(c->ev_seen, s));
@@ -814,7 +830,8 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
     c->bins.shift = bin_shift(V);
     c->bins.bins = int32_t((V + (int64_t(1) << c->bins.shift) - 1) >> c->bins.shift);
   }
-  const size_t words = map_words(c);
+  const size_t words = c->map_words = map_words(c);
+  c->status_words = status_words(c);
   hipError_t e = hipSuccess;
   auto step = [&](hipError_t r) {
     if (e == hipSuccess) e = r;
@@ -825,7 +842,7 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   step(dev_alloc(&c->feat_hot, size_t(V)));
   step(dev_alloc(&c->maps.frontier, words));
   step(dev_alloc(&c->maps.gather, words));
-  step(dev_alloc(&c->maps.status, status_words(c)));
+  step(dev_alloc(&c->maps.status, c->status_words));
   if (c->bins.bins) {
     step(dev_alloc(&c->bins.heads, segment_words(c) / kBinWords * kHeadWords));
     step(dev_alloc(&c->bins.tails, segment_words(c) / kBinWords * (kBinWords - kHeadWords)));
@@ -857,6 +874,7 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
     e = hipGetLastError();
   }
   if (e == hipSuccess && (c->either_map || (c->bins.bins && bin_marks(V) > 0))) e = count_samples(c);
+  if (e == hipSuccess && c->bins.bins) e = count_columns(c);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     (void)hipGetLastError();
@@ -1566,9 +1584,9 @@ int lgp_workspace_bytes(const lgp_ctx* c, int32_t max_seeds, const int32_t* fano
   }
   const size_t V = size_t(c->g.num_vertices);
   if (fixed) {
-    const size_t map = map_words(c) * 8;
+    const size_t map = c->map_words * 8;
     // row table 8 + remap 4 + two hotness vectors 4 + 4 + two rankings 4 + 4 bytes per vertex
-    *fixed = V * 28 + 2 * map + status_words(c) * 8 + segment_words(c) * 4 + 64;
+    *fixed = V * 28 + 2 * map + c->status_words * 8 + segment_words(c) * 4 + 64;
   }
   if (scratch) {
     int64_t need[LGP_MAX_HOPS + 1], gather_need;

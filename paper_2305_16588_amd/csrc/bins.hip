@@ -5,10 +5,11 @@
 //
 // What bounds it: a chain of latencies (segments, LDS, status words of the bins before, ids), not bytes.  Segment heads are at
 // fixed places, so that counts and ids arrive in one round trip; the count of a bin comes out of the atomics that set its bits, so
-// that it is published before the words are ranked; status words are read from one of eight copies, so
-// that not all workgroups ask one channel of memory (8192 seeds (15, 10, 5) of 12 M vertices, 184 bins: one copy 60.2 us a call, two
-// 58.6, eight 57.1, sixteen 57.0).  Kernel times, map -> bins: 250 M vertices, 8192 seeds (25, 10), hops 6.6 -> 7.2 and 24.4 -> 13.6 us, lists 13.3 ->
-// 7.4 and 13.4 -> 11.0; 111 M, (15, 10, 5), hops 4.8 -> 6.0, 10.5 -> 9.3 and 23.0 -> 11.7, lists 6.6 -> 5.3, 7.6 -> 6.8 and 8.4 -> 9.9.
+// that it is published before the words are ranked; status words are read from one of eight copies, so that not all workgroups
+// ask one channel of memory (8192 seeds (15, 10, 5) of 12 M vertices, 184 bins: one copy 60.2 us a call, two 58.6, eight 57.1,
+// sixteen 57.0).  Kernel times, map -> bins: 250 M vertices, 8192 seeds (25, 10), hops 6.6 -> 7.2 and 24.4 -> 13.6 us, lists
+// 13.3 -> 7.4 and 13.4 -> 11.0; 111 M, (15, 10, 5), hops 4.8 -> 6.0, 10.5 -> 9.3 and 23.0 -> 11.7, lists 6.6 -> 5.3, 7.6 -> 6.8
+// and 8.4 -> 9.9.
 // Built and left: ids gathered in a list in LDS and ranked through their group's words (union 11.4 us at 111 M, and the list has
 // an end).
 //
@@ -124,7 +125,8 @@ struct Lister {
       if (used[l] >= uint32_t(kBinWords)) used[l] = kBinWords - 1;
 #pragma unroll 1
       for (uint32_t o = kHeadWords; o <= used[l]; o += kHeadWords)
-        set_four(reinterpret_cast<const uint4*>(a.maps.tails)[segment(bin, l) * ((kBinWords - kHeadWords) / 4) + (o - kHeadWords) / 4 + (t & 3)],
+        set_four(reinterpret_cast<const uint4*>(a.maps.tails)[segment(bin, l) * ((kBinWords - kHeadWords) / 4) +
+                                                              (o - kHeadWords) / 4 + (t & 3)],
                  o + k, used[l]);
     }
     if (!spilled) return;

@@ -191,6 +191,30 @@ __global__ __launch_bounds__(256) void count_degrees_kernel(const uint64_t* __re
     if (mine[k]) atomicAdd(&counts[k], mine[k]);
 }
 
+// One column id of each of kColumnSamples rows that lie evenly in the table, by the bin of the column and by its distance in bins.
+__global__ __launch_bounds__(256) void count_columns_kernel(const uint64_t* __restrict__ row_tab, const int32_t* __restrict__ indices,
+                                                            int64_t num_vertices, int64_t num_edges, int shift,
+                                                            uint32_t* __restrict__ counts) {
+  __shared__ uint32_t mine[2 * kMaxBins];
+  for (int k = threadIdx.x; k < 2 * kMaxBins; k += 256) mine[k] = 0;
+  __syncthreads();
+  for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < kColumnSamples; i += int64_t(gridDim.x) * 256) {
+    const uint32_t r = uint32_t(i) * 0x9E3779B9u;
+    const int64_t v = (i * num_vertices + int64_t((uint64_t(r) * uint64_t(num_vertices)) >> 32)) / kColumnSamples;
+    const uint64_t row = row_tab[v], d = uint32_t(row) & kRowDegOverflow;
+    const int64_t at = int64_t((row >> kRowStartShift) & kRowStartMask) + int64_t((uint64_t(r * 0x85EBCA6Bu) * d) >> 32);
+    if (d == 0 || d == kRowDegOverflow || at >= num_edges) continue;
+    const int32_t u = indices[at];
+    if (u < 0 || u >= num_vertices) continue;
+    const int bin = u >> shift, far = bin - int(v >> shift);
+    atomicAdd(&mine[bin], 1u);
+    atomicAdd(&mine[kMaxBins + (far < 0 ? -far : far)], 1u);
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < 2 * kMaxBins; k += 256)
+    if (mine[k]) atomicAdd(&counts[k], mine[k]);
+}
+
 __global__ void set_cached_rows_kernel(const int32_t* __restrict__ order, int64_t n_topo,
                                        const int64_t* __restrict__ t_indptr, uint64_t* __restrict__ row_tab) {
   for (int64_t r = int64_t(blockIdx.x) * blockDim.x + threadIdx.x; r < n_topo; r += int64_t(gridDim.x) * blockDim.x) {
@@ -388,6 +412,12 @@ void launch_init_row_table(const DeviceInfo& di, const void* h_indptr, int32_t i
 
 void launch_count_degrees(const DeviceInfo& di, const uint64_t* row_tab, int64_t num_vertices, uint32_t* counts, hipStream_t s) {
   hipLaunchKernelGGL(count_degrees_kernel, dim3(grid_for(di, num_vertices)), dim3(256), 0, s, row_tab, num_vertices, counts);
+}
+
+void launch_count_columns(const DeviceInfo& di, const uint64_t* row_tab, const int32_t* indices, int64_t num_vertices,
+                          int64_t num_edges, int shift, uint32_t* counts, hipStream_t s) {
+  hipLaunchKernelGGL(count_columns_kernel, dim3(grid_for(di, kColumnSamples)), dim3(256), 0, s, row_tab, indices,
+                     num_vertices, num_edges, shift, counts);
 }
 
 void launch_set_cached_rows(const DeviceInfo& di, const int32_t* order, int64_t n_topo, const int64_t* t_indptr,

@@ -4,7 +4,9 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -84,7 +86,7 @@ struct DedupMaps {
 // Binned marks, for large graphs.  A sample is not marked in a map but appended to a segment of its workgroup and its bin
 // (2^shift consecutive vertices), at a place that a counter in LDS hands out: a plain store, where an atomic on a bit runs at
 // 26 G/s.  The workgroup of a bin then sets the bits in LDS (bins.hip), so the map in HBM is neither read nor cleared.  Samples
-// beyond a segment's room are marked in the frontier map, and the bin is flagged: a list crowded into few bins costs what marks cost.
+// beyond a segment's room are marked in the frontier map, and the bin is flagged: right, but dearer than marks alone (columns_spread).
 constexpr int kBinThreads = 1024;     // of a workgroup of either kernel
 constexpr int kBinWriters = 512;      // most workgroups of a hop: two per CU
 constexpr int kBinWords = 128;        // words of a segment
@@ -109,6 +111,29 @@ inline int32_t bin_max_seeds(int64_t num_vertices) { return num_vertices <= int6
 inline double bin_marks(int64_t num_vertices) {
   return num_vertices <= int64_t(1) << 24 ? 510e3 : num_vertices <= int64_t(1) << 26 ? 400e3
          : num_vertices <= int64_t(1) << 27 ? 200e3 : num_vertices <= int64_t(5) << 25 ? 60e3 : 0.0;
+}
+// And only graphs whose column ids are spread: where a call's samples crowd into few bins, few workgroups make its list and most samples
+// are marked in the map after all.  Degrees of 12, map -> bins, 8192 (15, 10, 5) and 8000 (25, 10): all columns within half of
+// the ids 12 M vertices 199 -> 179 us and 41 -> 38, 111 M 310 -> 218 and 68 -> 39; a third 160 -> 206, 39 -> 42 and 311 -> 260,
+// 68 -> 44; an eighth 97 -> 243, 39 -> 62 and 329 -> 379, 74 -> 65; a 64th 83 -> 267, 49 -> 132 and 413 -> 805, 129 -> 247.
+// Columns within 4096 ids of their rows crowd where seeds do: seeds spread 147 -> 186, 37 -> 48 and 196 -> 217, 48 -> 60; a run of
+// ids 52 -> 194, 33 -> 138 and 157 -> 226, 134 -> 163; one column in 16 so and the others spread, a run of ids 216 -> 160, 45 -> 45
+// and 315 -> 214, 83 -> 68; one in 32 214 -> 156, 43 -> 40 and 316 -> 202, 80 -> 61.  So for any number of bins, w of them may take
+// one column in 20 and twice their part: of the bins themselves, and of those around each column's row.
+constexpr double kCrowdedColumns = 0.05, kCrowdedBins = 2.0;
+inline bool columns_spread(const uint32_t* counts, int32_t bins) {
+  uint32_t by_bin[kMaxBins];
+  std::copy(counts, counts + kMaxBins, by_bin);
+  std::sort(by_bin, by_bin + kMaxBins, std::greater<uint32_t>());
+  double total = 0, fullest = 0, near = 0;
+  for (uint32_t n : by_bin) total += double(n);
+  for (int32_t w = 0; w < bins; ++w) {
+    fullest += double(by_bin[w]);
+    near += double(counts[kMaxBins + w]);
+    if (fullest > total * (kCrowdedColumns + kCrowdedBins * double(w + 1) / double(bins))) return false;
+    if (near > total * (kCrowdedColumns + kCrowdedBins * double(2 * w + 1) / double(bins))) return false;
+  }
+  return true;
 }
 inline int bin_shift(int64_t num_vertices) {
   int shift = 16;
@@ -388,6 +413,10 @@ hipError_t cslp_rank(const DeviceInfo& di, int32_t k_g, int64_t num_vertices, co
 // row_tab[v] = (not cached, CPU offset, degree) for every vertex, streamed from the CPU-resident offsets.
 // counts[k] += vertices of degree k, counts[LGP_MAX_FANOUT] += those of that degree and more.
 void launch_count_degrees(const DeviceInfo& di, const uint64_t* row_tab, int64_t num_vertices, uint32_t* counts, hipStream_t s);
+// counts[bin] += columns of the bin, counts[kMaxBins + d] += columns that lie d bins from their row, of kColumnSamples column ids.
+constexpr int64_t kColumnSamples = 1 << 16;
+void launch_count_columns(const DeviceInfo& di, const uint64_t* row_tab, const int32_t* indices, int64_t num_vertices,
+                          int64_t num_edges, int shift, uint32_t* counts, hipStream_t s);
 void launch_init_row_table(const DeviceInfo& di, const void* h_indptr, int32_t indptr_bytes, int64_t num_vertices,
                            uint64_t* row_tab, hipStream_t s);
 // row_tab[order[r]] = (cached, t_indptr[r], degree) for r < n_topo (rows too long to pack keep their CPU entry).

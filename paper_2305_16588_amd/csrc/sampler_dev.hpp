@@ -79,7 +79,7 @@ __device__ __forceinline__ void append_to_bin(const HopArgs& a, uint32_t* used, 
     a.bins.tails[segment * uint32_t(kBinWords - kHeadWords) + at - kHeadWords] = uint32_t(u);
   } else {
     mark_vertex<0>(a.mark_bits, u);
-    a.bins.spilled[bin] = 1;
+    if (at == uint32_t(kBinWords)) a.bins.spilled[bin] = 1;      // the workgroup's first: not all samples store to one address
   }
 }
 

@@ -713,7 +713,7 @@ def test_samples_sorted_into_bins(V, deg):
     """Calls with many samples on a large graph sort them by ranges of vertices into segments of limited room.  Samples spread over the
     graph, at the edges of the ranges, in one range and on one vertex (segments overflow), with polls and without, with more seeds and
     more inner frontiers than the kernel loads ahead, and calls that mark maps between them; a caller who uses one buffer for two
-    frontiers gets the marks in maps."""
+    frontiers gets the marks in maps, and so does a graph that is crowded all over, where the others are so around the seeds only."""
     import oracle
     import paper_2305_16588_amd as lgp
     from gpu_common import assert_batch_equal
@@ -737,7 +737,8 @@ def test_samples_sorted_into_bins(V, deg):
         return r % step // gap * gap if kind == "crowd" else torch.full((n,), V - 1, device="cuda")
 
     indices = lgp.pinned_empty(rows * deg, np.int32)
-    for lists in (("spread", "edges", "crowd", "one"), ("crowd",), ("one",)) if V <= 1 << 25 else (("spread", "edges", "spread", "one"),):
+    all_lists = (("spread", "edges", "crowd", "one"), ("crowd",), ("one",)) if V <= 1 << 25 else (("spread", "edges", "spread", "one"),)
+    for lists, crowded in [(lists, rows // 32) for lists in all_lists] + [(("crowd",), rows)] * (V <= 1 << 25):
         part = 1 << 24
         for lo in range(0, indices.size, part):
             n = min(part, indices.size - lo)
@@ -745,9 +746,12 @@ def test_samples_sorted_into_bins(V, deg):
             got = torch.zeros(n, dtype=torch.int64, device="cuda")
             for k, kind in enumerate(lists):
                 got = torch.where(pick == k, draw(kind, n), got)
+            if lo + n > crowded * deg:
+                at = max(crowded * deg - lo, 0)
+                got[at:] = draw("spread", n - at)
             torch.from_numpy(indices[lo:lo + n]).copy_(got.to(torch.int32))
-        ctx, orc = lgp.Context(indptr, indices), oracle.Oracle(indptr, indices, None)
-        order = (rng.permutation(min(rows, 1 << 20))[:140_000] * gap).astype(np.int32)
+        ctx, orc = lgp.Context(indptr, torch.from_numpy(indices).cuda()), oracle.Oracle(indptr, indices, None)
+        order = (rng.permutation(min(crowded, 1 << 20))[:140_000] * gap).astype(np.int32)
         for n_seeds, fanouts in ((30_000, (7, 6, 3)), (1, (9, 9, 2)), (60_001, (2, 2, 2, 2, 2)), (8192, (5,)), (131_073, (3, 2))):
             seeds = order[:n_seeds]
             dev = torch.from_numpy(seeds).cuda()
