@@ -297,31 +297,39 @@ def measure(inp: Inputs, steps: int, warmup: int, reps: int, topo_frac=None, fea
     # the L compactions reads its map once and writes its id list (4 per id).  A map holds a word, a half-word or a byte
     # per vertex, marked with a plain store, on graphs of up to 2^19, 2^20 and 2^23 vertices (and a byte up to 2^24 for
     # calls whose seeds, degrees and fan-outs promise a mark for 0.04 of the vertices), and a bit set with an atomic
-    # otherwise.
+    # otherwise.  Calls that promise many marks on graphs of 9 to 268 M vertices, with no rows over PCIe and column ids spread
+    # over the vertices (as these are), append the samples to segments instead, which are read once (4 bytes per sample either way), and have no map to read.
     roofline_sampler = None
     if prof.n_sample:
         f = np.asarray(spec.fanouts, np.int64)
         bits = 32 if V <= 1 << 19 else 16 if V <= 1 << 20 else 8 if V <= 1 << 23 else 1
-        if 1 << 23 < V <= 1 << 24:
+        binned = False
+        if 1 << 23 < V <= 1 << 28:
             degrees, n, expected = np.diff(inp.indptr), float(spec.batch), 0.0
             for fan in spec.fanouts:
                 sampled = n * float(np.minimum(degrees, fan).mean())
                 expected += sampled
                 n = V * -np.expm1(-sampled / V)
-            bits = 8 if expected >= 0.04 * V else 1
+            if V <= 1 << 24 and expected >= 0.04 * V:
+                bits = 8
+            enough = 510e3 if V <= 1 << 24 else 400e3 if V <= 1 << 26 else 200e3 if V <= 1 << 27 else 60e3 if V <= 5 << 25 else 0
+            binned = (V > 9 << 20 and plan.n_topo == V and spec.batch <= (1 << 16 if V <= 1 << 24 else 1 << 17) and
+                      (enough == 0 or expected >= enough + 4 * spec.batch))
         marks = float(n_edges.sum()) / steps + spec.batch
-        sampler_bytes = int((n_front * (4 + 8 + 4 + 4 * f)).sum() + 4 * n_edges.sum() + 4 * n_lists) + steps * L * (V * bits // 8)
+        sampler_bytes = int((n_front * (4 + 8 + 4 + 4 * f)).sum() + 4 * n_edges.sum() + 4 * n_lists)
+        sampler_bytes += int(8 * n_edges.sum()) if binned else steps * L * (V * bits // 8)
         ms_call = prof.ms_sample / prof.n_sample
         ach = sampler_bytes / steps / (ms_call * 1e-3) / 1e9
         s_traffic = (prof_rec or {}).get("sampler_hbm_bytes_per_call")
-        roofline_sampler = {"bound": "hbm", "kernel": "lgp_sample_khop (sample_hop_kernel per hop, compact_kernel per dedup)",
+        roofline_sampler = {"bound": "hbm", "kernel": "lgp_sample_khop (sample_hop_binned_kernel per hop, list_bins_kernel per dedup)" if binned
+                            else "lgp_sample_khop (sample_hop_kernel per hop, compact_kernel per dedup)",
                             "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                             "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": s_traffic,
                             "traffic_source": (prof_rec or {}).get("source") if s_traffic else prof_why or "no sampler figure",
                             "occupancy_percent": (prof_rec or {}).get("sampler_occupancy_percent"),
                             "avg_call_ms": round(ms_call, 4), "bytes_per_call": round(sampler_bytes / steps),
                             "expanded_vertices_per_call": round(float(n_front.sum()) / steps, 1),
-                            "mark": "atomic on a bit" if bits == 1 else f"store of {bits} bits",
+                            "mark": "append to a segment" if binned else "atomic on a bit" if bits == 1 else f"store of {bits} bits",
                             "bitmap_atomics_per_call": round(marks, 1)}   # marks of either kind
 
     rec = {
