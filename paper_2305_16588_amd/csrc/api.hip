@@ -307,6 +307,14 @@ hipError_t count_samples(lgp_ctx* c) {
   return hipSuccess;
 }
 
+// Without bins: samples are marked in maps.
+void give_up_bins(lgp_ctx* c) {
+  void* ptrs[] = {c->bins.heads, c->bins.tails, c->bins.spilled, c->bins.first};
+  for (void* p : ptrs)
+    if (p) (void)hipFree(p);
+  c->bins = BinMaps{};
+}
+
 // Gives up the bins of a context whose column ids are crowded (columns_spread).  As count_samples does.
 hipError_t count_columns(lgp_ctx* c) {
   uint32_t host[2 * kMaxBins];
@@ -314,11 +322,7 @@ hipError_t count_columns(lgp_ctx* c) {
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpy(host, c->topo_hot, sizeof(host), hipMemcpyDeviceToHost);
   if (e == hipSuccess) e = hipMemset(c->topo_hot, 0, sizeof(host));
-  if (e != hipSuccess || columns_spread(host, c->bins.bins)) return e;
-  for (void* p : {static_cast<void*>(c->bins.heads), static_cast<void*>(c->bins.tails), static_cast<void*>(c->bins.spilled),
-                  static_cast<void*>(c->bins.first)})
-    if (e == hipSuccess) e = hipFree(p);
-  c->bins = BinMaps{};
+  if (e == hipSuccess && !columns_spread(host, c->bins.bins)) give_up_bins(c);
   return e;
 }
 
@@ -843,12 +847,6 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   step(dev_alloc(&c->maps.frontier, words));
   step(dev_alloc(&c->maps.gather, words));
   step(dev_alloc(&c->maps.status, c->status_words));
-  if (c->bins.bins) {
-    step(dev_alloc(&c->bins.heads, segment_words(c) / kBinWords * kHeadWords));
-    step(dev_alloc(&c->bins.tails, segment_words(c) / kBinWords * (kBinWords - kHeadWords)));
-    step(dev_alloc(&c->bins.spilled, kMaxBins));
-    step(dev_alloc(&c->bins.first, LGP_MAX_HOPS * (kMaxBins + 1)));
-  }
   step(dev_alloc(&c->d_err, 1));
   step(dev_alloc(&c->counters, 3));
   step(dev_alloc(&c->hs_n, LGP_MAX_HOPS + 1));
@@ -856,6 +854,14 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   step(dev_alloc(&c->seg, LGP_MAX_HOPS + 2));
   step(dev_alloc(&c->unordered, LGP_MAX_HOPS + 1));
   step(dev_alloc(&c->seg_counters, (LGP_MAX_HOPS + 1) * 3));
+  if (e == hipSuccess && c->bins.bins &&
+      (dev_alloc(&c->bins.heads, segment_words(c) / kBinWords * kHeadWords) != hipSuccess ||
+       dev_alloc(&c->bins.tails, segment_words(c) / kBinWords * (kBinWords - kHeadWords)) != hipSuccess ||
+       dev_alloc(&c->bins.spilled, kMaxBins) != hipSuccess ||
+       dev_alloc(&c->bins.first, LGP_MAX_HOPS * (kMaxBins + 1)) != hipSuccess)) {
+    (void)hipGetLastError();                                 // memory is short, and maps do without segments
+    give_up_bins(c);
+  }
   if (e == hipSuccess) e = hipMemset(c->f_remap, 0xff, sizeof(int32_t) * size_t(V));
   if (e == hipSuccess) e = hipMemset(c->topo_hot, 0, sizeof(uint32_t) * size_t(V));
   if (e == hipSuccess) e = hipMemset(c->feat_hot, 0, sizeof(uint32_t) * size_t(V));
