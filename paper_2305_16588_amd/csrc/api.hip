@@ -391,7 +391,7 @@ int stage_topology(lgp_ctx* c, int64_t n_seeds, int32_t n_hops, hipStream_t s, S
 // (15, 10, 5), none and half of the topology cached 618 -> 621 and 225 -> 231 us).
 bool binned(const lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops, const int64_t* need,
             int64_t gather_need, const lgp_sample_out* out) {
-  if (c->bins.bins == 0 || n_seeds > bin_max_seeds(c->g.num_vertices) || topo_view(c).over_pcie) return false;
+  if (c->bins.bins == 0 || n_seeds == 0 || n_seeds > bin_max_seeds(c->g.num_vertices) || topo_view(c).over_pcie) return false;
   const double enough = bin_marks(c->g.num_vertices);
   if (enough > 0 && expected_marks(c, n_seeds, fanouts, n_hops, [&](int32_t f) { return c->mean_samples[size_t(f)]; }) <
                         enough + kBinMarksPerSeed * double(n_seeds))
@@ -438,7 +438,7 @@ int binned_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t
                                          out->cnt[h], c->bins, reinterpret_cast<uint32_t*>(c->maps.frontier), c->d_err,
                                          c->maps.status, s);
     const bool last = h + 1 == n_hops;
-    const bool want = out->frontier[h + 1] != nullptr;      // given, but for the last one
+    const bool want = !last || out->frontier[n_hops] != nullptr;
     a.list = out->frontier[h + 1];
     a.list_cap = out->cap[h + 1];
     a.n_list = want ? out->n_frontier + h + 1 : nullptr;

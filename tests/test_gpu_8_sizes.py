@@ -781,3 +781,30 @@ def test_samples_sorted_into_bins(V, deg):
         assert (buf.to_host(dev)[3] == ref.gather_ids).all()
         ctx.check()
         del ctx, orc
+
+
+@pytest.mark.parametrize("V", [(9 << 20) + 1, (5 << 25) + 1, 1 << 28])
+def test_no_seeds_on_a_large_graph(V):
+    """An empty batch is valid on every graph, with null inner frontiers as empty buffers have them: every size is written as 0.  From
+    5 * 2^25 vertices on no call has too few samples for the bins, so there this one would be the only one that they hold nothing of."""
+    import paper_2305_16588_amd as lgp
+    gap = 61                                                   # every 61st vertex has 7 edges
+    indptr = torch.arange(gap - 1, V + gap, device="cuda").div_(gap, rounding_mode="floor").mul_(7).to(torch.int32)
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    ctx = lgp.Context(indptr, torch.randint(0, V, (int(indptr[-1]),), generator=gen, device="cuda", dtype=torch.int32))
+    none = torch.empty(0, dtype=torch.int32, device="cuda")
+    some = torch.arange(0, 61 * 8192, 61, device="cuda", dtype=torch.int32)
+    for fanouts in ((25, 10), (5,), (3, 2, 2, 4)):
+        for last in (False, True):
+            buf = lgp.SampleBuffers(V, 0, fanouts, last_frontier=last)
+            assert all(f.data_ptr() == 0 for f in buf.frontier[1:])
+            buf.n_frontier.fill_(77)
+            buf.n_gather.fill_(77)
+            ctx.sample_khop(none, fanouts, 3, out=buf)
+            assert buf.n_gather.item() == 0 and buf.n_frontier.tolist() == [0] * len(fanouts) + [77]
+            # maps and segments are in order for the calls around it
+            got, again = (ctx.sample_khop(some, fanouts, 3) for _ in range(2))
+            assert got.n_gather.item() == again.n_gather.item() > 8192
+            n = int(got.n_gather)
+            assert torch.equal(got.gather_ids[:n], again.gather_ids[:n]) and torch.equal(got.gather_ids[:n], got.gather_ids[:n].unique())
+    ctx.check()
