@@ -309,7 +309,7 @@ hipError_t count_samples(lgp_ctx* c) {
 
 // Without bins: samples are marked in maps.
 void give_up_bins(lgp_ctx* c) {
-  void* ptrs[] = {c->bins.heads, c->bins.tails, c->bins.spilled, c->bins.first};
+  void* ptrs[] = {c->bins.heads, c->bins.tails, c->bins.spilled, c->bins.first, c->bins.odd_seeds};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   c->bins = BinMaps{};
@@ -421,6 +421,7 @@ bool binned(const lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32
 int binned_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops, const int64_t* need,
                 uint64_t rng_seed, const lgp_sample_out* out, hipStream_t s) {
   const TopoView tv = topo_view(c);
+  if (++c->bins.call == 0) c->bins.call = 1;       // 0 marks no call: skipped after 2^32 of them
   BinArgs a = {};
   a.maps = c->bins;
   a.spill = c->maps.frontier;
@@ -858,7 +859,8 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
       (dev_alloc(&c->bins.heads, segment_words(c) / kBinWords * kHeadWords) != hipSuccess ||
        dev_alloc(&c->bins.tails, segment_words(c) / kBinWords * (kBinWords - kHeadWords)) != hipSuccess ||
        dev_alloc(&c->bins.spilled, kMaxBins) != hipSuccess ||
-       dev_alloc(&c->bins.first, LGP_MAX_HOPS * (kMaxBins + 1)) != hipSuccess)) {
+       dev_alloc(&c->bins.first, LGP_MAX_HOPS * (kMaxBins + 1)) != hipSuccess ||
+       dev_alloc(&c->bins.odd_seeds, 1) != hipSuccess)) {
     (void)hipGetLastError();                                 // memory is short, and maps do without segments
     give_up_bins(c);
   }
@@ -868,6 +870,7 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   if (e == hipSuccess) e = hipMemset(c->maps.frontier, 0, sizeof(uint64_t) * words);
   if (e == hipSuccess) e = hipMemset(c->maps.gather, 0, sizeof(uint64_t) * words);
   if (e == hipSuccess && c->bins.bins) e = hipMemset(c->bins.spilled, 0, sizeof(uint32_t) * kMaxBins);
+  if (e == hipSuccess && c->bins.bins) e = hipMemset(c->bins.odd_seeds, 0, sizeof(uint32_t));
   if (e == hipSuccess) e = hipMemset(c->d_err, 0, sizeof(uint32_t));
   if (e == hipSuccess) e = hipMemset(c->counters, 0, 3 * sizeof(int32_t));
   if (e == hipSuccess) e = hipMemset(c->unordered, 0, (LGP_MAX_HOPS + 1) * sizeof(uint32_t));
@@ -898,7 +901,7 @@ int lgp_destroy(lgp_ctx* c) {
   void* ptrs[] = {c->row_tab, c->f_remap, c->topo_hot, c->feat_hot, c->maps.frontier, c->maps.gather, c->maps.status,
                   c->d_err,   c->counters, c->order_t, c->order_f,  c->lists, c->hs_n, c->pos_table, c->tile_sums, c->hs_expansions,
                   c->seg, c->seg_counters, c->unordered, c->bins.heads, c->bins.tails,
-                  c->bins.spilled, c->bins.first};
+                  c->bins.spilled, c->bins.first, c->bins.odd_seeds};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (int h = 0; h < LGP_MAX_HOPS; ++h)

@@ -146,6 +146,11 @@ struct BinMaps {
   uint32_t* tails = nullptr;          // the others
   uint32_t* spilled = nullptr;        // [bin]: the frontier map has taken something; all zero between calls
   int32_t* first = nullptr;           // [hop][kMaxBins + 1]: where the ids of each bin begin in frontier `hop`
+  // The number of the last call that met a seed without a row, or with one that makes no sense, and the number of this call (a value
+  // of its own, so that nothing is cleared).  The context's error word says neither: kernels of a gather on another stream set it
+  // and lgp_check on that stream clears it while this call runs.
+  uint32_t* odd_seeds = nullptr;
+  uint32_t call = 0;
   int32_t shift = 0, bins = 0;        // bins == 0: this context marks maps
 };
 

@@ -808,3 +808,69 @@ def test_no_seeds_on_a_large_graph(V):
             n = int(got.n_gather)
             assert torch.equal(got.gather_ids[:n], again.gather_ids[:n]) and torch.equal(got.gather_ids[:n], got.gather_ids[:n].unique())
     ctx.check()
+
+
+def test_invalid_seeds_of_binned_calls():
+    """Seeds without a row, or with one that makes no sense, are no members of the batch; a row of 2^24 vertices and more, whose degree
+    the row table does not hold, is like any other.  Which seeds count does not depend on the context's error word: while batches
+    run, a gather of invalid ids on another stream sets it and a check there clears it."""
+    import oracle
+    import paper_2305_16588_amd as lgp
+    V, deg, odd, long_row, more = (9 << 20) + 1, 8, 4_000_000, 6_000_000, 17_000_000
+    indptr = np.arange(V + 1, dtype=np.int32) * deg
+    indptr[long_row + 1:] += more
+    indptr[odd + 1] -= deg + 5                                 # of `odd` the offsets descend
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    indices = torch.randint(0, V, (int(indptr[-1]),), generator=gen, device="cuda", dtype=torch.int32)
+    indices[(indices == odd)] = 7
+    features = torch.zeros((V, 1), dtype=torch.float16, device="cuda")
+    ctx = lgp.Context(lgp.pinned_copy(indptr), indices, features)
+    rng = np.random.default_rng(5)
+    fanouts = (7, 6, 3)
+    good = rng.permutation(V)[:12_001].astype(np.int32)
+    good = good[good != odd]
+    good[[17, 11_000]] = [long_row, odd + 1]
+    good = good[np.sort(np.unique(good, return_index=True)[1])]
+    ref = oracle.Oracle(indptr, indices.cpu().numpy(), None).sample_khop(good, fanouts, 31)
+    at = np.array([0, 5, 6, 4099, 9_000, good.size])
+    mixed = np.insert(good, at, np.array([-1, V, odd, odd, -(2 ** 31), 2 ** 31 - 1], dtype=np.int32))
+    valid = (mixed >= 0) & (mixed < V) & (mixed != odd)
+    assert (mixed[valid] == good).all()
+
+    def check(buf, dev, rows):
+        fr, nbr, cnt, ids = buf.to_host(dev)
+        assert ids.shape == ref.gather_ids.shape and (ids == ref.gather_ids).all()
+        assert all(fr[h].shape == ref.frontier[h].shape and (fr[h] == ref.frontier[h]).all() for h in (1, 2))
+        assert (nbr[0][rows] == ref.nbr[0]).all() and (nbr[0][~rows] == -1).all() and (cnt[0][~rows] == 0).all()
+        assert all((nbr[h] == ref.nbr[h]).all() and (cnt[h] == ref.cnt[h]).all() for h in (1, 2))
+
+    torch.cuda.synchronize()
+    beside, sampler = torch.cuda.Stream(), torch.cuda.Stream()
+    invalid = torch.full((1000,), -1, dtype=torch.int32, device="cuda")
+    out = torch.empty((1000, 1), dtype=torch.float16, device="cuda")
+    for seeds, rows in ((mixed, valid), (good, np.ones(good.size, bool))):
+        dev = torch.from_numpy(seeds).cuda()
+        for polls in (4096, 0):
+            ctx.set_wait_polls(polls)
+            buf = ctx.sample_khop(dev, fanouts, 31)
+            check(buf, dev, rows)
+            if not rows.all():
+                with pytest.raises(lgp.LegionPrepError):
+                    ctx.check()
+            ctx.check()
+        ctx.set_wait_polls(4096)
+        bufs = [lgp.SampleBuffers(V, seeds.size, fanouts) for _ in range(12)]
+        torch.cuda.synchronize()
+        for buf in bufs:
+            ctx.sample_khop(dev, fanouts, 31, out=buf, stream=sampler)
+        for _ in range(12):
+            ctx.gather_features(invalid, out=out, stream=beside)
+            with pytest.raises(lgp.LegionPrepError):
+                ctx.check(beside)
+        torch.cuda.synchronize()
+        for buf in bufs:
+            check(buf, dev, rows)
+        try:
+            ctx.check()
+        except lgp.LegionPrepError:
+            assert not rows.all()
