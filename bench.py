@@ -294,28 +294,15 @@ def measure(inp: Inputs, steps: int, warmup: int, reps: int, topo_frac=None, fea
     # The sampler (whole lgp_sample_khop call: hop kernels + dedup compactions).  Algorithmic bytes per call:
     # per expanded vertex its id (4), its row-table entry (8) and the sampled column ids (4 each) are read, its
     # nbr row (4 f) and cnt (4) written; every sample marks its vertex in a dedup map (not counted as bytes); each of
-    # the L compactions reads its map once and writes its id list (4 per id).  A map holds a word, a half-word or a byte
-    # per vertex, marked with a plain store, on graphs of up to 2^19, 2^20 and 2^23 vertices (and a byte up to 2^24 for
-    # calls whose seeds, degrees and fan-outs promise a mark for 0.04 of the vertices), and a bit set with an atomic
-    # otherwise.  Calls that promise many marks on graphs of 9 to 268 M vertices, with no rows over PCIe and column ids spread
-    # over the vertices (as these are), append the samples to segments instead, which are read once (4 bytes per sample either way), and have no map to read.
+    # the L compactions reads its map once and writes its id list (4 per id).  A map holds a word, a half-word, a byte or a
+    # bit per vertex.  Calls that sort their samples into bins append them to segments instead, which are read once (4 bytes
+    # per sample either way), and have no map to read.  The library says which it was.
     roofline_sampler = None
     if prof.n_sample:
         f = np.asarray(spec.fanouts, np.int64)
-        bits = 32 if V <= 1 << 19 else 16 if V <= 1 << 20 else 8 if V <= 1 << 23 else 1
-        binned = False
-        if 1 << 23 < V <= 1 << 28:
-            degrees, n, expected = np.diff(inp.indptr), float(spec.batch), 0.0
-            for fan in spec.fanouts:
-                sampled = n * float(np.minimum(degrees, fan).mean())
-                expected += sampled
-                n = V * -np.expm1(-sampled / V)
-            if V <= 1 << 24 and expected >= 0.04 * V:
-                bits = 8
-            enough = 510e3 if V <= 1 << 24 else 400e3 if V <= 1 << 26 else 200e3 if V <= 1 << 27 else 60e3 if V <= 5 << 25 else 0
-            binned = (V > 9 << 20 and plan.n_topo == V and spec.batch <= (1 << 16 if V <= 1 << 24 else 1 << 17) and
-                      (enough == 0 or expected >= enough + 4 * spec.batch))
-        marks = float(n_edges.sum()) / steps + spec.batch
+        bits = ctx.sample_marks()
+        binned = bits == 0
+        marks = float(n_edges.sum()) / steps + (0 if binned else spec.batch)      # seeds are marked, but not appended
         sampler_bytes = int((n_front * (4 + 8 + 4 + 4 * f)).sum() + 4 * n_edges.sum() + 4 * n_lists)
         sampler_bytes += int(8 * n_edges.sum()) if binned else steps * L * (V * bits // 8)
         ms_call = prof.ms_sample / prof.n_sample
@@ -330,7 +317,7 @@ def measure(inp: Inputs, steps: int, warmup: int, reps: int, topo_frac=None, fea
                             "avg_call_ms": round(ms_call, 4), "bytes_per_call": round(sampler_bytes / steps),
                             "expanded_vertices_per_call": round(float(n_front.sum()) / steps, 1),
                             "mark": "append to a segment" if binned else "atomic on a bit" if bits == 1 else f"store of {bits} bits",
-                            "bitmap_atomics_per_call": round(marks, 1)}   # marks of either kind
+                            "appended_samples_per_call" if binned else "bitmap_atomics_per_call": round(marks, 1)}   # marks of either kind
 
     rec = {
         "value": round(n_steps * spec.batch / elapsed, 1), "unit": "seeds/s", "steps": steps, "warmup": warmup,

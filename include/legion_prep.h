@@ -364,6 +364,11 @@ int lgp_reserve(lgp_ctx* ctx, int32_t max_seeds, const int32_t* fanouts, int32_t
  * whatever it is: it is there so that a test can reach the second way.  Applies to later calls. */
 int lgp_set_wait_polls(lgp_ctx* ctx, int32_t polls);
 
+/* How the last lgp_sample_khop on this context recorded its samples: *bits [host] = bits per vertex of the maps it
+ * marked (32, 16, 8 or 1), 0 = it sorted the samples into bins, -1 = there was none yet.  Results do not depend on it:
+ * it is there for tests and for accounts of what a call moves. */
+int lgp_get_sample_marks(const lgp_ctx* ctx, int32_t* bits);
+
 /* Sticky device-side error flag (invalid vertex id met by a kernel, output overrun).
  * Synchronises `stream`, returns LGP_EDEVICE if set, and clears it. */
 int lgp_check(lgp_ctx* ctx, void* stream);

@@ -62,7 +62,7 @@ class Profile(C.Structure):
 EXPORTS = ["lgp_host_alloc", "lgp_host_free", "lgp_shuffle_tablet", "lgp_create", "lgp_destroy", "lgp_build_hotness", "lgp_get_presample_stats", "lgp_get_hotness",
            "lgp_set_hotness", "lgp_plan_cache", "lgp_search_cache_plan", "lgp_cslp", "lgp_build_cache", "lgp_build_clique_cache", "lgp_get_clique_plan",
            "lgp_gather_features_clique", "lgp_get_cache_plan", "lgp_get_cache", "lgp_get_cache_part", "lgp_reserve",
-           "lgp_sample_khop", "lgp_sample_extract", "lgp_build_blocks", "lgp_gather_features", "lgp_gather_features_static", "lgp_set_overlap", "lgp_workspace_bytes", "lgp_check", "lgp_set_wait_polls", "lgp_set_profiling", "lgp_get_profile",
+           "lgp_sample_khop", "lgp_sample_extract", "lgp_build_blocks", "lgp_gather_features", "lgp_gather_features_static", "lgp_set_overlap", "lgp_workspace_bytes", "lgp_check", "lgp_set_wait_polls", "lgp_get_sample_marks", "lgp_set_profiling", "lgp_get_profile",
            "lgp_strerror", "lgp_last_error"]
 
 _lib = None
@@ -109,6 +109,7 @@ def load_library():
     L.lgp_workspace_bytes.argtypes = [vp, i32, vp, i32, vp, vp]
     L.lgp_check.argtypes = [vp, vp]
     L.lgp_set_wait_polls.argtypes = [vp, i32]
+    L.lgp_get_sample_marks.argtypes = [vp, vp]
     L.lgp_set_profiling.argtypes = [vp, C.c_int]
     L.lgp_get_profile.argtypes = [vp, C.POINTER(Profile)]
     L.lgp_strerror.argtypes = [C.c_int]
@@ -495,6 +496,12 @@ class Context:
 
     def set_wait_polls(self, polls: int):
         self._ok(self._L.lgp_set_wait_polls(self._h, int(polls)))
+
+    def sample_marks(self) -> int:
+        """How the last sample_khop recorded its samples: bits per vertex of its maps, 0 = sorted into bins, -1 = none yet."""
+        bits = C.c_int32()
+        self._ok(self._L.lgp_get_sample_marks(self._h, C.addressof(bits)))
+        return bits.value
 
     def set_profiling(self, mode):
         """False / 0 = off, True / 1 = every kernel group, 2 = the two row gathers only."""

@@ -63,6 +63,7 @@ struct lgp_ctx {
   bool either_map = false;     // a call may lay the maps out as bytes instead (kEitherMapMaxVertices), with this geometry
   MapGeom byte_geom;
   BinMaps bins;
+  int32_t sample_marks = -1;   // of the last lgp_sample_khop: bits per vertex of its maps, 0 = binned
   size_t map_words = 0, status_words = 0;   // 64-bit words of each map, and of its status
   std::vector<double> mean_samples;   // where a rule asks for it, [f]: samples of a vertex at fan-out f, mean over the graph
   uint32_t* d_err = nullptr;
@@ -421,6 +422,7 @@ bool binned(const lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32
 int binned_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops, const int64_t* need,
                 uint64_t rng_seed, const lgp_sample_out* out, hipStream_t s) {
   const TopoView tv = topo_view(c);
+  c->sample_marks = 0;
   if (++c->bins.call == 0) c->bins.call = 1;       // 0 marks no call: skipped after 2^32 of them
   BinArgs a = {};
   a.maps = c->bins;
@@ -477,6 +479,7 @@ int sample_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t
     di.spread_shift = 3;
     maps.geom = c->byte_geom;
   }
+  if (!hot_mode) c->sample_marks = 1 << di.spread_shift;
   uint32_t* fbits32 = reinterpret_cast<uint32_t*>(maps.frontier);
   uint32_t* gbits32 = reinterpret_cast<uint32_t*>(maps.gather);
   int32_t* n_frontier = hot_mode ? c->hs_n : out->n_frontier;
@@ -1635,6 +1638,12 @@ int lgp_set_wait_polls(lgp_ctx* c, int32_t polls) {
   if (!c) return LGP_EINVAL;
   if (polls < 0) return fail(c, LGP_EINVAL, "polls is negative");
   c->maps.polls = polls;
+  return LGP_OK;
+}
+
+int lgp_get_sample_marks(const lgp_ctx* c, int32_t* bits) {
+  if (!c || !bits) return LGP_EINVAL;
+  *bits = c->sample_marks;
   return LGP_OK;
 }
 

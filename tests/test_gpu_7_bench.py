@@ -38,6 +38,7 @@ def test_bench_line_on_the_tiny_workload(monkeypatch):
     assert 0 < r["frac"] <= 1 and r["frac"] == pytest.approx(r["achieved"] / r["peak"], abs=1e-3)
     assert "traffic" in r
     s = d["roofline_sampler"]
+    assert s["mark"] == "store of 32 bits"
     assert 0 < s["frac"] <= 1 and s["bytes_per_call"] > 0 and s["bitmap_atomics_per_call"] > 0
     c = d["cpu_baseline"]
     assert c["kind"] == "oracle" and c["unit"] == "seeds/s" and c["value"] > 0 and c["cores"] >= 1 and c["sample"]

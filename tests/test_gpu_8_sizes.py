@@ -761,6 +761,7 @@ def test_samples_sorted_into_bins(V, deg):
                 for polls in (4096, 0, 4096):
                     ctx.set_wait_polls(polls)
                     ctx.sample_khop(dev, fanouts, 23, out=buf)
+                    assert (ctx.sample_marks() == 0) == (crowded < rows and (n_seeds in (30_000, 60_001) or (V == 1 << 28 and n_seeds < 131_073)))
                     assert_batch_equal(ref, buf.to_host(dev), f"{V} {lists} {n_seeds} {fanouts} {polls} {last}")
         seeds = order[:40_000]
         dev = torch.from_numpy(seeds).cuda()
@@ -768,6 +769,7 @@ def test_samples_sorted_into_bins(V, deg):
         buf = lgp.SampleBuffers(V, seeds.size, (4, 4, 4))
         buf.c_struct.frontier[1] = buf.frontier[2].data_ptr()
         ctx.sample_khop(dev, (4, 4, 4), 29, out=buf)
+        assert ctx.sample_marks() in (1, 8)
         fr, nbr, _, ids = buf.to_host(dev)
         assert (ids == ref.gather_ids).all() and (fr[2] == ref.frontier[2]).all()
         assert all((nbr[h] == ref.nbr[h]).all() for h in range(3))
@@ -801,9 +803,11 @@ def test_no_seeds_on_a_large_graph(V):
             buf.n_frontier.fill_(77)
             buf.n_gather.fill_(77)
             ctx.sample_khop(none, fanouts, 3, out=buf)
+            assert ctx.sample_marks() in (1, 8)
             assert buf.n_gather.item() == 0 and buf.n_frontier.tolist() == [0] * len(fanouts) + [77]
             # maps and segments are in order for the calls around it
             got, again = (ctx.sample_khop(some, fanouts, 3) for _ in range(2))
+            assert (ctx.sample_marks() == 0) == (V > 5 << 25)
             assert got.n_gather.item() == again.n_gather.item() > 8192
             n = int(got.n_gather)
             assert torch.equal(got.gather_ids[:n], again.gather_ids[:n]) and torch.equal(got.gather_ids[:n], got.gather_ids[:n].unique())
@@ -853,6 +857,7 @@ def test_invalid_seeds_of_binned_calls():
         for polls in (4096, 0):
             ctx.set_wait_polls(polls)
             buf = ctx.sample_khop(dev, fanouts, 31)
+            assert ctx.sample_marks() == 0
             check(buf, dev, rows)
             if not rows.all():
                 with pytest.raises(lgp.LegionPrepError):
