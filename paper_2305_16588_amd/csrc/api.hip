@@ -269,10 +269,10 @@ size_t status_words(const lgp_ctx* c) {
 size_t segment_words(const lgp_ctx* c) { return size_t(c->bins.bins) * kBinWriters * kBinWords; }
 
 // Marks of a mini-batch on a graph whose vertices are equally popular: more than where popularity is skewed.  samples(f): of a
-// vertex at fan-out f.  *rows, if given: vertices expanded.
+// vertex at fan-out f.  *rows, if given: vertices expanded; hop_marks[h], if given: marks of hop h.
 template <typename Samples>
 double expected_marks(const lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts, int32_t n_hops, Samples samples,
-                      double* rows = nullptr) {
+                      double* rows = nullptr, double* hop_marks = nullptr) {
   const double V = double(c->g.num_vertices);
   double n = double(n_seeds), marks = 0;
   if (rows) *rows = 0;
@@ -280,6 +280,7 @@ double expected_marks(const lgp_ctx* c, int64_t n_seeds, const int32_t* fanouts,
     if (rows) *rows += n;
     const double m = n * samples(fanouts[h]);
     marks += m;
+    if (hop_marks) hop_marks[h] = m;
     n = V * -std::expm1(-m / V);
   }
   return marks;
@@ -386,17 +387,26 @@ int stage_topology(lgp_ctx* c, int64_t n_seeds, int32_t n_hops, hipStream_t s, S
   return LGP_OK;
 }
 
-// Whether lgp_sample_khop bins its samples (bin_marks).  Every bin's workgroup looks through all seeds, and reads its share of
+// Whether lgp_sample_khop bins its samples (bin_marks, kBinFill), and the most workgroups of each of its hops.  Every bin's workgroup looks through all seeds, and reads its share of
 // the inner frontiers again after all of them were written, so these must not share memory with anything the call writes.  Where rows
 // cross PCIe the link bounds the hops, and its two workgroups of 1024 threads per CU serve it a little worse (20 M vertices, 8192 seeds
 // (15, 10, 5), none and half of the topology cached 618 -> 621 and 225 -> 231 us).
 bool binned(const lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops, const int64_t* need,
-            int64_t gather_need, const lgp_sample_out* out) {
+            int64_t gather_need, const lgp_sample_out* out, int32_t* writers) {
   if (c->bins.bins == 0 || n_seeds == 0 || n_seeds > bin_max_seeds(c->g.num_vertices) || topo_view(c).over_pcie) return false;
+  for (int h = 0; h < n_hops; ++h) writers[h] = bin_writers(fanouts[h]);
   const double enough = bin_marks(c->g.num_vertices);
-  if (enough > 0 && expected_marks(c, n_seeds, fanouts, n_hops, [&](int32_t f) { return c->mean_samples[size_t(f)]; }) <
-                        enough + kBinMarksPerSeed * double(n_seeds))
-    return false;
+  if (enough > 0) {
+    double marks[LGP_MAX_HOPS];
+    if (expected_marks(c, n_seeds, fanouts, n_hops, [&](int32_t f) { return c->mean_samples[size_t(f)]; }, nullptr, marks) <
+        enough + kBinMarksPerSeed * double(n_seeds))
+      return false;
+    const double room = kBinFill * double(c->bins.bins) * double(kBinWords - 1);       // of a workgroup
+    for (int h = 0; h < n_hops && c->either_map; ++h) {
+      if (marks[h] > room * kBinWriters) return false;
+      if (marks[h] > room * writers[h]) writers[h] = kBinWriters;
+    }
+  }
   struct Span {
     uintptr_t at, end;
   };
@@ -420,7 +430,7 @@ bool binned(const lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32
 }
 
 int binned_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops, const int64_t* need,
-                uint64_t rng_seed, const lgp_sample_out* out, hipStream_t s) {
+                const int32_t* writers, uint64_t rng_seed, const lgp_sample_out* out, hipStream_t s) {
   const TopoView tv = topo_view(c);
   c->sample_marks = 0;
   if (++c->bins.call == 0) c->bins.call = 1;       // 0 marks no call: skipped after 2^32 of them
@@ -438,8 +448,8 @@ int binned_core(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t
   int64_t cap = n_seeds;
   for (int h = 0; h < n_hops; ++h) {
     a.writers = launch_sample_hop_binned(c->di, tv, frontier, out->n_frontier + h, cap, fanouts[h], h, rng_seed, out->nbr[h],
-                                         out->cnt[h], c->bins, reinterpret_cast<uint32_t*>(c->maps.frontier), c->d_err,
-                                         c->maps.status, s);
+                                         out->cnt[h], c->bins, writers[h], reinterpret_cast<uint32_t*>(c->maps.frontier),
+                                         c->d_err, c->maps.status, s);
     const bool last = h + 1 == n_hops;
     const bool want = !last || out->frontier[n_hops] != nullptr;
     a.list = out->frontier[h + 1];
@@ -1342,8 +1352,9 @@ int lgp_sample_khop(lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int
   hipStream_t s = static_cast<hipStream_t>(stream);
   LGP_HIP(c, hipSetDevice(c->di.device));
   EvPair ev = prof_begin(c, PK_SAMPLE, s);
-  st = binned(c, seeds, n_seeds, fanouts, n_hops, need, gather_need, out)
-           ? binned_core(c, seeds, n_seeds, fanouts, n_hops, need, rng_seed, out, s)
+  int32_t writers[LGP_MAX_HOPS];
+  st = binned(c, seeds, n_seeds, fanouts, n_hops, need, gather_need, out, writers)
+           ? binned_core(c, seeds, n_seeds, fanouts, n_hops, need, writers, rng_seed, out, s)
            : sample_core(c, seeds, n_seeds, fanouts, n_hops, need, rng_seed, out, s);
   prof_end(c, ev, s);
   return st;

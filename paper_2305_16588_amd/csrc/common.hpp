@@ -112,6 +112,20 @@ inline double bin_marks(int64_t num_vertices) {
   return num_vertices <= int64_t(1) << 24 ? 510e3 : num_vertices <= int64_t(1) << 26 ? 400e3
          : num_vertices <= int64_t(1) << 27 ? 200e3 : num_vertices <= int64_t(5) << 25 ? 60e3 : 0.0;
 }
+// Most workgroups of a hop.  Half as many segments to read and their heads fuller, against half as many waves to hide the loads: with
+// up to six samples per vertex a wave takes ten vertices and more at once, and one workgroup per CU is enough.  Calls at two -> one:
+// 8192 seeds (15, 10, f) of 111 M vertices, f = 2 47.4 -> 45.4 us, 3 46.3 -> 44.5, 5 46.8 -> 45.5, 6 48.5 -> 47.1, 8 48.5 -> 49.0, 12 51.3
+// -> 52.8; 32000 (15, 10, 5) 103 -> 95.5, of 12 M 141 -> 127; (10, 6) 39.1 -> 38.8, (10, 7) 40.6 -> 40.7, (10, 16) 48.3 -> 53.0.
+inline int32_t bin_writers(int32_t fanout) { return fanout <= 6 ? kBinWriters / 2 : kBinWriters; }
+// And, where bytes are the other way (up to 2^24 vertices), only while segments hold what a hop promises: samples beyond their room are
+// marked with atomics in a map of bits, which the lists then read and clear as well.  A hop that promises more than kBinFill times
+// its room takes all workgroups, and a call with a hop of more than kBinFill times the room of those marks bytes.  Calls, bytes -> one
+// workgroup per CU -> two, and the promise over the room of two: uniform degrees, 9.5 M vertices 16384 seeds (10, 10, 5) 284 -> 282 -> 240
+// us, 0.79; 20000 (15, 10, 5) 376 -> 426 -> 321, 1.11; 32000 529 -> 671 -> 539, 1.65; 65536 890 -> 1170 -> 1032, 2.8; 12 M 65536 (25, 10)
+// 438 -> 406, 1.28; 16384 (15, 10, 10) 636 -> 700, 1.84; 16.5 M 65536 (15, 25) 739 -> 632, 1.46.  Where popularity is skewed hops are
+// smaller than promised: 9.5 M of mean degree 40, 32000 (15, 10, 5) 226 -> 180 -> 192, 1.24; 65536 329 -> 332 -> 292, 2.2; 12 M of 60 289 ->
+// 252 -> 265, 1.36.  Against bits no promise is too large (33 M, 131072 (15, 10, 5), 4.4 times the room: 3824 -> 3300).
+constexpr double kBinFill = 1.5;
 // And only graphs whose column ids are spread: where a call's samples crowd into few bins, few workgroups make its list and most samples
 // are marked in the map after all.  Degrees of 12, map -> bins, 8192 (15, 10, 5) and 8000 (25, 10): all columns within half of
 // the ids 12 M vertices 199 -> 179 us and 41 -> 38, 111 M 310 -> 218 and 68 -> 39; a third 160 -> 206, 39 -> 42 and 311 -> 260,
@@ -205,10 +219,10 @@ void launch_sample_hop(const DeviceInfo& di, const TopoView& tv, const int32_t* 
                        int64_t n_status, hipStream_t s, const FirstGroup& first = FirstGroup{});
 
 // The same for binned marks: no hotness, and seeds are not marked; what finds no room is marked in mark_bits.  status[0 ..
-// kBinStatusWords) of 32 bits is cleared.  Returns the number of workgroups, which is the number of segments of a bin.
+// kBinStatusWords) of 32 bits is cleared.  At most `writers` workgroups; returns their number, which is that of the segments of a bin.
 int32_t launch_sample_hop_binned(const DeviceInfo& di, const TopoView& tv, const int32_t* frontier, int32_t* n_frontier,
                                  int64_t cap, int32_t fanout, int32_t hop, uint64_t rng_seed, int32_t* nbr, int32_t* cnt,
-                                 const BinMaps& m, uint32_t* mark_bits, uint32_t* d_err, uint64_t* status, hipStream_t s);
+                                 const BinMaps& m, int32_t writers, uint32_t* mark_bits, uint32_t* d_err, uint64_t* status, hipStream_t s);
 
 // Pre-sampling: staged[0 .. n_edges) = h_indices[0 .. n_edges), from CPU memory to HBM.  The two addresses are equal modulo 16.
 void launch_stage_topology(const int32_t* h_indices, int32_t* staged, int64_t n_edges, hipStream_t s);

@@ -86,16 +86,11 @@ void launch_sample_hop(const DeviceInfo& di, const TopoView& tv, const int32_t* 
 
 int32_t launch_sample_hop_binned(const DeviceInfo& di, const TopoView& tv, const int32_t* frontier, int32_t* n_frontier,
                                  int64_t cap, int32_t fanout, int32_t hop, uint64_t rng_seed, int32_t* nbr, int32_t* cnt,
-                                 const BinMaps& m, uint32_t* mark_bits, uint32_t* d_err, uint64_t* status, hipStream_t s) {
+                                 const BinMaps& m, int32_t writers, uint32_t* mark_bits, uint32_t* d_err, uint64_t* status, hipStream_t s) {
   const HopArgs a{tv,  frontier, n_frontier, cap,     fanout,  hop_lanes(tv, fanout), hop,    uint32_t(rng_seed), uint32_t(rng_seed >> 32),
                   nbr, cnt,      mark_bits,  nullptr, nullptr, d_err,                 status, kBinStatusWords / 2, m};
-  // Half as many segments to read and their heads fuller, against half as many waves to hide the loads: with up to six lanes per
-  // vertex a wave takes ten vertices and more at once, and one workgroup per CU is enough.  Calls at two -> one: 8192 seeds (15, 10,
-  // f) of 111 M vertices, f = 2 47.4 -> 45.4 us, 3 46.3 -> 44.5, 5 46.8 -> 45.5, 6 48.5 -> 47.1, 8 48.5 -> 49.0, 12 51.3 -> 52.8; 32000
-  // (15, 10, 5) 103 -> 95.5, of 12 M 141 -> 127; (10, 6) 39.1 -> 38.8, (10, 7) 40.6 -> 40.7, (10, 16) 48.3 -> 53.0.
-  const int64_t most = a.lanes <= 6 ? kBinWriters / 2 : kBinWriters;
   const int64_t per_block = kBinThreads / 64 * (64 / a.lanes), blocks = (cap + per_block - 1) / per_block;
-  const int32_t writers = int32_t(std::max<int64_t>(1, std::min(blocks, most)));
+  writers = int32_t(std::max<int64_t>(1, std::min<int64_t>(blocks, writers)));
   hipLaunchKernelGGL(sample_hop_binned_kernel, dim3(unsigned(writers)), dim3(unsigned(kBinThreads)), 0, s, a);
   return writers;
 }
