@@ -883,19 +883,19 @@ def test_invalid_seeds_of_binned_calls():
 
 def test_bins_while_their_segments_hold_a_call():
     """Up to 2^24 vertices: a hop that promises more than the segments of one workgroup per CU hold takes two per CU, and a call with
-    one that promises more than those hold marks bytes."""
+    one that promises more than those hold marks bytes, as does a single hop."""
     import oracle
     import paper_2305_16588_amd as lgp
     from gpu_common import assert_batch_equal
-    V, deg = (9 << 20) + 1, 8
+    V, deg = (9 << 20) + 1, 16
     gen = torch.Generator(device="cuda").manual_seed(9)
     indptr = np.arange(V + 1, dtype=np.int32) * deg
     indices = torch.randint(0, V, (V * deg,), generator=gen, device="cuda", dtype=torch.int32)
     ctx, orc = lgp.Context(lgp.pinned_copy(indptr), indices), oracle.Oracle(indptr, indices.cpu().numpy(), None)
-    seeds = np.random.default_rng(1).permutation(V)[:40_000].astype(np.int32)
+    seeds = np.random.default_rng(1).permutation(V)[:60_000].astype(np.int32)
     # samples of the last hop over the room of two workgroups per CU (145 bins * 512 * 127): 0.7, 0.9, 1.1, 1.9, 0.7
     for n_seeds, fanouts, marks in ((30_000, (8, 8, 4), 0), (30_000, (8, 8, 5), 0), (40_000, (8, 8, 5), 0), (40_000, (8, 8, 8), 8),
-                                    (30_000, (8, 8, 4), 0)):
+                                    (60_000, (16,), 8), (30_000, (8, 8, 4), 0)):
         dev = torch.from_numpy(seeds[:n_seeds]).cuda()
         buf = ctx.sample_khop(dev, fanouts, 37)
         assert ctx.sample_marks() == marks, f"{n_seeds} {fanouts}"
