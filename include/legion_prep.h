@@ -122,7 +122,10 @@ int lgp_host_free(void* ptr);
  * lookup state in HBM: a row table (offset + degree + "cached" flag, 8 bytes per
  * vertex, filled from indptr), the feature remap, two hotness vectors and the dedup
  * maps -- about 20.3 bytes per vertex (22 to 28 on graphs of up to 2^24 vertices, whose maps
- * have room for a byte or more per vertex), outside the cache budgets.  It starts with
+ * have room for a byte or more per vertex), outside the cache budgets.  On graphs of 9 * 2^20 to
+ * 2^28 vertices whose column ids are spread it reads 65536 of these ids, and 33 to 64 MiB more are
+ * taken for the sampler's segments, here if the column ids are in HBM, else when a cache with all of
+ * them is built; where memory is short the sampler does without.  It starts with
  * empty caches, so sampling and gathering already work, with every column id and
  * feature row read from CPU memory (Sec. 3.2's mode with the topology kept in CPU memory).
  * Synchronous. */
@@ -340,9 +343,9 @@ int lgp_set_overlap(lgp_ctx* ctx, int enable);
 /* HBM the library holds or will allocate on its own for calls of one shape, in bytes, so that a
  * caller can budget device memory before building caches (Sec. 4.3.1: B is what is left after
  * everything else is reserved).  fixed [host] = the per-context tables that exist since
- * lgp_create (row table, feature remap, hotness vectors, dedup maps, the sampler's segments on
- * graphs of more than 9 * 2^20 vertices whose column ids are spread, rankings once a plan was
- * made); scratch [host] = what pre-sampling, lgp_gather_features(_clique) with up to the
+ * lgp_create (row table, feature remap, hotness vectors, dedup maps), the rankings of a plan,
+ * and the sampler's segments (33 to 64 MiB) on graphs of 9 * 2^20 to 2^28 vertices whose column ids are
+ * spread, whether they are there already (lgp_create) or not; scratch [host] = what pre-sampling, lgp_gather_features(_clique) with up to the
  * worst-case number of ids and lgp_build_blocks allocate on first use for batches of up to
  * max_seeds seeds with these fan-outs.  The caches themselves are reported by lgp_plan_cache /
  * lgp_get_cache_plan.  The column ids that lgp_build_hotness may hold in HBM while it runs are in

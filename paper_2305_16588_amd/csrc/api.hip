@@ -265,8 +265,11 @@ size_t map_words(const lgp_ctx* c) {
 size_t status_words(const lgp_ctx* c) {
   return size_t(std::max<int64_t>({c->maps.geom.groups, c->byte_geom.groups, c->bins.bins ? kBinStatusWords / 2 : 0}));
 }
-// Room for the segments of a context with binned marks, in words.
+// Room for the segments of a context with binned marks, and for what goes with them, in words.
 size_t segment_words(const lgp_ctx* c) { return size_t(c->bins.bins) * kBinWriters * kBinWords; }
+size_t bin_words(const lgp_ctx* c) {
+  return c->bins.bins ? segment_words(c) + kMaxBins + LGP_MAX_HOPS * (kMaxBins + 1) + 1 : 0;
+}
 
 // Marks of a mini-batch on a graph whose vertices are equally popular: more than where popularity is skewed.  samples(f): of a
 // vertex at fan-out f.  *rows, if given: vertices expanded; hop_marks[h], if given: marks of hop h.
@@ -309,12 +312,31 @@ hipError_t count_samples(lgp_ctx* c) {
   return hipSuccess;
 }
 
-// Without bins: samples are marked in maps.
-void give_up_bins(lgp_ctx* c) {
-  void* ptrs[] = {c->bins.heads, c->bins.tails, c->bins.spilled, c->bins.first, c->bins.odd_seeds};
+void drop_segments(lgp_ctx* c) {
+  BinMaps& b = c->bins;
+  void* ptrs[] = {b.heads, b.tails, b.spilled, b.first, b.odd_seeds};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
-  c->bins = BinMaps{};
+  b.heads = b.tails = b.spilled = b.odd_seeds = nullptr;
+  b.first = nullptr;
+}
+
+// Segments, once calls can use them, which is when no row crosses PCIe; where memory is short calls do without.  Synchronous.
+hipError_t hold_segments(lgp_ctx* c) {
+  BinMaps& b = c->bins;
+  if (b.bins == 0 || b.heads || topo_view(c).over_pcie) return hipSuccess;
+  if (dev_alloc(&b.heads, segment_words(c) / kBinWords * kHeadWords) != hipSuccess ||
+      dev_alloc(&b.tails, segment_words(c) / kBinWords * (kBinWords - kHeadWords)) != hipSuccess ||
+      dev_alloc(&b.spilled, kMaxBins) != hipSuccess || dev_alloc(&b.first, LGP_MAX_HOPS * (kMaxBins + 1)) != hipSuccess ||
+      dev_alloc(&b.odd_seeds, 1) != hipSuccess) {
+    (void)hipGetLastError();
+    drop_segments(c);
+    return hipSuccess;
+  }
+  hipError_t e = hipMemset(b.spilled, 0, sizeof(uint32_t) * kMaxBins);
+  if (e == hipSuccess) e = hipMemset(b.odd_seeds, 0, sizeof(uint32_t));
+  if (e == hipSuccess) e = hipDeviceSynchronize();
+  return e;
 }
 
 // Gives up the bins of a context whose column ids are crowded (columns_spread).  As count_samples does.
@@ -324,7 +346,7 @@ hipError_t count_columns(lgp_ctx* c) {
   hipError_t e = hipGetLastError();
   if (e == hipSuccess) e = hipMemcpy(host, c->topo_hot, sizeof(host), hipMemcpyDeviceToHost);
   if (e == hipSuccess) e = hipMemset(c->topo_hot, 0, sizeof(host));
-  if (e == hipSuccess && !columns_spread(host, c->bins.bins)) give_up_bins(c);
+  if (e == hipSuccess && !columns_spread(host, c->bins.bins)) c->bins = BinMaps{};
   return e;
 }
 
@@ -394,7 +416,7 @@ int stage_topology(lgp_ctx* c, int64_t n_seeds, int32_t n_hops, hipStream_t s, S
 bool binned(const lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops, const int64_t* need,
             int64_t gather_need, const lgp_sample_out* out, int32_t* writers) {
   if (c->either_map && n_hops == 1) return false;
-  if (c->bins.bins == 0 || n_seeds == 0 || n_seeds > bin_max_seeds(c->g.num_vertices) || topo_view(c).over_pcie) return false;
+  if (!c->bins.heads || n_seeds == 0 || n_seeds > bin_max_seeds(c->g.num_vertices) || topo_view(c).over_pcie) return false;
   for (int h = 0; h < n_hops; ++h) writers[h] = bin_writers(fanouts[h]);
   const double enough = bin_marks(c->g.num_vertices);
   if (enough > 0) {
@@ -869,22 +891,11 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   step(dev_alloc(&c->seg, LGP_MAX_HOPS + 2));
   step(dev_alloc(&c->unordered, LGP_MAX_HOPS + 1));
   step(dev_alloc(&c->seg_counters, (LGP_MAX_HOPS + 1) * 3));
-  if (e == hipSuccess && c->bins.bins &&
-      (dev_alloc(&c->bins.heads, segment_words(c) / kBinWords * kHeadWords) != hipSuccess ||
-       dev_alloc(&c->bins.tails, segment_words(c) / kBinWords * (kBinWords - kHeadWords)) != hipSuccess ||
-       dev_alloc(&c->bins.spilled, kMaxBins) != hipSuccess ||
-       dev_alloc(&c->bins.first, LGP_MAX_HOPS * (kMaxBins + 1)) != hipSuccess ||
-       dev_alloc(&c->bins.odd_seeds, 1) != hipSuccess)) {
-    (void)hipGetLastError();                                 // memory is short, and maps do without segments
-    give_up_bins(c);
-  }
   if (e == hipSuccess) e = hipMemset(c->f_remap, 0xff, sizeof(int32_t) * size_t(V));
   if (e == hipSuccess) e = hipMemset(c->topo_hot, 0, sizeof(uint32_t) * size_t(V));
   if (e == hipSuccess) e = hipMemset(c->feat_hot, 0, sizeof(uint32_t) * size_t(V));
   if (e == hipSuccess) e = hipMemset(c->maps.frontier, 0, sizeof(uint64_t) * words);
   if (e == hipSuccess) e = hipMemset(c->maps.gather, 0, sizeof(uint64_t) * words);
-  if (e == hipSuccess && c->bins.bins) e = hipMemset(c->bins.spilled, 0, sizeof(uint32_t) * kMaxBins);
-  if (e == hipSuccess && c->bins.bins) e = hipMemset(c->bins.odd_seeds, 0, sizeof(uint32_t));
   if (e == hipSuccess) e = hipMemset(c->d_err, 0, sizeof(uint32_t));
   if (e == hipSuccess) e = hipMemset(c->counters, 0, 3 * sizeof(int32_t));
   if (e == hipSuccess) e = hipMemset(c->unordered, 0, (LGP_MAX_HOPS + 1) * sizeof(uint32_t));
@@ -898,6 +909,7 @@ int lgp_create(const lgp_graph* g, int device, lgp_ctx** out) {
   }
   if (e == hipSuccess && (c->either_map || (c->bins.bins && bin_marks(V) > 0))) e = count_samples(c);
   if (e == hipSuccess && c->bins.bins) e = count_columns(c);
+  if (e == hipSuccess) e = hold_segments(c);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) {
     (void)hipGetLastError();
@@ -914,8 +926,8 @@ int lgp_destroy(lgp_ctx* c) {
   free_cache(c);
   void* ptrs[] = {c->row_tab, c->f_remap, c->topo_hot, c->feat_hot, c->maps.frontier, c->maps.gather, c->maps.status,
                   c->d_err,   c->counters, c->order_t, c->order_f,  c->lists, c->hs_n, c->pos_table, c->tile_sums, c->hs_expansions,
-                  c->seg, c->seg_counters, c->unordered, c->bins.heads, c->bins.tails,
-                  c->bins.spilled, c->bins.first, c->bins.odd_seeds};
+                  c->seg, c->seg_counters, c->unordered};
+  drop_segments(c);
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   for (int h = 0; h < LGP_MAX_HOPS; ++h)
@@ -1165,6 +1177,7 @@ int lgp_build_cache(lgp_ctx* c, uint64_t topo_budget, uint64_t feat_budget, void
   }
   c->plan = p;
   c->fc_identity = (p.n_feat == V);
+  LGP_HIP(c, hold_segments(c));
   return LGP_OK;
 }
 
@@ -1280,6 +1293,7 @@ int lgp_build_clique_cache(lgp_ctx* c, int32_t k_g, const uint32_t* topo_hot, co
     c->clique_te[g] = te[g];
     c->clique_fn[g] = fn[g];
   }
+  LGP_HIP(c, hold_segments(c));
   return LGP_OK;
 }
 
@@ -1610,7 +1624,7 @@ int lgp_workspace_bytes(const lgp_ctx* c, int32_t max_seeds, const int32_t* fano
   if (fixed) {
     const size_t map = c->map_words * 8;
     // row table 8 + remap 4 + two hotness vectors 4 + 4 + two rankings 4 + 4 bytes per vertex
-    *fixed = V * 28 + 2 * map + c->status_words * 8 + segment_words(c) * 4 + 64;
+    *fixed = V * 28 + 2 * map + c->status_words * 8 + bin_words(c) * 4 + 64;
   }
   if (scratch) {
     int64_t need[LGP_MAX_HOPS + 1], gather_need;

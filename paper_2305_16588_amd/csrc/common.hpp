@@ -145,6 +145,7 @@ inline bool columns_spread(const uint32_t* counts, int32_t bins) {
   std::sort(by_bin, by_bin + kMaxBins, std::greater<uint32_t>());
   double total = 0, fullest = 0, near = 0;
   for (uint32_t n : by_bin) total += double(n);
+  if (total == 0) return false;            // no edges, so there will be no samples
   for (int32_t w = 0; w < bins; ++w) {
     fullest += double(by_bin[w]);
     near += double(counts[kMaxBins + w]);
@@ -159,6 +160,7 @@ inline int bin_shift(int64_t num_vertices) {
   return shift;
 }
 struct BinMaps {
+  // null while the context holds no segments (hold_segments).
   // Segments [bin][workgroup of the hop]; word 0 of a segment is its count, which may be larger than its room.
   uint32_t* heads = nullptr;          // the first kHeadWords words of each, which are always read
   uint32_t* tails = nullptr;          // the others
@@ -169,7 +171,7 @@ struct BinMaps {
   // and lgp_check on that stream clears it while this call runs.
   uint32_t* odd_seeds = nullptr;
   uint32_t call = 0;
-  int32_t shift = 0, bins = 0;        // bins == 0: this context marks maps
+  int32_t shift = 0, bins = 0;        // bins == 0: this context marks maps in every call
 };
 
 struct DeviceInfo {

@@ -901,3 +901,52 @@ def test_bins_while_their_segments_hold_a_call():
         assert ctx.sample_marks() == marks, f"{n_seeds} {fanouts}"
         assert_batch_equal(orc.sample_khop(seeds[:n_seeds], fanouts, 37), buf.to_host(dev), f"{n_seeds} {fanouts}")
     ctx.check()
+
+
+def test_segments_are_held_where_calls_use_them():
+    """The room for binned samples is taken when no row crosses PCIe any more, and never on a graph without edges or with crowded column
+    ids; the figure for the caller's budget has it in either case."""
+    import oracle
+    import paper_2305_16588_amd as lgp
+    from gpu_common import assert_batch_equal
+    V, deg = (9 << 20) + 1, 8
+    words = 145 * 512 * 128 + 256 + 8 * 257 + 1                # 145 bins of 512 segments; flags, bounds of eight hops, one word
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    indptr = lgp.pinned_copy(np.arange(V + 1, dtype=np.int32) * deg)
+    spread = torch.randint(0, V, (V * deg,), generator=gen, device="cuda", dtype=torch.int32)
+    host = lgp.pinned_copy(spread.cpu().numpy())
+    none = lgp.pinned_copy(np.zeros(V + 1, np.int32))
+    fanouts = (7, 6, 3)
+
+    def made(*graph):
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        ctx = lgp.Context(*graph)
+        return ctx, before - torch.cuda.mem_get_info()[0], ctx.workspace_bytes(1, fanouts)[0]
+
+    keep, _, _ = made(indptr, spread)                          # what the first context of a process takes beside its own
+    ctx_none, used_none, fixed_none = made(none, host[:0])
+    ctx_crowd, used_crowd, fixed_crowd = made(indptr, spread % (1 << 16))
+    ctx_dev, used_dev, fixed_dev = made(indptr, spread)
+    ctx, used, fixed = made(indptr, host)
+    assert fixed_none == fixed_crowd == fixed - words * 4 and fixed_dev == fixed
+    assert abs(used_none - used) <= 4 << 20 and abs(used_crowd - used) <= 4 << 20
+    assert abs(used_dev - used - words * 4) <= 4 << 20
+    seeds = np.random.default_rng(1).permutation(V)[:20_000].astype(np.int32)
+    dev = torch.from_numpy(seeds).cuda()
+    ref = oracle.Oracle(indptr, host, None).sample_khop(seeds, fanouts, 41)
+    ctx.set_hotness(np.ones(V, np.uint32), np.ones(V, np.uint32))
+    half = V // 2 * (4 * deg + 8)
+    for budget, binned in ((0, False), (half, False), (4 * half, True), (half, False), (4 * half, True)):
+        assert (ctx.build_cache(budget, 0).n_topo == V) == binned
+        assert_batch_equal(ref, ctx.sample_khop(dev, fanouts, 41).to_host(dev), f"{budget}")
+        assert (ctx.sample_marks() == 0) == binned
+    assert_batch_equal(ref, ctx_dev.sample_khop(dev, fanouts, 41).to_host(dev), "in HBM")
+    assert ctx_dev.sample_marks() == 0
+    hot = torch.ones((2, V), dtype=torch.int32, device="cuda")
+    other, _, _ = made(indptr, host)
+    assert sum(p.n_topo for p in other.build_clique_cache(hot, hot, 4 * half, 0)) == V
+    assert_batch_equal(ref, other.sample_khop(dev, fanouts, 41).to_host(dev), "clique")
+    assert other.sample_marks() == 0
+    for c in (keep, ctx_none, ctx_crowd, ctx_dev, ctx, other):
+        c.check()
