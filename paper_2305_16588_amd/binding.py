@@ -144,11 +144,16 @@ def pinned_copy(a: np.ndarray) -> np.ndarray:
     return out
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)    # no public name: where it is missing, the public way
+
+
 def _stream_ptr(stream):
     # The current stream without a torch.cuda.Stream around it, which takes 3 us to make: a call of a few dozen seeds is a chain of
     # launches of 3 us each, and the host kept it waiting (sample_khop + gather_features of 64 seeds (15, 10, 5) 28.7 -> 25.4 us).
     if stream is None:
-        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+        if _raw_stream is not None:
+            return C.c_void_p(_raw_stream(torch.cuda.current_device()))
+        stream = torch.cuda.current_stream()
     return C.c_void_p(stream.cuda_stream)
 
 

@@ -51,6 +51,19 @@ def test_null_arguments_are_rejected_without_a_gpu():
     assert lib.lgp_get_sample_marks(None, None) == -1
 
 
+def test_current_stream_without_the_private_look_up(monkeypatch):
+    import types
+    import torch
+    import paper_2305_16588_amd as lgp
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=4711))
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(lgp.binding, "_raw_stream", lambda device: 1000 + device)
+    assert lgp.binding._stream_ptr(None).value == 1003
+    monkeypatch.setattr(lgp.binding, "_raw_stream", None)
+    assert lgp.binding._stream_ptr(None).value == 4711
+    assert lgp.binding._stream_ptr(types.SimpleNamespace(cuda_stream=5)).value == 5
+
+
 def test_worst_case_sizes():
     import paper_2305_16588_amd as lgp
     need, g = lgp.worst_case_sizes(2_400_000, 8192, (15, 10, 5))

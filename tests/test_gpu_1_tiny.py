@@ -630,3 +630,14 @@ def test_randomized_small_workloads(case):
     assert tuple(stats3.tolist()) == orc.count_three_way(ref.gather_ids, feat_ids, member)
     ctx.check()
     ctx.close()
+
+
+def test_current_stream_of_the_binding(monkeypatch):
+    """Calls without a stream go to the current one, by the quick look-up and by the public one, inside a stream's context and outside."""
+    import paper_2305_16588_amd as lgp
+    side = torch.cuda.Stream()
+    for look_up in (lgp.binding._raw_stream, None):
+        monkeypatch.setattr(lgp.binding, "_raw_stream", look_up)
+        assert (lgp.binding._stream_ptr(None).value or 0) == torch.cuda.current_stream().cuda_stream
+        with torch.cuda.stream(side):
+            assert lgp.binding._stream_ptr(None).value == side.cuda_stream
