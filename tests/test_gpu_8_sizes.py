@@ -950,3 +950,63 @@ def test_segments_are_held_where_calls_use_them():
     assert other.sample_marks() == 0
     for c in (keep, ctx_none, ctx_crowd, ctx_dev, ctx, other):
         c.check()
+
+
+@pytest.mark.parametrize("V", [(9 << 20) + 1, (1 << 25) + 1])
+def test_binned_calls_from_a_graph_and_from_any_address(V):
+    """Binned calls captured once and replayed on other seeds, invalid ones among them, with calls made directly between the replays; and
+    seed lists that begin at any multiple of four bytes and end at any remainder of four seeds."""
+    import oracle
+    import paper_2305_16588_amd as lgp
+    from gpu_common import assert_batch_equal
+    deg, fanouts = 8, (7, 6, 3)
+    gen = torch.Generator(device="cuda").manual_seed(V)
+    indptr = np.arange(V + 1, dtype=np.int32) * deg
+    indices = torch.randint(0, V, (V * deg,), generator=gen, device="cuda", dtype=torch.int32)
+    ctx, orc = lgp.Context(lgp.pinned_copy(indptr), indices), oracle.Oracle(indptr, indices.cpu().numpy(), None)
+    perm = np.random.default_rng(V).permutation(V)[:40_000].astype(np.int32)
+    room = torch.from_numpy(perm).cuda()
+    for shift, n in ((0, 20_001), (1, 20_002), (2, 20_003), (3, 20_000), (1, 8191), (3, 8194)):
+        buf = ctx.sample_khop(room[shift:shift + n], (7, 6, 6), 43)
+        assert ctx.sample_marks() == 0
+        assert_batch_equal(orc.sample_khop(perm[shift:shift + n], (7, 6, 6), 43), buf.to_host(room[shift:shift + n]), f"{shift} {n}")
+
+    n = 20_000
+    bad = perm[n:].copy()
+    bad[[0, 7777, n - 1]] = [-1, V, -7]
+    lists = [perm[:n], perm[n:], bad]
+    refs = [orc.sample_khop(ids[(ids >= 0) & (ids < V)], fanouts, 47) for ids in lists]
+    devs = [torch.from_numpy(ids).cuda() for ids in lists]
+    hold = devs[0].clone()
+    out = lgp.SampleBuffers(V, n, fanouts, last_frontier=True)
+    direct = lgp.SampleBuffers(V, n, fanouts)
+    ctx.sample_khop(hold, fanouts, 47, out=out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.sample_khop(hold, fanouts, 47, out=out)
+    assert ctx.sample_marks() == 0
+
+    def check(buf, k):
+        fr, nbr, cnt, ids = buf.to_host(devs[k])
+        rows = (lists[k] >= 0) & (lists[k] < V)
+        assert ids.shape == refs[k].gather_ids.shape and (ids == refs[k].gather_ids).all(), f"list {k}"
+        for h in range(1, len(fr)):
+            assert fr[h].shape == refs[k].frontier[h].shape and (fr[h] == refs[k].frontier[h]).all(), f"list {k}, frontier {h}"
+        assert (nbr[0][rows] == refs[k].nbr[0]).all() and (cnt[0][rows] == refs[k].cnt[0]).all(), f"list {k}"
+        assert all((nbr[h] == refs[k].nbr[h]).all() and (cnt[h] == refs[k].cnt[h]).all() for h in (1, 2)), f"list {k}"
+
+    for k, other in ((1, 0), (0, 1), (2, 0), (1, 2), (2, 2), (0, 0)):
+        hold.copy_(devs[k])
+        graph.replay()
+        torch.cuda.synchronize()
+        ctx.sample_khop(devs[other], fanouts, 47, out=direct)
+        torch.cuda.synchronize()
+        check(out, k)
+        check(direct, other)
+        try:
+            ctx.check()
+        except lgp.LegionPrepError:
+            assert 2 in (k, other)
+        else:
+            assert 2 not in (k, other)
