@@ -415,7 +415,7 @@ int stage_topology(lgp_ctx* c, int64_t n_seeds, int32_t n_hops, hipStream_t s, S
 // (15, 10, 5), none and half of the topology cached 618 -> 621 and 225 -> 231 us).
 bool binned(const lgp_ctx* c, const int32_t* seeds, int32_t n_seeds, const int32_t* fanouts, int32_t n_hops, const int64_t* need,
             int64_t gather_need, const lgp_sample_out* out, int32_t* writers) {
-  if (c->either_map && n_hops == 1) return false;
+  if (n_hops == 1 && (c->either_map || (fanouts[0] == 1 && n_seeds >= kBinSeedsOfOne))) return false;
   if (!c->bins.heads || n_seeds == 0 || n_seeds > bin_max_seeds(c->g.num_vertices) || topo_view(c).over_pcie) return false;
   for (int h = 0; h < n_hops; ++h) writers[h] = bin_writers(fanouts[h]);
   const double enough = bin_marks(c->g.num_vertices);

@@ -129,7 +129,10 @@ constexpr double kBinFill = 1.5;
 // Against bytes one hop alone is no gain either: every bin's workgroup looks through all seeds, and there are more than 8000 of them
 // before one hop has enough samples.  Bytes -> bins, 65536 seeds: 9.5 M vertices of degree 12 (25) 25.8 -> 29.4 us, (64) 28.8 -> 34.1;
 // 16.5 M (12) 26.6 -> 27.4; 12 M of power-law degrees, mean 40, (40) 32.6 -> 39.0; 9.5 M of degree 64 (40) 76.4 -> 89.1, 32000 seeds 44.0 ->
-// 47.5.  Faster were those that take all of each row, (64) there 84.6 -> 70.9.
+// 47.5.  Faster were those that take all of each row, (64) there 84.6 -> 70.9.  Against bits that holds for one sample per seed only, from
+// kBinSeedsOfOne seeds on: 168 M vertices, 131072 seeds (1) 26.7 -> 32.7, (2) 32.1 -> 33.6, (4) 42.5 -> 36.4; 65536 (1) 19.7 -> 21.9, (3) 25.6 ->
+// 21.8; 250 M 28.6 -> 32.6, 34.1 -> 33.2, 44.8 -> 35.6, 21.8 -> 22.8, 27.3 -> 22.0.
+constexpr int32_t kBinSeedsOfOne = 1 << 16;
 // And only graphs whose column ids are spread: where a call's samples crowd into few bins, few workgroups make its list and most samples
 // are marked in the map after all.  Degrees of 12, map -> bins, 8192 (15, 10, 5) and 8000 (25, 10): all columns within half of
 // the ids 12 M vertices 199 -> 179 us and 41 -> 38, 111 M 310 -> 218 and 68 -> 39; a third 160 -> 206, 39 -> 42 and 311 -> 260,

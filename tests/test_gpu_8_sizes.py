@@ -811,6 +811,14 @@ def test_no_seeds_on_a_large_graph(V):
             assert got.n_gather.item() == again.n_gather.item() > 8192
             n = int(got.n_gather)
             assert torch.equal(got.gather_ids[:n], again.gather_ids[:n]) and torch.equal(got.gather_ids[:n], got.gather_ids[:n].unique())
+    # one sample per seed is in no bin from 2^16 seeds on
+    many = torch.arange(0, 61 * (1 << 16), 61, device="cuda", dtype=torch.int32)
+    for seeds, fanouts, binned in ((many, (1,), False), (many[1:], (1,), True), (many, (2,), True), (many, (1, 1), True)):
+        got = ctx.sample_khop(seeds, fanouts, 5)
+        assert (ctx.sample_marks() == 0) == (binned and V > 5 << 25)
+        rows = [got.nbr[h][:int(got.n_frontier[h])].flatten() for h in range(len(fanouts))]
+        ids = torch.cat([seeds, *rows])
+        assert torch.equal(got.gather_ids[:int(got.n_gather)], ids[ids >= 0].unique())
     ctx.check()
 
 
