@@ -268,7 +268,7 @@ size_t status_words(const lgp_ctx* c) {
 // Room for the segments of a context with binned marks, and for what goes with them, in words.
 size_t segment_words(const lgp_ctx* c) { return size_t(c->bins.bins) * kBinWriters * kBinWords; }
 size_t bin_words(const lgp_ctx* c) {
-  return c->bins.bins ? segment_words(c) + kMaxBins + LGP_MAX_HOPS * (kMaxBins + 1) + 1 : 0;
+  return c->bins.bins ? segment_words(c) + (kMaxBins + 1) + LGP_MAX_HOPS * (kMaxBins + 1) : 0;
 }
 
 // Marks of a mini-batch on a graph whose vertices are equally popular: more than where popularity is skewed.  samples(f): of a
@@ -314,10 +314,10 @@ hipError_t count_samples(lgp_ctx* c) {
 
 void drop_segments(lgp_ctx* c) {
   BinMaps& b = c->bins;
-  void* ptrs[] = {b.heads, b.tails, b.spilled, b.first, b.odd_seeds};
+  void* ptrs[] = {b.heads, b.tails, b.spilled, b.first};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
-  b.heads = b.tails = b.spilled = b.odd_seeds = nullptr;
+  b.heads = b.tails = b.spilled = nullptr;
   b.first = nullptr;
 }
 
@@ -327,14 +327,13 @@ hipError_t hold_segments(lgp_ctx* c) {
   if (b.bins == 0 || b.heads || topo_view(c).over_pcie) return hipSuccess;
   if (dev_alloc(&b.heads, segment_words(c) / kBinWords * kHeadWords) != hipSuccess ||
       dev_alloc(&b.tails, segment_words(c) / kBinWords * (kBinWords - kHeadWords)) != hipSuccess ||
-      dev_alloc(&b.spilled, kMaxBins) != hipSuccess || dev_alloc(&b.first, LGP_MAX_HOPS * (kMaxBins + 1)) != hipSuccess ||
-      dev_alloc(&b.odd_seeds, 1) != hipSuccess) {
+      dev_alloc(&b.spilled, kMaxBins + 1) != hipSuccess ||
+      dev_alloc(&b.first, LGP_MAX_HOPS * (kMaxBins + 1)) != hipSuccess) {
     (void)hipGetLastError();
     drop_segments(c);
     return hipSuccess;
   }
-  hipError_t e = hipMemset(b.spilled, 0, sizeof(uint32_t) * kMaxBins);
-  if (e == hipSuccess) e = hipMemset(b.odd_seeds, 0, sizeof(uint32_t));
+  hipError_t e = hipMemset(b.spilled, 0, sizeof(uint32_t) * (kMaxBins + 1));
   if (e == hipSuccess) e = hipDeviceSynchronize();
   return e;
 }

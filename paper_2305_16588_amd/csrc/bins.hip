@@ -306,7 +306,7 @@ __global__ __launch_bounds__(kBinThreads) void list_bins_kernel(BinArgs a) {
   l.load_heads(bin, heads);
   const bool spilled = agent_load(&a.maps.spilled[bin]) != 0;
   if (M & kUnion) {
-    odd_rows = *a.maps.odd_seeds == a.maps.call;             // set by the first hop, so all threads see the same
+    odd_rows = a.maps.spilled[kMaxBins] == a.maps.call;    // set by the hops, so all threads see the same
     const int32_t whole = odd_rows ? 0 : (a.n_seeds < kHeldSeeds ? a.n_seeds : kHeldSeeds) / 4;
     held_seeds = whole * 4;
 #pragma unroll

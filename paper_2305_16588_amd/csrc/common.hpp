@@ -167,12 +167,11 @@ struct BinMaps {
   // Segments [bin][workgroup of the hop]; word 0 of a segment is its count, which may be larger than its room.
   uint32_t* heads = nullptr;          // the first kHeadWords words of each, which are always read
   uint32_t* tails = nullptr;          // the others
-  uint32_t* spilled = nullptr;        // [bin]: the frontier map has taken something; all zero between calls
+  uint32_t* spilled = nullptr;        // [bin]: the frontier map has taken something; all zero between calls.  And [kMaxBins], below
   int32_t* first = nullptr;           // [hop][kMaxBins + 1]: where the ids of each bin begin in frontier `hop`
-  // The number of the last call that met a seed without a row, or with one that makes no sense, and the number of this call (a value
-  // of its own, so that nothing is cleared).  The context's error word says neither: kernels of a gather on another stream set it
-  // and lgp_check on that stream clears it while this call runs.
-  uint32_t* odd_seeds = nullptr;
+  // The number of this call, a value of its own.  spilled[kMaxBins] is that of the last call that met a vertex without a row, or with
+  // one that makes no sense: its seeds are looked at one by one.  The context's error word does not say so: kernels of a gather on another stream set it and lgp_check on
+  // that stream clears it while this call runs.
   uint32_t call = 0;
   int32_t shift = 0, bins = 0;        // bins == 0: this context marks maps in every call
 };

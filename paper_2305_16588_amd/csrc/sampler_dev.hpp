@@ -161,7 +161,7 @@ __device__ __forceinline__ void sample_hop(const HopArgs& a, uint32_t block, uin
     }
     if (bad) {
       if (slot == 0) atomicOr(a.d_err, ERR_BAD_ID);
-      if (SHIFT == kBinned && seeds) *a.bins.odd_seeds = a.bins.call;
+      if (SHIFT == kBinned) a.bins.spilled[kMaxBins] = a.bins.call;
       d64 = 0;
     }
     const int32_t d = int32_t(d64);
