@@ -362,8 +362,8 @@ int lgp_workspace_bytes(const lgp_ctx* ctx, int32_t max_seeds, const int32_t* fa
  * Synchronous. */
 int lgp_reserve(lgp_ctx* ctx, int32_t max_seeds, const int32_t* fanouts, int32_t n_hops);
 
-/* How often a workgroup of the dedup compaction looks for the count of one before it until it counts that
- * share itself (4096 by default; 0: at once).  Results and errors do not depend on it and every wait ends
+/* How often a workgroup of the dedup -- a compaction of a map, or the listing of bins -- looks for the count of one
+ * before it until it counts that share itself (4096 by default; 0: at once).  Results and errors do not depend on it and every wait ends
  * whatever it is: it is there so that a test can reach the second way.  Applies to later calls. */
 int lgp_set_wait_polls(lgp_ctx* ctx, int32_t polls);
 

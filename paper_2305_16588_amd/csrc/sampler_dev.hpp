@@ -84,7 +84,7 @@ __device__ __forceinline__ void append_to_bin(const HopArgs& a, uint32_t* used, 
 }
 
 // Marks bound this kernel (last hop of 190 k vertices x 5 at 2.4 M vertices: 23 us with its 950 k byte marks, 11 without;
-// 490 k atomic marks at 250 M: 24 and 9); what is left is loads and issue slots, so lanes are packed without gaps (but see
+// 490 k atomic marks of a map of 250 M: 24 and 9; appended to segments instead they take 13); what is left is loads and issue slots, so lanes are packed without gaps (but see
 // hop_lanes).  Against a power of two of lanes per vertex and a chain of fanout - 1 broadcasts for Floyd's test, calls on
 // 2.4 M vertices from 8192 seeds: fan-outs 17, 17 28.2 -> 25.1 us, 64 17.5 -> 15.4, 9, 9 21.2 -> 20.2, 15, 10, 5 with blocks
 // and gather 190 -> 186; 25 or 3, 3, 3 and graphs with atomic marks are level.
@@ -214,8 +214,8 @@ inline int32_t hop_lanes(const TopoView& tv, int32_t f) {
 
 // Workgroups for a hop over at most `cap` vertices.
 // Six workgroups (24 waves) per CU: more waves do not make scattered marks faster.  Calls at 4 / 6 / 8 per CU: 2.4 M
-// vertices, half of the topology over PCIe 279.9 / 276.3 / 276.4 us, 111 M vertices 67.7 / 64.8 / 67.0, 250 M 63.3 / 61.7 /
-// 63.4; sampling server step at 2.4 M 194.6 / 189.9 / 192.6.  Sampling a batch beside the extraction of the one before, 2.4 M
+// vertices, half of the topology over PCIe 279.9 / 276.3 / 276.4 us; marking bits, as the pipeline inside a batch and calls of few
+// samples do (calls like these two are binned), 111 M vertices 67.7 / 64.8 / 67.0, 250 M 63.3 / 61.7 / 63.4; sampling server step at 2.4 M 194.6 / 189.9 / 192.6.  Sampling a batch beside the extraction of the one before, 2.4 M
 // vertices, at 4 / 6: half of the topology and 30 % of the features cached 1869 / 1870 us a step, half and 90 % 574 / 575,
 // everything 148.7 / 145.0.
 inline uint32_t hop_blocks(const DeviceInfo& di, int64_t cap, int32_t lanes) {

@@ -69,6 +69,7 @@ int main() {
   EXPECT(lgp_set_overlap(nullptr, 1) == LGP_EINVAL);
   EXPECT(lgp_set_profiling(nullptr, 1) == LGP_EINVAL);
   EXPECT(lgp_set_wait_polls(nullptr, 0) == LGP_EINVAL);
+  EXPECT(lgp_get_sample_marks(nullptr, nullptr) == LGP_EINVAL);
   EXPECT(lgp_get_profile(nullptr, &prof) == LGP_EINVAL);
   // calls that need no context check their arguments before they touch a device
   EXPECT(lgp_shuffle_tablet(0, nullptr, nullptr, 5, 1, 0, nullptr) == LGP_EINVAL);
