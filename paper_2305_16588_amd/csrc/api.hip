@@ -335,6 +335,7 @@ hipError_t hold_segments(lgp_ctx* c) {
   }
   hipError_t e = hipMemset(b.spilled, 0, sizeof(uint32_t) * (kMaxBins + 1));
   if (e == hipSuccess) e = hipDeviceSynchronize();
+  if (e != hipSuccess) drop_segments(c);
   return e;
 }
 

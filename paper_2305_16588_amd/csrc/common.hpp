@@ -162,16 +162,15 @@ inline int bin_shift(int64_t num_vertices) {
   while ((num_vertices - 1) >> shift >= kMaxBins) ++shift;
   return shift;
 }
-struct BinMaps {
-  // null while the context holds no segments (hold_segments).
+struct BinMaps {                      // all null while the context holds no segments (hold_segments)
   // Segments [bin][workgroup of the hop]; word 0 of a segment is its count, which may be larger than its room.
   uint32_t* heads = nullptr;          // the first kHeadWords words of each, which are always read
   uint32_t* tails = nullptr;          // the others
   uint32_t* spilled = nullptr;        // [bin]: the frontier map has taken something; all zero between calls.  And [kMaxBins], below
   int32_t* first = nullptr;           // [hop][kMaxBins + 1]: where the ids of each bin begin in frontier `hop`
   // The number of this call, a value of its own.  spilled[kMaxBins] is that of the last call that met a vertex without a row, or with
-  // one that makes no sense: its seeds are looked at one by one.  The context's error word does not say so: kernels of a gather on another stream set it and lgp_check on
-  // that stream clears it while this call runs.
+  // one that makes no sense: its seeds are looked at one by one.  The context's error word does not say so: kernels of a gather on
+  // another stream set it and lgp_check on that stream clears it while this call runs.
   uint32_t call = 0;
   int32_t shift = 0, bins = 0;        // bins == 0: this context marks maps in every call
 };
